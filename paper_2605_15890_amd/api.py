@@ -6,6 +6,7 @@ is no fallback of any kind.
 """
 import ctypes as C
 import os
+import struct
 
 import numpy as np
 
@@ -73,18 +74,19 @@ def load():
     L.agc_code_bytes.restype = C.c_int64
     L.agc_last_error.argtypes = [_vp]
     L.agc_last_error.restype = C.c_char_p
-    L.agc_encode_quantize.argtypes = [_vp, _vp, C.c_int64, _u8p, C.c_uint64, C.c_uint64,
-                                      C.POINTER(_vp), _vp, _vp]
+    # the per-step calls read their small host arrays (streams, widths, weights, mask) before they return:
+    # the binding passes them as bytes objects, which costs a tenth of a typed ctypes pointer
+    L.agc_encode_quantize.argtypes = [_vp, _vp, C.c_int64, _vp, C.c_uint64, C.c_uint64, _vp, _vp, _vp]
     L.agc_encode_quantize.restype = C.c_int
-    L.agc_decode.argtypes = [_vp, C.POINTER(_vp), _vp, _u8p, _f32p, _u8p, _vp, _vp]
+    L.agc_decode.argtypes = [_vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp]
     L.agc_decode.restype = C.c_int
     L.agc_scales_per_worker.argtypes = [_vp]
     L.agc_scales_per_worker.restype = C.c_int64
     L.agc_set_layers.argtypes = [_vp, C.c_int, C.POINTER(C.c_int64)]
     L.agc_set_layers.restype = C.c_int
-    L.agc_decode2.argtypes = [_vp, C.POINTER(_vp), _vp, _u8p, _f32p, _f32p, _u8p, _vp, _vp, _vp]
+    L.agc_decode2.argtypes = [_vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp, _vp]
     L.agc_decode2.restype = C.c_int
-    L.agc_decode_noalloc.argtypes = [C.c_int, C.c_int64, C.c_int, C.POINTER(_vp), _vp, _u8p, _f32p, _u8p, _vp, _vp]
+    L.agc_decode_noalloc.argtypes = [C.c_int, C.c_int64, C.c_int, _vp, _vp, _vp, _vp, _vp, _vp, _vp]
     L.agc_decode_noalloc.restype = C.c_int
     L.agc_adam_update.argtypes = [_vp, _vp, _vp, _vp, _vp, C.c_float, C.c_float, C.c_float, C.c_float,
                                   C.c_int64, C.c_int64, _vp]
@@ -92,8 +94,7 @@ def load():
     L.agc_second_moment_decoder.argtypes = [C.c_int, C.c_int, _i32p, _i32p, _f32p, _f64p, _u8p, C.c_double,
                                             C.c_double, _f32p]
     L.agc_second_moment_decoder.restype = C.c_int
-    L.agc_step.argtypes = [_vp, _vp, C.c_int64, _u8p, _f32p, _u8p, C.c_uint64, C.c_uint64,
-                           C.POINTER(_vp), _vp, _vp, _vp]
+    L.agc_step.argtypes = [_vp, _vp, C.c_int64, _vp, _vp, _vp, C.c_uint64, C.c_uint64, _vp, _vp, _vp, _vp]
     L.agc_step.restype = C.c_int
     L.agc_ls_workspace_floats.argtypes = [C.c_int64, C.c_int, C.c_int]
     L.agc_ls_workspace_floats.restype = C.c_int64
@@ -250,6 +251,16 @@ def agc_second_moment_decoder(k, row_ptr, col, val, p, bits, phi_coef, lam):
 
 
 # --------------------------------------------------------------------------- hot path
+def _check_streams(codes, bits, d):
+    """Every stream holds agc_code_bytes(d, b) bytes.  The sizes are formed here, without a library call
+    per worker: at 64 workers those calls took longer than everything else a pass does on the host.
+    Widths outside 1..16 need nothing here (agc_code_bytes is 0): the library refuses them."""
+    unit = (int(d) + 127) // 128 * 16 if d > 0 else 0
+    for i, (t, b) in enumerate(zip(codes, bits.tolist())):
+        if 1 <= b <= AGC_MAX_BITS and t.nbytes < unit * b:
+            raise AgcError(AGC_ESHAPE, f"codes[{i}] holds {t.nbytes} bytes, {unit * b} needed for d={d}, bits={b}")
+
+
 def _stream_handle(stream):
     if stream is None:
         import torch
@@ -316,21 +327,14 @@ class Context:
 
     @staticmethod
     def _code_ptrs(codes):
-        arr = (_vp * len(codes))()
-        for i, t in enumerate(codes):
-            arr[i] = t.data_ptr()
-        return arr
+        return struct.pack(f"{len(codes)}P", *[t.data_ptr() for t in codes])
 
     def _check_buffers(self, codes, bits, scales=None, ghat=None):
         """The C ABI sees bare pointers; the binding knows the tensors and refuses buffers that
         are too small for the geometry the kernels will write or read."""
         if len(codes) != self.n or len(bits) != self.n:
             raise AgcError(AGC_ESHAPE, f"expected {self.n} streams and bit-widths")
-        for i, t in enumerate(codes):
-            need = agc_code_bytes(self.d, int(bits[i]))
-            if need and t.numel() * t.element_size() < need:
-                raise AgcError(AGC_ESHAPE, f"codes[{i}] holds {t.numel() * t.element_size()} bytes, "
-                                           f"{need} needed for d={self.d}, bits={int(bits[i])}")
+        _check_streams(codes, bits, self.d)
         if scales is not None and scales.numel() < self.n * self.agc_scales_per_worker():
             raise AgcError(AGC_ESHAPE, "scales tensor too small")
         if ghat is not None and ghat.numel() < self.d:
@@ -349,7 +353,7 @@ class Context:
         bits = _np(bits, np.uint8)
         self._check_gradients(G)
         self._check_buffers(codes, bits, scales)
-        st = self.lib.agc_encode_quantize(self.h, C.c_void_p(G.data_ptr()), G.stride(0), _ptr(bits, _u8p),
+        st = self.lib.agc_encode_quantize(self.h, C.c_void_p(G.data_ptr()), G.stride(0), bits.tobytes(),
                                           int(seed), int(step), self._code_ptrs(codes),
                                           C.c_void_p(scales.data_ptr()), _stream_handle(stream))
         if check:
@@ -360,7 +364,7 @@ class Context:
         bits, w, mask = _np(bits, np.uint8), _np(w, np.float32), _np(mask, np.uint8)
         self._check_buffers(codes, bits, scales, ghat)
         st = self.lib.agc_decode(self.h, self._code_ptrs(codes), C.c_void_p(scales.data_ptr()),
-                                 _ptr(bits, _u8p), _ptr(w, _f32p), _ptr(mask, _u8p),
+                                 bits.tobytes(), w.tobytes(), mask.tobytes(),
                                  C.c_void_p(ghat.data_ptr()), _stream_handle(stream))
         if check:
             self._check(st)
@@ -369,9 +373,10 @@ class Context:
     def agc_decode2(self, codes, scales, bits, w, v, mask, ghat, ghat2, stream=None, check=True):
         bits, w, v, mask = _np(bits, np.uint8), _np(w, np.float32), _np(v, np.float32), _np(mask, np.uint8)
         self._check_buffers(codes, bits, scales, ghat)
-        self._check_buffers(codes, bits, None, ghat2)
+        if ghat2.numel() < self.d:
+            raise AgcError(AGC_ESHAPE, "ghat tensor too small")
         st = self.lib.agc_decode2(self.h, self._code_ptrs(codes), C.c_void_p(scales.data_ptr()),
-                                  _ptr(bits, _u8p), _ptr(w, _f32p), _ptr(v, _f32p), _ptr(mask, _u8p),
+                                  bits.tobytes(), w.tobytes(), v.tobytes(), mask.tobytes(),
                                   C.c_void_p(ghat.data_ptr()), C.c_void_p(ghat2.data_ptr()),
                                   _stream_handle(stream))
         if check:
@@ -382,8 +387,8 @@ class Context:
         bits, w, mask = _np(bits, np.uint8), _np(w, np.float32), _np(mask, np.uint8)
         self._check_gradients(G)
         self._check_buffers(codes, bits, scales, ghat)
-        st = self.lib.agc_step(self.h, C.c_void_p(G.data_ptr()), G.stride(0), _ptr(bits, _u8p), _ptr(w, _f32p),
-                               _ptr(mask, _u8p), int(seed), int(step), self._code_ptrs(codes),
+        st = self.lib.agc_step(self.h, C.c_void_p(G.data_ptr()), G.stride(0), bits.tobytes(), w.tobytes(),
+                               mask.tobytes(), int(seed), int(step), self._code_ptrs(codes),
                                C.c_void_p(scales.data_ptr()), C.c_void_p(ghat.data_ptr()),
                                _stream_handle(stream))
         if check:
@@ -444,15 +449,12 @@ def agc_decode_noalloc(n, d, bucket, codes, scales, bits, w, mask, ghat, stream=
     if len(codes) != n or len(bits) != n or len(w) != n or len(mask) != n:
         raise AgcError(AGC_ESHAPE, f"expected {n} streams, bit-widths, weights and mask entries")
     if n <= AGC_MAX_WORKERS:   # sizes the library would refuse are left for it to refuse
-        for i, t in enumerate(codes):
-            need = agc_code_bytes(d, int(bits[i]))
-            if need and t.numel() * t.element_size() < need:
-                raise AgcError(AGC_ESHAPE, f"codes[{i}] is smaller than d={d}, bits={int(bits[i])} require")
+        _check_streams(codes, bits, d)
         per = (int(d) + 255) // 256 if bucket == 256 else 1
         if scales.numel() < n * per or ghat.numel() < d:
             raise AgcError(AGC_ESHAPE, "scales or ghat tensor too small")
     st = L.agc_decode_noalloc(int(n), int(d), int(bucket), Context._code_ptrs(codes),
-                              C.c_void_p(scales.data_ptr()), _ptr(bits, _u8p), _ptr(w, _f32p), _ptr(mask, _u8p),
+                              C.c_void_p(scales.data_ptr()), bits.tobytes(), w.tobytes(), mask.tobytes(),
                               C.c_void_p(ghat.data_ptr()), _stream_handle(stream))
     if check and st != AGC_OK:
         raise AgcError(st, L.agc_last_error(None).decode())
