@@ -219,8 +219,8 @@ agc_status agc_decode2(agc_ctx *ctx, void *const *codes_dev, const float *scales
  * code under HIP graph capture, tight serving loops on the master, harnesses that forbid
  * hipMalloc.  No context: n_workers, d and bucket (0, or 256 for bucket-wise scales) are passed
  * directly; a one-bit stream is always accepted.  Same kernels, same arithmetic and the same bits
- * in g_hat as agc_decode.  The small tables the decode kernel reads (one 16-byte record and one
- * row pointer per arrived worker) live in a fixed 6144-byte device array inside the library,
+ * in g_hat as agc_decode.  The small tables the decode kernel reads (one record and some 24 stream
+ * pieces per arrived worker) live in a fixed device array of 106 KB inside the library,
  * which every GPU the library runs on holds until the process ends; hence n_workers <= 256
  * (AGC_ESHAPE with a message otherwise).  The call itself and everything below it performs no
  * hipMalloc/hipFree; the first call on a device looks the array's address up once (make that

@@ -169,6 +169,16 @@ agc_status check_streams(agc_ctx* c, void* const* codes)
     return AGC_OK;
 }
 
+void add_arrived(agc::DecodeStreams& ds, int i, const void* codes, float w, float v, uint8_t bits)
+{
+    const int s = ds.n_arrived++;
+    ds.codes[s] = codes;
+    ds.w[s] = w;
+    ds.v[s] = v;
+    ds.bits[s] = bits;
+    ds.worker[s] = (uint8_t)i;
+}
+
 agc::CodeDev code_dev(const agc_ctx* c)
 {
     return agc::CodeDev{c->d_row_ptr, c->d_col, c->d_val, c->opts.force_generic ? 0 : c->band, c->d_win};
@@ -224,7 +234,7 @@ agc_status agc_create(agc_ctx** out, int n, int k, int64_t d, const agc_opts* op
     c->ws.ngroup = (c->ws.nseg + 63) / 64;
     c->ws.nsuper = (c->ws.ngroup + 63) / 64;
     if (o.bucket) {
-        e = dev_alloc(&c->ws.srow, (size_t)n);  // the scales need no reduction workspace
+        // the scales need no reduction workspace
     } else if (o.scale_mode == AGC_SCALE_MAXABS) {
         c->ws.max_rows = agc::kMaxSlots;
         e = dev_alloc(&c->ws.part_max, (size_t)agc::kMaxSlots * n);
@@ -238,8 +248,7 @@ agc_status agc_create(agc_ctx** out, int n, int k, int64_t d, const agc_opts* op
         if (e == hipSuccess) e = dev_alloc(&c->ws.super_sq, (size_t)c->ws.nsuper * n);
     }
     if (e == hipSuccess) e = dev_alloc(&c->ws.wq, (size_t)n);
-    if (e == hipSuccess) e = dev_alloc(&c->ws.wd, (size_t)n);
-    if (e == hipSuccess) e = dev_alloc(&c->ws.coef2, (size_t)n);
+    if (e == hipSuccess) e = hipMalloc(&c->ws.dec, agc::decode_table_bytes(n));
     if (e != hipSuccess) {
         agc_destroy(c);
         return fail(nullptr, e == hipErrorOutOfMemory ? AGC_ENOMEM : AGC_EHIP,
@@ -259,9 +268,7 @@ void agc_destroy(agc_ctx* c)
     if (c->ws.group_sq) (void)hipFree(c->ws.group_sq);
     if (c->ws.super_sq) (void)hipFree(c->ws.super_sq);
     if (c->ws.wq) (void)hipFree(c->ws.wq);
-    if (c->ws.wd) (void)hipFree(c->ws.wd);
-    if (c->ws.coef2) (void)hipFree(c->ws.coef2);
-    if (c->ws.srow) (void)hipFree(c->ws.srow);
+    if (c->ws.dec) (void)hipFree(c->ws.dec);
     for (auto& ring : c->events)
         for (auto& ep : ring) {
             if (ep.beg) (void)hipEventDestroy(ep.beg);
@@ -558,17 +565,13 @@ agc_status agc_decode(agc_ctx* c, void* const* codes, const float* scales, const
     st = check_streams(c, codes);
     if (st != AGC_OK) return st;
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
-    agc::DecodeStreams ds{};
-    int n_arrived = 0;
-    for (int i = 0; i < c->n; ++i) {
-        ds.codes[i] = codes[i];
-        ds.w[i] = w[i];
-        ds.bits[i] = bits[i];
-        ds.slot[i] = mask[i] ? (uint16_t)n_arrived++ : (uint16_t)0xFFFF;
-    }
+    agc::DecodeStreams ds;
+    ds.n_arrived = 0;
+    for (int i = 0; i < c->n; ++i)
+        if (mask[i]) add_arrived(ds, i, codes[i], w[i], 0.f, bits[i]);
     KernelTimer t{c, 3, stream};
     if ((st = t.begin()) != AGC_OK) return st;
-    hipError_t e = agc::launch_decode(c->n, n_arrived, c->d, ds, scales, c->opts.bucket ? (c->d + 255) / 256 : 0, c->ws, ghat, stream);
+    hipError_t e = agc::launch_decode(c->n, c->d, ds, false, scales, c->opts.bucket ? (c->d + 255) / 256 : 0, c->ws, ghat, nullptr, stream);
     if (e != hipSuccess) return hip_fail(c, e, "decode launch");
     return t.end();
 }
@@ -588,19 +591,13 @@ agc_status agc_decode2(agc_ctx* c, void* const* codes, const float* scales, cons
     st = check_streams(c, codes);
     if (st != AGC_OK) return st;
     hipStream_t stream = reinterpret_cast<hipStream_t>(hip_stream);
-    agc::DecodeStreams ds{};
-    agc::DecodeSecond d2{};
-    int n_arrived = 0;
-    for (int i = 0; i < c->n; ++i) {
-        ds.codes[i] = codes[i];
-        ds.w[i] = w[i];
-        d2.v[i] = v[i];
-        ds.bits[i] = d2.bits[i] = bits[i];
-        ds.slot[i] = d2.slot[i] = mask[i] ? (uint16_t)n_arrived++ : (uint16_t)0xFFFF;
-    }
+    agc::DecodeStreams ds;
+    ds.n_arrived = 0;
+    for (int i = 0; i < c->n; ++i)
+        if (mask[i]) add_arrived(ds, i, codes[i], w[i], v[i], bits[i]);
     KernelTimer t{c, 3, stream};
     if ((st = t.begin()) != AGC_OK) return st;
-    hipError_t e = agc::launch_decode2(c->n, n_arrived, c->d, ds, d2, scales, c->opts.bucket ? (c->d + 255) / 256 : 0, c->ws, ghat, ghat2, stream);
+    hipError_t e = agc::launch_decode(c->n, c->d, ds, true, scales, c->opts.bucket ? (c->d + 255) / 256 : 0, c->ws, ghat, ghat2, stream);
     if (e != hipSuccess) return hip_fail(c, e, "two-track decode launch");
     return t.end();
 }
@@ -617,8 +614,8 @@ agc_status agc_decode_noalloc(int n, int64_t d, int bucket, void* const* codes, 
     if (bucket != 0 && bucket != 256) return fail(nullptr, AGC_EINVAL, "bucket must be 0 or 256");
     if (!codes || !scales || !bits || !w || !mask || !ghat) return fail(nullptr, AGC_EINVAL, "null argument");
     if (reinterpret_cast<uintptr_t>(ghat) & 15u) return fail(nullptr, AGC_EALIGN, "ghat_dev is not 16-byte aligned");
-    agc::DecodeStreams ds{};
-    int n_arrived = 0;
+    agc::DecodeStreams ds;
+    ds.n_arrived = 0;
     for (int i = 0; i < n; ++i) {
         if (bits[i] < 1 || bits[i] > AGC_MAX_BITS)
             return fail(nullptr, AGC_EBITS, "bit-width of worker " + std::to_string(i) + " is " +
@@ -626,12 +623,9 @@ agc_status agc_decode_noalloc(int n, int64_t d, int bucket, void* const* codes, 
         if (!codes[i]) return fail(nullptr, AGC_EINVAL, "codes_dev[" + std::to_string(i) + "] is null");
         if (reinterpret_cast<uintptr_t>(codes[i]) & 15u)
             return fail(nullptr, AGC_EALIGN, "codes_dev[" + std::to_string(i) + "] is not 16-byte aligned");
-        ds.codes[i] = codes[i];
-        ds.w[i] = w[i];
-        ds.bits[i] = bits[i];
-        ds.slot[i] = mask[i] ? (uint16_t)n_arrived++ : (uint16_t)0xFFFF;
+        if (mask[i]) add_arrived(ds, i, codes[i], w[i], 0.f, bits[i]);
     }
-    hipError_t e = agc::launch_decode_static(n, n_arrived, d, ds, scales, bucket ? (d + 255) / 256 : 0, ghat,
+    hipError_t e = agc::launch_decode_static(d, ds, scales, bucket ? (d + 255) / 256 : 0, ghat,
                                              reinterpret_cast<hipStream_t>(hip_stream));
     if (e != hipSuccess) return hip_fail(nullptr, e, "allocation-free decode");
     return AGC_OK;

@@ -88,12 +88,42 @@ inline int stage_bits_needed(const uint8_t* bits, int n)
     return most;
 }
 
-// one arrived worker as the decode pass sees it
-struct WorkerD {
-    const void* codes;
-    float coef;           // w_i * scale_i / L_i
-    uint32_t bits;
+// ---- tables of the decode pass.  A tile of the vector is 256 * COORDS coordinates; a worker's part of it
+// is `bits` units of 32 * COORDS contiguous bytes.  Units of consecutive workers, whole workers only, fill
+// chunks of kDecChunkBytes, which is what a workgroup fetches at a time.
+constexpr int kDecChunkBytes = 12288;
+
+struct DecWorker {        // one arrived worker; read with scalar loads
+    float coef;           // w_i * scale_i / L_i (bucket-wise scales: w_i / L_i; layer-wise: unused)
+    float coef2;          // the same with the second decoding vector
+    uint32_t width;       // 1 << bits; 1 for two bits and weights that can be halved exactly
+    uint32_t pos;         // its first unit within its chunk
+    uint32_t worker;
+    uint32_t pad[3];
 };
+static_assert(sizeof(DecWorker) == 32, "one record is two 16-byte scalar loads");
+
+struct DecUnit {
+    const char* codes;    // the unit of tile 0
+    uint32_t tile_pieces; // 16-byte pieces from one tile to the next
+    uint32_t pieces;      // 16-byte pieces from here to the end of the stream, >= 1
+};
+static_assert(sizeof(DecUnit) == 16, "one record is one 16-byte load");
+
+struct DecodeTables {
+    DecWorker* workers;
+    DecUnit* units;
+    int* chunk_first;     // [n_chunks + 1]
+};
+
+// Most units the chunks of n workers have room for: a chunk of 24 (48) units holds at least one worker, and
+// is closed when the next one of up to 16 units does not fit, i.e. with at least 33 of the 48 in use.
+// So there are at most n chunks of 24, or 16n/33 + 1 chunks of 48.
+constexpr int64_t decode_units(int n) { return 24 * (int64_t)n + 48; }
+constexpr size_t decode_table_bytes(int n)
+{
+    return sizeof(DecWorker) * (size_t)n + sizeof(DecUnit) * (size_t)decode_units(n) + sizeof(int) * ((size_t)n + 2);
+}
 
 struct Workspace {
     uint32_t* part_max;   // [max_rows][n] running max |f_i| as bit patterns, all zero between steps (max-abs scale)
@@ -102,9 +132,7 @@ struct Workspace {
     double* group_sq;     // [n][ngroup]
     double* super_sq;     // [n][nsuper]
     WorkerQ* wq;          // [n]  written by the scale finalize
-    WorkerD* wd;          // [n]  arrived workers, compacted, written by the decode prologue
-    float* coef2;         // [n]  second-track weights v_i * scale_i / L_i of the arrived workers
-    const float** srow;   // [n]  bucket-wise scales: row of scales of every arrived worker
+    void* dec;            // decode_table_bytes(n) bytes: tables of the arrived workers, written by the decode prologue
     int64_t nseg, ngroup, nsuper;
     // layer-wise scales (n_layers > 0; max-abs only): the layer of every 256-coordinate block, and
     // the decode weights w_i * scale_il / L_i (and v_i * ...) of the arrived workers, [layer][slot].
@@ -137,17 +165,27 @@ struct StepWeights {       // decode side of a fused step, as kernel arguments o
     int fuse;              // 0: plain encode+quantize, the two arrays are ignored
 };
 
-struct DecodeStreams {     // host arrays of the decode call, as kernel arguments of its prologue
+struct DecodeStreams {     // the arrived workers of a decode call, in ascending order (host side)
+    int n_arrived;
     const void* codes[kArgWorkers];
     float w[kArgWorkers];
+    float v[kArgWorkers];        // second decoding vector of the two-track decode (Sec. V)
     uint8_t bits[kArgWorkers];
-    uint16_t slot[kArgWorkers];  // position among the arrived workers, 0xFFFF for a straggler
+    uint8_t worker[kArgWorkers]; // which worker it is
 };
 
-struct DecodeSecond {      // second decoding vector of the two-track decode (Sec. V)
-    float v[kArgWorkers];
-    uint8_t bits[kArgWorkers];
-    uint16_t slot[kArgWorkers];
+template <int CAP>
+struct DecodeList {        // the same as kernel arguments of the decode's prologue, with the places in the chunks
+    int n_arrived;
+    int units_per_chunk;
+    uint32_t groups;       // 128-code groups of a stream
+    const void* codes[CAP];
+    float w[CAP];
+    float v[CAP];
+    uint8_t bits[CAP];
+    uint8_t worker[CAP];
+    uint8_t chunk[CAP];
+    uint8_t pos[CAP];
 };
 
 // K1: partial results of every worker's scale (max-abs: running maxima in ws.part_max, per layer
@@ -175,22 +213,15 @@ hipError_t launch_quantize_bucket(const float* G, int64_t ldg, int n, int k, int
                                   int scale_mode, const QuantStreams& out, const StepWeights& sw,
                                   const Workspace& ws, float* scales, uint64_t seed, uint64_t step, float* ghat,
                                   hipStream_t stream);
-// K3: table of the arrived workers (a one-workgroup prologue), then masked dequantize +
-// weighted sum.
+// K3: tables of the arrived workers (a prologue), then masked dequantize + weighted sum.
 // nb = 0: one scale per worker; nb > 0: scales is n x nb, one scale per 256-coordinate bucket.
-hipError_t launch_decode(int n, int n_arrived, int64_t d, const DecodeStreams& in,
-                         const float* scales, int64_t nb, const Workspace& ws, float* ghat,
-                         hipStream_t stream);
-// Two-track variant: the same read of the codes feeds a second weighted sum with weights v.
-hipError_t launch_decode2(int n, int n_arrived, int64_t d, const DecodeStreams& in, const DecodeSecond& second,
-                          const float* scales, int64_t nb, const Workspace& ws, float* ghat, float* ghat2,
-                          hipStream_t stream);
-// The decode of launch_decode with its two small tables (arrived workers, their rows of
-// bucket-wise scales) in a fixed device array of kStaticScratchBytes bytes instead of a context's
-// workspace: no allocation anywhere, n <= 256.  Calls on one GPU share the array.
-constexpr size_t kStaticScratchBytes = 6144;
-hipError_t launch_decode_static(int n, int n_arrived, int64_t d, const DecodeStreams& in, const float* scales,
-                                int64_t nb, float* ghat, hipStream_t stream);
+// two: the same read of the codes feeds a second weighted sum, with weights in.v, into ghat2.
+hipError_t launch_decode(int n, int64_t d, const DecodeStreams& in, bool two, const float* scales, int64_t nb,
+                         const Workspace& ws, float* ghat, float* ghat2, hipStream_t stream);
+// The one-track decode with its tables in a fixed device array instead of a context's workspace: no
+// allocation anywhere, n <= 256.  Calls on one GPU share the array.
+hipError_t launch_decode_static(int64_t d, const DecodeStreams& in, const float* scales, int64_t nb, float* ghat,
+                                hipStream_t stream);
 // Adam update that takes its first moment from ghat and its second moment from ghat2.
 hipError_t launch_adam_update(float* beta, float* m1, float* m2, const float* ghat, const float* ghat2,
                               float lr, float beta1, float beta2, float eps, float corr1, float corr2,

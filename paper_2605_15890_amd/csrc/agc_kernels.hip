@@ -540,75 +540,111 @@ hipError_t launch_quantize(const float* G, int64_t ldg, int n, int k, int64_t d,
 // =======================================================================================
 // K3  masked dequantize + weighted sum
 // =======================================================================================
-// A lane owns 32 consecutive coordinates: for a b-bit worker these are exactly b consecutive
-// 32-bit words of the stream, so unpacking needs no cross-lane traffic and every shift is a
-// compile-time constant.
-constexpr int kDecCoords = 32;
+// A workgroup walks over tiles of 256 * COORDS coordinates (a lane owns COORDS consecutive ones) and, in
+// every tile, over the arrived workers in ascending order.  A b-bit worker's part of a tile is b "units"
+// of 32 * COORDS contiguous bytes of its stream; the units of consecutive workers are packed into chunks
+// of 12 KB.  All lanes fetch a chunk together, three 16-byte pieces each, wholly coalesced
+// and without a branch, into registers while the chunk before it is decoded from LDS, also across the end
+// of a tile.
+//
+// What bounds it: instruction issue.  At the metric size (25.6 M coordinates, 43 of 64 workers arrived) a
+// wave spends about 70 vector and 30 scalar instructions on 16 codes of each lane, and the vector units are
+// a little over 40 % busy; the memory would allow 0.08 ms.  The first form of the kernel let every lane
+// load its own b words of one worker right before they were used and decode 32 codes of them: one request
+// in flight per wave, 0.169 ms, and 26 us even for 200 000 coordinates (20 workers times one round trip to
+// memory).  This form: 0.148 ms and 18 us.  Six waves per SIMD (74 vector registers, 24 KB of LDS): five
+// take 0.162 ms, four with chunks of 16 KB 0.166 ms, eight with 8 KB 0.160 ms.
+constexpr int kDecPieces = kDecChunkBytes / 16;            // 16-byte pieces of a chunk
+constexpr int kDecPerThread = kDecPieces / kWgThreads;
+static_assert(kDecPerThread * kWgThreads == kDecPieces, "every lane fetches the same number of pieces");
+constexpr int kDecAux = 512;                               // (workers of a chunk) x (buckets of a tile), at most
 
-// prologue: one entry per ARRIVED worker, in ascending worker order
-// nb == 0: one scale per worker, folded into the weight here.  nb > 0: bucket-wise scales; the
-// table holds w_i / L_i and the worker's row of scales, the product is formed per bucket.
-__global__ __launch_bounds__(kWgThreads) void k_decode_table(int n, DecodeStreams in,
-                                                             const float* scales, int64_t nb, WorkerD* wd,
-                                                             const float** srow)
+// true when x / 2 is exact in binary32: zero, or a normal number that stays normal
+__device__ __forceinline__ bool halves_exactly(float x)
+{
+    const uint32_t u = __float_as_uint(x), e = (u >> 23) & 0xFFu;
+    return ((u << 1) == 0u) | (e - 2u < 0xFDu);
+}
+
+// One workgroup per layer (one in all without layer-wise scales); the first also writes the tables of
+// streams: one record per arrived worker, one per unit, and the first worker of every chunk.
+// SCALES 0: one scale per worker, folded into the weight here.  1: bucket-wise; the record holds w_i / L_i
+// and the product with the bucket's scale is formed in the decode.  2: layer-wise; the weights go to
+// [layer][slot].
+template <int CAP, int SCALES, bool TWO>
+__global__ __launch_bounds__(kWgThreads) void k_decode_table(DecodeList<CAP> in, const float* scales, int n_layers,
+                                                             DecodeTables tab, float* coef_layer, float* coef2_layer)
 {
     const int i = threadIdx.x;
+    const int l = blockIdx.x;
+    const int n = in.n_arrived;
     if (i >= n) return;
-    const uint32_t slot = in.slot[i];
-    if (slot == 0xFFFFu) return;
     const int b = in.bits[i];
-    // weight of one grid unit of worker i: w_i * scale_i / L_i, binary64 then one rounding
+    const int worker = in.worker[i];
+    // weight of one grid unit of the worker: w_i * scale_i / L_i, binary64 then one rounding
     const double L = b >= 2 ? (double)((1 << (b - 1)) - 1) : 1.0;
-    if (nb == 0) {
-        wd[slot] = WorkerD{in.codes[i], (float)(((double)in.w[i] * (double)scales[i]) / L), (uint32_t)b};
-    } else {
-        wd[slot] = WorkerD{in.codes[i], (float)((double)in.w[i] / L), (uint32_t)b};
-        srow[slot] = scales + (int64_t)i * nb;
+    const double sc = SCALES == 0 ? (double)scales[worker] : (SCALES == 2 ? (double)scales[(int64_t)worker * n_layers + l] : 1.0);
+    const float c1 = (float)(SCALES == 1 ? (double)in.w[i] / L : ((double)in.w[i] * sc) / L);
+    float c2 = 0.f;
+    if (TWO) c2 = (float)(SCALES == 1 ? (double)in.v[i] / L : ((double)in.v[i] * sc) / L);
+    if (SCALES == 2) {
+        coef_layer[(int64_t)l * n + i] = c1;
+        if (TWO) coef2_layer[(int64_t)l * n + i] = c2;
+        if (l != 0) return;
+    }
+    const int chunk = in.chunk[i], pos = in.pos[i];
+    const int per_chunk = in.units_per_chunk, unit_pieces = kDecPieces / per_chunk;
+    const bool halves = SCALES == 0 && b == 2 && halves_exactly(c1) && (!TWO || halves_exactly(c2));
+    tab.workers[i] = DecWorker{c1, c2, halves ? 1u : 1u << b, (uint32_t)pos, (uint32_t)worker, {0u, 0u, 0u}};
+    if (pos == 0) tab.chunk_first[chunk] = i;
+    if (i == n - 1) tab.chunk_first[chunk + 1] = n;
+    // the worker's units; the last worker of a chunk repeats its last unit up to the chunk's end (a second
+    // request of the same lines), so that every piece of a chunk can be requested without a test
+    const bool last = i == n - 1 || in.pos[i + 1] == 0;
+    const int end = last ? per_chunk : pos + b;
+    const uint32_t pieces = in.groups * (uint32_t)b;  // of the whole stream
+    for (int u = pos; u < end; ++u) {
+        uint32_t at = (uint32_t)((u - pos < b ? u - pos : b - 1) * unit_pieces);
+        if (at >= pieces) at = 0;  // a unit past the end of a short stream: nobody uses what is read
+        tab.units[(int64_t)chunk * per_chunk + u] = DecUnit{(const char*)in.codes[i] + (int64_t)at * 16,
+                                                            (uint32_t)(b * unit_pieces), pieces - at};
     }
 }
 
-// second table of the two-track decode: weight of one grid unit of worker i under the
-// second decoding vector, v_i * scale_i / L_i, same rounding as the first
-__global__ __launch_bounds__(kWgThreads) void k_decode_table2(int n, DecodeSecond in, const float* scales,
-                                                              int64_t nb, float* coef2)
+// acc = fma(c, v, acc), in acc's own register: left to itself the compiler gives every bit-width's branch
+// registers of its own and copies all accumulators back where the branches meet (32 moves per worker
+// next to 96 useful instructions for a two-bit one)
+__device__ __forceinline__ void fma_into(float& acc, float c, float v)
 {
-    const int i = threadIdx.x;
-    if (i >= n) return;
-    const uint32_t slot = in.slot[i];
-    if (slot == 0xFFFFu) return;
-    const int b = in.bits[i];
-    const double L = b >= 2 ? (double)((1 << (b - 1)) - 1) : 1.0;
-    coef2[slot] = nb == 0 ? (float)(((double)in.v[i] * (double)scales[i]) / L) : (float)((double)in.v[i] / L);
+    asm("v_fmac_f32_e32 %0, %1, %2" : "+v"(acc) : "v"(c), "v"(v));
 }
 
-template <int B, bool TWO>
-__device__ __forceinline__ void decode_words(const global_u32* __restrict__ src, float coef, float coef2,
-                                             float (&acc)[kDecCoords], float (&acc2)[TWO ? kDecCoords : 1])
+// COORDS codes of B bits, from words in which the first one starts at bit 0
+template <int B, int COORDS, int NW, bool TWO>
+__device__ __forceinline__ void decode_words(const uint32_t (&w)[NW], float coef, float coef2, float (&acc)[COORDS],
+                                             float (&acc2)[TWO ? COORDS : 1])
 {
-    uint32_t w[B];
 #pragma unroll
-    for (int t = 0; t < B; ++t) w[t] = __builtin_nontemporal_load(src + t);  // each code word is read once
-#pragma unroll
-    for (int q = 0; q < kDecCoords; ++q) {
+    for (int q = 0; q < COORDS; ++q) {
         const int bit = q * B;
         const int wi = bit >> 5, sh = bit & 31;
         float v;
         if (B == 1) {
-            v = ((w[wi] >> sh) & 1u) ? 1.0f : -1.0f;
+            v = __uint_as_float((~(w[wi] << (31 - sh)) & 0x80000000u) | 0x3F800000u);  // 1: +1, 0: -1
         } else {
             // the code's low B-1 bits are the level, its top bit the sign
             uint32_t x = w[wi];
             int s = sh;
             if (sh + B > 32) {  // the code straddles two words: bring it down to bit 0
-                x = __builtin_amdgcn_alignbit(w[(wi + 1) < B ? (wi + 1) : wi], w[wi], sh);
+                x = __builtin_amdgcn_alignbit(w[(wi + 1) < NW ? (wi + 1) : wi], w[wi], sh);
                 s = 0;
             }
             const uint32_t level = (x >> s) & ((1u << (B - 1)) - 1u);
             const uint32_t sign = (x << (32 - B - s)) & 0x80000000u;
             v = __uint_as_float(__float_as_uint((float)level) | sign);
         }
-        acc[q] = fmaf(coef, v, acc[q]);
-        if (TWO) acc2[TWO ? q : 0] = fmaf(coef2, v, acc2[TWO ? q : 0]);
+        fma_into(acc[q], coef, v);
+        if (TWO) fma_into(acc2[TWO ? q : 0], coef2, v);
     }
 }
 
@@ -618,230 +654,352 @@ __device__ __forceinline__ void decode_words(const global_u32* __restrict__ src,
 // same exact product and therefore the same rounded result as fma(coef, +-level, acc): three
 // vector instructions per code (shift, mask, fma) instead of five.  The caller guarantees that
 // halving the weights is exact (they are zero or normal numbers above the smallest exponent).
-template <bool TWO>
-__device__ __forceinline__ void decode_words_2bit(const global_u32* __restrict__ src, float half_coef,
-                                                  float half_coef2, float (&acc)[kDecCoords],
-                                                  float (&acc2)[TWO ? kDecCoords : 1])
+template <int COORDS, int NW, bool TWO>
+__device__ __forceinline__ void decode_words_2bit(const uint32_t (&w)[NW], float half_coef, float half_coef2,
+                                                  float (&acc)[COORDS], float (&acc2)[TWO ? COORDS : 1])
 {
-    uint32_t w[2];
-    w[0] = __builtin_nontemporal_load(src);
-    w[1] = __builtin_nontemporal_load(src + 1);
 #pragma unroll
-    for (int q = 0; q < kDecCoords; ++q) {
+    for (int q = 0; q < COORDS; ++q) {
         const int sh = 30 - 2 * (q & 15);  // brings code q of its word to bits 31..30
         const float v2 = __uint_as_float((w[q >> 4] << sh) & 0xC0000000u);
-        acc[q] = fmaf(half_coef, v2, acc[q]);
-        if (TWO) acc2[TWO ? q : 0] = fmaf(half_coef2, v2, acc2[TWO ? q : 0]);
+        fma_into(acc[q], half_coef, v2);
+        if (TWO) fma_into(acc2[TWO ? q : 0], half_coef2, v2);
     }
 }
 
-// true when x / 2 is exact in binary32: zero, or a normal number that stays normal
-__device__ __forceinline__ bool halves_exactly(float x)
+// a lane's COORDS codes of one worker, from the worker's part of the chunk in LDS
+template <int B, int COORDS, bool TWO, bool HALVES = false>
+__device__ __forceinline__ void decode_worker(const uint32_t* part, float c1, float c2, float (&acc)[COORDS],
+                                              float (&acc2)[TWO ? COORDS : 1])
 {
-    const uint32_t e = (__float_as_uint(x) >> 23) & 0xFFu;
-    return x == 0.0f || (e >= 2u && e != 0xFFu);
+    constexpr int kBytes = COORDS / 8 * B;                                  // of one lane
+    constexpr int kAway = kBytes % 4 == 0 ? 0 : (kBytes % 2 == 0 ? 2 : 3);  // furthest first byte from its word
+    constexpr int NW = (kBytes + 3) / 4, NIN = (kBytes + kAway + 3) / 4;
+    const uint32_t off = threadIdx.x * (uint32_t)kBytes;
+    uint32_t w[NW];
+    if constexpr (kBytes % 16 == 0) {
+        const u32x4_t* p = reinterpret_cast<const u32x4_t*>(part) + threadIdx.x * (uint32_t)(kBytes / 16);
+#pragma unroll
+        for (int t = 0; t < NW; t += 4) {
+            const u32x4_t v = p[t / 4];
+            w[t] = v.x;
+            w[t + 1] = v.y;
+            w[t + 2] = v.z;
+            w[t + 3] = v.w;
+        }
+    } else if constexpr (kBytes % 8 == 0) {
+        const uint2* p = reinterpret_cast<const uint2*>(part) + threadIdx.x * (uint32_t)(kBytes / 8);
+#pragma unroll
+        for (int t = 0; t < NW; t += 2) {
+            const uint2 v = p[t / 2];
+            w[t] = v.x;
+            w[t + 1] = v.y;
+        }
+    } else {
+        const uint32_t* p = part + (off >> 2);
+        uint32_t in[NIN];
+#pragma unroll
+        for (int t = 0; t < NIN; ++t) in[t] = p[t];
+#pragma unroll
+        for (int t = 0; t < NW; ++t)
+            w[t] = kAway ? __builtin_amdgcn_alignbyte(in[t + 1 < NIN ? t + 1 : t], in[t], off & 3u) : in[t];
+    }
+    if constexpr (HALVES) decode_words_2bit<COORDS, NW, TWO>(w, 0.5f * c1, 0.5f * c2, acc, acc2);
+    else decode_words<B, COORDS, NW, TWO>(w, c1, c2, acc, acc2);
 }
 
-struct DecodeArgs {
-    int n_arrived;
-    int64_t d;
-    float* ghat;
-    float* ghat2;  // second track (two-track decode only)
-    // layer-wise scales only: the layer of every block and the weights [layer][arrived slot]
-    const uint8_t* block_layer;
-    const float* coef_layer;
-    const float* coef2_layer;
-};
-
-__device__ __forceinline__ void store_coords(float* dst, const float (&acc)[kDecCoords], int64_t m0, int64_t d)
+// Wave-uniform choice among the bit-widths.  The width comes as a one-hot mask (bit b; bit 0 stands for a
+// two-bit worker whose weights halve exactly): the compiler does not know that only one bit is set, so the
+// tests stay one-armed ifs.  An else arm would keep the accumulators' old values alive across the other
+// arm, and with them a copy of every one of them (32 moves per worker next to 96 useful instructions).
+template <int LO, int HI, int COORDS, bool TWO>
+__device__ __forceinline__ void decode_any(uint32_t mask, const uint32_t* part, float c1, float c2,
+                                           float (&acc)[COORDS], float (&acc2)[TWO ? COORDS : 1])
 {
-    if (m0 + kDecCoords <= d) {
+    if (mask & (1u << LO)) decode_worker<LO == 0 ? 2 : LO, COORDS, TWO, LO == 0>(part, c1, c2, acc, acc2);
+    if constexpr (LO < HI) decode_any<LO + 1, HI, COORDS, TWO>(mask, part, c1, c2, acc, acc2);
+}
+
+template <int COORDS>
+__device__ __forceinline__ void store_coords(float* dst, const float (&acc)[COORDS], int64_t m0, int64_t d)
+{
+    if (m0 + COORDS <= d) {
 #pragma unroll
-        for (int q = 0; q < kDecCoords; q += 4)
+        for (int q = 0; q < COORDS; q += 4)
             *reinterpret_cast<float4*>(dst + q) = make_float4(acc[q], acc[q + 1], acc[q + 2], acc[q + 3]);
     } else {
 #pragma unroll
-        for (int q = 0; q < kDecCoords; ++q)
+        for (int q = 0; q < COORDS; ++q)
             if (m0 + q < d) dst[q] = acc[q];
     }
 }
 
-// Planned for six waves per SIMD (77 registers instead of 82): the kernel is short (12 waves per
-// SIMD at the metric size), so one more resident wave shortens its last, partly filled round;
-// measured 0.175 -> 0.168 ms.  Eight would spill.
+struct DecodeArgs {
+    int n_arrived;
+    int n_chunks;
+    int64_t d;
+    int64_t n_tiles;
+    float* ghat;
+    float* ghat2;               // second track (two-track decode only)
+    const float* scales;        // bucket-wise scales only: n x nb
+    int64_t nb;
+    const uint8_t* block_layer; // layer-wise scales only: the layer of every block
+    const float* coef_layer;    // and the weights [layer][arrived slot]
+    const float* coef2_layer;
+};
+
+constexpr int kDecodeWaves = 6;  // per SIMD, that is resident workgroups per compute unit
 // SCALES 0: one scale per worker (the weight of the table).  1: bucket-wise (weight of the table
-// times the bucket's scale).  2: layer-wise (the weight of the lane's layer, read from the
-// [layer][slot] table; a lane's 32 coordinates lie in one block and therefore in one layer).
+// times the bucket's scale).  2: layer-wise (the weight of the lane's layer; a lane's coordinates lie in
+// one block and therefore in one layer).
+template <bool TWO, int SCALES, int COORDS>
+__global__ __launch_bounds__(kWgThreads)
+__attribute__((amdgpu_waves_per_eu(kDecodeWaves, kDecodeWaves)))
+void k_decode(const DecWorker* __restrict__ workers, const DecUnit* __restrict__ units,
+              const int* __restrict__ chunk_first, DecodeArgs a)
+{
+    constexpr int kUnitPieces = 2 * COORDS;                  // 32 * COORDS bytes
+    constexpr int kChunkUnits = kDecPieces / kUnitPieces;
+    static_assert(COORDS * kChunkUnits <= kDecAux, "a worker has at least one unit");
+    static_assert(kChunkUnits >= 16, "every worker fits a chunk");
+    __shared__ u32x4_t lds_chunk[2][kDecPieces + 1];         // one more: a lane may read a word past its own
+    __shared__ float lds_aux[SCALES ? 2 : 1][SCALES ? kDecAux : 1];
+    __shared__ float lds_aux2[SCALES == 2 && TWO ? 2 : 1][SCALES == 2 && TWO ? kDecAux : 1];
+    __shared__ uint8_t lds_worker[kMaxWorkers];
+    const int tid = threadIdx.x;
+    float acc[COORDS];
+    float acc2[TWO ? COORDS : 1];
+#pragma unroll
+    for (int q = 0; q < COORDS; ++q) acc[q] = 0.f;
+#pragma unroll
+    for (int q = 0; q < (TWO ? COORDS : 1); ++q) acc2[q] = 0.f;
+    auto store_tile = [&](int64_t tile) {
+        const int64_t m0 = (tile * kWgThreads + tid) * COORDS;
+        store_coords<COORDS>(a.ghat + m0, acc, m0, a.d);
+        if constexpr (TWO) store_coords<COORDS>(a.ghat2 + m0, acc2, m0, a.d);
+    };
+    int64_t tile = blockIdx.x;
+    if (a.n_chunks == 0) {  // nobody arrived
+        for (; tile < a.n_tiles; tile += gridDim.x) store_tile(tile);
+        return;
+    }
+    if (SCALES == 1) {
+        for (int i = tid; i < a.n_arrived; i += kWgThreads) lds_worker[i] = (uint8_t)workers[i].worker;
+        __syncthreads();
+    }
+    u32x4_t r[kDecPerThread];
+    float aux[2] = {0.f, 0.f}, aux2[2] = {0.f, 0.f};
+    auto request = [&](int64_t t, int c) {
+        if (SCALES != 0) {  // weights or scales of the chunk's workers in the tile's buckets (= blocks)
+            const int s0 = load_uniform(chunk_first + c), s1 = load_uniform(chunk_first + c + 1);
+            const int64_t last_block = (a.d - 1) / kBlockCoords;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int e = tid + j * kWgThreads;
+                const int slot = s0 + e / COORDS < s1 ? s0 + e / COORDS : s1 - 1;
+                int64_t block = t * COORDS + e % COORDS;
+                block = block < last_block ? block : last_block;
+                if (SCALES == 1) {
+                    aux[j] = a.scales[(int64_t)lds_worker[slot] * a.nb + block];
+                } else {
+                    const int64_t row = (int64_t)a.block_layer[block] * a.n_arrived;
+                    aux[j] = a.coef_layer[row + slot];
+                    if (TWO) aux2[j] = a.coef2_layer[row + slot];
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < kDecPerThread; ++j) {
+            const int p = tid + j * kWgThreads;
+            const DecUnit un = units[c * kChunkUnits + p / kUnitPieces];
+            // pieces past the end of the stream (coordinates past the end of the vector): its last one instead
+            uint32_t at = (uint32_t)t * un.tile_pieces + (uint32_t)(p % kUnitPieces);
+            at = at < un.pieces ? at : un.pieces - 1u;
+            r[j] = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4_t*)un.codes + at);
+        }
+    };
+    auto deliver = [&](int x) {
+#pragma unroll
+        for (int j = 0; j < kDecPerThread; ++j) lds_chunk[x][tid + j * kWgThreads] = r[j];
+        if (SCALES != 0) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                lds_aux[SCALES ? x : 0][SCALES ? tid + j * kWgThreads : 0] = aux[j];
+                if (SCALES == 2 && TWO)
+                    lds_aux2[SCALES == 2 && TWO ? x : 0][SCALES == 2 && TWO ? tid + j * kWgThreads : 0] = aux2[j];
+            }
+        }
+    };
+    request(tile, 0);
+    deliver(0);
+    __syncthreads();
+    int c = 0, x = 0;
+    for (;;) {
+        const bool tile_ends = c + 1 == a.n_chunks;
+        const int c_next = tile_ends ? 0 : c + 1;
+        const int64_t tile_next = tile_ends ? tile + gridDim.x : tile;
+        const bool more = tile_next < a.n_tiles;
+        if (more) request(tile_next, c_next);
+        const int s0 = load_uniform(chunk_first + c), s1 = load_uniform(chunk_first + c + 1);
+        auto record = [&](int slot) {  // coef, coef2, width, pos
+            return *(const __attribute__((address_space(4))) u32x4_t*)(workers + slot);
+        };
+        u32x4_t next = record(s0);
+        for (int slot = s0; slot < s1; ++slot) {
+            const u32x4_t wk = next;
+            next = record(slot + 1 < s1 ? slot + 1 : slot);  // in flight during this worker
+            float c1 = __uint_as_float(wk.x), c2 = TWO ? __uint_as_float(wk.y) : 0.f;
+            if (SCALES != 0) {
+                const int e = (slot - s0) * COORDS + tid * COORDS / kWgThreads;
+                const float s = lds_aux[x][e];
+                if (SCALES == 1) {
+                    c1 = c1 * s;
+                    c2 = c2 * s;
+                } else {
+                    c1 = s;
+                    if (TWO) c2 = lds_aux2[SCALES == 2 && TWO ? x : 0][SCALES == 2 && TWO ? e : 0];
+                }
+            }
+            const uint32_t* part = reinterpret_cast<const uint32_t*>(&lds_chunk[x][wk.w * kUnitPieces]);
+            uint32_t mask = wk.z;
+            if (SCALES != 0) {  // the weights differ from lane to lane: one choice for the wave
+                const uint64_t no = __builtin_amdgcn_ballot_w64(!(halves_exactly(c1) & (TWO ? halves_exactly(c2) : true)));
+                mask = mask == 4u && no == 0 ? 1u : mask;
+            }
+            if (mask & 0x1Fu) decode_any<0, 4, COORDS, TWO>(mask, part, c1, c2, acc, acc2);
+            if (mask & ~0x1Fu) {
+                if (mask & 0x1E0u) decode_any<5, 8, COORDS, TWO>(mask, part, c1, c2, acc, acc2);
+                if (mask & 0x1E00u) decode_any<9, 12, COORDS, TWO>(mask, part, c1, c2, acc, acc2);
+                if (mask & 0x1E000u) decode_any<13, 16, COORDS, TWO>(mask, part, c1, c2, acc, acc2);
+            }
+        }
+        if (tile_ends) {
+            store_tile(tile);
+#pragma unroll
+            for (int q = 0; q < COORDS; ++q) acc[q] = 0.f;
+#pragma unroll
+            for (int q = 0; q < (TWO ? COORDS : 1); ++q) acc2[q] = 0.f;
+        }
+        if (!more) break;  // the same for every wave of the workgroup
+        // the other buffer was last read before the barrier that ended the previous turn
+        x ^= 1;
+        deliver(x);
+        __syncthreads();
+        c = c_next;
+        tile = tile_next;
+    }
+}
+
+// ---- host side
+template <bool TWO, int SCALES, int COORDS>
+static void launch_decode_main(hipStream_t stream, const DecodeTables& tab, DecodeArgs a)
+{
+    a.n_tiles = (a.d + kWgThreads * COORDS - 1) / (kWgThreads * COORDS);
+    const int64_t resident = 256 * kDecodeWaves;  // workgroups the chip holds: one wave each on every SIMD
+    const unsigned grid = (unsigned)(a.n_tiles < resident ? a.n_tiles : resident);
+    hipLaunchKernelGGL((k_decode<TWO, SCALES, COORDS>), dim3(grid), dim3(kWgThreads), 0, stream, tab.workers, tab.units,
+                       tab.chunk_first, a);
+}
+
+template <bool TWO, int SCALES, int CAP>
+static hipError_t launch_decode_cap(const DecodeStreams& in, int coords, const DecodeTables& tab, int n_layers,
+                                    const float* scales, const Workspace* ws, DecodeArgs a, hipStream_t stream)
+{
+    DecodeList<CAP> list;
+    list.n_arrived = in.n_arrived;
+    list.groups = (uint32_t)((a.d + 127) / 128);
+    list.units_per_chunk = kDecChunkBytes / (32 * coords);
+    int chunk = -1, fill = list.units_per_chunk;
+    for (int i = 0; i < in.n_arrived; ++i) {  // consecutive workers, whole, as long as the chunk holds them
+        const int b = in.bits[i];
+        if (fill + b > list.units_per_chunk) {
+            ++chunk;
+            fill = 0;
+        }
+        list.codes[i] = in.codes[i];
+        list.w[i] = in.w[i];
+        list.v[i] = in.v[i];
+        list.bits[i] = in.bits[i];
+        list.worker[i] = in.worker[i];
+        list.chunk[i] = (uint8_t)chunk;
+        list.pos[i] = (uint8_t)fill;
+        fill += b;
+    }
+    a.n_arrived = in.n_arrived;
+    a.n_chunks = chunk + 1;
+    if (in.n_arrived > 0) {
+        hipLaunchKernelGGL((k_decode_table<CAP, SCALES, TWO>), dim3(SCALES == 2 ? n_layers : 1), dim3(kWgThreads), 0,
+                           stream, list, scales, n_layers, tab, SCALES == 2 ? ws->coef_layer : nullptr,
+                           SCALES == 2 ? ws->coef2_layer : nullptr);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if constexpr (!TWO) {
+        if (coords == 16) launch_decode_main<TWO, SCALES, 16>(stream, tab, a);
+    }
+    if (coords == 8) launch_decode_main<TWO, SCALES, 8>(stream, tab, a);
+    return hipGetLastError();
+}
+
+// Coordinates per lane.  Sixteen halve the per-worker overhead of eight, eight double the number of waves:
+// below 2^21 coordinates a 16-coordinate tiling leaves most of the chip's wave slots empty (64 workers,
+// three bits: 1 M coordinates 26.2 us with eight, 29.6 with sixteen; 4 M 42.5 and 39.5; 25.6 M 183 and
+// 148).  The two-track decode holds twice the accumulators and is faster with eight throughout (50 workers,
+// four bits, 5.4 M coordinates, with the update: 79.5 us with eight, 86.8 with sixteen; 24 workers, 25.6 M:
+// 260 and 285).
+constexpr int64_t kDecodeWide = (int64_t)1 << 21;
 template <bool TWO, int SCALES>
-__global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_waves_per_eu(TWO ? 1 : 6, TWO ? 8 : 6))) void k_decode(const WorkerD* __restrict__ wd,
-                                                       const float* __restrict__ coef2,
-                                                       const float* const* __restrict__ srow, DecodeArgs a)
+static hipError_t launch_decode_scales(const DecodeStreams& in, const DecodeTables& tab, int n_layers,
+                                       const float* scales, const Workspace* ws, const DecodeArgs& a, hipStream_t stream)
 {
-    const int64_t t = (int64_t)blockIdx.x * kWgThreads + threadIdx.x;
-    const int64_t m0 = t * kDecCoords;
-    if (m0 >= a.d) return;
-    float acc[kDecCoords];
-    float acc2[TWO ? kDecCoords : 1];
-#pragma unroll
-    for (int q = 0; q < kDecCoords; ++q) acc[q] = 0.f;
-#pragma unroll
-    for (int q = 0; q < (TWO ? kDecCoords : 1); ++q) acc2[q] = 0.f;
-    constexpr bool BUCKET = SCALES != 0;  // the weights differ from lane to lane
-    int64_t layer_row = 0;
-    if (SCALES == 2) layer_row = (int64_t)a.block_layer[t >> 3] * a.n_arrived;
-    for (int e = 0; e < a.n_arrived; ++e) {
-        const WorkerD wk = wd[e];  // wave-uniform: one scalar 16-byte load
-        float c1 = wk.coef;
-        float c2 = TWO ? coef2[e] : 0.f;
-        if (SCALES == 1) {  // the lane's 32 coordinates lie in one 256-coordinate bucket
-            const float sc = ((const __attribute__((address_space(1))) float*)srow[e])[t >> 3];
-            c1 = c1 * sc;
-            c2 = c2 * sc;
-        } else if (SCALES == 2) {
-            c1 = a.coef_layer[layer_row + e];
-            if (TWO) c2 = a.coef2_layer[layer_row + e];
-        }
-        const int b = (int)wk.bits;
-        const global_u32* src = (const global_u32*)wk.codes + t * b;
-        switch (b) {
-            case 1: decode_words<1, TWO>(src, c1, c2, acc, acc2); break;
-            case 2:
-                // wave-uniform choice (without bucket-wise scales the weights are per worker)
-                if (!BUCKET && halves_exactly(c1) && (!TWO || halves_exactly(c2)))
-                    decode_words_2bit<TWO>(src, 0.5f * c1, 0.5f * c2, acc, acc2);
-                else
-                    decode_words<2, TWO>(src, c1, c2, acc, acc2);
-                break;
-            case 3: decode_words<3, TWO>(src, c1, c2, acc, acc2); break;
-            case 4: decode_words<4, TWO>(src, c1, c2, acc, acc2); break;
-            case 5: decode_words<5, TWO>(src, c1, c2, acc, acc2); break;
-            case 6: decode_words<6, TWO>(src, c1, c2, acc, acc2); break;
-            case 7: decode_words<7, TWO>(src, c1, c2, acc, acc2); break;
-            case 8: decode_words<8, TWO>(src, c1, c2, acc, acc2); break;
-            case 9: decode_words<9, TWO>(src, c1, c2, acc, acc2); break;
-            case 10: decode_words<10, TWO>(src, c1, c2, acc, acc2); break;
-            case 11: decode_words<11, TWO>(src, c1, c2, acc, acc2); break;
-            case 12: decode_words<12, TWO>(src, c1, c2, acc, acc2); break;
-            case 13: decode_words<13, TWO>(src, c1, c2, acc, acc2); break;
-            case 14: decode_words<14, TWO>(src, c1, c2, acc, acc2); break;
-            case 15: decode_words<15, TWO>(src, c1, c2, acc, acc2); break;
-            default: decode_words<16, TWO>(src, c1, c2, acc, acc2); break;
-        }
-    }
-    store_coords(a.ghat + m0, acc, m0, a.d);
-    if constexpr (TWO) store_coords(a.ghat2 + m0, acc2, m0, a.d);
+    const int coords = !TWO && a.d >= kDecodeWide ? 16 : 8;
+    // the launch copies its arguments at about 1.7 ns a byte: 20 bytes per worker it has room for
+    if (in.n_arrived <= 16) return launch_decode_cap<TWO, SCALES, 16>(in, coords, tab, n_layers, scales, ws, a, stream);
+    if (in.n_arrived <= 64) return launch_decode_cap<TWO, SCALES, 64>(in, coords, tab, n_layers, scales, ws, a, stream);
+    return launch_decode_cap<TWO, SCALES, kArgWorkers>(in, coords, tab, n_layers, scales, ws, a, stream);
 }
 
-template <bool TWO>
-static void launch_decode_kernel(int scales_kind, unsigned grid, hipStream_t stream, const Workspace& ws,
-                                 const DecodeArgs& a)
+// tables inside a block of decode_table_bytes(n) bytes
+static DecodeTables decode_tables(void* base, int n)
 {
-    const float* c2 = TWO ? ws.coef2 : nullptr;
-    if (scales_kind == 2)
-        hipLaunchKernelGGL((k_decode<TWO, 2>), dim3(grid), dim3(kWgThreads), 0, stream, ws.wd, c2,
-                           (const float* const*)nullptr, a);
-    else if (scales_kind == 1)
-        hipLaunchKernelGGL((k_decode<TWO, 1>), dim3(grid), dim3(kWgThreads), 0, stream, ws.wd, c2,
-                           (const float* const*)ws.srow, a);
-    else
-        hipLaunchKernelGGL((k_decode<TWO, 0>), dim3(grid), dim3(kWgThreads), 0, stream, ws.wd, c2,
-                           (const float* const*)nullptr, a);
+    char* p = static_cast<char*>(base);
+    DecodeTables t;
+    t.workers = reinterpret_cast<DecWorker*>(p);
+    t.units = reinterpret_cast<DecUnit*>(p + sizeof(DecWorker) * (size_t)n);
+    t.chunk_first = reinterpret_cast<int*>(p + sizeof(DecWorker) * (size_t)n + sizeof(DecUnit) * (size_t)decode_units(n));
+    return t;
 }
 
-// Layer-wise scales, prologue: workgroup l, thread i.  The weight of arrived worker i in layer l,
-// w_i * scale_il / L_i (binary64, one rounding: the per-vector formula with the layer's scale),
-// goes to [l][slot]; workgroup 0 also writes the table of streams and bit-widths.
-__global__ __launch_bounds__(kWgThreads) void k_decode_table_layers(int n, int n_layers, int n_arrived,
-                                                                    DecodeStreams in, const float* scales,
-                                                                    WorkerD* wd, float* coef_layer)
+hipError_t launch_decode(int n, int64_t d, const DecodeStreams& in, bool two, const float* scales, int64_t nb,
+                         const Workspace& ws, float* ghat, float* ghat2, hipStream_t stream)
 {
-    const int l = blockIdx.x;
-    for (int i = threadIdx.x; i < n; i += kWgThreads) {
-        const uint32_t slot = in.slot[i];
-        if (slot == 0xFFFFu) continue;
-        const int b = in.bits[i];
-        const double L = b >= 2 ? (double)((1 << (b - 1)) - 1) : 1.0;
-        coef_layer[(int64_t)l * n_arrived + slot] =
-            (float)(((double)in.w[i] * (double)scales[(int64_t)i * n_layers + l]) / L);
-        if (l == 0) wd[slot] = WorkerD{in.codes[i], 0.f, (uint32_t)b};
-    }
-}
-
-// the same for the second decoding vector of the two-track decode
-__global__ __launch_bounds__(kWgThreads) void k_decode_table2_layers(int n, int n_layers, int n_arrived,
-                                                                     DecodeSecond in, const float* scales,
-                                                                     float* coef2_layer)
-{
-    const int l = blockIdx.x;
-    for (int i = threadIdx.x; i < n; i += kWgThreads) {
-        const uint32_t slot = in.slot[i];
-        if (slot == 0xFFFFu) continue;
-        const int b = in.bits[i];
-        const double L = b >= 2 ? (double)((1 << (b - 1)) - 1) : 1.0;
-        coef2_layer[(int64_t)l * n_arrived + slot] =
-            (float)(((double)in.v[i] * (double)scales[(int64_t)i * n_layers + l]) / L);
-    }
-}
-
-hipError_t launch_decode(int n, int n_arrived, int64_t d, const DecodeStreams& in,
-                         const float* scales, int64_t nb, const Workspace& ws, float* ghat,
-                         hipStream_t stream)
-{
-    const bool layers = ws.n_layers > 0;
-    if (layers)
-        hipLaunchKernelGGL(k_decode_table_layers, dim3(ws.n_layers), dim3(kWgThreads), 0, stream, n, ws.n_layers,
-                           n_arrived, in, scales, ws.wd, ws.coef_layer);
-    else
-        hipLaunchKernelGGL(k_decode_table, dim3(1), dim3(kWgThreads), 0, stream, n, in, scales, nb, ws.wd, ws.srow);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    DecodeArgs a{n_arrived, d, ghat, nullptr, ws.block_layer, ws.coef_layer, nullptr};
-    const int64_t nthreads = (d + kDecCoords - 1) / kDecCoords;
-    const unsigned grid = (unsigned)((nthreads + kWgThreads - 1) / kWgThreads);
-    launch_decode_kernel<false>(layers ? 2 : (nb > 0 ? 1 : 0), grid, stream, ws, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_decode2(int n, int n_arrived, int64_t d, const DecodeStreams& in, const DecodeSecond& second,
-                          const float* scales, int64_t nb, const Workspace& ws, float* ghat, float* ghat2,
-                          hipStream_t stream)
-{
-    const bool layers = ws.n_layers > 0;
-    if (layers)
-        hipLaunchKernelGGL(k_decode_table_layers, dim3(ws.n_layers), dim3(kWgThreads), 0, stream, n, ws.n_layers,
-                           n_arrived, in, scales, ws.wd, ws.coef_layer);
-    else
-        hipLaunchKernelGGL(k_decode_table, dim3(1), dim3(kWgThreads), 0, stream, n, in, scales, nb, ws.wd, ws.srow);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (layers)
-        hipLaunchKernelGGL(k_decode_table2_layers, dim3(ws.n_layers), dim3(kWgThreads), 0, stream, n, ws.n_layers,
-                           n_arrived, second, scales, ws.coef2_layer);
-    else
-        hipLaunchKernelGGL(k_decode_table2, dim3(1), dim3(kWgThreads), 0, stream, n, second, scales, nb, ws.coef2);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    DecodeArgs a{n_arrived, d, ghat, ghat2, ws.block_layer, ws.coef_layer, ws.coef2_layer};
-    const int64_t nthreads = (d + kDecCoords - 1) / kDecCoords;
-    const unsigned grid = (unsigned)((nthreads + kWgThreads - 1) / kWgThreads);
-    launch_decode_kernel<true>(layers ? 2 : (nb > 0 ? 1 : 0), grid, stream, ws, a);
-    return hipGetLastError();
+    DecodeArgs a{};
+    a.d = d;
+    a.ghat = ghat;
+    a.ghat2 = ghat2;
+    a.scales = scales;
+    a.nb = nb;
+    a.block_layer = ws.block_layer;
+    a.coef_layer = ws.coef_layer;
+    a.coef2_layer = ws.coef2_layer;
+    const DecodeTables tab = decode_tables(ws.dec, n);
+    if (ws.n_layers > 0)
+        return two ? launch_decode_scales<true, 2>(in, tab, ws.n_layers, scales, &ws, a, stream)
+                   : launch_decode_scales<false, 2>(in, tab, ws.n_layers, scales, &ws, a, stream);
+    if (nb > 0)
+        return two ? launch_decode_scales<true, 1>(in, tab, 0, scales, &ws, a, stream)
+                   : launch_decode_scales<false, 1>(in, tab, 0, scales, &ws, a, stream);
+    return two ? launch_decode_scales<true, 0>(in, tab, 0, scales, &ws, a, stream)
+               : launch_decode_scales<false, 0>(in, tab, 0, scales, &ws, a, stream);
 }
 
 // ---------------------------------------------------------------------------------------
-// Decode for callers that cannot allocate (HIP graph capture, tight serving loops): the table
-// of arrived workers and their rows of bucket-wise scales, which agc_decode keeps in the
-// context's workspace, live in a fixed device array instead.  Each GPU holds its own copy of
-// the array at its own address; host code only ever uses the address that
-// hipGetSymbolAddress returned for the device that was current.
+// Decode for callers that cannot allocate (HIP graph capture, tight serving loops): the tables of
+// arrived workers, which agc_decode keeps in the context's workspace, live in a fixed device array
+// instead.  Each GPU holds its own copy of the array at its own address; host code only ever uses
+// the address that hipGetSymbolAddress returned for the device that was current.
 // ---------------------------------------------------------------------------------------
-constexpr size_t kScratchTableBytes = sizeof(WorkerD) * kMaxWorkers;          // 4096
-constexpr size_t kScratchRowsBytes = sizeof(const float*) * kMaxWorkers;      // 2048
-constexpr size_t kScratchBytes = kScratchTableBytes + kScratchRowsBytes;
-static_assert(kScratchBytes == kStaticScratchBytes, "size stated in the launch interface");
-static_assert(kScratchTableBytes % 256 == 0, "the rows of scales start on an aligned offset");
-
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+static __device__ __align__(256) unsigned char scratch[decode_table_bytes(kMaxWorkers)];
 
 namespace {
 constexpr int kMaxDevices = 64;
@@ -849,8 +1007,8 @@ std::mutex g_scratch_lock;
 void* g_scratch_ptr[kMaxDevices];  // per device: the device address of `scratch`, null = not resolved yet
 }  // namespace
 
-hipError_t launch_decode_static(int n, int n_arrived, int64_t d, const DecodeStreams& in, const float* scales,
-                                int64_t nb, float* ghat, hipStream_t stream)
+hipError_t launch_decode_static(int64_t d, const DecodeStreams& in, const float* scales, int64_t nb, float* ghat,
+                                hipStream_t stream)
 {
     int dev = -1;
     hipError_t e = hipGetDevice(&dev);
@@ -868,23 +1026,16 @@ hipError_t launch_decode_static(int n, int n_arrived, int64_t d, const DecodeStr
         }
         base = g_scratch_ptr[dev];
     }
-    WorkerD* wd = reinterpret_cast<WorkerD*>(base);
-    const float** srow = reinterpret_cast<const float**>(static_cast<unsigned char*>(base) + kScratchTableBytes);
-    // the prologue rewrites every entry that the decode kernel reads (slots 0..n_arrived-1), so
-    // nothing of the previous call's contents has to be cleared
-    hipLaunchKernelGGL(k_decode_table, dim3(1), dim3(kWgThreads), 0, stream, n, in, scales, nb, wd, srow);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    DecodeArgs a{n_arrived, d, ghat, nullptr, nullptr, nullptr, nullptr};
-    const int64_t nthreads = (d + kDecCoords - 1) / kDecCoords;
-    const unsigned grid = (unsigned)((nthreads + kWgThreads - 1) / kWgThreads);
-    if (nb > 0)
-        hipLaunchKernelGGL((k_decode<false, 1>), dim3(grid), dim3(kWgThreads), 0, stream, wd, (const float*)nullptr,
-                           (const float* const*)srow, a);
-    else
-        hipLaunchKernelGGL((k_decode<false, 0>), dim3(grid), dim3(kWgThreads), 0, stream, wd,
-                           (const float*)nullptr, (const float* const*)nullptr, a);
-    return hipGetLastError();
+    // the prologue rewrites every entry that the decode kernel reads, so nothing of the previous
+    // call's contents has to be cleared
+    DecodeArgs a{};
+    a.d = d;
+    a.ghat = ghat;
+    a.scales = scales;
+    a.nb = nb;
+    const DecodeTables tab = decode_tables(base, kMaxWorkers);
+    return nb > 0 ? launch_decode_scales<false, 1>(in, tab, 0, scales, nullptr, a, stream)
+                  : launch_decode_scales<false, 0>(in, tab, 0, scales, nullptr, a, stream);
 }
 
 // Adam with the two-track estimates (Sec. V): first moment from the unbiased estimate, second
