@@ -77,11 +77,14 @@ void free_layers(agc_ctx* c)
     if (c->ws.block_layer) (void)hipFree(const_cast<uint8_t*>(c->ws.block_layer));
     if (c->ws.seg_first) (void)hipFree(const_cast<int*>(c->ws.seg_first));
     if (c->ws.seg_blocks) (void)hipFree(const_cast<uint8_t*>(c->ws.seg_blocks));
-    if (c->ws.layer_seg) (void)hipFree(const_cast<int*>(c->ws.layer_seg));
+    if (c->ws.group_seg) (void)hipFree(const_cast<int*>(c->ws.group_seg));
+    if (c->ws.layer_group) (void)hipFree(const_cast<int*>(c->ws.layer_group));
     c->ws.seg_first = nullptr;
     c->ws.seg_blocks = nullptr;
-    c->ws.layer_seg = nullptr;
+    c->ws.group_seg = nullptr;
+    c->ws.layer_group = nullptr;
     c->ws.nseg_layers = 0;
+    c->ws.ngroup_layers = 0;
     if (c->ws.coef_layer) (void)hipFree(c->ws.coef_layer);
     if (c->ws.coef2_layer) (void)hipFree(c->ws.coef2_layer);
     c->ws.block_layer = nullptr;
@@ -232,7 +235,6 @@ agc_status agc_create(agc_ctx** out, int n, int k, int64_t d, const agc_opts* op
     const int64_t nblocks = (d + 255) / 256;
     c->ws.nseg = (nblocks + 3) / 4;
     c->ws.ngroup = (c->ws.nseg + 63) / 64;
-    c->ws.nsuper = (c->ws.ngroup + 63) / 64;
     if (o.bucket) {
         // the scales need no reduction workspace
     } else if (o.scale_mode == AGC_SCALE_MAXABS) {
@@ -245,7 +247,6 @@ agc_status agc_create(agc_ctx** out, int n, int k, int64_t d, const agc_opts* op
     } else {
         e = dev_alloc(&c->ws.part_sq, (size_t)c->ws.nseg * n);
         if (e == hipSuccess) e = dev_alloc(&c->ws.group_sq, (size_t)c->ws.ngroup * n);
-        if (e == hipSuccess) e = dev_alloc(&c->ws.super_sq, (size_t)c->ws.nsuper * n);
     }
     if (e == hipSuccess) e = dev_alloc(&c->ws.wq, (size_t)n);
     if (e == hipSuccess) e = hipMalloc(&c->ws.dec, agc::decode_table_bytes(n));
@@ -266,7 +267,6 @@ void agc_destroy(agc_ctx* c)
     if (c->ws.part_max) (void)hipFree(c->ws.part_max);
     if (c->ws.part_sq) (void)hipFree(c->ws.part_sq);
     if (c->ws.group_sq) (void)hipFree(c->ws.group_sq);
-    if (c->ws.super_sq) (void)hipFree(c->ws.super_sq);
     if (c->ws.wq) (void)hipFree(c->ws.wq);
     if (c->ws.dec) (void)hipFree(c->ws.dec);
     for (auto& ring : c->events)
@@ -387,25 +387,28 @@ agc_status agc_set_layers(agc_ctx* c, int n_layers, const int64_t* layer_end)
     }
     // Euclidean scale: the segments of every layer's own summation tree
     const bool l2 = c->opts.scale_mode == AGC_SCALE_L2;
-    std::vector<int> seg_first, layer_seg;
+    std::vector<int> seg_first, group_seg, layer_group;
     std::vector<uint8_t> seg_blocks;
     if (l2) {
         int64_t first = 0;
         for (int l = 0; l < n_layers; ++l) {
             const int64_t end_block = (layer_end[l] + 255) / 256;  // one past the layer's last block
-            layer_seg.push_back((int)seg_first.size());
+            layer_group.push_back((int)group_seg.size());
             for (int64_t blk = first; blk < end_block; blk += 4) {
+                if ((blk - first) % (4 * 64) == 0) group_seg.push_back((int)seg_first.size());
                 seg_first.push_back((int)blk);
                 seg_blocks.push_back((uint8_t)std::min<int64_t>(4, end_block - blk));
             }
             first = end_block;
         }
-        layer_seg.push_back((int)seg_first.size());
+        layer_group.push_back((int)group_seg.size());
+        group_seg.push_back((int)seg_first.size());
     }
     int* d_seg_first = nullptr;
     uint8_t* d_seg_blocks = nullptr;
-    int* d_layer_seg = nullptr;
-    double* d_part_sq = nullptr;
+    int* d_group_seg = nullptr;
+    int* d_layer_group = nullptr;
+    double *d_part_sq = nullptr, *d_group_sq = nullptr;
     uint8_t* d_layer = nullptr;
     agc::WorkerQ* d_wq = nullptr;
     float *d_c1 = nullptr, *d_c2 = nullptr;
@@ -421,11 +424,14 @@ agc_status agc_set_layers(agc_ctx* c, int n_layers, const int64_t* layer_end)
     if (e == hipSuccess && l2) {
         e = dev_alloc(&d_seg_first, seg_first.size());
         if (e == hipSuccess) e = dev_alloc(&d_seg_blocks, seg_blocks.size());
-        if (e == hipSuccess) e = dev_alloc(&d_layer_seg, layer_seg.size());
+        if (e == hipSuccess) e = dev_alloc(&d_group_seg, group_seg.size());
+        if (e == hipSuccess) e = dev_alloc(&d_layer_group, layer_group.size());
+        if (e == hipSuccess) e = dev_alloc(&d_group_sq, (group_seg.size() - 1) * (size_t)c->n);
         if (e == hipSuccess) e = dev_alloc(&d_part_sq, seg_first.size() * (size_t)c->n);
         if (e == hipSuccess) e = hipMemcpy(d_seg_first, seg_first.data(), sizeof(int) * seg_first.size(), hipMemcpyHostToDevice);
         if (e == hipSuccess) e = hipMemcpy(d_seg_blocks, seg_blocks.data(), seg_blocks.size(), hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = hipMemcpy(d_layer_seg, layer_seg.data(), sizeof(int) * layer_seg.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemcpy(d_group_seg, group_seg.data(), sizeof(int) * group_seg.size(), hipMemcpyHostToDevice);
+        if (e == hipSuccess) e = hipMemcpy(d_layer_group, layer_group.data(), sizeof(int) * layer_group.size(), hipMemcpyHostToDevice);
     }
     if (e == hipSuccess) e = dev_alloc(&d_wq, entries);
     if (e == hipSuccess) e = dev_alloc(&d_c1, entries);
@@ -435,7 +441,9 @@ agc_status agc_set_layers(agc_ctx* c, int n_layers, const int64_t* layer_end)
         if (d_layer) (void)hipFree(d_layer);
         if (d_seg_first) (void)hipFree(d_seg_first);
         if (d_seg_blocks) (void)hipFree(d_seg_blocks);
-        if (d_layer_seg) (void)hipFree(d_layer_seg);
+        if (d_group_seg) (void)hipFree(d_group_seg);
+        if (d_layer_group) (void)hipFree(d_layer_group);
+        if (d_group_sq) (void)hipFree(d_group_sq);
         if (d_part_sq) (void)hipFree(d_part_sq);
         if (d_max) (void)hipFree(d_max);
         if (d_wq) (void)hipFree(d_wq);
@@ -458,8 +466,12 @@ agc_status agc_set_layers(agc_ctx* c, int n_layers, const int64_t* layer_end)
         c->ws.part_sq = d_part_sq;
         c->ws.seg_first = d_seg_first;
         c->ws.seg_blocks = d_seg_blocks;
-        c->ws.layer_seg = d_layer_seg;
+        (void)hipFree(c->ws.group_sq);   // likewise for the groups
+        c->ws.group_sq = d_group_sq;
+        c->ws.group_seg = d_group_seg;
+        c->ws.layer_group = d_layer_group;
         c->ws.nseg_layers = (int64_t)seg_first.size();
+        c->ws.ngroup_layers = (int64_t)group_seg.size() - 1;
     }
     c->ws.coef_layer = d_c1;
     c->ws.coef2_layer = d_c2;

@@ -129,11 +129,10 @@ struct Workspace {
     uint32_t* part_max;   // [max_rows][n] running max |f_i| as bit patterns, all zero between steps (max-abs scale)
     int max_rows;         // kMaxSlots, or n_layers * kLayerSub if that is more
     double* part_sq;      // [nseg][n]   per-segment sum of squares             (Euclidean scale)
-    double* group_sq;     // [n][ngroup]
-    double* super_sq;     // [n][nsuper]
+    double* group_sq;     // [n][ngroup] (layer-wise: [n][ngroup_layers])
     WorkerQ* wq;          // [n]  written by the scale finalize
     void* dec;            // decode_table_bytes(n) bytes: tables of the arrived workers, written by the decode prologue
-    int64_t nseg, ngroup, nsuper;
+    int64_t nseg, ngroup;
     // layer-wise scales (n_layers > 0; max-abs only): the layer of every 256-coordinate block, and
     // the decode weights w_i * scale_il / L_i (and v_i * ...) of the arrived workers, [layer][slot].
     // wq then holds one table per layer, [layer][n].
@@ -143,8 +142,9 @@ struct Workspace {
     // (up to four blocks) are counted from each layer's first block
     const int* seg_first;        // [nseg_layers] first block of the segment
     const uint8_t* seg_blocks;   // [nseg_layers] its number of blocks, 1..4
-    const int* layer_seg;        // [n_layers + 1] first segment of every layer
-    int64_t nseg_layers;
+    const int* group_seg;        // [ngroup_layers + 1] first segment of every group (64 of one layer at most)
+    const int* layer_group;      // [n_layers + 1] first group of every layer
+    int64_t nseg_layers, ngroup_layers;
     float* coef_layer;    // [n_layers][n]
     float* coef2_layer;   // [n_layers][n]
 };
@@ -153,16 +153,26 @@ constexpr int kMaxSlots = 256;  // rows of the max-abs array; a block folds into
 constexpr int kMaxLayers = 256;  // layer-wise scales: a block's layer fits a byte
 constexpr int kLayerSub = 16;    // with layer-wise scales layer l owns rows l*kLayerSub .. +kLayerSub-1 of the array
 
-struct QuantStreams {      // host arrays of the encode call, as kernel arguments of the finalize
+struct QuantStreams {      // host arrays of the encode call
     void* codes[kArgWorkers];
     uint8_t bits[kArgWorkers];
     uint8_t stage_start[kArgWorkers];  // stage_starts() of the bit-widths
 };
 
-struct StepWeights {       // decode side of a fused step, as kernel arguments of the table kernels
+struct StepWeights {       // decode side of a fused step
     float w[kArgWorkers];
     uint8_t arrived[kArgWorkers];
     int fuse;              // 0: plain encode+quantize, the two arrays are ignored
+};
+
+template <int CAP>
+struct QuantList {         // both as kernel arguments of the table kernels, for up to CAP workers
+    void* codes[CAP];
+    float w[CAP];
+    uint8_t bits[CAP];
+    uint8_t stage_start[CAP];
+    uint8_t arrived[CAP];
+    int fuse;
 };
 
 struct DecodeStreams {     // the arrived workers of a decode call, in ascending order (host side)

@@ -324,36 +324,61 @@ __device__ __forceinline__ float inv16_of(float scale, int bits)
     return (q <= 3.402823466e+38f) ? q : 0.f;
 }
 
-// Euclidean scale, level 3 of the tree: one workgroup per group of 64 segments, thread t follows
-// worker t through the group's rows of [segment][worker] (coalesced) and adds them in segment order.
-__global__ __launch_bounds__(kWgThreads) void k_scale_groups(int n, Workspace ws)
+// Euclidean scale, level 3 of the tree: one workgroup per group of up to 64 segments, thread t follows
+// worker t through the group's rows of [segment][worker] (coalesced) and adds them in segment order.  The
+// rows are requested 32 at a time before the first addition: the kernel is one round trip to memory per
+// batch (batches of eight took 7-9 us, mostly waiting; now 5-6).  With layer-wise scales the groups of
+// every layer are counted from its first segment and listed in group_seg.
+__global__ __launch_bounds__(kWgThreads) void k_scale_groups(int n, Workspace ws, int64_t ngroup)
 {
+    constexpr int kBatch = 32;
     const int64_t g = blockIdx.x;
-    const int64_t s1 = (g + 1) * kGroupSegs < ws.nseg ? (g + 1) * kGroupSegs : ws.nseg;
+    int64_t s0 = g * kGroupSegs, s1 = s0 + kGroupSegs < ws.nseg ? s0 + kGroupSegs : ws.nseg;
+    if (ws.n_layers > 0) {
+        s0 = ws.group_seg[g];
+        s1 = ws.group_seg[g + 1];
+    }
     for (int i = threadIdx.x; i < n; i += kWgThreads) {
         const double* part = ws.part_sq + i;
         double acc = 0.0;
-        for (int64_t s0 = g * kGroupSegs; s0 < s1; s0 += 8) {
-            double v[8];  // loads first, then the additions in segment order
+        for (int64_t b0 = s0; b0 < s1; b0 += kBatch) {
+            double v[kBatch];  // past the group's end its last row is read again
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = s0 + u < s1 ? part[(s0 + u) * n] : 0.0;
+            for (int u = 0; u < kBatch; ++u) v[u] = part[(b0 + u < s1 ? b0 + u : s1 - 1) * n];
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (s0 + u < s1) acc = acc + v[u];
+            for (int u = 0; u < kBatch; ++u) acc = b0 + u < s1 ? acc + v[u] : acc;
         }
-        ws.group_sq[(int64_t)i * ws.ngroup + g] = acc;
+        ws.group_sq[(int64_t)i * ngroup + g] = acc;
     }
 }
 
-template <int MODE>
-__global__ __launch_bounds__(kWgThreads) void k_scale_finalize(int n, QuantStreams out, StepWeights sw,
-                                                               Workspace ws, float* scales)
+// record of one worker for the quantize pass
+template <int CAP>
+__device__ __forceinline__ WorkerQ worker_record(const QuantList<CAP>& in, int i, int n, float inv, float coef)
+{
+    // the staging area is written out after the last worker and before every worker that starts a new fill
+    const uint32_t flush = (i == n - 1 || in.stage_start[i + 1] == 0) ? 1u : 0u;
+    return WorkerQ{inv, (uint32_t)in.bits[i], in.codes[i], in.fuse ? coef : 0.f, in.fuse ? (uint32_t)in.arrived[i] : 0u,
+                   8u * in.stage_start[i], flush};
+}
+
+// decode weight of one grid unit, as the decode prologue forms it
+__device__ __forceinline__ float unit_weight(float w, float scale, int b)
+{
+    const double L = b >= 2 ? (double)((1 << (b - 1)) - 1) : 1.0;
+    return (float)(((double)w * (double)scale) / L);
+}
+
+// One workgroup per worker (and layer, with the Euclidean scale).
+template <int MODE, int CAP>
+__global__ __launch_bounds__(kWgThreads) void k_scale_finalize(int n, QuantList<CAP> in, Workspace ws, int64_t ngroup,
+                                                               float* scales)
 {
     const int i = blockIdx.x;
     const int tid = threadIdx.x;
-    __shared__ uint32_t red[kWgThreads];
     float scale;
     if (MODE == 1) {
+        __shared__ uint32_t red[kWgThreads];
         // this worker's column of the slot array: read it with loads that see the atomics of the
         // scale pass (they were performed in memory, past the caches), and leave zeros behind
         uint32_t m = 0u;
@@ -370,118 +395,107 @@ __global__ __launch_bounds__(kWgThreads) void k_scale_finalize(int n, QuantStrea
         }
         scale = __uint_as_float(red[0]);
     } else {
-        // level 3 (64 segments -> group) was formed by k_scale_groups
-        // level 4: 64 groups -> supergroup, in order
-        for (int64_t u = tid; u < ws.nsuper; u += kWgThreads) {
-            double acc = 0.0;
-            const int64_t g1 = (u + 1) * kGroupSegs < ws.ngroup ? (u + 1) * kGroupSegs : ws.ngroup;
-            for (int64_t g = u * kGroupSegs; g < g1; ++g) acc = acc + ws.group_sq[(int64_t)i * ws.ngroup + g];
-            ws.super_sq[(int64_t)i * ws.nsuper + u] = acc;
+        // Level 3 (64 segments -> group) was formed by k_scale_groups.  Four supergroups at a time: one
+        // thread per group fetches it, one per supergroup adds its 64 groups in order (level 4), the first
+        // adds the supergroups in order (level 5).
+        __shared__ double group[kWgThreads];
+        __shared__ double super[kWgThreads / kGroupSegs];
+        const int64_t g_begin = ws.n_layers > 0 ? ws.layer_group[blockIdx.y] : 0;
+        const int64_t g_end = ws.n_layers > 0 ? ws.layer_group[blockIdx.y + 1] : ngroup;
+        const double* sq = ws.group_sq + (int64_t)i * ngroup;
+        double total = 0.0;
+        for (int64_t g0 = g_begin; g0 < g_end; g0 += kWgThreads) {
+            if (g0 + tid < g_end) group[tid] = sq[g0 + tid];
+            __syncthreads();
+            if (tid < kWgThreads / kGroupSegs) {
+                const int64_t left = g_end - g0 - tid * kGroupSegs;
+                const int have = left < kGroupSegs ? (int)left : kGroupSegs;
+                double acc = 0.0;
+                for (int u = 0; u < have; ++u) acc = acc + group[tid * kGroupSegs + u];
+                super[tid] = acc;
+            }
+            __syncthreads();
+            if (tid == 0)
+                for (int u = 0; u < kWgThreads / kGroupSegs && g0 + u * kGroupSegs < g_end; ++u) total = total + super[u];
         }
-        __syncthreads();
-        // level 5: supergroups in order
-        if (tid == 0) {
-            double total = 0.0;
-            for (int64_t u = 0; u < ws.nsuper; ++u) total = total + ws.super_sq[(int64_t)i * ws.nsuper + u];
-            red[0] = __float_as_uint((float)sqrt(total));
-        }
-        __syncthreads();
-        scale = __uint_as_float(red[0]);
+        scale = (float)sqrt(total);  // thread 0 holds the total, and it alone goes on
     }
     if (tid == 0) {
-        scales[i] = scale;
-        const int b = out.bits[i];
-        // the staging area is written out after the last worker and before every worker that starts a new fill
-        const uint32_t flush = (i == n - 1 || out.stage_start[i + 1] == 0) ? 1u : 0u;
-        WorkerQ e{inv16_of(scale, b), (uint32_t)b, out.codes[i], 0.f, 0u, 8u * out.stage_start[i], flush};
-        if (sw.fuse) {  // decode weight of one grid unit, as the decode prologue forms it
-            const double L = b >= 2 ? (double)((1 << (b - 1)) - 1) : 1.0;
-            e.coef = (float)(((double)sw.w[i] * (double)scale) / L);
-            e.arrived = (uint32_t)sw.arrived[i];
-        }
-        ws.wq[i] = e;
+        const int l = MODE == 0 ? (int)blockIdx.y : 0, per = MODE == 0 ? (int)gridDim.y : 1;
+        scales[(int64_t)i * per + l] = scale;
+        const int b = in.bits[i];
+        ws.wq[(int64_t)l * n + i] = worker_record(in, i, n, inv16_of(scale, b), unit_weight(in.w[i], scale, b));
     }
 }
 
-// Layer-wise scales: workgroup l, thread i.  The kLayerSub rows of layer l in the slot array hold
-// the layer's maxima; every (worker, layer) gets its scale, and table l of the quantize pass gets the
-// worker's record with the multiplier and the decode weight of that layer (the formulas of the
+// Layer-wise largest-magnitude scales: workgroup l, thread i.  The kLayerSub rows of layer l in the slot
+// array hold the layer's maxima; every (worker, layer) gets its scale, and table l of the quantize pass gets
+// the worker's record with the multiplier and the decode weight of that layer (the formulas of the
 // per-vector case with the layer's scale).  The rows are handed back zeroed.
-// Euclidean scale (MODE 0): thread i walks the layer's segment sums [segment][worker] in the order of
-// the tree - 64 segments into a group, 64 groups into a supergroup, supergroups into the total,
-// every sum from 0.0 in index order - with the loads of eight segments requested together.
-template <int MODE>
-__global__ __launch_bounds__(kWgThreads) void k_scale_finalize_layers(int n, QuantStreams out, StepWeights sw,
-                                                                      Workspace ws, float* scales)
+template <int CAP>
+__global__ __launch_bounds__(kWgThreads) void k_scale_finalize_layers(int n, QuantList<CAP> in, Workspace ws, float* scales)
 {
     const int l = blockIdx.x;
     for (int i = threadIdx.x; i < n; i += kWgThreads) {
-        float scale;
-        if (MODE == 1) {
-            uint32_t m = 0u;
-            for (int r = 0; r < kLayerSub; ++r) {
-                uint32_t* p = ws.part_max + ((int64_t)l * kLayerSub + r) * n + i;
-                m = max(m, __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-                __hip_atomic_store(p, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            scale = __uint_as_float(m);
-        } else {
-            const int64_t s_begin = ws.layer_seg[l], s_end = ws.layer_seg[l + 1];
-            const double* part = ws.part_sq + i;
-            double total = 0.0;
-            for (int64_t u0 = s_begin; u0 < s_end; u0 += (int64_t)kGroupSegs * kGroupSegs) {  // supergroups
-                const int64_t u1 = u0 + (int64_t)kGroupSegs * kGroupSegs < s_end ? u0 + (int64_t)kGroupSegs * kGroupSegs : s_end;
-                double super = 0.0;
-                for (int64_t g0 = u0; g0 < u1; g0 += kGroupSegs) {  // groups
-                    const int64_t g1 = g0 + kGroupSegs < u1 ? g0 + kGroupSegs : u1;
-                    double group = 0.0;
-                    for (int64_t s0 = g0; s0 < g1; s0 += 8) {
-                        double v[8];
-#pragma unroll
-                        for (int t = 0; t < 8; ++t) v[t] = s0 + t < g1 ? part[(s0 + t) * n] : 0.0;
-#pragma unroll
-                        for (int t = 0; t < 8; ++t)
-                            if (s0 + t < g1) group = group + v[t];
-                    }
-                    super = super + group;
-                }
-                total = total + super;
-            }
-            scale = (float)sqrt(total);
+        uint32_t m = 0u;
+        for (int r = 0; r < kLayerSub; ++r) {
+            uint32_t* p = ws.part_max + ((int64_t)l * kLayerSub + r) * n + i;
+            m = max(m, __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            __hip_atomic_store(p, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
+        const float scale = __uint_as_float(m);
         scales[(int64_t)i * ws.n_layers + l] = scale;
-        const int b = out.bits[i];
-        const uint32_t flush = (i == n - 1 || out.stage_start[i + 1] == 0) ? 1u : 0u;
-        WorkerQ e{inv16_of(scale, b), (uint32_t)b, out.codes[i], 0.f, 0u, 8u * out.stage_start[i], flush};
-        if (sw.fuse) {
-            const double L = b >= 2 ? (double)((1 << (b - 1)) - 1) : 1.0;
-            e.coef = (float)(((double)sw.w[i] * (double)scale) / L);
-            e.arrived = (uint32_t)sw.arrived[i];
-        }
-        ws.wq[(int64_t)l * n + i] = e;
+        const int b = in.bits[i];
+        ws.wq[(int64_t)l * n + i] = worker_record(in, i, n, inv16_of(scale, b), unit_weight(in.w[i], scale, b));
     }
 }
 
+// the per-worker arguments of the table kernels, as large as n needs
+template <int CAP>
+static QuantList<CAP> quant_list(int n, const QuantStreams& out, const StepWeights& sw)
+{
+    QuantList<CAP> q;
+    q.fuse = sw.fuse;
+    for (int i = 0; i < n; ++i) {
+        q.codes[i] = out.codes[i];
+        q.bits[i] = out.bits[i];
+        q.stage_start[i] = out.stage_start[i];
+        q.w[i] = sw.fuse ? sw.w[i] : 0.f;
+        q.arrived[i] = sw.fuse ? sw.arrived[i] : (uint8_t)0;
+    }
+    return q;
+}
+
+template <int CAP>
+static hipError_t launch_scale_finalize_cap(int n, int scale_mode, const QuantStreams& out, const StepWeights& sw,
+                                            const Workspace& ws, float* scales, hipStream_t stream)
+{
+    const QuantList<CAP> q = quant_list<CAP>(n, out, sw);
+    const int layers = ws.n_layers;
+    if (scale_mode == 1) {
+        if (layers > 0)
+            hipLaunchKernelGGL((k_scale_finalize_layers<CAP>), dim3(layers), dim3(kWgThreads), 0, stream, n, q, ws, scales);
+        else
+            hipLaunchKernelGGL((k_scale_finalize<1, CAP>), dim3(n), dim3(kWgThreads), 0, stream, n, q, ws, (int64_t)0, scales);
+        return hipGetLastError();
+    }
+    const int64_t ngroup = layers > 0 ? ws.ngroup_layers : ws.ngroup;
+    hipLaunchKernelGGL(k_scale_groups, dim3((unsigned)ngroup), dim3(kWgThreads), 0, stream, n, ws, ngroup);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_scale_finalize<0, CAP>), dim3(n, layers > 0 ? layers : 1), dim3(kWgThreads), 0, stream, n, q, ws,
+                       ngroup, scales);
+    return hipGetLastError();
+}
+
+// The host pays about 1.7 ns per byte of kernel arguments (64 bytes 2.5 us a launch, 4000 bytes 9.1 us), so the
+// lists come in three sizes.
 hipError_t launch_scale_finalize(int n, int scale_mode, const QuantStreams& out, const StepWeights& sw,
                                  const Workspace& ws, float* scales, hipStream_t stream)
 {
-    if (ws.n_layers > 0) {
-        if (scale_mode == 1)
-            hipLaunchKernelGGL((k_scale_finalize_layers<1>), dim3(ws.n_layers), dim3(kWgThreads), 0, stream, n, out, sw,
-                               ws, scales);
-        else
-            hipLaunchKernelGGL((k_scale_finalize_layers<0>), dim3(ws.n_layers), dim3(kWgThreads), 0, stream, n, out, sw,
-                               ws, scales);
-        return hipGetLastError();
-    }
-    if (scale_mode == 0) {
-        hipLaunchKernelGGL(k_scale_groups, dim3((unsigned)ws.ngroup), dim3(kWgThreads), 0, stream, n, ws);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_scale_finalize<0>), dim3(n), dim3(kWgThreads), 0, stream, n, out, sw, ws, scales);
-    } else
-        hipLaunchKernelGGL((k_scale_finalize<1>), dim3(n), dim3(kWgThreads), 0, stream, n, out, sw, ws, scales);
-    return hipGetLastError();
+    if (n <= 16) return launch_scale_finalize_cap<16>(n, scale_mode, out, sw, ws, scales, stream);
+    if (n <= 64) return launch_scale_finalize_cap<64>(n, scale_mode, out, sw, ws, scales, stream);
+    return launch_scale_finalize_cap<kArgWorkers>(n, scale_mode, out, sw, ws, scales, stream);
 }
 
 // =======================================================================================
@@ -490,22 +504,17 @@ hipError_t launch_scale_finalize(int n, int scale_mode, const QuantStreams& out,
 // =======================================================================================
 // table of the bucket-wise pass: bit-width and stream of every worker (the multiplier is
 // found per block inside the pass)
-__global__ __launch_bounds__(kWgThreads) void k_quant_table(int n, QuantStreams out, StepWeights sw, WorkerQ* wq)
+template <int CAP>
+__global__ __launch_bounds__(kWgThreads) void k_quant_table(int n, QuantList<CAP> in, WorkerQ* wq)
 {
     const int i = threadIdx.x;
     if (i >= n) return;
-    const int b = out.bits[i];
+    const int b = in.bits[i];
     // bucket-wise scales: the multiplier is num / scale with the block's own scale; the record
     // carries the numerator L * 2^16 (2^15 for a one-bit worker)
     const float num = b >= 2 ? (float)(((1u << (b - 1)) - 1u) << 16) : 32768.0f;
-    const uint32_t flush = (i == n - 1 || out.stage_start[i + 1] == 0) ? 1u : 0u;
-    WorkerQ e{num, (uint32_t)b, out.codes[i], 0.f, 0u, 8u * out.stage_start[i], flush};
-    if (sw.fuse) {
-        const double L = b >= 2 ? (double)((1 << (b - 1)) - 1) : 1.0;
-        e.coef = (float)((double)sw.w[i] / L);
-        e.arrived = (uint32_t)sw.arrived[i];
-    }
-    wq[i] = e;
+    const double L = b >= 2 ? (double)((1 << (b - 1)) - 1) : 1.0;
+    wq[i] = worker_record(in, i, n, num, (float)((double)in.w[i] / L));
 }
 
 hipError_t launch_quantize_bucket(const float* G, int64_t ldg, int n, int k, int64_t d, const CodeDev& code,
@@ -513,7 +522,13 @@ hipError_t launch_quantize_bucket(const float* G, int64_t ldg, int n, int k, int
                                   const Workspace& ws, float* scales, uint64_t seed, uint64_t step, float* ghat,
                                   hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_quant_table, dim3(1), dim3(kWgThreads), 0, stream, n, out, sw, ws.wq);
+    if (n <= 16)
+        hipLaunchKernelGGL(k_quant_table<16>, dim3(1), dim3(kWgThreads), 0, stream, n, quant_list<16>(n, out, sw), ws.wq);
+    else if (n <= 64)
+        hipLaunchKernelGGL(k_quant_table<64>, dim3(1), dim3(kWgThreads), 0, stream, n, quant_list<64>(n, out, sw), ws.wq);
+    else
+        hipLaunchKernelGGL(k_quant_table<kArgWorkers>, dim3(1), dim3(kWgThreads), 0, stream, n,
+                           quant_list<kArgWorkers>(n, out, sw), ws.wq);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     QuantArgs a{ldg, n, k, d, (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32),
