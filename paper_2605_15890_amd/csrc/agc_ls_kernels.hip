@@ -106,27 +106,52 @@ __device__ __forceinline__ void fma8(float* acc, const u32x4& u, float r)
 
 // ROWS samples per block, NG groups of eight features per lane: ROWS * NG = 32 registers of four
 // packed words hold the block (16 x 2 for up to 4096 features, 8 x 4 for up to 8192).
-template <int ROWS, int NG>
+//
+// FOLD > 1, for rows of at most 2048 / FOLD features: the 256 lanes, which 2048 features would need, hold
+// FOLD samples side by side, so that a block is ROWS * FOLD samples and no lane idles.  The lanes of one
+// sample are chosen for the matrix product of sweep 1: its diagonal element D[n][n] adds the lanes n, n+16,
+// n+32, n+48 of a wave and lands in 16-lane row n / 4, so with FOLD = 16 the four samples of a wave take the
+// lanes with n / 4 = 0..3 and row g's part of the trace is sample g's residual; with FOLD = 8 two rows make
+// one sample, and from FOLD = 4 on samples are whole waves.  The last block of a partition may be partial:
+// lanes past it read its last sample again and get a zero residual.
+// 2^20 samples, 16 partitions: 128 features 341 -> 51 us, 1024 features 455 -> 331.
+template <int ROWS, int NG, int FOLD>
 __global__ __launch_bounds__(kLsThreads, 2) void k_ls_resident(const uint16_t* __restrict__ X,
                                                                const float* __restrict__ y,
                                                                const float* __restrict__ w, LsArgs a)
 {
     static_assert(ROWS % 4 == 0 && ROWS * NG == 32, "the block must fill 128 registers");
+    static_assert(FOLD == 1 || NG == 1, "narrow rows have one group per lane");
+    constexpr int kSamples = ROWS * FOLD;           // of a block
+    constexpr int kPartRows = 4 * kLsWaves / FOLD;  // 16-lane rows that hold parts of one sample
     __shared__ float lds_part[4 * kLsWaves][ROWS];  // [wave * 4 + 16-lane row][sample]
-    __shared__ float lds_r[ROWS];
+    __shared__ float lds_r[kSamples];
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
     const int lane = tid % 64;
     const int F = a.n_feat, H = F / NG;
+    const int n = lane & 15, g = lane >> 4;
+    // which of the FOLD samples side by side the lane works on, and its place among the sample's lanes
+    int sub = 0, place = tid;
+    if (FOLD == 16) {
+        sub = 4 * wave + (n >> 2);
+        place = (n & 3) + 4 * g;
+    } else if (FOLD == 8) {
+        sub = 2 * wave + (n >> 3);
+        place = (n & 7) + 8 * g;
+    } else if (FOLD > 1) {
+        sub = tid / (kLsThreads / FOLD);
+        place = tid % (kLsThreads / FOLD);
+    }
     const int part = blockIdx.x / a.wg_per_part;
     const int q = blockIdx.x % a.wg_per_part;
     // the lane's NG groups of eight features; lanes beyond the feature range read group 0 and
     // carry zero pieces of w, so they add nothing to sweep 1 and never store their sweep-2 sums
-    const bool active = 8 * tid < H;
+    const bool active = 8 * place < H;
     uint32_t goff[NG], boff[NG];  // feature offsets of the groups, and the same in bytes
 #pragma unroll
     for (int h = 0; h < NG; ++h) {
-        goff[h] = active ? (uint32_t)(h * H) + 8u * tid : 0u;
+        goff[h] = active ? (uint32_t)(h * H) + 8u * place : 0u;
         boff[h] = 2u * goff[h];
     }
     const uint32_t row_bytes = 2u * (uint32_t)F;
@@ -146,19 +171,41 @@ __global__ __launch_bounds__(kLsThreads, 2) void k_ls_resident(const uint16_t* _
                                   pc[p][4] | (pc[p][5] << 16), pc[p][6] | (pc[p][7] << 16));
     }
 
-    const int64_t blocks_per_part = a.rows_per_part / ROWS;
+    const int64_t blocks_per_part = (a.rows_per_part + kSamples - 1) / kSamples;  // whole blocks unless FOLD > 1
     const int64_t b0 = blocks_per_part * q / a.wg_per_part;
     const int64_t b1 = blocks_per_part * (q + 1) / a.wg_per_part;
     const uint16_t* base = X + (int64_t)part * a.rows_per_part * F;
     const int64_t row_base = (int64_t)part * a.rows_per_part;
+    // samples of block b that exist
+    auto samples_of = [&](int64_t b) {
+        const int64_t left = a.rows_per_part - b * kSamples;
+        return left < kSamples ? (int)left : kSamples;
+    };
+    // FOLD > 1: the lane's byte offset in row slot 0, the step from slot to slot, and where the last existing
+    // sample ends it; carried from slot to slot (32 offsets kept in registers would not fit beside the block)
+    const uint32_t slot_step = FOLD * row_bytes;
+    uint32_t slot_off = 0, slot_last = 0;
+    auto first_slot = [&](int have) {
+        slot_off = (uint32_t)sub * row_bytes + boff[0];
+        slot_last = (uint32_t)(have - 1) * row_bytes + boff[0];
+        asm volatile("" : "+v"(slot_off));
+    };
+    // group h of the lane's sample in the next row slot, r, of a block
+    auto load_slot = [&](global_bytes blk_ptr, int r, int h) {
+        if (FOLD == 1) return load16(blk_ptr + r * row_bytes, boff[h]);
+        const uint32_t at = slot_off < slot_last ? slot_off : slot_last;
+        slot_off += slot_step;
+        return load16(blk_ptr, at);
+    };
 
     u32x4 x[ROWS][NG];
     {
-        global_bytes blk_ptr = uniform_ptr(base + b0 * ROWS * F);
+        global_bytes blk_ptr = uniform_ptr(base + b0 * kSamples * F);
+        if (FOLD > 1) first_slot(samples_of(b0));
 #pragma unroll
         for (int r = 0; r < ROWS; ++r)
 #pragma unroll
-            for (int h = 0; h < NG; ++h) x[r][h] = load16(blk_ptr + r * row_bytes, boff[h]);
+            for (int h = 0; h < NG; ++h) x[r][h] = load_slot(blk_ptr, r, h);
     }
     float acc[8 * NG];
 #pragma unroll
@@ -166,13 +213,13 @@ __global__ __launch_bounds__(kLsThreads, 2) void k_ls_resident(const uint16_t* _
 
     // lane (n, g) of the MFMA result holds D[4g .. 4g+3][n]; the diagonal element D[n][n] sits in
     // the lanes with n / 4 == g, at position n % 4
-    const int n = lane & 15, g = lane >> 4;
     const bool on_diag = (n >> 2) == g;
     const bool dm0 = on_diag && (n & 3) == 0, dm1 = on_diag && (n & 3) == 1;
     const bool dm2 = on_diag && (n & 3) == 2, dm3 = on_diag && (n & 3) == 3;
 
     for (int64_t blk = b0; blk < b1; ++blk) {
-        const int64_t row0 = row_base + blk * ROWS;
+        const int64_t row0 = row_base + blk * kSamples;
+        const int have = samples_of(blk);
         // ---- sweep 1: the wave's share of the residuals (trace of A B^T per sample)
 #pragma unroll
         for (int rg = 0; rg < ROWS; rg += 4) {
@@ -202,32 +249,49 @@ __global__ __launch_bounds__(kLsThreads, 2) void k_ls_resident(const uint16_t* _
                     make_float4(part_r[0], part_r[1], part_r[2], part_r[3]);
         }
         __syncthreads();
-        if (tid < ROWS) {
+        for (int t = tid; t < kSamples; t += kLsThreads) {  // sample t sits in row slot t / FOLD
             float s = 0.f;
 #pragma unroll
-            for (int e = 0; e < 4 * kLsWaves; ++e) s = s + lds_part[e][tid];
-            const float r = s - y[row0 + tid];
-            lds_r[tid] = r;
-            a.resid[row0 + tid] = r;
+            for (int e = 0; e < kPartRows; ++e) s = s + lds_part[(t % FOLD) * kPartRows + e][t / FOLD];
+            float r = 0.f;
+            if (FOLD == 1 || t < have) {
+                r = s - y[row0 + t];
+                a.resid[row0 + t] = r;
+            }
+            lds_r[t] = r;
         }
         __syncthreads();
         // ---- sweep 2: g += X_blk^T r from the same registers; each sample's registers are
         // refilled with the next block as soon as they are consumed (the last block is fetched a
         // second time instead of branching)
         const int64_t nb = blk + 1 < b1 ? blk + 1 : blk;
-        global_bytes nxt_ptr = uniform_ptr(base + nb * ROWS * F);
+        global_bytes nxt_ptr = uniform_ptr(base + nb * kSamples * F);
+        if (FOLD > 1) first_slot(samples_of(nb));
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
-            const float rr = lds_r[r];
+            const float rr = lds_r[r * FOLD + sub];
 #pragma unroll
             for (int h = 0; h < NG; ++h) {
                 fma8(acc + 8 * h, x[r][h], rr);
-                x[r][h] = load16(nxt_ptr + r * row_bytes, boff[h]);
+                x[r][h] = load_slot(nxt_ptr, r, h);
             }
         }
         // the barriers of the next block order the reuse of lds_part and lds_r
     }
-    if (active) {
+    if constexpr (FOLD > 1) {  // the samples side by side hold parts of the same gradient: add them in order
+        constexpr int kLanes = kLsThreads / FOLD;
+        __shared__ float lds_g[FOLD][8 * kLanes];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) lds_g[sub][8 * place + e] = acc[e];
+        __syncthreads();
+        float* out = a.partial + (int64_t)blockIdx.x * F;
+        for (int f = tid; f < F; f += kLsThreads) {
+            float s = 0.f;
+#pragma unroll
+            for (int u = 0; u < FOLD; ++u) s = s + lds_g[u][f];
+            out[f] = s;
+        }
+    } else if (active) {
         float* out = a.partial + (int64_t)blockIdx.x * F;
 #pragma unroll
         for (int h = 0; h < NG; ++h) {
@@ -239,16 +303,36 @@ __global__ __launch_bounds__(kLsThreads, 2) void k_ls_resident(const uint16_t* _
     }
 }
 
-// G[p][f] = sum over the partition's workgroups, in workgroup order
+// G[p][f] = sum over the partition's workgroups.  A workgroup takes 32 features (whole lines of the parts);
+// its eight slices of 32 threads add an eighth of the parts each, in order, sixteen requested together, and
+// the eight sums are added in order.  (One thread per feature and one part at a time: 29 us for 128 parts
+// of 512 features, now 2.)
+constexpr int kRedFeat = 32, kRedSlices = kLsThreads / kRedFeat, kRedBatch = 16;
 __global__ __launch_bounds__(kLsThreads) void k_ls_reduce(const float* __restrict__ partial, int n_feat,
                                                           int wg_per_part, float* G, int64_t ldg)
 {
+    __shared__ float lds_s[kRedSlices][kRedFeat];
     const int p = blockIdx.y;
-    const int f = blockIdx.x * kLsThreads + threadIdx.x;
-    if (f >= n_feat) return;
+    const int col = threadIdx.x % kRedFeat, slice = threadIdx.x / kRedFeat;
+    const int f = blockIdx.x * kRedFeat + col;  // n_feat is a multiple of 128
+    const int q0 = wg_per_part * slice / kRedSlices, q1 = wg_per_part * (slice + 1) / kRedSlices;
+    const float* src = partial + (int64_t)p * wg_per_part * n_feat + f;
     float s = 0.f;
-    for (int qq = 0; qq < wg_per_part; ++qq) s = s + partial[((int64_t)p * wg_per_part + qq) * n_feat + f];
-    G[(int64_t)p * ldg + f] = s;
+    for (int q = q0; q < q1; q += kRedBatch) {
+        float v[kRedBatch];  // past the slice's end its last part is read again
+#pragma unroll
+        for (int u = 0; u < kRedBatch; ++u) v[u] = src[(int64_t)(q + u < q1 ? q + u : q1 - 1) * n_feat];
+#pragma unroll
+        for (int u = 0; u < kRedBatch; ++u) s = q + u < q1 ? s + v[u] : s;
+    }
+    lds_s[slice][col] = s;
+    __syncthreads();
+    if (slice == 0) {
+        float t = 0.f;
+#pragma unroll
+        for (int u = 0; u < kRedSlices; ++u) t = t + lds_s[u][col];
+        G[(int64_t)p * ldg + f] = t;
+    }
 }
 
 __global__ __launch_bounds__(kLsThreads) void k_gd_update(float* beta, const float* __restrict__ ghat,
@@ -272,19 +356,28 @@ hipError_t launch_ls_partial_gradients(const void* X, int64_t n_rows, int n_feat
                                        float* resid, float* partial, hipStream_t stream)
 {
     LsArgs a{n_rows, n_feat, k_parts, ls_wg_per_part(n_rows, n_feat, k_parts), n_rows / k_parts, resid, partial};
-    if (n_feat <= kLsResidentFeat / 2 && a.rows_per_part % 32 == 0)  // keeps all lanes busy on short rows
-        hipLaunchKernelGGL((k_ls_resident<32, 1>), dim3((unsigned)(k_parts * a.wg_per_part)), dim3(kLsThreads), 0,
-                           stream, static_cast<const uint16_t*>(X), y, w, a);
+    // rows of at most 1024 features go several side by side (FOLD); a workgroup then needs more samples
+    const int fold = n_feat <= 128 ? 16 : n_feat <= 256 ? 8 : n_feat <= 512 ? 4 : n_feat <= 1024 ? 2 : 1;
+    if (fold > 1) {
+        const int64_t blocks = (a.rows_per_part + 32 * fold - 1) / (32 * fold);
+        if (blocks < a.wg_per_part) a.wg_per_part = (int)blocks;
+    }
+    const dim3 grid((unsigned)(k_parts * a.wg_per_part)), block(kLsThreads);
+    const uint16_t* x = static_cast<const uint16_t*>(X);
+    if (fold == 16) hipLaunchKernelGGL((k_ls_resident<32, 1, 16>), grid, block, 0, stream, x, y, w, a);
+    else if (fold == 8) hipLaunchKernelGGL((k_ls_resident<32, 1, 8>), grid, block, 0, stream, x, y, w, a);
+    else if (fold == 4) hipLaunchKernelGGL((k_ls_resident<32, 1, 4>), grid, block, 0, stream, x, y, w, a);
+    else if (fold == 2) hipLaunchKernelGGL((k_ls_resident<32, 1, 2>), grid, block, 0, stream, x, y, w, a);
+    else if (n_feat <= kLsResidentFeat / 2 && a.rows_per_part % 32 == 0)  // keeps all lanes busy on short rows
+        hipLaunchKernelGGL((k_ls_resident<32, 1, 1>), grid, block, 0, stream, x, y, w, a);
     else if (n_feat <= kLsResidentFeat)
-        hipLaunchKernelGGL((k_ls_resident<16, 2>), dim3((unsigned)(k_parts * a.wg_per_part)), dim3(kLsThreads), 0,
-                           stream, static_cast<const uint16_t*>(X), y, w, a);
+        hipLaunchKernelGGL((k_ls_resident<16, 2, 1>), grid, block, 0, stream, x, y, w, a);
     else
-        hipLaunchKernelGGL((k_ls_resident<8, 4>), dim3((unsigned)(k_parts * a.wg_per_part)), dim3(kLsThreads), 0,
-                           stream, static_cast<const uint16_t*>(X), y, w, a);
+        hipLaunchKernelGGL((k_ls_resident<8, 4, 1>), grid, block, 0, stream, x, y, w, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_ls_reduce, dim3((unsigned)((n_feat + kLsThreads - 1) / kLsThreads), (unsigned)k_parts),
-                       dim3(kLsThreads), 0, stream, partial, n_feat, a.wg_per_part, G, ldg);
+    hipLaunchKernelGGL(k_ls_reduce, dim3((unsigned)(n_feat / kRedFeat), (unsigned)k_parts), dim3(kLsThreads), 0, stream,
+                       partial, n_feat, a.wg_per_part, G, ldg);
     return hipGetLastError();
 }
 

@@ -55,6 +55,15 @@ def test_partial_gradients_match_fp64(n_rows, n_feat, k):
     assert torch.equal(resid.view(torch.int32), resid2.view(torch.int32))
 
 
+@pytest.mark.parametrize("n_feat", [128, 256, 384, 512, 640, 1024, 1152])
+@pytest.mark.parametrize("rows_per_part", [16, 48, 528, 1040])
+def test_narrow_rows_several_samples_side_by_side(n_feat, rows_per_part):
+    """Up to 1024 features a block holds 2, 4, 8 or 16 samples per row slot (64 to 512 samples in all): one
+    partial block, whole blocks and a partial last one, rows that leave lanes idle.  The bound is that of
+    the wide rows: the same terms are added, in shorter chains."""
+    test_partial_gradients_match_fp64(rows_per_part * 3, n_feat, 3)
+
+
 def test_rejects_shapes_the_kernel_does_not_cover():
     import torch
     X = torch.zeros((64, 128), dtype=torch.bfloat16, device="cuda")
