@@ -48,44 +48,46 @@ struct WorkerQ {
 static_assert(sizeof(WorkerQ) == 32, "one record is two 16-byte scalar loads");
 
 // The staging area of a workgroup holds the codes of consecutive workers whose bit-widths sum to
-// at most kStageBits (8 * kStageBits pieces of 16 bytes); workers beyond that start a new fill.
-constexpr int kStageBits = 256;
+// at most a cap (8 * cap pieces of 16 bytes); workers beyond that start a new fill.  Up to the limit the
+// codes of all workers wait in one fill, which leaves the loop over the workers free of stores.
+// The limit is what leaves room for four workgroups per compute unit.  50 workers with 300 bits in all: one
+// fill 478 us, two fills (a limit of 256) 493 us for the whole encode; 64 workers with 384 bits: two fills at
+// four workgroups 644-675 us, one fill at three workgroups 650-678 us.
+constexpr int kStageLds = 160 * 1024 / 4;
+constexpr int kStageBits = (kStageLds - 16) / 128;  // 319
+// the same beside the bucket-wise scales of four blocks
+inline int stage_limit(int n, bool bucket) { return bucket ? (kStageLds - 16 - 16 * n) / 128 : kStageBits; }
 
-// Places the workers in the staging area (host side): start[i] = sum of the bit-widths staged
-// before worker i in its fill (< kStageBits, fits a byte); a fill ends before the worker that
-// would overflow it, and that worker starts the next one at 0.
-inline void stage_starts(const uint8_t* bits, int n, uint8_t* start)
+// All fills about equally full: the area, and with it the LDS of a workgroup, is as small as the number of
+// fills allows.  A fill that is closed because a worker of up to 16 bits does not fit holds more than
+// cap - 16 bits.
+inline int stage_cap(const uint8_t* bits, int n, int limit)
 {
-    int acc = 0;
-    for (int j = 0; j < n; ++j) {
-        if (acc + bits[j] > kStageBits) acc = 0;
-        start[j] = (uint8_t)acc;
-        acc += bits[j];
-    }
+    int sum = 0;
+    for (int j = 0; j < n; ++j) sum += bits[j];
+    const int fills = (sum + limit - 1) / limit;
+    if (fills <= 1) return limit;
+    const int cap = (sum + fills - 1) / fills + 15;
+    return cap < limit ? cap : limit;
 }
-// number of fills the workers need
-inline int stage_fills(const uint8_t* bits, int n)
+// Places the workers in the staging area (host side): start[i] = sum of the bit-widths staged
+// before worker i in its fill; a fill ends before the worker that would overflow it, and that worker starts
+// the next one at 0.  Returns the number of fills; *most is the fullest one, in bits.
+inline int stage_starts(const uint8_t* bits, int n, int limit, uint16_t* start, int* most)
 {
+    const int cap = stage_cap(bits, n, limit);
     int acc = 0, fills = n > 0 ? 1 : 0;
+    *most = 0;
     for (int j = 0; j < n; ++j) {
-        if (acc + bits[j] > kStageBits) {
+        if (acc + bits[j] > cap) {
             acc = 0;
             ++fills;
         }
+        start[j] = (uint16_t)acc;
         acc += bits[j];
+        if (acc > *most) *most = acc;
     }
     return fills;
-}
-// largest fill over all groups, in bits (host side: sizes the LDS area of a launch)
-inline int stage_bits_needed(const uint8_t* bits, int n)
-{
-    int acc = 0, most = 0;
-    for (int j = 0; j < n; ++j) {
-        if (acc + bits[j] > kStageBits) acc = 0;
-        acc += bits[j];
-        if (acc > most) most = acc;
-    }
-    return most;
 }
 
 // ---- tables of the decode pass.  A tile of the vector is 256 * COORDS coordinates; a worker's part of it
@@ -156,7 +158,8 @@ constexpr int kLayerSub = 16;    // with layer-wise scales layer l owns rows l*k
 struct QuantStreams {      // host arrays of the encode call
     void* codes[kArgWorkers];
     uint8_t bits[kArgWorkers];
-    uint8_t stage_start[kArgWorkers];  // stage_starts() of the bit-widths
+    uint16_t stage_start[kArgWorkers];  // stage_starts() of the bit-widths
+    int stage_fills, stage_bits;        // and what it returns: fills, the fullest one in bits
 };
 
 struct StepWeights {       // decode side of a fused step
@@ -170,7 +173,7 @@ struct QuantList {         // both as kernel arguments of the table kernels, for
     void* codes[CAP];
     float w[CAP];
     uint8_t bits[CAP];
-    uint8_t stage_start[CAP];
+    uint16_t stage_start[CAP];
     uint8_t arrived[CAP];
     int fuse;
 };
@@ -213,9 +216,9 @@ hipError_t launch_scale_finalize(int n, int scale_mode, const QuantStreams& out,
                                  const Workspace& ws, float* scales, hipStream_t stream);
 // K2: fused encode + stochastic quantize + bit-pack.
 // ghat != nullptr: fused step (the table must have been written with sw.fuse != 0).
-// bits: host array of the n bit-widths (sizes the LDS staging area; the table holds them too).
+// out: its bit-widths size the LDS staging area (the table holds them too).
 hipError_t launch_quantize(const float* G, int64_t ldg, int n, int k, int64_t d,
-                           const CodeDev& code, const Workspace& ws, const uint8_t* bits, uint64_t seed,
+                           const CodeDev& code, const Workspace& ws, const QuantStreams& out, uint64_t seed,
                            uint64_t step, float* ghat, hipStream_t stream);
 // Bucket-wise scales (one per 256-coordinate block and worker): a table prologue, then ONE pass
 // over G that derives each block's scale from the block itself.  scales: n x nb, nb = ceil(d/256).

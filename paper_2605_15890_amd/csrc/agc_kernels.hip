@@ -532,7 +532,7 @@ hipError_t launch_quantize_bucket(const float* G, int64_t ldg, int n, int k, int
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     QuantArgs a{ldg, n, k, d, (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32),
-                scales, (d + kBlockCoords - 1) / kBlockCoords, ghat, nullptr, stage_bits_needed(out.bits, n), stage_fills(out.bits, n),
+                scales, (d + kBlockCoords - 1) / kBlockCoords, ghat, nullptr, out.stage_bits, out.stage_fills,
                 nullptr};
     if (a.stage_fills > 1)
         return scale_mode == 0 ? launch_quantize_band2m(G, code, ws, a, stream)
@@ -542,11 +542,11 @@ hipError_t launch_quantize_bucket(const float* G, int64_t ldg, int n, int k, int
 }
 
 hipError_t launch_quantize(const float* G, int64_t ldg, int n, int k, int64_t d,
-                           const CodeDev& code, const Workspace& ws, const uint8_t* bits, uint64_t seed,
+                           const CodeDev& code, const Workspace& ws, const QuantStreams& out, uint64_t seed,
                            uint64_t step, float* ghat, hipStream_t stream)
 {
     QuantArgs a{ldg, n, k, d, (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32),
-                nullptr, 0, ghat, nullptr, stage_bits_needed(bits, n), stage_fills(bits, n),
+                nullptr, 0, ghat, nullptr, out.stage_bits, out.stage_fills,
                 ws.n_layers > 0 ? ws.block_layer : nullptr};
     return a.stage_fills > 1 ? launch_quantize_band0m(G, code, ws, a, stream)
                              : launch_quantize_band0s(G, code, ws, a, stream);

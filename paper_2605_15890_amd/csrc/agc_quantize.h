@@ -387,17 +387,7 @@ __global__ __launch_bounds__(kQuantThreads) __attribute__((amdgpu_waves_per_eu(S
     extern __shared__ __attribute__((aligned(16))) uint32_t lds_stage[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // wave-uniform by construction
     const int lane = threadIdx.x % kWave;
-#ifdef AGC_XCD_ORDER
-    int64_t wg = blockIdx.x;
-    {
-        const int64_t per = gridDim.x / 8;
-        if (wg < per * 8) wg = (wg % 8) * per + wg / 8;
-    }
-#elif defined(AGC_REVERSE_ORDER)
-    const int64_t wg = (int64_t)gridDim.x - 1 - blockIdx.x;
-#else
     const int64_t wg = blockIdx.x;
-#endif
     const int64_t block = wg * kQuantWaves + wave;
     const int64_t base = block * (int64_t)kBlockCoords;
     {
