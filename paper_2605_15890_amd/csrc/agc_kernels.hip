@@ -533,7 +533,7 @@ hipError_t launch_quantize_bucket(const float* G, int64_t ldg, int n, int k, int
     if (e != hipSuccess) return e;
     QuantArgs a{ldg, n, k, d, (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32),
                 scales, (d + kBlockCoords - 1) / kBlockCoords, ghat, nullptr, out.stage_bits, out.stage_fills,
-                nullptr};
+                nullptr, 0u};
     if (a.stage_fills > 1)
         return scale_mode == 0 ? launch_quantize_band2m(G, code, ws, a, stream)
                                : launch_quantize_band1m(G, code, ws, a, stream);
@@ -547,7 +547,7 @@ hipError_t launch_quantize(const float* G, int64_t ldg, int n, int k, int64_t d,
 {
     QuantArgs a{ldg, n, k, d, (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32),
                 nullptr, 0, ghat, nullptr, out.stage_bits, out.stage_fills,
-                ws.n_layers > 0 ? ws.block_layer : nullptr};
+                ws.n_layers > 0 ? ws.block_layer : nullptr, 0u};
     return a.stage_fills > 1 ? launch_quantize_band0m(G, code, ws, a, stream)
                              : launch_quantize_band0s(G, code, ws, a, stream);
 }
