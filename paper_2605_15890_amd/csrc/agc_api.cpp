@@ -184,7 +184,8 @@ void add_arrived(agc::DecodeStreams& ds, int i, const void* codes, float w, floa
 
 agc::CodeDev code_dev(const agc_ctx* c)
 {
-    return agc::CodeDev{c->d_row_ptr, c->d_col, c->d_val, c->opts.force_generic ? 0 : c->band, c->d_win};
+    const int band = c->opts.force_generic ? 0 : c->band;
+    return agc::CodeDev{c->d_row_ptr, c->d_col, c->d_val, band, c->d_win, agc::use_parts(c->d, c->n, c->k, c->nnz, band)};
 }
 
 }  // namespace
@@ -512,8 +513,11 @@ agc_status encode_quantize_impl(agc_ctx* c, const float* G, int64_t ldg, const u
         qs.bits[i] = bits[i];
         qs.codes[i] = codes[i];
     }
-    qs.stage_fills = agc::stage_starts(qs.bits, c->n, agc::stage_limit(c->n, c->opts.bucket != 0), qs.stage_start,
-                                       &qs.stage_bits);
+    int sum_bits = 0;
+    for (int i = 0; i < c->n; ++i) sum_bits += bits[i];
+    qs.parts = code.parts && sum_bits <= agc::kPartBits;
+    qs.stage_fills = agc::stage_starts(qs.bits, c->n, qs.parts ? agc::kPartBits : agc::stage_limit(c->n, c->opts.bucket != 0),
+                                       qs.stage_start, &qs.stage_bits);
     hipError_t e;
     if (c->opts.bucket) {  // one pass: every block finds its own scale
         KernelTimer t{c, 2, stream};

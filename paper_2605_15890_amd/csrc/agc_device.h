@@ -639,6 +639,151 @@ __device__ __forceinline__ void encode_window_batched(const float* __restrict__ 
         window_batches<W, 0>(ring, G, ldg, k, B, lc, row0, steps, i, cur, epi);
 }
 
+// ---------------------------------------------------------------------------------------
+// The same drivers for a range of workers i0..i1-1 (i0 even, i0 < i1), for passes that give the waves of a
+// workgroup a part of the workers each.  The cyclic band loads the rows that wrap around once more.
+// ---------------------------------------------------------------------------------------
+template <int S, int PF, int r, class Epi>
+__device__ __forceinline__ void ring_part_step(float4 (&ring)[(RingShapeT<S, PF>::R)], const float* __restrict__ G,
+                                               int64_t ldg, int k, const float* __restrict__ bval,
+                                               const LaneCoords& lc, int j0, int i0, int m, int& row,
+                                               float (&coef)[S], Epi& epi)
+{
+    constexpr int P = RingShapeT<S, PF>::P;
+    constexpr int R = RingShapeT<S, PF>::R;
+    const int j = j0 + r;
+    if (j + P < m + S - 1) {
+        ring[(r + P) % R] = load_row4<false, true>(G + (int64_t)row * ldg, lc);
+        row = row + 1 < k ? row + 1 : 0;
+    }
+    const int t = j - (S - 1);
+    if (t >= 0 && t < m) {
+        const int i = i0 + t;
+        float next[S];
+        const float* bv = bval + (int64_t)(t + 1 < m ? i + 1 : i) * S;
+#pragma unroll
+        for (int u = 0; u < S; ++u) next[u] = bv[u];
+        float4 f = mul4(coef[0], ring[(r + R - (S - 1)) % R]);
+#pragma unroll
+        for (int u = 1; u < S; ++u) f = fma4(coef[u], ring[(r + R - (S - 1) + u) % R], f);
+        epi.template worker<(((r + R - (S - 1)) & 1) == 0)>(i, f);
+#pragma unroll
+        for (int u = 0; u < S; ++u) coef[u] = next[u];
+    }
+}
+
+template <int S, int PF, class Epi, int... Rs>
+__device__ __forceinline__ void ring_part_round(float4 (&ring)[(RingShapeT<S, PF>::R)], const float* __restrict__ G,
+                                                int64_t ldg, int k, const float* __restrict__ bval,
+                                                const LaneCoords& lc, int j0, int i0, int m, int& row,
+                                                float (&coef)[S], Epi& epi, std::integer_sequence<int, Rs...>)
+{
+    (ring_part_step<S, PF, Rs>(ring, G, ldg, k, bval, lc, j0, i0, m, row, coef, epi), ...);
+}
+
+template <int S, int PF, class Epi>
+__device__ __forceinline__ void encode_ring_part(const float* __restrict__ G, int64_t ldg, int k,
+                                                 const float* __restrict__ bval, const LaneCoords& lc, int i0, int i1,
+                                                 Epi& epi)
+{
+    constexpr int P = RingShapeT<S, PF>::P;
+    constexpr int R = RingShapeT<S, PF>::R;
+    const int m = i1 - i0;
+    int row = i0;
+    float4 ring[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) ring[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int r = 0; r < P; ++r) {
+        if (r < m + S - 1) {
+            ring[r] = load_row4<false, true>(G + (int64_t)row * ldg, lc);
+            row = row + 1 < k ? row + 1 : 0;
+        }
+    }
+    float coef[S];
+#pragma unroll
+    for (int u = 0; u < S; ++u) coef[u] = bval[(int64_t)i0 * S + u];
+    for (int j0 = 0; j0 < m + S - 1; j0 += R)
+        ring_part_round<S, PF>(ring, G, ldg, k, bval, lc, j0, i0, m, row, coef, epi, std::make_integer_sequence<int, R>{});
+}
+
+template <int W, int PF, int r, class Epi>
+__device__ __forceinline__ void window_part_step(float4 (&ring)[(RingShapeT<W, PF>::R)], const float* __restrict__ G,
+                                                 int64_t ldg, int k, const CsrView& B, const LaneCoords& lc, int j0,
+                                                 int i1, int& i, WindowCur& cur, Epi& epi)
+{
+    constexpr int P = RingShapeT<W, PF>::P;
+    constexpr int R = RingShapeT<W, PF>::R;
+    const int j = j0 + r;
+    if (j + P < k) ring[(r + P) % R] = load_row4<false, true>(G + (int64_t)(j + P) * ldg, lc);
+    const int lo = j - (W - 1);
+    while (i < i1 && cur.lo == lo) {
+        const WindowCur nxt = load_window_rec(B.win + i + 1);  // the sentinel record ends the table
+        float4 f = mul4(cur.val[0], ring[(r + R - (W - 1)) % R]);
+#pragma unroll
+        for (int u = 1; u < W; ++u)
+            if (u < cur.len) f = fma4(cur.val[u], ring[(r + R - (W - 1) + u) % R], f);
+        epi.worker_any(i, f);
+        cur = nxt;
+        ++i;
+    }
+}
+
+template <int W, int PF, class Epi, int... Rs>
+__device__ __forceinline__ void window_part_round(float4 (&ring)[(RingShapeT<W, PF>::R)], const float* __restrict__ G,
+                                                  int64_t ldg, int k, const CsrView& B, const LaneCoords& lc, int j0,
+                                                  int i1, int& i, WindowCur& cur, Epi& epi,
+                                                  std::integer_sequence<int, Rs...>)
+{
+    (window_part_step<W, PF, Rs>(ring, G, ldg, k, B, lc, j0, i1, i, cur, epi), ...);
+}
+
+// rows are counted from 0, ring positions from the first row the range needs
+template <int W, int PF, class Epi>
+__device__ __forceinline__ void encode_window_part(const float* __restrict__ G, int64_t ldg, int k, const CsrView& B,
+                                                   const LaneCoords& lc, int i0, int i1, Epi& epi)
+{
+    constexpr int P = RingShapeT<W, PF>::P;
+    constexpr int R = RingShapeT<W, PF>::R;
+    int i = i0;
+    WindowCur cur = load_window_rec(B.win + i);
+    const int first = cur.lo / R * R;  // a whole number of rounds: row j sits at position j mod R
+    float4 ring[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) ring[r] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int r = 0; r < P; ++r)
+        if (first + r < k) ring[r] = load_row4<false, true>(G + (int64_t)(first + r) * ldg, lc);
+    for (int j0 = first; i < i1; j0 += R)  // every worker is met: its lo is at most k - 1
+        window_part_round<W, PF>(ring, G, ldg, k, B, lc, j0, i1, i, cur, epi, std::make_integer_sequence<int, R>{});
+}
+
+template <bool RAGGED, class Epi>
+__device__ __forceinline__ void encode_gather_part(const float* __restrict__ G, int64_t ldg, const CsrView& B,
+                                                   const LaneCoords& lc, int i0, int i1, Epi& epi)
+{
+    for (int i = i0; i < i1; i += 2) {
+        epi.template worker<true>(i, encode_gather_one<RAGGED>(G, ldg, B, i, lc));
+        if (i + 1 < i1) epi.template worker<false>(i + 1, encode_gather_one<RAGGED>(G, ldg, B, i + 1, lc));
+    }
+}
+
+// workers i0..i1-1 of one block; nothing if the range is empty
+template <int S, class Epi>
+__device__ __forceinline__ void encode_block_part(const float* __restrict__ G, int64_t ldg, int k, const CsrView& B,
+                                                  const LaneCoords& lc, int i0, int i1, Epi& epi)
+{
+    if (i0 >= i1) return;
+    if (lc.wave_ragged) encode_gather_part<true>(G, ldg, B, lc, i0, i1, epi);
+    else if constexpr (S > 0) encode_ring_part<S, Epi::kPrefetchRows>(G, ldg, k, B.val, lc, i0, i1, epi);
+    else if constexpr (S < 0) encode_window_part<-S, Epi::kPrefetchRows>(G, ldg, k, B, lc, i0, i1, epi);
+    else encode_gather_part<false>(G, ldg, B, lc, i0, i1, epi);
+}
+
+// Short vectors: how many waves share the workers of a block (each takes a run of an even number of them).
+constexpr int kParts = 4;
+__host__ __device__ inline int part_size(int n) { return ((n + kParts - 1) / kParts + 1) / 2 * 2; }
+
 // One block of 256 coordinates for all workers.  S > 0: cyclic band of width S; S < 0: monotone
 // intervals of at most -S columns; S == 0: any code.  The register ring serves whole blocks; the
 // one block that straddles d (and any other code) goes through the gather driver, which masks

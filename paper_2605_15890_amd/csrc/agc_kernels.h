@@ -27,6 +27,7 @@ struct CodeDev {          // the code matrix B on the device
     const float* val;     // [nnz]
     int band;             // 0: generic CSR; s>0: cyclic band with s entries per row; -W: monotone intervals
     const WindowRec* win; // [n+1], monotone-interval codes only (else null)
+    bool parts;           // use_parts() of this code
 };
 
 // what the quantize pass needs to know about worker i, read with one scalar 32-byte load
@@ -89,6 +90,26 @@ inline int stage_starts(const uint8_t* bits, int n, int limit, uint16_t* start, 
     }
     return fills;
 }
+
+// Vectors short enough that a block's workers are shared among the waves of a workgroup: up to 2^18
+// coordinates, where one wave per block leaves every SIMD with at most one, always (whole step, without and
+// with: 16 workers x 200 000 coordinates 30.7 and 21.2 us; 50 x 240 000, runs of up to 8 partitions, 70.9 and
+// 60.4; 24 x 240 000, longer runs, 59.5 and 37.9).  Beyond that from sixteen workers on (the parts of fewer are
+// uneven), and only where a part does not pay for its start: with a cyclic band up to 2^19 coordinates
+// (16 x 500 000 35.3 and 31.8, 32 x 500 000 70 and 59; 16 x 1 M 38 and 59); with the gather driver up to 2^20
+// if the workers share their partitions so that rows are gathered at least twice (24 workers, 4 rows each:
+// 900 000 coordinates 103 and 82; 60, 8 rows each: 500 000 361 and 268), not for long intervals (20 workers
+// x 1 M 91 and 110).  The window driver starts a part up to a ring's length early (50 x 400 000 83 and 93).
+inline bool use_parts(int64_t d, int n, int k, int nnz, int band)
+{
+    const int64_t blocks = (d + 255) / 256;
+    if (blocks <= 1024) return true;
+    if (n < 16) return false;
+    return band > 0 ? blocks <= 2048 : band == 0 && nnz >= 2 * k && blocks <= 4096;
+}
+// The codes of one block then wait in LDS in a single fill, 32 bytes per bit of width: all 256 workers at
+// four bits or 64 at sixteen.
+constexpr int kPartBits = 1024;
 
 // ---- tables of the decode pass.  A tile of the vector is 256 * COORDS coordinates; a worker's part of it
 // is `bits` units of 32 * COORDS contiguous bytes.  Units of consecutive workers, whole workers only, fill
@@ -160,6 +181,7 @@ struct QuantStreams {      // host arrays of the encode call
     uint8_t bits[kArgWorkers];
     uint16_t stage_start[kArgWorkers];  // stage_starts() of the bit-widths
     int stage_fills, stage_bits;        // and what it returns: fills, the fullest one in bits
+    bool parts;                         // the quantize pass shares the workers of a block among the waves
 };
 
 struct StepWeights {       // decode side of a fused step

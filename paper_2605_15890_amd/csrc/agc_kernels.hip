@@ -240,6 +240,62 @@ __global__ __launch_bounds__(kWave * WAVES) void k_scale_pass(const float* __res
     }
 }
 
+// Short vectors: the waves of a workgroup share the workers of a block, kParts ways.  A wave alone on its
+// SIMD issues one instruction in about five cycles, and walking over 64 workers one after the other takes it
+// longer than the memory needs for everything; the rows at the seams of the parts are read twice, which is
+// nothing at these sizes.  Max-abs: one block per workgroup, and every wave hands its maxima to the slot
+// array itself.  Euclidean: the four blocks of a segment, sixteen waves.
+template <int S, int MODE>
+__global__ __launch_bounds__(kWave * (MODE == 1 ? kParts : kParts * kSegBlocks)) void k_scale_pass_parts(
+    const float* __restrict__ G, const int* __restrict__ row_ptr, const int* __restrict__ col,
+    const float* __restrict__ val, ScaleArgs a)
+{
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int lane = threadIdx.x % kWave;
+    const CsrView B{row_ptr, col, val, a.win};
+    const int size = part_size(a.n);
+    const int i0 = (MODE == 1 ? wave : wave / kSegBlocks) * size;
+    const int i1 = i0 + size < a.n ? i0 + size : a.n;
+    if constexpr (MODE == 1) {
+        __shared__ uint32_t lds_max[kMaxWorkers];
+        const int64_t blk = blockIdx.x;
+        const int64_t base = blk * kBlockCoords;
+        const LaneCoords lc = lane_coords(base, lane, a.d);
+        EpiMaxAbs epi{lds_max, lane};
+        encode_block_part<S>(G + base, a.ldg, a.k, B, lc, i0, i1, epi);
+        const int64_t slot = a.block_layer ? (int64_t)a.block_layer[blk] * kLayerSub + blk % kLayerSub : blk & (kMaxSlots - 1);
+        for (int i = i0 + lane; i < i1; i += kWave) {  // written by this wave's lane 0
+            const uint32_t m = lds_max[i];
+            if (m != 0u)
+                (void)__hip_atomic_fetch_max(a.part_max + slot * a.n + i, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    } else {
+        __shared__ double lds_sq[kSegBlocks][kMaxWorkers];
+        const int64_t seg = blockIdx.x;
+        const int b = wave % kSegBlocks;
+        int64_t base = (seg * kSegBlocks + b) * (int64_t)kBlockCoords;
+        bool has = base < a.d;
+        if (a.seg_first) {
+            base = ((int64_t)a.seg_first[seg] + b) * (int64_t)kBlockCoords;
+            has = b < (int)a.seg_blocks[seg];
+        }
+        if (has) {
+            const LaneCoords lc = lane_coords(base, lane, a.d);
+            EpiSumSq epi{lds_sq[b], lane};
+            encode_block_part<S>(G + base, a.ldg, a.k, B, lc, i0, i1, epi);
+        } else {
+            for (int i = i0 + lane; i < i1; i += kWave) lds_sq[b][i] = 0.0;
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < a.n; i += kWave * kParts * kSegBlocks) {
+            double sum = 0.0;
+#pragma unroll
+            for (int w = 0; w < kSegBlocks; ++w) sum = sum + lds_sq[w][i];
+            __builtin_nontemporal_store(sum, a.part_sq + seg * (int64_t)a.n + i);
+        }
+    }
+}
+
 // rows of the max-abs slot array back to zero (context creation does it with a memset; this
 // kernel serves a call that follows one whose launches failed half-way)
 __global__ __launch_bounds__(kWgThreads) void k_scale_clear_slots(uint32_t* slots, int count)
@@ -275,6 +331,15 @@ template <int S>
 static hipError_t launch_scale_pass_s(const float* G, const CodeDev& code, const ScaleArgs& a,
                                       int scale_mode, hipStream_t stream)
 {
+    if (code.parts) {
+        if (scale_mode == 0)
+            hipLaunchKernelGGL((k_scale_pass_parts<S, 0>), dim3((unsigned)a.nseg), dim3(kWave * kParts * kSegBlocks), 0,
+                               stream, G, code.row_ptr, code.col, code.val, a);
+        else
+            hipLaunchKernelGGL((k_scale_pass_parts<S, 1>), dim3((unsigned)((a.d + kBlockCoords - 1) / kBlockCoords)),
+                               dim3(kWave * kParts), 0, stream, G, code.row_ptr, code.col, code.val, a);
+        return hipGetLastError();
+    }
     if (scale_mode == 0) {
         hipLaunchKernelGGL((k_scale_pass<S, 0, kSegBlocks, 1>), dim3((unsigned)a.nseg), dim3(kWgThreads), 0, stream, G,
                            code.row_ptr, code.col, code.val, a);
@@ -533,7 +598,7 @@ hipError_t launch_quantize_bucket(const float* G, int64_t ldg, int n, int k, int
     if (e != hipSuccess) return e;
     QuantArgs a{ldg, n, k, d, (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32),
                 scales, (d + kBlockCoords - 1) / kBlockCoords, ghat, nullptr, out.stage_bits, out.stage_fills,
-                nullptr, 0u};
+                nullptr, 0u, out.parts};
     if (a.stage_fills > 1)
         return scale_mode == 0 ? launch_quantize_band2m(G, code, ws, a, stream)
                                : launch_quantize_band1m(G, code, ws, a, stream);
@@ -547,7 +612,7 @@ hipError_t launch_quantize(const float* G, int64_t ldg, int n, int k, int64_t d,
 {
     QuantArgs a{ldg, n, k, d, (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32),
                 nullptr, 0, ghat, nullptr, out.stage_bits, out.stage_fills,
-                ws.n_layers > 0 ? ws.block_layer : nullptr, 0u};
+                ws.n_layers > 0 ? ws.block_layer : nullptr, 0u, out.parts};
     return a.stage_fills > 1 ? launch_quantize_band0m(G, code, ws, a, stream)
                              : launch_quantize_band0s(G, code, ws, a, stream);
 }

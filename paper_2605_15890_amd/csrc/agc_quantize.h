@@ -24,7 +24,8 @@ struct QuantArgs {
     int stage_bits;        // largest sum of bit-widths one fill of the staging area holds (<= kStageBits)
     int stage_fills;       // how many fills the workers need (1 unless the widths sum to more than kStageBits)
     const uint8_t* block_layer;  // layer-wise scales only: the layer of every block; wq is then [layer][n]
-    unsigned wg_first;     // the workgroups take the groups of blocks from here upwards and then from 0
+    unsigned wg_first;     // (a workgroup has four blocks) the workgroups take the groups of blocks from here upwards and then from 0
+    bool parts;            // short vectors: one block per workgroup, its workers shared among the waves
 };
 
 typedef __attribute__((address_space(1))) uint32_t global_u32;  // a pointer known to be device memory
@@ -45,11 +46,12 @@ constexpr int kQuantThreads = kWave * kQuantWaves;
 // 598 / 582 / 582 / 578, of 10 workers with 30 x 5.4 M 253 / 249 / 247 / 245, 64 x 25.6 M 2332 / 2331 / 2332 / 2334.
 constexpr int64_t kKeptBytes = (int64_t)400 << 20;
 static_assert(kQuantWaves % 4 == 0 && kQuantWaves <= 16, "the per-worker table counts pieces for four waves");
+static_assert(kParts == kQuantWaves, "a workgroup has four waves in either form");
 
-// LDS staging area of a workgroup, in 16-byte pieces: 2 * kQuantWaves * bits pieces per worker
+// LDS staging area of a workgroup, in 16-byte pieces: 2 * blocks * bits pieces per worker
 // (the blocks of the workgroup, 2 * bits pieces each), plus one piece that takes the zero bits the
 // packer spills past a block's last word
-__host__ __device__ constexpr int stage_pieces(int stage_bits) { return 2 * kQuantWaves * stage_bits + 1; }
+__host__ __device__ constexpr int stage_pieces(int stage_bits, int blocks) { return 2 * blocks * stage_bits + 1; }
 
 // raw buffer descriptor, last word: 32-bit untyped data format of this target; the bounds check is
 // on the byte offset against num_records (stride 0)
@@ -127,19 +129,23 @@ __device__ __forceinline__ float grid_pos(float f, float inv)
 // workers, inside the streaming loop.  Without MULTI (the common case: widths sum to at most
 // kStageBits) the loop over the workers contains no store at all and the kernel writes the area
 // out once, after the loop; the encode drivers then keep their rolling prefetch.
-template <int BUCKET, bool FUSE, bool MULTI>
+// PARTS: short vectors.  The workgroup has one block, its waves share the workers (encode_block_part); the
+// estimate needs them in ascending order and is formed from the staged codes by the kernel (staged_estimate).
+template <int BUCKET, bool FUSE, bool MULTI, bool PARTS>
 struct EpiQuant {
+    static constexpr int kBlocks = PARTS ? 1 : kQuantWaves;  // of the workgroup
     static constexpr bool kStoresPerWorker = MULTI;  // stores inside the worker loop (a flush between workers)
     static constexpr int kPrefetchRows = AGC_PREFETCH_ROWS;
     const WorkerQ* __restrict__ wq;
     uint32_t key0, key1, step_lo, step_hi;
     uint32_t* stage;     // the workgroup's LDS staging area, all zero between fills
-    float* stage_scales; // bucket-wise scales: [n][kQuantWaves] floats behind the staging area
+    float* stage_scales; // bucket-wise scales: [n][kBlocks] floats behind the staging area
     int lane;
-    int wave;            // this wave's block inside the workgroup
+    int wave;
+    int blk;             // this wave's block inside the workgroup
     int n;               // workers
     int64_t wg;          // index of the workgroup = index of its group of four blocks
-    int wg_groups;       // 128-code groups of the workgroup's blocks that exist in the streams (1..2*kQuantWaves)
+    int wg_groups;       // 128-code groups of the workgroup's blocks that exist in the streams (1..2*kBlocks)
     int64_t block;       // index of this wave's 256-coordinate block
     uint32_t ctr0;       // m >> 2 of this lane's coordinates
     int nvalid;
@@ -164,10 +170,10 @@ struct EpiQuant {
         for (int j = group_first + wave; j <= last; j += kQuantWaves) {
             const WorkerQ w = load_uniform(wq + j);
             const int b = (int)w.bits;
-            const int np = 2 * kQuantWaves * b;  // pieces of this worker in the area
+            const int np = 2 * kBlocks * b;  // pieces of this worker in the area
             const __amdgpu_buffer_rsrc_t rsrc = uniform_buffer(
-                (const char*)w.codes + (uint64_t)wg * (uint64_t)(32 * kQuantWaves * b), 16 * b * wg_groups);
-            const uint32_t first = w.stage_piece * (uint32_t)(kQuantWaves / 4);  // the table counts for four waves
+                (const char*)w.codes + (uint64_t)wg * (uint64_t)(32 * kBlocks * b), 16 * b * wg_groups);
+            const uint32_t first = w.stage_piece * (uint32_t)kBlocks / 4u;  // the table counts for four blocks
             for (int off = 0; off < np; off += kWave) {
                 const int piece = off + lane;
                 u32x4_t v = u32x4_t{0u, 0u, 0u, 0u};
@@ -187,23 +193,23 @@ struct EpiQuant {
             __syncthreads();  // the area is reused by the next fill
         } else if (BUCKET != 0) {
             // after the last worker: the scales of all workers for the workgroup's blocks, one run of
-            // kQuantWaves floats per worker (the barrier above made every wave's entries visible)
-            const int64_t first_block = wg * kQuantWaves;
-            const int have = nb - first_block >= kQuantWaves ? kQuantWaves : (int)(nb - first_block);
+            // kBlocks floats per worker (the barrier above made every wave's entries visible)
+            const int64_t first_block = wg * kBlocks;
+            const int have = nb - first_block >= kBlocks ? kBlocks : (int)(nb - first_block);
             for (int t = wave * kWave + lane; t < n; t += kQuantThreads) {
                 __attribute__((address_space(1))) float* dst =
                     (__attribute__((address_space(1))) float*)scales + ((int64_t)t * nb + first_block);
-                if (have == kQuantWaves) {  // one run per worker, dword-aligned (a row of scales starts anywhere)
+                if (kBlocks > 1 && have == kBlocks) {  // one run per worker, dword-aligned (a row of scales starts anywhere)
                     typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 #pragma unroll
-                    for (int u = 0; u < kQuantWaves; u += 4)
+                    for (int u = 0; u + 3 < kBlocks; u += 4)
                         *(__attribute__((address_space(1))) f32x4_a4*)(dst + u) =
-                            f32x4_a4{stage_scales[t * kQuantWaves + u], stage_scales[t * kQuantWaves + u + 1],
-                                     stage_scales[t * kQuantWaves + u + 2], stage_scales[t * kQuantWaves + u + 3]};
+                            f32x4_a4{stage_scales[t * kBlocks + u], stage_scales[t * kBlocks + u + 1],
+                                     stage_scales[t * kBlocks + u + 2], stage_scales[t * kBlocks + u + 3]};
                 } else {
 #pragma unroll
-                    for (int u = 0; u < kQuantWaves; ++u)
-                        if (u < have) dst[u] = stage_scales[t * kQuantWaves + u];
+                    for (int u = 0; u < kBlocks; ++u)
+                        if (u < have) dst[u] = stage_scales[t * kBlocks + u];
                 }
             }
         }
@@ -231,7 +237,7 @@ struct EpiQuant {
         }
         // the block's scale waits in LDS next to the codes ([worker][block of the workgroup]) and
         // leaves with the last flush: 4-byte stores scattered over n rows cost far more than their bytes
-        if (lane == 0) stage_scales[i * kQuantWaves + wave] = scale;
+        if (lane == 0) stage_scales[i * kBlocks + blk] = scale;
         // num = L * 2^16 (2^15 for a one-bit worker) comes with the worker's record
         const float q = num / scale;  // correctly rounded binary32 division
         return q <= 3.402823466e+38f ? q : 0.0f;  // scale == 0 gives +inf and ends here too
@@ -327,7 +333,7 @@ struct EpiQuant {
         float scale = 0.f;
         const float inv = BUCKET == 0 ? q.inv16 : block_multiplier(i, f, q.inv16, scale);
         codes4(i, f, inv, b, wa, wb, c, lev);
-        if constexpr (FUSE) {
+        if constexpr (FUSE && !PARTS) {
             if (q.arrived) {  // wave-uniform
                 const float coef = BUCKET == 0 ? q.coef : q.coef * scale;
                 const float fv[4] = {f.x, f.y, f.z, f.w};
@@ -350,7 +356,7 @@ struct EpiQuant {
         // bit-pack: this lane's four codes start at bit lane*4b of the block's 256*b bits, the block's
         // 8b words start at piece q.stage_piece + wave*2b of the staging area
         const uint32_t bitpos = __umul24((uint32_t)lane, 4u * (uint32_t)b);
-        uint32_t* slot = stage + 4u * (q.stage_piece * (uint32_t)(kQuantWaves / 4) + (uint32_t)wave * 2u * (uint32_t)b) +
+        uint32_t* slot = stage + 4u * (q.stage_piece * (uint32_t)kBlocks / 4u + (uint32_t)blk * 2u * (uint32_t)b) +
                          (bitpos >> 5);
         const uint32_t sh = bitpos & 31u;
 #ifdef AGC_ABLATE_PACK
@@ -377,7 +383,49 @@ struct EpiQuant {
     }
 };
 
-template <int S, int BUCKET, bool FUSE, bool MULTI>
+// The fused estimate of short vectors: thread t forms coordinate t of the workgroup's block from the staged
+// codes of all workers, arrived ones in ascending order, one fused multiply-add each - the arithmetic of the
+// other forms.  Four workers' words are requested together.
+template <int BUCKET>
+__device__ __forceinline__ float staged_estimate(const WorkerQ* __restrict__ wq, const uint32_t* stage,
+                                                 const float* stage_scales, int n)
+{
+    constexpr int kBatch = 4;
+    const uint32_t t = threadIdx.x;
+    float acc = 0.f;
+    for (int e0 = 0; e0 < n; e0 += kBatch) {
+        WorkerQ q[kBatch];
+        uint32_t w0[kBatch], w1[kBatch];
+        float sc[kBatch];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) q[u] = load_uniform(wq + (e0 + u < n ? e0 + u : n - 1));
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const uint32_t* p = stage + q[u].stage_piece + ((t * q[u].bits) >> 5);  // a quarter of the pieces, four words each
+            w0[u] = p[0];
+            w1[u] = p[1];
+            sc[u] = BUCKET != 0 ? stage_scales[e0 + u < n ? e0 + u : n - 1] : 1.f;
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            if (e0 + u >= n || !q[u].arrived) continue;  // wave-uniform
+            const uint32_t b = q[u].bits;
+            const uint32_t code = __builtin_amdgcn_alignbit(w1[u], w0[u], (t * b) & 31u);
+            const float coef = BUCKET == 0 ? q[u].coef : q[u].coef * sc[u];
+            float v;
+            if (b >= 2) {
+                const uint32_t level = code & ((1u << (b - 1)) - 1u);
+                v = __uint_as_float(__float_as_uint((float)level) | ((code << (32 - b)) & 0x80000000u));
+            } else {
+                v = (code & 1u) ? 1.0f : -1.0f;
+            }
+            acc = fmaf(coef, v, acc);
+        }
+    }
+    return acc;
+}
+
+template <int S, int BUCKET, bool FUSE, bool MULTI, bool PARTS>
 // The compiler is told to plan for four waves per SIMD: with a register count just under the
 // five-wave limit it otherwise schedules for five and gives up instruction-level parallelism;
 // measured 1.45 ms against 1.51 ms on the metric workload (three: 1.51 ms).  The gather driver
@@ -391,22 +439,24 @@ __global__ __launch_bounds__(kQuantThreads) __attribute__((amdgpu_waves_per_eu(S
                                                          const float* __restrict__ val,
                                                          const WorkerQ* __restrict__ wq, QuantArgs a)
 {
-    // stage_pieces(a.stage_bits) pieces, then (bucket-wise scales) n * kQuantWaves floats
+    static_assert(!(MULTI && PARTS), "the parts of the workers meet in one fill");
+    constexpr int kBlocks = PARTS ? 1 : kQuantWaves;
+    // stage_pieces(a.stage_bits, kBlocks) pieces, then (bucket-wise scales) n * kBlocks floats
     extern __shared__ __attribute__((aligned(16))) uint32_t lds_stage[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);  // wave-uniform by construction
     const int lane = threadIdx.x % kWave;
     unsigned wg_index = blockIdx.x + a.wg_first;  // < 2 * grid <= 2^24
     if (wg_index >= gridDim.x) wg_index -= gridDim.x;
     const int64_t wg = wg_index;
-    const int64_t block = wg * kQuantWaves + wave;
+    const int64_t block = PARTS ? wg : wg * kQuantWaves + wave;
     const int64_t base = block * (int64_t)kBlockCoords;
     {
         u32x4_t* pieces = reinterpret_cast<u32x4_t*>(lds_stage);
-        const int np = stage_pieces(a.stage_bits);
+        const int np = stage_pieces(a.stage_bits, kBlocks);
         for (int p = threadIdx.x; p < np; p += kQuantThreads) pieces[p] = u32x4_t{0u, 0u, 0u, 0u};
     }
     __syncthreads();
-    const int64_t groups_left = (a.d + 127) / 128 - 2 * kQuantWaves * wg;  // >= 1: the workgroup's first block exists
+    const int64_t groups_left = (a.d + 127) / 128 - 2 * kBlocks * wg;  // >= 1: the workgroup's first block exists
     const bool has_block = base < a.d;
     LaneCoords lc{};
     if (has_block) lc = lane_coords(base, lane, a.d);
@@ -414,11 +464,24 @@ __global__ __launch_bounds__(kQuantThreads) __attribute__((amdgpu_waves_per_eu(S
     // layer to layer; bit-width, stream and staging place are the same in every table, so the
     // waves of a workgroup may hold different tables when they meet at a flush)
     if (a.block_layer && has_block) wq += (int64_t)__builtin_amdgcn_readfirstlane((int)a.block_layer[block]) * a.n;
-    EpiQuant<BUCKET, FUSE, MULTI> epi{wq, a.key0, a.key1, a.step_lo, a.step_hi, lds_stage,
-                               reinterpret_cast<float*>(lds_stage + 4 * stage_pieces(a.stage_bits)), lane, wave, a.n, wg,
-                               groups_left >= 2 * kQuantWaves ? 2 * kQuantWaves : (int)groups_left, block, (uint32_t)((base + 4 * lane) >> 2),
+    const int part = PARTS ? part_size(a.n) : 0;
+    const int i0 = PARTS ? (wave * part < a.n ? wave * part : a.n) : 0, i1 = PARTS ? (i0 + part < a.n ? i0 + part : a.n) : a.n;
+    float* stage_scales = reinterpret_cast<float*>(lds_stage + 4 * stage_pieces(a.stage_bits, kBlocks));
+    EpiQuant<BUCKET, FUSE, MULTI, PARTS> epi{wq, a.key0, a.key1, a.step_lo, a.step_hi, lds_stage, stage_scales, lane, wave,
+                               PARTS ? 0 : wave, a.n, wg,
+                               groups_left >= 2 * kBlocks ? 2 * kBlocks : (int)groups_left, block, (uint32_t)((base + 4 * lane) >> 2),
                                lc.nvalid, lc.wave_ragged, 0u, 0u, a.scales, a.nb, 0, {0.f, 0.f, 0.f, 0.f},
-                               load_uniform(wq)};
+                               load_uniform(wq + (i0 < a.n ? i0 : 0))};
+    if constexpr (PARTS) {  // every workgroup has its block
+        encode_block_part<S>(G + base, a.ldg, a.k, CsrView{row_ptr, col, val, a.win}, lc, i0, i1, epi);
+        if constexpr (FUSE) {
+            __syncthreads();
+            const float g = staged_estimate<BUCKET>(wq, lds_stage, stage_scales, a.n);
+            if (base + (int64_t)threadIdx.x < a.d) a.ghat[base + threadIdx.x] = g;
+        }
+        epi.flush_fill(a.n - 1);  // its barrier: the codes have been read before the pieces are handed back
+        return;
+    }
     if (!has_block) {  // nothing to encode, but the other waves of the workgroup wait at the flushes
         if constexpr (MULTI) epi.flush_only();
         else epi.flush_fill(a.n - 1);
@@ -450,22 +513,35 @@ static hipError_t launch_quantize_s(const float* G, const CodeDev& code, const W
     if (S < 0 && !a.win) return hipErrorInvalidValue;  // the window driver reads the records
     const int64_t nblocks = (a.d + kBlockCoords - 1) / kBlockCoords;
     const unsigned grid = (unsigned)((nblocks + kQuantWaves - 1) / kQuantWaves);
-    if (a.stage_bits < 1 || a.stage_bits > kStageBits) return hipErrorInvalidValue;
+    if (a.stage_bits < 1 || a.stage_bits > (a.parts ? kPartBits : kStageBits)) return hipErrorInvalidValue;
     if (MULTI ? a.stage_fills < 2 : a.stage_fills != 1) return hipErrorInvalidValue;
     a.wg_first = 0;
+    if constexpr (!MULTI) {
+        if (a.parts) {
+            const unsigned lds = 16u * (unsigned)stage_pieces(a.stage_bits, 1) + (BUCKET != 0 ? 4u * (unsigned)a.n : 0u);
+            const dim3 g((unsigned)nblocks), b(kWave * kParts);
+            if (a.ghat)
+                hipLaunchKernelGGL((k_quantize<S, BUCKET, true, false, true>), g, b, lds, stream, G, code.row_ptr, code.col,
+                                   code.val, ws.wq, a);
+            else
+                hipLaunchKernelGGL((k_quantize<S, BUCKET, false, false, true>), g, b, lds, stream, G, code.row_ptr,
+                                   code.col, code.val, ws.wq, a);
+            return hipGetLastError();
+        }
+    }
     if (BUCKET == 0) {
         const int64_t per_wg = 4 * (int64_t)a.k * kBlockCoords * kQuantWaves;
         const int64_t kept = kKeptBytes / per_wg;
         if (kept > 0 && kept < (int64_t)grid) a.wg_first = (unsigned)(grid - kept);
     }
-    const unsigned lds_bytes = 16u * (unsigned)stage_pieces(a.stage_bits) +
+    const unsigned lds_bytes = 16u * (unsigned)stage_pieces(a.stage_bits, kQuantWaves) +
                                (BUCKET != 0 ? (unsigned)(sizeof(float) * kQuantWaves * a.n) : 0u);
     const dim3 g(grid), b(kQuantThreads);
     if (a.ghat)
-        hipLaunchKernelGGL((k_quantize<S, BUCKET, true, MULTI>), g, b, lds_bytes, stream, G, code.row_ptr, code.col,
+        hipLaunchKernelGGL((k_quantize<S, BUCKET, true, MULTI, false>), g, b, lds_bytes, stream, G, code.row_ptr, code.col,
                            code.val, ws.wq, a);
     else
-        hipLaunchKernelGGL((k_quantize<S, BUCKET, false, MULTI>), g, b, lds_bytes, stream, G, code.row_ptr, code.col,
+        hipLaunchKernelGGL((k_quantize<S, BUCKET, false, MULTI, false>), g, b, lds_bytes, stream, G, code.row_ptr, code.col,
                            code.val, ws.wq, a);
     return hipGetLastError();
 }
