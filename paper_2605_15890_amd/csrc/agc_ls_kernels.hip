@@ -113,7 +113,7 @@ __device__ __forceinline__ void fma8(float* acc, const u32x4& u, float r)
 // n+32, n+48 of a wave and lands in 16-lane row n / 4, so with FOLD = 16 the four samples of a wave take the
 // lanes with n / 4 = 0..3 and row g's part of the trace is sample g's residual; with FOLD = 8 two rows make
 // one sample, and from FOLD = 4 on samples are whole waves.  The last block of a partition may be partial:
-// lanes past it read its last sample again and get a zero residual.
+// lanes past it read its last sample again for sweep 1 and hold zeros in sweep 2.
 // 2^20 samples, 16 partitions: 128 features 341 -> 51 us, 1024 features 455 -> 331.
 template <int ROWS, int NG, int FOLD>
 __global__ __launch_bounds__(kLsThreads, 2) void k_ls_resident(const uint16_t* __restrict__ X,
@@ -261,6 +261,13 @@ __global__ __launch_bounds__(kLsThreads, 2) void k_ls_resident(const uint16_t* _
             lds_r[t] = r;
         }
         __syncthreads();
+        if (FOLD > 1 && have < kSamples) {
+            // lanes past a partial block hold its last sample a second time: away with it, because a zero
+            // residual alone would turn an infinity in that sample into a NaN
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r)
+                if (r * FOLD + sub >= have) x[r][0] = u32x4{0u, 0u, 0u, 0u};
+        }
         // ---- sweep 2: g += X_blk^T r from the same registers; each sample's registers are
         // refilled with the next block as soon as they are consumed (the last block is fetched a
         // second time instead of branching)

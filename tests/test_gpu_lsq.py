@@ -64,6 +64,35 @@ def test_narrow_rows_several_samples_side_by_side(n_feat, rows_per_part):
     test_partial_gradients_match_fp64(rows_per_part * 3, n_feat, 3)
 
 
+@pytest.mark.parametrize("n_feat", [128, 256, 512, 1024])
+def test_infinity_in_the_last_sample_of_a_partial_block(n_feat):
+    """48 samples are less than a block of any of these widths, so the last one stands in for the samples
+    that do not exist: they must add nothing, also where that sample holds an infinity (whose product with
+    a zero residual is a NaN).  All three bfloat16 pieces of the model's entry at that feature are positive,
+    so the residual is +inf and the gradient +-inf, as in binary64."""
+    import torch
+    k, rows, at = 3, 48, 77
+    Xb, y, _, X, y_d = _device_problem(k * rows, n_feat)
+    beta = np.random.default_rng(n_feat).standard_normal(n_feat).astype(np.float32)
+    beta[at] = 1.0 + 2.0 ** -9 + 2.0 ** -18
+    last = rows - 1                      # of the first partition
+    Xb[last][Xb[last] & 0x7FFF == 0] = 0x3F80
+    Xb[last, at] = 0x7F80
+    X.copy_(torch.from_numpy(Xb.view(np.int16)).cuda().view(torch.bfloat16))
+    G = api.padded_rows(k, n_feat)
+    resid = torch.empty(k * rows, dtype=torch.float32, device="cuda")
+    ws = torch.empty(api.agc_ls_workspace_floats(k * rows, n_feat, k), dtype=torch.float32, device="cuda")
+    api.agc_ls_partial_gradients(X, y_d, torch.from_numpy(beta).cuda(), k, G, resid, ws)
+    torch.cuda.synchronize()
+    G_o, r_o = LS.partial_gradients(Xb, y, beta, k)
+    got = G.cpu().numpy()
+    assert np.isposinf(r_o[last]) and np.all(np.isinf(G_o[0])) and np.all(np.isfinite(G_o[1:]))
+    assert np.isposinf(resid[last].item())
+    assert np.array_equal(got[0], G_o[0].astype(np.float32))
+    for p in range(1, k):
+        assert _rel(got[p], G_o[p]) <= REL_L2_TOL, p
+
+
 def test_rejects_shapes_the_kernel_does_not_cover():
     import torch
     X = torch.zeros((64, 128), dtype=torch.bfloat16, device="cuda")
