@@ -254,9 +254,10 @@ def agc_second_moment_decoder(k, row_ptr, col, val, p, bits, phi_coef, lam):
 def _check_streams(codes, bits, d):
     """Every stream holds agc_code_bytes(d, b) bytes.  The sizes are formed here, without a library call
     per worker: at 64 workers those calls took longer than everything else a pass does on the host.
-    Widths outside 1..16 need nothing here (agc_code_bytes is 0): the library refuses them."""
+    Widths outside 1..16 need nothing here (agc_code_bytes is 0): the library refuses them.  Widths that
+    come as a column (n, 1) are n widths."""
     unit = (int(d) + 127) // 128 * 16 if d > 0 else 0
-    for i, (t, b) in enumerate(zip(codes, bits.tolist())):
+    for i, (t, b) in enumerate(zip(codes, bits.reshape(len(bits)).tolist())):
         if 1 <= b <= AGC_MAX_BITS and t.nbytes < unit * b:
             raise AgcError(AGC_ESHAPE, f"codes[{i}] holds {t.nbytes} bytes, {unit * b} needed for d={d}, bits={b}")
 

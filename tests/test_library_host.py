@@ -77,6 +77,19 @@ def test_noalloc_decode_rejects_sizes_beyond_its_fixed_scratch_without_touching_
     assert lib.agc_decode_noalloc(4, 1024, 0, *args) == api.AGC_EINVAL      # null scales / estimate
 
 
+def test_stream_sizes_are_checked_for_widths_in_a_row_or_in_a_column():
+    import torch
+    d, widths = 1000, [2, 16, 5]
+    codes = [torch.empty(api.agc_code_bytes(d, b), dtype=torch.uint8) for b in widths]
+    short = codes[:1] + [codes[1][1:]] + codes[2:]
+    for bits in (np.array(widths, np.uint8), np.array(widths, np.uint8)[:, None]):
+        api._check_streams(codes, bits, d)
+        with pytest.raises(api.AgcError, match=r"codes\[1\] holds 2047 bytes, 2048 needed"):
+            api._check_streams(short, bits, d)
+    with pytest.raises((TypeError, ValueError)):
+        api._check_streams(codes, np.ones((3, 2), np.uint8), d)
+
+
 def test_phi_coef_balanced():
     rng = np.random.default_rng(0)
     p = rng.uniform(0.05, 0.6, 16)
