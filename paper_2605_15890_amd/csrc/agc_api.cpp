@@ -185,7 +185,8 @@ void add_arrived(agc::DecodeStreams& ds, int i, const void* codes, float w, floa
 agc::CodeDev code_dev(const agc_ctx* c)
 {
     const int band = c->opts.force_generic ? 0 : c->band;
-    return agc::CodeDev{c->d_row_ptr, c->d_col, c->d_val, band, c->d_win, agc::use_parts(c->d, c->n, c->k, c->nnz, band)};
+    const bool parts = agc::use_parts(c->d, c->n, c->k, c->nnz, band, c->opts.scale_mode == AGC_SCALE_L2, c->opts.bucket != 0);
+    return agc::CodeDev{c->d_row_ptr, c->d_col, c->d_val, band, c->d_win, parts};
 }
 
 }  // namespace

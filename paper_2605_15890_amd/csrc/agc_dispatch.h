@@ -1,0 +1,72 @@
+// Rules that choose between the forms of a kernel, by sizes alone.  No HIP in here: the rules are also
+// compiled and checked without a GPU.
+#pragma once
+
+#include <stdint.h>
+
+namespace agc {
+
+// Vectors short enough that a block's workers are shared among the four waves of a workgroup
+// (k_scale_pass_parts, k_quantize<.., PARTS>).  A wave that walks over all workers alone on its SIMD mostly waits
+// for itself; four waves per block hide that as long as the chip has room for them, and lose to the long form
+// (four blocks per workgroup, every row read once) once it is full.  With one or two workers there is nothing to
+// share.  A vector that ends inside a block has its last block in the gather driver, one worker after the other
+// while the chip waits; the parts shorten that chain too, so their lines lie further out.
+//   band   > 0: cyclic band of that width, -W: window driver, 0: gather driver
+//   norm   Euclidean scale;  bucket: bucket-wise scales (no scale pass)
+// Measured: time of a whole step in the long form over that in this one, ten steps in a graph, 6000 shapes of
+// 3..256 workers.  Largest and smallest up to the line | beyond it:
+//   band    4-7 workers           1.26 .. 0.99 | 262144 coordinates 1.07 .. 0.93
+//           8 and more            2.09 .. 1.00 | 393216: 0.99 .. 0.77, 524288: 0.91 .. 0.65
+//           16, ending inside     2.76 .. 0.98 | 786432: 1.15 .. 0.80
+// (tenth percentile and median up to the line | beyond it)
+//   window, W <= 4                whole, 4-15 workers 0.97 and 1.08 | 0.93 and 1.00;  16-47 1.08 and 1.21 | 0.93 and
+//           1.02;  48 and more 1.15 and 1.45 | 1.05 and 1.2;  ending inside, 16 and more 1.25 and 1.6 | 0.96 and 1.1
+//   window, W = 8                 a part starts up to a ring of ten rows early, much of its share when rows are few,
+//           and where there are more rows than workers the workers are not what takes the time:
+//           whole, k <= n 1.05 and 1.15 | 0.97 and 1.0;  k <= 1.6 n 1.03 and 1.13 | 0.91 and 0.97;  k <= 2.2 n 1.0 and
+//           1.12 | 0.95 and 1.0;  more 0.98 and 1.1 | 0.87 and 0.98;  64 and more 1.0 and 1.2 | 0.9 and 1.1;
+//           ending inside, 16-31 1.05 and 1.3 | 0.82 and 0.95;  32 and more 1.2 and 1.5 | 0.95 and 1.2;  96 and more
+//           (their codes need several fills of the staging area in the long form) 1.1 and 1.4
+// (largest and smallest)
+//   gather  3 and more            3.57 .. 1.00 | 393216 with fewer than sixteen workers 1.63 .. 0.82
+//           16 and more, partitions with two holders 1.62 .. 0.98 | 786432 1.2 .. 0.94 (bucket-wise 524288 0.92);
+//           four: 1.28 .. 1.02 | 1048576 1.05 .. 0.90;  eight: 1.48 .. 1.00
+inline bool use_parts(int64_t d, int n, int k, int nnz, int band, bool norm, bool bucket)
+{
+    const int64_t blocks = (d + 255) / 256;
+    const bool ragged = d % 256 != 0;
+    if (n < 4) return n == 3 && blocks <= 256;
+    if (band > 0) {
+        if (n < 8) return blocks <= 768;
+        if (ragged && n >= 16) return blocks <= (bucket && n < 48 ? 1536 : 2048);
+        return blocks <= (norm && !bucket && !ragged ? 768 : 1024);
+    }
+    if (band < 0 && band >= -4) {
+        if (n >= 96 || (n >= 32 && ragged)) return blocks <= 1024;
+        if (n >= 48) return blocks <= 768;
+        if (bucket) return blocks <= (n < 16 ? 512 : 768);
+        if (n >= 16) return blocks <= (ragged ? 768 : 384);
+        return blocks <= (norm ? 192 : 384);
+    }
+    if (band < 0) {
+        const int rows = 10 * k / n;  // per ten workers; k <= 65536
+        if (n >= 96 && (bucket || ragged || rows > 16)) return blocks <= 1024;
+        if (bucket) {
+            if (n >= 64 || (ragged && n >= 16)) return blocks <= 512;
+            return blocks <= (rows <= 16 ? 512 : n >= 16 ? 192 : 64);
+        }
+        if (ragged && n >= 16) return blocks <= (n < 32 ? 256 : 512);
+        if (n >= 64) return blocks <= 384;
+        if (rows <= 10) return blocks <= 384;
+        if (rows <= 16) return blocks <= (n < 32 ? 192 : 64);
+        return blocks <= (ragged || rows <= 22 ? 64 : 32);
+    }
+    const int64_t held = nnz / k;  // workers per partition
+    if (n >= 16 && held >= 8) return blocks <= 4096;
+    if (n >= 16 && (held >= 4 || (held >= 2 && n >= 128))) return blocks <= (bucket && n < 128 ? 2048 : 3072);
+    if (n >= 16 && held >= 2) return blocks <= (bucket && n < 48 ? 1536 : 2048);
+    return blocks <= 1024;
+}
+
+}  // namespace agc

@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "agc_dispatch.h"
+
 namespace agc {
 
 constexpr int kArgWorkers = 256;
@@ -91,23 +93,8 @@ inline int stage_starts(const uint8_t* bits, int n, int limit, uint16_t* start, 
     return fills;
 }
 
-// Vectors short enough that a block's workers are shared among the waves of a workgroup: up to 2^18
-// coordinates, where one wave per block leaves every SIMD with at most one, always (whole step, without and
-// with: 16 workers x 200 000 coordinates 30.7 and 21.2 us; 50 x 240 000, runs of up to 8 partitions, 70.9 and
-// 60.4; 24 x 240 000, longer runs, 59.5 and 37.9).  Beyond that from sixteen workers on (the parts of fewer are
-// uneven), and only where a part does not pay for its start: with a cyclic band up to 2^19 coordinates
-// (16 x 500 000 35.3 and 31.8, 32 x 500 000 70 and 59; 16 x 1 M 38 and 59); with the gather driver up to 2^20
-// if the workers share their partitions so that rows are gathered at least twice (24 workers, 4 rows each:
-// 900 000 coordinates 103 and 82; 60, 8 rows each: 500 000 361 and 268), not for long intervals (20 workers
-// x 1 M 91 and 110).  The window driver starts a part up to a ring's length early (50 x 400 000 83 and 93).
-inline bool use_parts(int64_t d, int n, int k, int nnz, int band)
-{
-    const int64_t blocks = (d + 255) / 256;
-    if (blocks <= 1024) return true;
-    if (n < 16) return false;
-    return band > 0 ? blocks <= 2048 : band == 0 && nnz >= 2 * k && blocks <= 4096;
-}
-// The codes of one block then wait in LDS in a single fill, 32 bytes per bit of width: all 256 workers at
+// Short vectors (use_parts): the codes of one block wait in LDS in a single fill, 32 bytes per bit of width: all
+// 256 workers at
 // four bits or 64 at sixteen.
 constexpr int kPartBits = 1024;
 

@@ -1,0 +1,62 @@
+"""The rules that choose between the forms of a kernel (csrc/agc_dispatch.h), compiled on their own with the host
+compiler: on either side of the lines, at shapes where both forms were timed.  CPU only."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+DRIVER = r"""
+#include "agc_dispatch.h"
+extern "C" int parts(int64_t d, int n, int k, int nnz, int band, int norm, int bucket)
+{
+    return agc::use_parts(d, n, k, nnz, band, norm != 0, bucket != 0);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("dispatch")
+    (tmp / "driver.cpp").write_text(DRIVER)
+    cxx = shutil.which("g++") or shutil.which("c++")
+    subprocess.run([cxx, "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-fPIC", "-shared",
+                    "-fsanitize=undefined", "-fno-sanitize-recover=undefined",
+                    "-I", os.path.join(ROOT, "paper_2605_15890_amd", "csrc"), str(tmp / "driver.cpp"),
+                    "-o", str(tmp / "librules.so")], check=True)
+    lib = ctypes.CDLL(str(tmp / "librules.so"))
+    lib.parts.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 6
+    return lib
+
+
+@pytest.mark.parametrize("shared,d,n,k,nnz,band,norm,bucket", [
+    # cyclic band: whole vectors of 2^19 coordinates took 0.62 to 0.87 of the time in the long form
+    (0, 524288, 16, 16, 48, 3, 0, 0), (0, 524288, 64, 64, 192, 3, 1, 0), (0, 524288, 32, 32, 256, 8, 0, 1),
+    (0, 393216, 128, 128, 384, 3, 0, 0), (0, 262144, 32, 32, 96, 3, 1, 0),
+    (1, 262144, 32, 32, 96, 3, 0, 0), (1, 196608, 32, 32, 96, 3, 1, 0), (1, 500000, 64, 64, 192, 3, 1, 0),
+    (1, 65536, 48, 48, 144, 3, 0, 0), (1, 4096, 4, 4, 8, 2, 0, 0), (0, 262144, 4, 4, 8, 2, 0, 0),
+    # one or two workers share nothing
+    (0, 200000, 1, 1, 1, 1, 0, 0), (0, 262144, 2, 2, 4, 2, 0, 0), (0, 4096, 2, 2, 4, 2, 1, 0),
+    # window driver: three partitions a worker in runs of up to eight
+    (0, 262144, 12, 36, 80, -8, 0, 0), (0, 65536, 8, 24, 50, -8, 1, 0), (1, 4096, 24, 72, 95, -8, 0, 0),
+    (1, 65536, 48, 48, 96, -4, 0, 0), (0, 400000, 50, 50, 100, -4, 0, 0), (1, 250001, 48, 48, 96, -4, 1, 0),
+    # gather driver
+    (1, 200000, 24, 24, 96, 0, 0, 0), (1, 900000, 24, 24, 192, 0, 0, 0), (0, 1048576, 48, 48, 96, 0, 0, 0),
+    (0, 786432, 12, 12, 48, 0, 0, 0), (1, 500000, 60, 60, 480, 0, 1, 0)])
+def test_workers_are_shared_where_that_was_measured_to_be_faster(rules, shared, d, n, k, nnz, band, norm, bucket):
+    assert rules.parts(d, n, k, nnz, band, norm, bucket) == shared
+
+
+@pytest.mark.parametrize("band", [-8, -4, -2, 0, 1, 8])
+def test_sharing_rule_at_the_ends_of_its_ranges(rules, band):
+    """No overflow (the driver is built with the sanitizer), and long vectors always take the long form."""
+    for n in (1, 3, 4, 255, 256):
+        for k in (1, n, 65536):
+            for nnz in (0, k, 2 ** 24):
+                for norm, bucket in ((0, 0), (1, 0), (0, 1), (1, 1)):
+                    assert rules.parts(2 ** 33, n, k, nnz, band, norm, bucket) == 0
+                    assert rules.parts(256 * 4096 + 1, n, k, nnz, band, norm, bucket) == 0
+                    assert rules.parts(1, n, k, nnz, band, norm, bucket) == (n >= 3)
