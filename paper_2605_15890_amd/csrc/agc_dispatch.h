@@ -69,4 +69,19 @@ inline bool use_parts(int64_t d, int n, int k, int nnz, int band, bool norm, boo
     return blocks <= 1024;
 }
 
+// The quantize pass of long vectors: the group of four blocks that its first workgroup takes; the others follow
+// upwards and wrap around.  A vector that ends inside a block has that block in the gather driver, which takes
+// several times as long as the others: it must not be the last to start, so the pass starts 64 groups before the
+// end.  With no more groups than the chip holds at once (four workgroups on each of 256 compute units) all start
+// together and the order is left alone.  Whole step, upwards from 0 | from 64 groups before the end, us:
+// 64 workers x 2 000 000 257 | 238, 50 x 5 400 003 462 | 433, 32 x 11 700 000 549 | 535, 128 x 5 400 001 1193 | 1114,
+// 64 x 25 600 001 2423 | 2396.  Vectors of whole blocks take the same time from any group (32 x 11 700 224 521 | 522),
+// so nothing of G that the scale pass left in the memory-side cache is gained by the order.
+constexpr int64_t kChipGroups = 4 * 256;
+constexpr unsigned kEarlyGroups = 64;
+inline unsigned first_group(int64_t d, unsigned groups)
+{
+    return d % 256 != 0 && groups > kChipGroups ? groups - kEarlyGroups : 0u;
+}
+
 }  // namespace agc

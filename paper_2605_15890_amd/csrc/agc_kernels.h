@@ -94,8 +94,7 @@ inline int stage_starts(const uint8_t* bits, int n, int limit, uint16_t* start, 
 }
 
 // Short vectors (use_parts): the codes of one block wait in LDS in a single fill, 32 bytes per bit of width: all
-// 256 workers at
-// four bits or 64 at sixteen.
+// 256 workers at four bits or 64 at sixteen.
 constexpr int kPartBits = 1024;
 
 // ---- tables of the decode pass.  A tile of the vector is 256 * COORDS coordinates; a worker's part of it

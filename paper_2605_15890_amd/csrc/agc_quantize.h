@@ -24,7 +24,7 @@ struct QuantArgs {
     int stage_bits;        // largest sum of bit-widths one fill of the staging area holds (<= kStageBits)
     int stage_fills;       // how many fills the workers need (1 unless the widths sum to more than kStageBits)
     const uint8_t* block_layer;  // layer-wise scales only: the layer of every block; wq is then [layer][n]
-    unsigned wg_first;     // (a workgroup has four blocks) the workgroups take the groups of blocks from here upwards and then from 0
+    unsigned wg_first;     // the workgroups take the groups of four blocks from here upwards and then from 0; 0 with parts
     bool parts;            // short vectors: one block per workgroup, its workers shared among the waves
 };
 
@@ -39,12 +39,6 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));   // one 16-byte p
 constexpr int kQuantWaves = AGC_K2_WG_WAVES;
 constexpr int kQuantThreads = kWave * kQuantWaves;
 
-// The scale pass has just walked over all of G, and the last of it is still in the 256 MB memory-side cache:
-// the quantize pass starts with that part of the vector, upwards, and takes the rest after it (upwards as
-// well: a pass that walks downwards is 7 % slower).  Bytes of G, with some room because the lines leave
-// gradually; 0 / 128 / 256 / 400 MB: encode of 50 workers x 5.4 M 478 / 470 / 470 / 467 us, step of 32 x 11.7 M
-// 598 / 582 / 582 / 578, of 10 workers with 30 x 5.4 M 253 / 249 / 247 / 245, 64 x 25.6 M 2332 / 2331 / 2332 / 2334.
-constexpr int64_t kKeptBytes = (int64_t)400 << 20;
 static_assert(kQuantWaves % 4 == 0 && kQuantWaves <= 16, "the per-worker table counts pieces for four waves");
 static_assert(kParts == kQuantWaves, "a workgroup has four waves in either form");
 
@@ -515,7 +509,6 @@ static hipError_t launch_quantize_s(const float* G, const CodeDev& code, const W
     const unsigned grid = (unsigned)((nblocks + kQuantWaves - 1) / kQuantWaves);
     if (a.stage_bits < 1 || a.stage_bits > (a.parts ? kPartBits : kStageBits)) return hipErrorInvalidValue;
     if (MULTI ? a.stage_fills < 2 : a.stage_fills != 1) return hipErrorInvalidValue;
-    a.wg_first = 0;
     if constexpr (!MULTI) {
         if (a.parts) {
             const unsigned lds = 16u * (unsigned)stage_pieces(a.stage_bits, 1) + (BUCKET != 0 ? 4u * (unsigned)a.n : 0u);
@@ -529,11 +522,7 @@ static hipError_t launch_quantize_s(const float* G, const CodeDev& code, const W
             return hipGetLastError();
         }
     }
-    if (BUCKET == 0) {
-        const int64_t per_wg = 4 * (int64_t)a.k * kBlockCoords * kQuantWaves;
-        const int64_t kept = kKeptBytes / per_wg;
-        if (kept > 0 && kept < (int64_t)grid) a.wg_first = (unsigned)(grid - kept);
-    }
+    a.wg_first = BUCKET == 0 ? first_group(a.d, grid) : 0u;
     const unsigned lds_bytes = 16u * (unsigned)stage_pieces(a.stage_bits, kQuantWaves) +
                                (BUCKET != 0 ? (unsigned)(sizeof(float) * kQuantWaves * a.n) : 0u);
     const dim3 g(grid), b(kQuantThreads);
