@@ -84,4 +84,26 @@ inline unsigned first_group(int64_t d, unsigned groups)
     return d % 256 != 0 && groups > kChipGroups ? groups - kEarlyGroups : 0u;
 }
 
+// Workgroups of the decode pass that a compute unit holds: six, which was measured to be best with one scale per
+// vector (five 0.162, four 0.166 against 0.148 ms for 64 workers x 25.6 M), or as many as 160 KB of LDS has room
+// for beside the weights of bucket- and layer-wise scales: five, four with two tracks and layers.
+constexpr int decode_per_cu(unsigned lds_bytes)
+{
+    return 160 * 1024 / lds_bytes < 6 ? (int)(160 * 1024 / lds_bytes) : 6;
+}
+
+// Workgroups of the decode pass.  As many as the chip holds, which then walk over the tiles and fetch the next
+// tile's first chunk during the last of this one; more would start when the first ones have finished everything
+// (six per compute unit where five fit: 64 workers, layer-wise, 5.4 M 72 | 66 us, 10 workers 25.6 M 75 | 69).  But
+// with four chunks and more to a tile, that prefetch is a small part of the work, and from two tiles a workgroup on
+// the uneven rest of the tiles costs more than it saves: there one workgroup per tile, handed out as they finish
+// (128 workers, 25.6 M, walking | one per tile: 401 | 372 us, layer-wise 463 | 421, two tracks 481 | 442; two
+// chunks: 10 workers 64 | 73).
+inline int64_t decode_groups(int64_t tiles, int chunks, int per_cu)
+{
+    const int64_t resident = 256 * (int64_t)per_cu;
+    if (chunks >= 4 && tiles >= 2 * resident) return tiles;
+    return tiles < resident ? tiles : resident;
+}
+
 }  // namespace agc

@@ -828,13 +828,20 @@ struct DecodeArgs {
     const float* coef2_layer;
 };
 
-constexpr int kDecodeWaves = 6;  // per SIMD, that is resident workgroups per compute unit
+// LDS of a decode workgroup: two chunks, and with bucket- or layer-wise scales the weights of their workers
+template <bool TWO, int SCALES>
+struct DecodeLds {
+    u32x4_t chunk[2][kDecPieces + 1];   // one more: a lane may read a word past its own
+    float aux[SCALES ? 2 : 1][SCALES ? kDecAux : 1];
+    float aux2[SCALES == 2 && TWO ? 2 : 1][SCALES == 2 && TWO ? kDecAux : 1];
+    uint8_t worker[SCALES == 1 ? kMaxWorkers : 1];
+};
 // SCALES 0: one scale per worker (the weight of the table).  1: bucket-wise (weight of the table
 // times the bucket's scale).  2: layer-wise (the weight of the lane's layer; a lane's coordinates lie in
 // one block and therefore in one layer).
 template <bool TWO, int SCALES, int COORDS>
 __global__ __launch_bounds__(kWgThreads)
-__attribute__((amdgpu_waves_per_eu(kDecodeWaves, kDecodeWaves)))
+__attribute__((amdgpu_waves_per_eu(decode_per_cu(sizeof(DecodeLds<TWO, SCALES>)), decode_per_cu(sizeof(DecodeLds<TWO, SCALES>)))))
 void k_decode(const DecWorker* __restrict__ workers, const DecUnit* __restrict__ units,
               const int* __restrict__ chunk_first, DecodeArgs a)
 {
@@ -842,10 +849,10 @@ void k_decode(const DecWorker* __restrict__ workers, const DecUnit* __restrict__
     constexpr int kChunkUnits = kDecPieces / kUnitPieces;
     static_assert(COORDS * kChunkUnits <= kDecAux, "a worker has at least one unit");
     static_assert(kChunkUnits >= 16, "every worker fits a chunk");
-    __shared__ u32x4_t lds_chunk[2][kDecPieces + 1];         // one more: a lane may read a word past its own
-    __shared__ float lds_aux[SCALES ? 2 : 1][SCALES ? kDecAux : 1];
-    __shared__ float lds_aux2[SCALES == 2 && TWO ? 2 : 1][SCALES == 2 && TWO ? kDecAux : 1];
-    __shared__ uint8_t lds_worker[kMaxWorkers];
+    __shared__ DecodeLds<TWO, SCALES> lds;
+    auto& lds_chunk = lds.chunk;
+    auto& lds_aux = lds.aux;
+    auto& lds_aux2 = lds.aux2;
     const int tid = threadIdx.x;
     float acc[COORDS];
     float acc2[TWO ? COORDS : 1];
@@ -863,8 +870,8 @@ void k_decode(const DecWorker* __restrict__ workers, const DecUnit* __restrict__
         for (; tile < a.n_tiles; tile += gridDim.x) store_tile(tile);
         return;
     }
-    if (SCALES == 1) {
-        for (int i = tid; i < a.n_arrived; i += kWgThreads) lds_worker[i] = (uint8_t)workers[i].worker;
+    if constexpr (SCALES == 1) {
+        for (int i = tid; i < a.n_arrived; i += kWgThreads) lds.worker[i] = (uint8_t)workers[i].worker;
         __syncthreads();
     }
     u32x4_t r[kDecPerThread];
@@ -880,7 +887,7 @@ void k_decode(const DecWorker* __restrict__ workers, const DecUnit* __restrict__
                 int64_t block = t * COORDS + e % COORDS;
                 block = block < last_block ? block : last_block;
                 if (SCALES == 1) {
-                    aux[j] = a.scales[(int64_t)lds_worker[slot] * a.nb + block];
+                    aux[j] = a.scales[(int64_t)lds.worker[SCALES == 1 ? slot : 0] * a.nb + block];
                 } else {
                     const int64_t row = (int64_t)a.block_layer[block] * a.n_arrived;
                     aux[j] = a.coef_layer[row + slot];
@@ -975,8 +982,7 @@ template <bool TWO, int SCALES, int COORDS>
 static void launch_decode_main(hipStream_t stream, const DecodeTables& tab, DecodeArgs a)
 {
     a.n_tiles = (a.d + kWgThreads * COORDS - 1) / (kWgThreads * COORDS);
-    const int64_t resident = 256 * kDecodeWaves;  // workgroups the chip holds: one wave each on every SIMD
-    const unsigned grid = (unsigned)(a.n_tiles < resident ? a.n_tiles : resident);
+    const unsigned grid = (unsigned)decode_groups(a.n_tiles, a.n_chunks, decode_per_cu(sizeof(DecodeLds<TWO, SCALES>)));
     hipLaunchKernelGGL((k_decode<TWO, SCALES, COORDS>), dim3(grid), dim3(kWgThreads), 0, stream, tab.workers, tab.units,
                        tab.chunk_first, a);
 }

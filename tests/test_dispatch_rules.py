@@ -15,6 +15,8 @@ extern "C" int parts(int64_t d, int n, int k, int nnz, int band, int norm, int b
 {
     return agc::use_parts(d, n, k, nnz, band, norm != 0, bucket != 0);
 }
+extern "C" int decode_per_cu(unsigned lds_bytes) { return agc::decode_per_cu(lds_bytes); }
+extern "C" int64_t decode_groups(int64_t tiles, int chunks, int per_cu) { return agc::decode_groups(tiles, chunks, per_cu); }
 extern "C" unsigned first_group(int64_t d, unsigned groups) { return agc::first_group(d, groups); }
 """
 
@@ -30,6 +32,9 @@ def rules(tmp_path_factory):
                     "-o", str(tmp / "librules.so")], check=True)
     lib = ctypes.CDLL(str(tmp / "librules.so"))
     lib.parts.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 6
+    lib.decode_per_cu.argtypes = [ctypes.c_uint]
+    lib.decode_groups.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int]
+    lib.decode_groups.restype = ctypes.c_int64
     lib.first_group.argtypes = [ctypes.c_int64, ctypes.c_uint]
     lib.first_group.restype = ctypes.c_uint
     return lib
@@ -72,3 +77,16 @@ def test_the_block_that_the_vector_ends_in_starts_early(rules, d, early):
     1 000 000: 5 % slower in any other order)."""
     groups = -(-(-(-d // 256)) // 4)
     assert rules.first_group(d, groups) == (groups - early if early else 0)
+
+
+def test_decode_launches_what_a_compute_unit_holds(rules):
+    """160 KB of LDS: six workgroups with one scale per vector, five with bucket-wise scales and with layers, four
+    with layers and two tracks."""
+    assert [rules.decode_per_cu(b) for b in (24624, 28976, 28720, 32816)] == [6, 5, 5, 4]
+
+
+@pytest.mark.parametrize("tiles,chunks,per_cu,groups", [
+    (1, 1, 6, 1), (1319, 9, 6, 1319), (1319, 2, 5, 1280), (6250, 2, 6, 1536), (6250, 3, 5, 1280), (6250, 4, 6, 6250),
+    (6250, 20, 5, 6250), (2637, 20, 6, 1536), (2560, 20, 5, 2560), (2 ** 21, 1, 4, 1024)])
+def test_decode_walks_over_the_tiles_where_a_tile_is_little_work(rules, tiles, chunks, per_cu, groups):
+    assert rules.decode_groups(tiles, chunks, per_cu) == groups
