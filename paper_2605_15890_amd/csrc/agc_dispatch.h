@@ -102,8 +102,31 @@ constexpr int decode_per_cu(unsigned lds_bytes)
 inline int64_t decode_groups(int64_t tiles, int chunks, int per_cu)
 {
     const int64_t resident = 256 * (int64_t)per_cu;
-    if (chunks >= 4 && tiles >= 2 * resident) return tiles;
+    if (chunks >= 4 && 4 * tiles >= 7 * resident) return tiles;
     return tiles < resident ? tiles : resident;
+}
+
+// Decode of one track without chunks (k_decode_direct): one or two workers, where most of a chunk would be fetched
+// twice to fill it, and up to four on vectors so long that the stores of the estimate decide.  Whole decode with
+// eight coordinates per lane | direct, us: 1 worker, 4 bits, 4096 coordinates 5.1 | 4.6, 500 000 6.2 | 5.9, 25.6 M 44 | 41;
+// 2 workers, 4 bits each, 500 000 6.6 | 6.4;  3 workers 500 000 6.9 | 7.2, 25.6 M 47 | 46, 60 M 103 | 96;  4 workers
+// 60 M 105 | 99.
+inline bool decode_is_direct(int n_arrived, int64_t d)
+{
+    return n_arrived <= (d >= ((int64_t)1 << 25) ? 4 : 2);
+}
+
+// Coordinates per lane of the decode pass.  Sixteen halve the per-worker overhead of eight; eight double the number
+// of waves, and with a chunk's worth of codes the overhead is little.  us with eight | sixteen: 64 workers, 192 bits,
+// one scale: 2.1 M 36 | 41, 4 M 52 | 55, 5.4 M 70 | 70, 8 M 93 | 89, 25.6 M 183 | 148;  bucket-wise 3.5 M 54 | 58,
+// 4 M 63 | 59, 8 M 113 | 93;  8 workers, 32 bits: 5.4 M 17.6 | 22, 25.6 M 53 | 63;  16 workers, 48 bits, 25.6 M
+// 82 | 79.  The two-track decode holds twice the accumulators and is faster with eight throughout (50 workers, four
+// bits, 5.4 M coordinates, with the update: 79.5 us with eight, 86.8 with sixteen; 24 workers, 25.6 M: 260 and 285).
+//   many_scales: bucket- or layer-wise;  sum_bits: of the workers that arrived
+inline int decode_coords(int64_t d, bool two, bool many_scales, int sum_bits)
+{
+    if (two || sum_bits <= 40) return 8;
+    return d >= (many_scales ? (int64_t)15 << 18 : (int64_t)5 << 20) ? 16 : 8;
 }
 
 }  // namespace agc

@@ -102,13 +102,14 @@ constexpr int kPartBits = 1024;
 // chunks of kDecChunkBytes, which is what a workgroup fetches at a time.
 constexpr int kDecChunkBytes = 12288;
 
-struct DecWorker {        // one arrived worker; read with scalar loads
+struct DecWorker {        // one arrived worker; read with scalar loads (k_decode: the first half)
     float coef;           // w_i * scale_i / L_i (bucket-wise scales: w_i / L_i; layer-wise: unused)
     float coef2;          // the same with the second decoding vector
     uint32_t width;       // 1 << bits; 1 for two bits and weights that can be halved exactly
     uint32_t pos;         // its first unit within its chunk
     uint32_t worker;
-    uint32_t pad[3];
+    uint32_t bits;
+    const char* codes;    // its stream
 };
 static_assert(sizeof(DecWorker) == 32, "one record is two 16-byte scalar loads");
 
@@ -198,7 +199,8 @@ struct DecodeStreams {     // the arrived workers of a decode call, in ascending
 template <int CAP>
 struct DecodeList {        // the same as kernel arguments of the decode's prologue, with the places in the chunks
     int n_arrived;
-    int units_per_chunk;
+    int units_per_chunk;   // 0: the decode takes no chunks (k_decode_direct)
+    int unit_pieces;       // 16-byte pieces of a unit
     uint32_t groups;       // 128-code groups of a stream
     const void* codes[CAP];
     float w[CAP];

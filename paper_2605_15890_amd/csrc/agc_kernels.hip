@@ -658,6 +658,22 @@ __global__ __launch_bounds__(kWgThreads) void k_decode_table(DecodeList<CAP> in,
     const int i = threadIdx.x;
     const int l = blockIdx.x;
     const int n = in.n_arrived;
+    const int per_chunk = in.units_per_chunk;
+    auto write_unit = [&](int of, int u) {  // slot u of the chunk of worker `of`
+        const int bits = in.bits[of], mine = u - in.pos[of];
+        const uint32_t pieces = in.groups * (uint32_t)bits;  // of the whole stream
+        uint32_t at = (uint32_t)((mine < bits ? mine : bits - 1) * in.unit_pieces);
+        if (at >= pieces) at = 0;  // a unit past the end of a short stream: nobody uses what is read
+        tab.units[(int64_t)in.chunk[of] * per_chunk + u] =
+            DecUnit{(const char*)in.codes[of] + (int64_t)at * 16, (uint32_t)(bits * in.unit_pieces), pieces - at};
+    };
+    // The last worker of a chunk repeats its last unit up to the chunk's end (a second request of the same lines),
+    // so that every piece of a chunk can be requested without a test.  In the last chunk that may be nearly all of
+    // it: all threads share it (one thread alone took 2 us, a quarter of a decode of one to four workers).
+    if (l == 0) {
+        const int u = in.pos[n - 1] + in.bits[n - 1] + i;
+        if (u < per_chunk) write_unit(n - 1, u);
+    }
     if (i >= n) return;
     const int b = in.bits[i];
     const int worker = in.worker[i];
@@ -673,22 +689,14 @@ __global__ __launch_bounds__(kWgThreads) void k_decode_table(DecodeList<CAP> in,
         if (l != 0) return;
     }
     const int chunk = in.chunk[i], pos = in.pos[i];
-    const int per_chunk = in.units_per_chunk, unit_pieces = kDecPieces / per_chunk;
     const bool halves = SCALES == 0 && b == 2 && halves_exactly(c1) && (!TWO || halves_exactly(c2));
-    tab.workers[i] = DecWorker{c1, c2, halves ? 1u : 1u << b, (uint32_t)pos, (uint32_t)worker, {0u, 0u, 0u}};
+    tab.workers[i] = DecWorker{c1, c2, halves ? 1u : 1u << b, (uint32_t)pos, (uint32_t)worker, (uint32_t)b,
+                               (const char*)in.codes[i]};
+    if (per_chunk == 0) return;  // decoded without chunks
     if (pos == 0) tab.chunk_first[chunk] = i;
     if (i == n - 1) tab.chunk_first[chunk + 1] = n;
-    // the worker's units; the last worker of a chunk repeats its last unit up to the chunk's end (a second
-    // request of the same lines), so that every piece of a chunk can be requested without a test
-    const bool last = i == n - 1 || in.pos[i + 1] == 0;
-    const int end = last ? per_chunk : pos + b;
-    const uint32_t pieces = in.groups * (uint32_t)b;  // of the whole stream
-    for (int u = pos; u < end; ++u) {
-        uint32_t at = (uint32_t)((u - pos < b ? u - pos : b - 1) * unit_pieces);
-        if (at >= pieces) at = 0;  // a unit past the end of a short stream: nobody uses what is read
-        tab.units[(int64_t)chunk * per_chunk + u] = DecUnit{(const char*)in.codes[i] + (int64_t)at * 16,
-                                                            (uint32_t)(b * unit_pieces), pieces - at};
-    }
+    const int end = i < n - 1 && in.pos[i + 1] == 0 ? per_chunk : pos + b;
+    for (int u = pos; u < end; ++u) write_unit(i, u);
 }
 
 // acc = fma(c, v, acc), in acc's own register: left to itself the compiler gives every bit-width's branch
@@ -977,6 +985,51 @@ void k_decode(const DecWorker* __restrict__ workers, const DecUnit* __restrict__
     }
 }
 
+// The decode of a few workers: a lane owns 32 coordinates, which are `bits` whole words of a stream, and loads
+// them right before they are used.  One request per wave is in flight, which bounds many workers (see above); for
+// few of them the estimate's stores are most of the traffic, and here a lane writes a whole line of it.
+template <int LO, int HI>
+__device__ __forceinline__ void decode_direct(uint32_t mask, const global_u32* src, float c1, float (&acc)[32])
+{
+    if (mask & (1u << LO)) {
+        constexpr int B = LO == 0 ? 2 : LO;
+        uint32_t w[B];
+        float none[1];
+#pragma unroll
+        for (int t = 0; t < B; ++t) w[t] = __builtin_nontemporal_load(src + t);
+        if constexpr (LO == 0) decode_words_2bit<32, B, false>(w, 0.5f * c1, 0.f, acc, none);
+        else decode_words<B, 32, B, false>(w, c1, 0.f, acc, none);
+    }
+    if constexpr (LO < HI) decode_direct<LO + 1, HI>(mask, src, c1, acc);
+}
+
+template <int SCALES>
+__global__ __launch_bounds__(kWgThreads)
+__attribute__((amdgpu_waves_per_eu(6, 6)))
+void k_decode_direct(const DecWorker* __restrict__ workers, DecodeArgs a)
+{
+    const int64_t t = (int64_t)blockIdx.x * kWgThreads + threadIdx.x;
+    const int64_t m0 = t * 32, block = t >> 3;
+    if (m0 >= a.d) return;
+    float acc[32];
+#pragma unroll
+    for (int q = 0; q < 32; ++q) acc[q] = 0.f;
+    const float* layer_row = SCALES == 2 ? a.coef_layer + (int64_t)a.block_layer[block] * a.n_arrived : nullptr;
+    for (int e = 0; e < a.n_arrived; ++e) {
+        const DecWorker wk = load_uniform(workers + e);
+        float c1 = wk.coef;
+        uint32_t mask = wk.width;
+        if (SCALES == 1) c1 = c1 * a.scales[(int64_t)wk.worker * a.nb + block];
+        if (SCALES == 2) c1 = layer_row[e];
+        if (SCALES != 0 && mask == 4u && __builtin_amdgcn_ballot_w64(!halves_exactly(c1)) == 0) mask = 1u;
+        const global_u32* src = (const global_u32*)wk.codes + t * wk.bits;
+        if (mask & 0x1Fu) decode_direct<0, 4>(mask, src, c1, acc);
+        if (mask & 0x1E0u) decode_direct<5, 8>(mask, src, c1, acc);
+        if (mask & 0x1FE00u) decode_direct<9, 16>(mask, src, c1, acc);
+    }
+    store_coords<32>(a.ghat + m0, acc, m0, a.d);
+}
+
 // ---- host side
 template <bool TWO, int SCALES, int COORDS>
 static void launch_decode_main(hipStream_t stream, const DecodeTables& tab, DecodeArgs a)
@@ -994,7 +1047,9 @@ static hipError_t launch_decode_cap(const DecodeStreams& in, int coords, const D
     DecodeList<CAP> list;
     list.n_arrived = in.n_arrived;
     list.groups = (uint32_t)((a.d + 127) / 128);
-    list.units_per_chunk = kDecChunkBytes / (32 * coords);
+    const bool direct = !TWO && decode_is_direct(in.n_arrived, a.d);
+    list.units_per_chunk = direct ? 0 : kDecChunkBytes / (32 * coords);
+    list.unit_pieces = 2 * coords;
     int chunk = -1, fill = list.units_per_chunk;
     for (int i = 0; i < in.n_arrived; ++i) {  // consecutive workers, whole, as long as the chunk holds them
         const int b = in.bits[i];
@@ -1021,24 +1076,25 @@ static hipError_t launch_decode_cap(const DecodeStreams& in, int coords, const D
         if (e != hipSuccess) return e;
     }
     if constexpr (!TWO) {
+        if (direct) {
+            const int64_t lanes = (a.d + 31) / 32;
+            hipLaunchKernelGGL((k_decode_direct<SCALES>), dim3((unsigned)((lanes + kWgThreads - 1) / kWgThreads)),
+                               dim3(kWgThreads), 0, stream, tab.workers, a);
+            return hipGetLastError();
+        }
         if (coords == 16) launch_decode_main<TWO, SCALES, 16>(stream, tab, a);
     }
     if (coords == 8) launch_decode_main<TWO, SCALES, 8>(stream, tab, a);
     return hipGetLastError();
 }
 
-// Coordinates per lane.  Sixteen halve the per-worker overhead of eight, eight double the number of waves:
-// below 2^21 coordinates a 16-coordinate tiling leaves most of the chip's wave slots empty (64 workers,
-// three bits: 1 M coordinates 26.2 us with eight, 29.6 with sixteen; 4 M 42.5 and 39.5; 25.6 M 183 and
-// 148).  The two-track decode holds twice the accumulators and is faster with eight throughout (50 workers,
-// four bits, 5.4 M coordinates, with the update: 79.5 us with eight, 86.8 with sixteen; 24 workers, 25.6 M:
-// 260 and 285).
-constexpr int64_t kDecodeWide = (int64_t)1 << 21;
 template <bool TWO, int SCALES>
 static hipError_t launch_decode_scales(const DecodeStreams& in, const DecodeTables& tab, int n_layers,
                                        const float* scales, const Workspace* ws, const DecodeArgs& a, hipStream_t stream)
 {
-    const int coords = !TWO && a.d >= kDecodeWide ? 16 : 8;
+    int sum_bits = 0;
+    for (int i = 0; i < in.n_arrived; ++i) sum_bits += in.bits[i];
+    const int coords = decode_coords(a.d, TWO, SCALES != 0, sum_bits);
     // the launch copies its arguments at about 1.7 ns a byte: 20 bytes per worker it has room for
     if (in.n_arrived <= 16) return launch_decode_cap<TWO, SCALES, 16>(in, coords, tab, n_layers, scales, ws, a, stream);
     if (in.n_arrived <= 64) return launch_decode_cap<TWO, SCALES, 64>(in, coords, tab, n_layers, scales, ws, a, stream);

@@ -17,6 +17,11 @@ extern "C" int parts(int64_t d, int n, int k, int nnz, int band, int norm, int b
 }
 extern "C" int decode_per_cu(unsigned lds_bytes) { return agc::decode_per_cu(lds_bytes); }
 extern "C" int64_t decode_groups(int64_t tiles, int chunks, int per_cu) { return agc::decode_groups(tiles, chunks, per_cu); }
+extern "C" int decode_is_direct(int n, int64_t d) { return agc::decode_is_direct(n, d); }
+extern "C" int decode_coords(int64_t d, int two, int many_scales, int sum_bits)
+{
+    return agc::decode_coords(d, two != 0, many_scales != 0, sum_bits);
+}
 extern "C" unsigned first_group(int64_t d, unsigned groups) { return agc::first_group(d, groups); }
 """
 
@@ -35,6 +40,8 @@ def rules(tmp_path_factory):
     lib.decode_per_cu.argtypes = [ctypes.c_uint]
     lib.decode_groups.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int]
     lib.decode_groups.restype = ctypes.c_int64
+    lib.decode_is_direct.argtypes = [ctypes.c_int, ctypes.c_int64]
+    lib.decode_coords.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 3
     lib.first_group.argtypes = [ctypes.c_int64, ctypes.c_uint]
     lib.first_group.restype = ctypes.c_uint
     return lib
@@ -87,6 +94,20 @@ def test_decode_launches_what_a_compute_unit_holds(rules):
 
 @pytest.mark.parametrize("tiles,chunks,per_cu,groups", [
     (1, 1, 6, 1), (1319, 9, 6, 1319), (1319, 2, 5, 1280), (6250, 2, 6, 1536), (6250, 3, 5, 1280), (6250, 4, 6, 6250),
-    (6250, 20, 5, 6250), (2637, 20, 6, 1536), (2560, 20, 5, 2560), (2 ** 21, 1, 4, 1024)])
+    (6250, 20, 5, 6250), (2637, 20, 6, 1536), (2857, 20, 6, 2857), (2560, 20, 5, 2560), (2 ** 21, 1, 4, 1024)])
 def test_decode_walks_over_the_tiles_where_a_tile_is_little_work(rules, tiles, chunks, per_cu, groups):
     assert rules.decode_groups(tiles, chunks, per_cu) == groups
+
+
+@pytest.mark.parametrize("n,d,direct", [(0, 1, 1), (1, 4096, 1), (2, 25_600_000, 1), (3, 25_600_000, 0), (4, 2 ** 25 - 1, 0),
+                                        (4, 2 ** 25, 1), (5, 2 ** 33, 0)])
+def test_decode_of_a_few_workers_takes_no_chunks(rules, n, d, direct):
+    assert rules.decode_is_direct(n, d) == direct
+
+
+@pytest.mark.parametrize("d,two,many_scales,sum_bits,coords", [
+    (2 ** 21, 0, 0, 192, 8), (5 * 2 ** 20 - 1, 0, 0, 192, 8), (5 * 2 ** 20, 0, 0, 192, 16), (5_400_000, 0, 0, 40, 8),
+    (25_600_000, 0, 0, 32, 8), (25_600_000, 0, 0, 41, 16), (15 * 2 ** 18 - 1, 0, 1, 192, 8), (15 * 2 ** 18, 0, 1, 192, 16),
+    (25_600_000, 1, 0, 307, 8), (25_600_000, 1, 1, 307, 8)])
+def test_decode_takes_sixteen_coordinates_per_lane_on_long_vectors(rules, d, two, many_scales, sum_bits, coords):
+    assert rules.decode_coords(d, two, many_scales, sum_bits) == coords
