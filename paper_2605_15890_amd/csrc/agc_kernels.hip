@@ -389,14 +389,25 @@ __device__ __forceinline__ float inv16_of(float scale, int bits)
     return (q <= 3.402823466e+38f) ? q : 0.f;
 }
 
+// acc = acc + rows b0, b0 + 1, .. of part, BATCH of them or up to s1; past s1 the last row is read again
+template <int BATCH>
+__device__ __forceinline__ void add_rows(const double* part, int n, int64_t b0, int64_t s1, double& acc)
+{
+    double v[BATCH];
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) v[u] = part[(b0 + u < s1 ? b0 + u : s1 - 1) * n];
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) acc = b0 + u < s1 ? acc + v[u] : acc;
+}
+
 // Euclidean scale, level 3 of the tree: one workgroup per group of up to 64 segments, thread t follows
 // worker t through the group's rows of [segment][worker] (coalesced) and adds them in segment order.  The
 // rows are requested 32 at a time before the first addition: the kernel is one round trip to memory per
-// batch (batches of eight took 7-9 us, mostly waiting; now 5-6).  With layer-wise scales the groups of
+// batch (batches of eight took 7-9 us, mostly waiting; now 5-6); the last eight or fewer are a batch of eight
+// (of 32, where 28 additions are thrown away, one to three workers x 4096 were 1 us slower).  With layer-wise scales the groups of
 // every layer are counted from its first segment and listed in group_seg.
 __global__ __launch_bounds__(kWgThreads) void k_scale_groups(int n, Workspace ws, int64_t ngroup)
 {
-    constexpr int kBatch = 32;
     const int64_t g = blockIdx.x;
     int64_t s0 = g * kGroupSegs, s1 = s0 + kGroupSegs < ws.nseg ? s0 + kGroupSegs : ws.nseg;
     if (ws.n_layers > 0) {
@@ -406,13 +417,9 @@ __global__ __launch_bounds__(kWgThreads) void k_scale_groups(int n, Workspace ws
     for (int i = threadIdx.x; i < n; i += kWgThreads) {
         const double* part = ws.part_sq + i;
         double acc = 0.0;
-        for (int64_t b0 = s0; b0 < s1; b0 += kBatch) {
-            double v[kBatch];  // past the group's end its last row is read again
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) v[u] = part[(b0 + u < s1 ? b0 + u : s1 - 1) * n];
-#pragma unroll
-            for (int u = 0; u < kBatch; ++u) acc = b0 + u < s1 ? acc + v[u] : acc;
-        }
+        int64_t b0 = s0;
+        for (; s1 - b0 > 8; b0 += 32) add_rows<32>(part, n, b0, s1, acc);
+        if (b0 < s1) add_rows<8>(part, n, b0, s1, acc);
         ws.group_sq[(int64_t)i * ngroup + g] = acc;
     }
 }
