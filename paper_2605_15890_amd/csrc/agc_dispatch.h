@@ -129,4 +129,10 @@ inline int decode_coords(int64_t d, bool two, bool many_scales, int sum_bits)
     return d >= (many_scales ? (int64_t)15 << 18 : (int64_t)5 << 20) ? 16 : 8;
 }
 
+// Least squares: slices that share the parts of one feature in the sum of the workgroups' gradients.  Eight hide
+// the memory's latency where there are many parts (65536 x 512 samples x features, 512 parts 18 us, one slice 34);
+// up to sixteen parts one thread requests all of them together, and eight slices would only be eight times as many
+// workgroups (2^17 x 8192, one part: 387 us, now 346; 65536 x 4096, 8 parts 92, now 87).
+constexpr int ls_reduce_slices(int wg_per_part) { return wg_per_part > 16 ? 8 : 1; }
+
 }  // namespace agc

@@ -310,36 +310,39 @@ __global__ __launch_bounds__(kLsThreads, 2) void k_ls_resident(const uint16_t* _
     }
 }
 
-// G[p][f] = sum over the partition's workgroups.  A workgroup takes 32 features (whole lines of the parts);
-// its eight slices of 32 threads add an eighth of the parts each, in order, sixteen requested together, and
-// the eight sums are added in order.  (One thread per feature and one part at a time: 29 us for 128 parts
-// of 512 features, now 2.)
-constexpr int kRedFeat = 32, kRedSlices = kLsThreads / kRedFeat, kRedBatch = 16;
+// G[p][f] = sum over the partition's workgroups, BATCH parts requested together.  A workgroup takes FEAT features
+// (whole lines of the parts); its 256 / FEAT slices of threads add a share of the parts each, in order, and their
+// sums are added in order.
+template <int FEAT, int BATCH>
 __global__ __launch_bounds__(kLsThreads) void k_ls_reduce(const float* __restrict__ partial, int n_feat,
                                                           int wg_per_part, float* G, int64_t ldg)
 {
-    __shared__ float lds_s[kRedSlices][kRedFeat];
+    constexpr int kSlices = kLsThreads / FEAT;
+    __shared__ float lds_s[kSlices][FEAT];
     const int p = blockIdx.y;
-    const int col = threadIdx.x % kRedFeat, slice = threadIdx.x / kRedFeat;
-    const int f = blockIdx.x * kRedFeat + col;  // n_feat is a multiple of 128
-    const int q0 = wg_per_part * slice / kRedSlices, q1 = wg_per_part * (slice + 1) / kRedSlices;
+    const int col = threadIdx.x % FEAT, slice = threadIdx.x / FEAT;
+    const int f = blockIdx.x * FEAT + col;  // n_feat is a multiple of 128
+    const int q0 = wg_per_part * slice / kSlices, q1 = wg_per_part * (slice + 1) / kSlices;
     const float* src = partial + (int64_t)p * wg_per_part * n_feat + f;
     float s = 0.f;
-    for (int q = q0; q < q1; q += kRedBatch) {
-        float v[kRedBatch];  // past the slice's end its last part is read again
+    if (FEAT <= 128 || f < n_feat) {
+        for (int q = q0; q < q1; q += BATCH) {
+            float v[BATCH];  // past the slice's end its last part is read again
 #pragma unroll
-        for (int u = 0; u < kRedBatch; ++u) v[u] = src[(int64_t)(q + u < q1 ? q + u : q1 - 1) * n_feat];
+            for (int u = 0; u < BATCH; ++u) v[u] = src[(int64_t)(q + u < q1 ? q + u : q1 - 1) * n_feat];
 #pragma unroll
-        for (int u = 0; u < kRedBatch; ++u) s = q + u < q1 ? s + v[u] : s;
+            for (int u = 0; u < BATCH; ++u) s = q + u < q1 ? s + v[u] : s;
+        }
     }
-    lds_s[slice][col] = s;
-    __syncthreads();
-    if (slice == 0) {
-        float t = 0.f;
+    if constexpr (kSlices > 1) {
+        lds_s[slice][col] = s;
+        __syncthreads();
+        if (slice != 0) return;
+        s = 0.f;
 #pragma unroll
-        for (int u = 0; u < kRedSlices; ++u) t = t + lds_s[u][col];
-        G[(int64_t)p * ldg + f] = t;
+        for (int u = 0; u < kSlices; ++u) s = s + lds_s[u][col];
     }
+    if (FEAT <= 128 || f < n_feat) G[(int64_t)p * ldg + f] = s;
 }
 
 __global__ __launch_bounds__(kLsThreads) void k_gd_update(float* beta, const float* __restrict__ ghat,
@@ -383,8 +386,14 @@ hipError_t launch_ls_partial_gradients(const void* X, int64_t n_rows, int n_feat
         hipLaunchKernelGGL((k_ls_resident<8, 4, 1>), grid, block, 0, stream, x, y, w, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_ls_reduce, dim3((unsigned)(n_feat / kRedFeat), (unsigned)k_parts), dim3(kLsThreads), 0, stream,
-                       partial, n_feat, a.wg_per_part, G, ldg);
+    auto reduce = [&](auto kernel, int feat) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((n_feat + feat - 1) / feat), (unsigned)k_parts), block, 0, stream,
+                           static_cast<const float*>(partial), n_feat, a.wg_per_part, G, ldg);
+    };
+    const int slices = ls_reduce_slices(a.wg_per_part);
+    if (slices > 1) reduce(k_ls_reduce<32, 16>, 32);
+    else if (a.wg_per_part > 4) reduce(k_ls_reduce<256, 16>, 256);
+    else reduce(k_ls_reduce<256, 4>, 256);
     return hipGetLastError();
 }
 

@@ -22,6 +22,7 @@ extern "C" int decode_coords(int64_t d, int two, int many_scales, int sum_bits)
 {
     return agc::decode_coords(d, two != 0, many_scales != 0, sum_bits);
 }
+extern "C" int ls_reduce_slices(int wg_per_part) { return agc::ls_reduce_slices(wg_per_part); }
 extern "C" unsigned first_group(int64_t d, unsigned groups) { return agc::first_group(d, groups); }
 """
 
@@ -42,6 +43,7 @@ def rules(tmp_path_factory):
     lib.decode_groups.restype = ctypes.c_int64
     lib.decode_is_direct.argtypes = [ctypes.c_int, ctypes.c_int64]
     lib.decode_coords.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 3
+    lib.ls_reduce_slices.argtypes = [ctypes.c_int]
     lib.first_group.argtypes = [ctypes.c_int64, ctypes.c_uint]
     lib.first_group.restype = ctypes.c_uint
     return lib
@@ -111,3 +113,7 @@ def test_decode_of_a_few_workers_takes_no_chunks(rules, n, d, direct):
     (25_600_000, 1, 0, 307, 8), (25_600_000, 1, 1, 307, 8)])
 def test_decode_takes_sixteen_coordinates_per_lane_on_long_vectors(rules, d, two, many_scales, sum_bits, coords):
     assert rules.decode_coords(d, two, many_scales, sum_bits) == coords
+
+
+def test_least_squares_reduces_few_parts_without_slices(rules):
+    assert [rules.ls_reduce_slices(p) for p in (1, 16, 17, 512)] == [1, 1, 8, 8]

@@ -93,6 +93,13 @@ def test_infinity_in_the_last_sample_of_a_partial_block(n_feat):
         assert _rel(got[p], G_o[p]) <= REL_L2_TOL, p
 
 
+@pytest.mark.parametrize("n_rows,n_feat,k", [(3 * 2736, 2048, 3), (8192, 1152, 1), (6 * 1408, 128, 6), (16 * 80, 4096, 16),
+                                             (30 * 272, 1280, 30), (64 * 256, 640, 64)])
+def test_gradients_from_many_and_from_few_parts(n_rows, n_feat, k):
+    """Parts per partition: 170 (slices of 21, two batches), 512, 3, 5, 17 (the fewest that are sliced) and 4."""
+    test_partial_gradients_match_fp64(n_rows, n_feat, k)
+
+
 def test_rejects_shapes_the_kernel_does_not_cover():
     import torch
     X = torch.zeros((64, 128), dtype=torch.bfloat16, device="cuda")
