@@ -129,6 +129,20 @@ inline int decode_coords(int64_t d, bool two, bool many_scales, int sum_bits)
     return d >= (many_scales ? (int64_t)15 << 18 : (int64_t)5 << 20) ? 16 : 8;
 }
 
+// Least squares: samples side by side in a row slot (k_ls_resident), for rows of at most 1024 features.  The widest
+// fold keeps all lanes busy; but a block is then 32 * fold samples whether they exist or not, so the fold is no wider
+// than a partition fills.  Up to 4096 samples in all (128 workgroups of 32) nothing but the time of one block
+// counts, and that is shortest without.  Features, partitions, samples per partition: without | with the widest, us:
+// 128, 32, 16 7.0 | 9.4, 128, 1, 4096 9.2 | 9.2, 128, 16, 512 10.6 | 8.9, 128, 128, 64 9.9 | 9.6 (two 8.3),
+// 1024, 4, 256 8.1 | 9.2, 1024, 128, 48 10.3 | 11.3, 512, 4, 16384 28 | 17.
+inline int ls_fold(int64_t n_rows, int64_t rows_per_part, int n_feat)
+{
+    if (n_rows <= 4096) return 1;
+    int fold = n_feat <= 128 ? 16 : n_feat <= 256 ? 8 : n_feat <= 512 ? 4 : n_feat <= 1024 ? 2 : 1;
+    while (fold > 1 && 32 * fold > rows_per_part) fold /= 2;
+    return fold;
+}
+
 // Least squares: slices that share the parts of one feature in the sum of the workgroups' gradients.  Eight hide
 // the memory's latency where there are many parts (65536 x 512 samples x features, 512 parts 18 us, one slice 34);
 // up to sixteen parts one thread requests all of them together, and eight slices would only be eight times as many

@@ -107,7 +107,7 @@ __device__ __forceinline__ void fma8(float* acc, const u32x4& u, float r)
 // ROWS samples per block, NG groups of eight features per lane: ROWS * NG = 32 registers of four
 // packed words hold the block (16 x 2 for up to 4096 features, 8 x 4 for up to 8192).
 //
-// FOLD > 1, for rows of at most 2048 / FOLD features: the 256 lanes, which 2048 features would need, hold
+// FOLD > 1 (ls_fold), for rows of at most 2048 / FOLD features: the 256 lanes, which 2048 features would need, hold
 // FOLD samples side by side, so that a block is ROWS * FOLD samples and no lane idles.  The lanes of one
 // sample are chosen for the matrix product of sweep 1: its diagonal element D[n][n] adds the lanes n, n+16,
 // n+32, n+48 of a wave and lands in 16-lane row n / 4, so with FOLD = 16 the four samples of a wave take the
@@ -366,8 +366,8 @@ hipError_t launch_ls_partial_gradients(const void* X, int64_t n_rows, int n_feat
                                        float* resid, float* partial, hipStream_t stream)
 {
     LsArgs a{n_rows, n_feat, k_parts, ls_wg_per_part(n_rows, n_feat, k_parts), n_rows / k_parts, resid, partial};
-    // rows of at most 1024 features go several side by side (FOLD); a workgroup then needs more samples
-    const int fold = n_feat <= 128 ? 16 : n_feat <= 256 ? 8 : n_feat <= 512 ? 4 : n_feat <= 1024 ? 2 : 1;
+    // samples side by side (FOLD): a workgroup then needs more of them
+    const int fold = ls_fold(n_rows, a.rows_per_part, n_feat);
     if (fold > 1) {
         const int64_t blocks = (a.rows_per_part + 32 * fold - 1) / (32 * fold);
         if (blocks < a.wg_per_part) a.wg_per_part = (int)blocks;

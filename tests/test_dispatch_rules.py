@@ -22,6 +22,7 @@ extern "C" int decode_coords(int64_t d, int two, int many_scales, int sum_bits)
 {
     return agc::decode_coords(d, two != 0, many_scales != 0, sum_bits);
 }
+extern "C" int ls_fold(int64_t n_rows, int64_t rows_per_part, int n_feat) { return agc::ls_fold(n_rows, rows_per_part, n_feat); }
 extern "C" int ls_reduce_slices(int wg_per_part) { return agc::ls_reduce_slices(wg_per_part); }
 extern "C" unsigned first_group(int64_t d, unsigned groups) { return agc::first_group(d, groups); }
 """
@@ -43,6 +44,7 @@ def rules(tmp_path_factory):
     lib.decode_groups.restype = ctypes.c_int64
     lib.decode_is_direct.argtypes = [ctypes.c_int, ctypes.c_int64]
     lib.decode_coords.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 3
+    lib.ls_fold.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]
     lib.ls_reduce_slices.argtypes = [ctypes.c_int]
     lib.first_group.argtypes = [ctypes.c_int64, ctypes.c_uint]
     lib.first_group.restype = ctypes.c_uint
@@ -113,6 +115,14 @@ def test_decode_of_a_few_workers_takes_no_chunks(rules, n, d, direct):
     (25_600_000, 1, 0, 307, 8), (25_600_000, 1, 1, 307, 8)])
 def test_decode_takes_sixteen_coordinates_per_lane_on_long_vectors(rules, d, two, many_scales, sum_bits, coords):
     assert rules.decode_coords(d, two, many_scales, sum_bits) == coords
+
+
+@pytest.mark.parametrize("k,rows,n_feat,fold", [
+    (1, 4096, 128, 1), (4, 16, 128, 1), (32, 16, 1024, 1), (128, 32, 128, 1), (128, 48, 1024, 1), (128, 48, 128, 1),
+    (128, 64, 128, 2), (128, 96, 256, 2), (128, 128, 128, 4), (16, 512, 128, 16), (16, 512, 256, 8), (16, 512, 384, 4),
+    (16, 512, 512, 4), (16, 512, 640, 2), (16, 512, 1024, 2), (16, 512, 1152, 1), (32, 32768, 4096, 1), (1, 16384, 128, 16)])
+def test_least_squares_folds_no_wider_than_a_partition_fills(rules, k, rows, n_feat, fold):
+    assert rules.ls_fold(k * rows, rows, n_feat) == fold
 
 
 def test_least_squares_reduces_few_parts_without_slices(rules):

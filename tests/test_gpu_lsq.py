@@ -64,14 +64,20 @@ def test_narrow_rows_several_samples_side_by_side(n_feat, rows_per_part):
     test_partial_gradients_match_fp64(rows_per_part * 3, n_feat, 3)
 
 
+def _fold(n_feat):
+    """The most samples side by side that rows of this many features allow."""
+    return 16 if n_feat <= 128 else 8 if n_feat <= 256 else 4 if n_feat <= 512 else 2 if n_feat <= 1024 else 1
+
+
 @pytest.mark.parametrize("n_feat", [128, 256, 512, 1024])
 def test_infinity_in_the_last_sample_of_a_partial_block(n_feat):
-    """48 samples are less than a block of any of these widths, so the last one stands in for the samples
-    that do not exist: they must add nothing, also where that sample holds an infinity (whose product with
-    a zero residual is a NaN).  All three bfloat16 pieces of the model's entry at that feature are positive,
-    so the residual is +inf and the gradient +-inf, as in binary64."""
+    """Partitions of one whole block and sixteen samples more: the last of those stands in for the samples that
+    do not exist, and must add nothing, also where it holds an infinity (whose product with a zero residual
+    is a NaN).  All three bfloat16 pieces of the model's entry at that feature are positive, so the residual
+    is +inf and the gradient +-inf, as in binary64."""
     import torch
-    k, rows, at = 3, 48, 77
+    rows, at = 32 * _fold(n_feat) + 16, 77
+    k = 4096 // rows + 1                 # more than 4096 samples in all: below that nothing is folded
     Xb, y, _, X, y_d = _device_problem(k * rows, n_feat)
     beta = np.random.default_rng(n_feat).standard_normal(n_feat).astype(np.float32)
     beta[at] = 1.0 + 2.0 ** -9 + 2.0 ** -18
@@ -91,6 +97,15 @@ def test_infinity_in_the_last_sample_of_a_partial_block(n_feat):
     assert np.array_equal(got[0], G_o[0].astype(np.float32))
     for p in range(1, k):
         assert _rel(got[p], G_o[p]) <= REL_L2_TOL, p
+
+
+@pytest.mark.parametrize("n_feat", [128, 256, 384, 512, 640, 1024])
+@pytest.mark.parametrize("blocks,more", [(2, 0), (5, 48), (17, 16)])
+def test_folded_rows_in_several_blocks(n_feat, blocks, more):
+    """32 partitions have 16 workgroups each: with 17 whole blocks and a partial one, some workgroups refill
+    their registers with a second block, whole or partial; two and five blocks leave one to each.  The bound is
+    that of the wide rows: the same terms are added, in shorter chains."""
+    test_partial_gradients_match_fp64((32 * _fold(n_feat) * blocks + more) * 32, n_feat, 32)
 
 
 @pytest.mark.parametrize("n_rows,n_feat,k", [(3 * 2736, 2048, 3), (8192, 1152, 1), (6 * 1408, 128, 6), (16 * 80, 4096, 16),
