@@ -3,7 +3,7 @@
  * (include/agc.h is); these entry points exist so that benchmarks and tests can time the
  * library's kernels one by one, scale hardware counters against a kernel of known traffic,
  * measure what the memory system delivers for the access pattern of the two streaming passes,
- * and force a code onto the slow general path.
+ * and force a code onto the slow general path or a short vector onto the kernels of long ones.
  */
 #ifndef AGC_DEBUG_H
 #define AGC_DEBUG_H
@@ -19,6 +19,11 @@ extern "C" {
 /* Testing hook in agc_opts: force_generic != 0 makes agc_set_code ignore the structure of the
  * code (cyclic band, monotone intervals) so that the general gather driver runs; results are
  * the same bits, only slower. */
+
+/* Testing hook: on != 0 makes the worker side of this context take the kernels of long vectors at any
+ * length (short vectors share the workers of a block among the waves of a workgroup); results are the same
+ * bits.  AGC_EINVAL without a context. */
+agc_status agc_debug_force_long(agc_ctx *ctx, int on);
 
 /* --------------------------------------------------------------------------------------
  * Per-kernel timing (HIP events recorded on the caller's stream around each kernel)

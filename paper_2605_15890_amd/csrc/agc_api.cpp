@@ -38,6 +38,7 @@ struct agc_ctx {
     float* d_val = nullptr;
     agc::WindowRec* d_win = nullptr;   // monotone-interval codes only
     int band = 0;
+    bool force_long = false;  // testing hook
     // workspace
     agc::Workspace ws{};
     // profiling
@@ -185,7 +186,8 @@ void add_arrived(agc::DecodeStreams& ds, int i, const void* codes, float w, floa
 agc::CodeDev code_dev(const agc_ctx* c)
 {
     const int band = c->opts.force_generic ? 0 : c->band;
-    const bool parts = agc::use_parts(c->d, c->n, c->k, c->nnz, band, c->opts.scale_mode == AGC_SCALE_L2, c->opts.bucket != 0);
+    const bool parts = !c->force_long &&
+                       agc::use_parts(c->d, c->n, c->k, c->nnz, band, c->opts.scale_mode == AGC_SCALE_L2, c->opts.bucket != 0);
     return agc::CodeDev{c->d_row_ptr, c->d_col, c->d_val, band, c->d_win, parts};
 }
 
@@ -743,6 +745,13 @@ agc_status agc_debug_stream_rows(const float* G_dev, int64_t ldg, int k, int64_t
                                            waves_per_simd, fma_per_row, out_dev,
                                            reinterpret_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? AGC_OK : AGC_EHIP;
+}
+
+agc_status agc_debug_force_long(agc_ctx* c, int on)
+{
+    if (!c) return fail(nullptr, AGC_EINVAL, "null context");
+    c->force_long = on != 0;
+    return AGC_OK;
 }
 
 agc_status agc_profile_enable(agc_ctx* c, int on)
