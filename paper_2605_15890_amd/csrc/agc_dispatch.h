@@ -85,7 +85,7 @@ inline unsigned first_group(int64_t d, unsigned groups)
 }
 
 // Workgroups of the decode pass that a compute unit holds: six, which was measured to be best with one scale per
-// vector (five 0.162, four 0.166 against 0.148 ms for 64 workers x 25.6 M), or as many as 160 KB of LDS has room
+// vector (walking over the tiles: five 0.162, four 0.166 against 0.148 ms for 64 workers x 25.6 M), or as many as 160 KB of LDS has room
 // for beside the weights of bucket- and layer-wise scales: five, four with two tracks and layers.
 constexpr int decode_per_cu(unsigned lds_bytes)
 {

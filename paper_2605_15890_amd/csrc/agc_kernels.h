@@ -143,7 +143,7 @@ struct Workspace {
     WorkerQ* wq;          // [n]  written by the scale finalize
     void* dec;            // decode_table_bytes(n) bytes: tables of the arrived workers, written by the decode prologue
     int64_t nseg, ngroup;
-    // layer-wise scales (n_layers > 0; max-abs only): the layer of every 256-coordinate block, and
+    // layer-wise scales (n_layers > 0): the layer of every 256-coordinate block, and
     // the decode weights w_i * scale_il / L_i (and v_i * ...) of the arrived workers, [layer][slot].
     // wq then holds one table per layer, [layer][n].
     const uint8_t* block_layer;  // [ceil(d/256)]

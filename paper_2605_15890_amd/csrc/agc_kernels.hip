@@ -627,7 +627,7 @@ hipError_t launch_quantize(const float* G, int64_t ldg, int n, int k, int64_t d,
 // =======================================================================================
 // K3  masked dequantize + weighted sum
 // =======================================================================================
-// A workgroup walks over tiles of 256 * COORDS coordinates (a lane owns COORDS consecutive ones) and, in
+// A workgroup takes tiles of 256 * COORDS coordinates (a lane owns COORDS consecutive ones) and walks, in
 // every tile, over the arrived workers in ascending order.  A b-bit worker's part of a tile is b "units"
 // of 32 * COORDS contiguous bytes of its stream; the units of consecutive workers are packed into chunks
 // of 12 KB.  All lanes fetch a chunk together, three 16-byte pieces each, wholly coalesced
@@ -635,12 +635,13 @@ hipError_t launch_quantize(const float* G, int64_t ldg, int n, int k, int64_t d,
 // of a tile.
 //
 // What bounds it: instruction issue.  At the metric size (25.6 M coordinates, 43 of 64 workers arrived) a
-// wave spends about 70 vector and 30 scalar instructions on 16 codes of each lane, and the vector units are
-// a little over 40 % busy; the memory would allow 0.08 ms.  The first form of the kernel let every lane
-// load its own b words of one worker right before they were used and decode 32 codes of them: one request
-// in flight per wave, 0.169 ms, and 26 us even for 200 000 coordinates (20 workers times one round trip to
-// memory).  This form: 0.148 ms and 18 us.  Six waves per SIMD (74 vector registers, 24 KB of LDS): five
-// take 0.162 ms, four with chunks of 16 KB 0.166 ms, eight with 8 KB 0.160 ms.
+// wave spends about 70 vector and 28 scalar instructions on 16 codes of each lane: 7.6e7 vector instructions
+// in 0.14 ms, 0.86 of one in four clocks on every SIMD; the memory would allow 0.09 ms.  The first form of the
+// kernel let every lane load its own b words of one worker right before they were used and decode 32 codes of
+// them: one request in flight per wave, 0.169 ms, and 26 us even for 200 000 coordinates (20 workers times one
+// round trip to memory).  This form: 0.148 ms and 18 us with resident workgroups that walk over the tiles,
+// 0.137-0.143 ms with one workgroup per tile (decode_groups).  Six waves per SIMD (72 vector registers, 24 KB of
+// LDS), walking: five take 0.162 ms, four with chunks of 16 KB 0.166 ms, eight with 8 KB 0.160 ms.
 constexpr int kDecPieces = kDecChunkBytes / 16;            // 16-byte pieces of a chunk
 constexpr int kDecPerThread = kDecPieces / kWgThreads;
 static_assert(kDecPerThread * kWgThreads == kDecPieces, "every lane fetches the same number of pieces");

@@ -21,8 +21,8 @@ struct QuantArgs {
     int64_t nb;
     float* ghat;    // fused step only
     const WindowRec* win;  // monotone-interval codes only; filled in by the launcher
-    int stage_bits;        // largest sum of bit-widths one fill of the staging area holds (<= kStageBits)
-    int stage_fills;       // how many fills the workers need (1 unless the widths sum to more than kStageBits)
+    int stage_bits;        // bit-widths of the fullest fill of the staging area: at most stage_limit(), kPartBits with parts
+    int stage_fills;       // how many fills the workers need: 1 unless the widths sum to more than that; always 1 with parts
     const uint8_t* block_layer;  // layer-wise scales only: the layer of every block; wq is then [layer][n]
     unsigned wg_first;     // the workgroups take the groups of four blocks from here upwards and then from 0; 0 with parts
     bool parts;            // short vectors: one block per workgroup, its workers shared among the waves
@@ -121,8 +121,9 @@ __device__ __forceinline__ float grid_pos(float f, float inv)
 // them, reach memory as partial lines and cost several times their bytes on this memory system.
 // MULTI: the workers need more than one fill of the area, so it is also written out between
 // workers, inside the streaming loop.  Without MULTI (the common case: widths sum to at most
-// kStageBits) the loop over the workers contains no store at all and the kernel writes the area
-// out once, after the loop; the encode drivers then keep their rolling prefetch.
+// stage_limit(), 319 without bucket-wise scales, or kPartBits with PARTS) the loop over the workers
+// contains no store at all and the kernel writes the area out once, after the loop; the encode
+// drivers then keep their rolling prefetch.
 // PARTS: short vectors.  The workgroup has one block, its waves share the workers (encode_block_part); the
 // estimate needs them in ascending order and is formed from the staged codes by the kernel (staged_estimate).
 template <int BUCKET, bool FUSE, bool MULTI, bool PARTS>
