@@ -143,10 +143,10 @@ inline int ls_fold(int64_t n_rows, int64_t rows_per_part, int n_feat)
     return fold;
 }
 
-// Least squares: slices that share the parts of one feature in the sum of the workgroups' gradients.  Eight hide
-// the memory's latency where there are many parts (65536 x 512 samples x features, 512 parts 18 us, one slice 34);
-// up to sixteen parts one thread requests all of them together, and eight slices would only be eight times as many
-// workgroups (2^17 x 8192, one part: 387 us, now 346; 65536 x 4096, 8 parts 92, now 87).
-constexpr int ls_reduce_slices(int wg_per_part) { return wg_per_part > 16 ? 8 : 1; }
+// Least squares: few enough parts of a partition (one per workgroup) for one thread per feature in their sum.  Many
+// parts are shared by eight threads per feature, which hides the memory's latency (65536 x 512 samples x features,
+// 512 parts 18 us, one thread 34); up to sixteen parts one thread requests all of them together, and eight would only
+// be eight times as many workgroups (2^17 x 8192, one part: 387 us, now 346; 65536 x 4096, 8 parts 92, now 87).
+constexpr bool ls_reduce_few(int wg_per_part) { return wg_per_part <= 16; }
 
 }  // namespace agc

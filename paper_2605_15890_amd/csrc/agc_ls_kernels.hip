@@ -6,8 +6,8 @@
 // block of 16 samples in REGISTERS between its two uses:
 //   sweep 1  r = X_blk w - y_blk   (contraction over features)
 //   sweep 2  g += X_blk^T r        (contraction over samples)
-// k_ls_resident<ROWS, NG>: a lane owns NG groups of eight features of all ROWS samples of the
-// block, ROWS * NG = 32 (16 samples x 16 features for n_feat <= 4096, 8 samples x 32 features for
+// k_ls_resident<ROWS, NG, FOLD>: a lane owns NG groups of eight features of all ROWS samples of the
+// block, ROWS * NG = 32 (32 samples x 8 features for n_feat <= 2048, 16 samples x 16 features for n_feat <= 4096, 8 samples x 32 features for
 // n_feat <= 8192): 128 VGPRs of packed bfloat16.  Sweep 2 is then a plain per-lane FMA chain.
 // Sweep 1 runs on the matrix cores: v_mfma_f32_16x16x32_bf16 with A = the lane's 8 features of
 // one sample and B = the lane's own 8 entries of w; the diagonal D[i][i] is the sum over the four
@@ -32,8 +32,8 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 constexpr int kLsThreads = 256;
 constexpr int kLsWaves = 4;
+constexpr int kLsSlices = 8;       // of the parts of a partition in their sum
 constexpr int kLsRows = 16;        // largest number of samples per block; n_rows is a multiple of it per partition
-
 
 struct LsArgs {
     int64_t n_rows;
@@ -310,39 +310,63 @@ __global__ __launch_bounds__(kLsThreads, 2) void k_ls_resident(const uint16_t* _
     }
 }
 
-// G[p][f] = sum over the partition's workgroups, BATCH parts requested together.  A workgroup takes FEAT features
-// (whole lines of the parts); its 256 / FEAT slices of threads add a share of the parts each, in order, and their
-// sums are added in order.
-template <int FEAT, int BATCH>
+// G[p][f] = sum over the partition's workgroups, in eight slices: the parts of a slice are added in order, and so
+// are the slices' sums (one after the other, the sum of sixteen parts is up to 1.2 times as far from the binary64
+// one).  Up to sixteen parts: one thread per feature, BATCH parts of every slice, all requested together.
+template <int BATCH>
+__global__ __launch_bounds__(kLsThreads) void k_ls_reduce_few(const float* __restrict__ partial, int n_feat,
+                                                              int wg_per_part, float* G, int64_t ldg)
+{
+    const int p = blockIdx.y;
+    const int f = blockIdx.x * kLsThreads + threadIdx.x;
+    if (f >= n_feat) return;
+    const float* src = partial + (int64_t)p * wg_per_part * n_feat + f;
+    float v[kLsSlices][BATCH];
+    int parts[kLsSlices];  // at most BATCH each
+#pragma unroll
+    for (int u = 0; u < kLsSlices; ++u) {
+        const int q0 = wg_per_part * u / kLsSlices, q1 = wg_per_part * (u + 1) / kLsSlices;
+        parts[u] = q1 - q0;
+#pragma unroll
+        for (int t = 0; t < BATCH; ++t) v[u][t] = src[(int64_t)(q0 + t < q1 ? q0 + t : wg_per_part - 1) * n_feat];
+    }
+    float s = 0.f;
+#pragma unroll
+    for (int u = 0; u < kLsSlices; ++u) {
+        float s_u = 0.f;
+#pragma unroll
+        for (int t = 0; t < BATCH; ++t) s_u = t < parts[u] ? s_u + v[u][t] : s_u;
+        s = s + s_u;
+    }
+    G[(int64_t)p * ldg + f] = s;
+}
+
+// More parts: a workgroup takes 32 features (whole lines of the parts), its 256 threads are the eight slices.
 __global__ __launch_bounds__(kLsThreads) void k_ls_reduce(const float* __restrict__ partial, int n_feat,
                                                           int wg_per_part, float* G, int64_t ldg)
 {
-    constexpr int kSlices = kLsThreads / FEAT;
-    __shared__ float lds_s[kSlices][FEAT];
+    constexpr int kFeat = kLsThreads / kLsSlices, kBatch = 16;
+    __shared__ float lds_s[kLsSlices][kFeat];
     const int p = blockIdx.y;
-    const int col = threadIdx.x % FEAT, slice = threadIdx.x / FEAT;
-    const int f = blockIdx.x * FEAT + col;  // n_feat is a multiple of 128
-    const int q0 = wg_per_part * slice / kSlices, q1 = wg_per_part * (slice + 1) / kSlices;
+    const int col = threadIdx.x % kFeat, slice = threadIdx.x / kFeat;
+    const int f = blockIdx.x * kFeat + col;  // n_feat is a multiple of 128
+    const int q0 = wg_per_part * slice / kLsSlices, q1 = wg_per_part * (slice + 1) / kLsSlices;
     const float* src = partial + (int64_t)p * wg_per_part * n_feat + f;
     float s = 0.f;
-    if (FEAT <= 128 || f < n_feat) {
-        for (int q = q0; q < q1; q += BATCH) {
-            float v[BATCH];  // past the slice's end its last part is read again
+    for (int q = q0; q < q1; q += kBatch) {
+        float v[kBatch];  // past the slice's end its last part is read again
 #pragma unroll
-            for (int u = 0; u < BATCH; ++u) v[u] = src[(int64_t)(q + u < q1 ? q + u : q1 - 1) * n_feat];
+        for (int u = 0; u < kBatch; ++u) v[u] = src[(int64_t)(q + u < q1 ? q + u : q1 - 1) * n_feat];
 #pragma unroll
-            for (int u = 0; u < BATCH; ++u) s = q + u < q1 ? s + v[u] : s;
-        }
+        for (int u = 0; u < kBatch; ++u) s = q + u < q1 ? s + v[u] : s;
     }
-    if constexpr (kSlices > 1) {
-        lds_s[slice][col] = s;
-        __syncthreads();
-        if (slice != 0) return;
-        s = 0.f;
+    lds_s[slice][col] = s;
+    __syncthreads();
+    if (slice != 0) return;
+    s = 0.f;
 #pragma unroll
-        for (int u = 0; u < kSlices; ++u) s = s + lds_s[u][col];
-    }
-    if (FEAT <= 128 || f < n_feat) G[(int64_t)p * ldg + f] = s;
+    for (int u = 0; u < kLsSlices; ++u) s = s + lds_s[u][col];
+    G[(int64_t)p * ldg + f] = s;
 }
 
 __global__ __launch_bounds__(kLsThreads) void k_gd_update(float* beta, const float* __restrict__ ghat,
@@ -390,10 +414,9 @@ hipError_t launch_ls_partial_gradients(const void* X, int64_t n_rows, int n_feat
         hipLaunchKernelGGL(kernel, dim3((unsigned)((n_feat + feat - 1) / feat), (unsigned)k_parts), block, 0, stream,
                            static_cast<const float*>(partial), n_feat, a.wg_per_part, G, ldg);
     };
-    const int slices = ls_reduce_slices(a.wg_per_part);
-    if (slices > 1) reduce(k_ls_reduce<32, 16>, 32);
-    else if (a.wg_per_part > 4) reduce(k_ls_reduce<256, 16>, 256);
-    else reduce(k_ls_reduce<256, 4>, 256);
+    if (!ls_reduce_few(a.wg_per_part)) reduce(k_ls_reduce, kLsThreads / kLsSlices);
+    else if (a.wg_per_part > kLsSlices) reduce(k_ls_reduce_few<2>, kLsThreads);
+    else reduce(k_ls_reduce_few<1>, kLsThreads);
     return hipGetLastError();
 }
 

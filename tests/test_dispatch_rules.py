@@ -23,7 +23,7 @@ extern "C" int decode_coords(int64_t d, int two, int many_scales, int sum_bits)
     return agc::decode_coords(d, two != 0, many_scales != 0, sum_bits);
 }
 extern "C" int ls_fold(int64_t n_rows, int64_t rows_per_part, int n_feat) { return agc::ls_fold(n_rows, rows_per_part, n_feat); }
-extern "C" int ls_reduce_slices(int wg_per_part) { return agc::ls_reduce_slices(wg_per_part); }
+extern "C" int ls_reduce_few(int wg_per_part) { return agc::ls_reduce_few(wg_per_part); }
 extern "C" unsigned first_group(int64_t d, unsigned groups) { return agc::first_group(d, groups); }
 """
 
@@ -45,7 +45,7 @@ def rules(tmp_path_factory):
     lib.decode_is_direct.argtypes = [ctypes.c_int, ctypes.c_int64]
     lib.decode_coords.argtypes = [ctypes.c_int64] + [ctypes.c_int] * 3
     lib.ls_fold.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int]
-    lib.ls_reduce_slices.argtypes = [ctypes.c_int]
+    lib.ls_reduce_few.argtypes = [ctypes.c_int]
     lib.first_group.argtypes = [ctypes.c_int64, ctypes.c_uint]
     lib.first_group.restype = ctypes.c_uint
     return lib
@@ -125,5 +125,5 @@ def test_least_squares_folds_no_wider_than_a_partition_fills(rules, k, rows, n_f
     assert rules.ls_fold(k * rows, rows, n_feat) == fold
 
 
-def test_least_squares_reduces_few_parts_without_slices(rules):
-    assert [rules.ls_reduce_slices(p) for p in (1, 16, 17, 512)] == [1, 1, 8, 8]
+def test_least_squares_sums_few_parts_by_one_thread(rules):
+    assert [rules.ls_reduce_few(p) for p in (1, 16, 17, 512)] == [1, 1, 0, 0]

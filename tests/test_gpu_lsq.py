@@ -115,6 +115,28 @@ def test_gradients_from_many_and_from_few_parts(n_rows, n_feat, k):
     test_partial_gradients_match_fp64(n_rows, n_feat, k)
 
 
+@pytest.mark.parametrize("k,wg_per_part", [(500, 1), (200, 2), (64, 8), (56, 9), (40, 12), (32, 16), (30, 17), (4, 128)])
+def test_the_sum_of_the_parts_has_one_order_for_any_number(k, wg_per_part):
+    """Eight slices, their parts one after the other, then the slices: the workspace still holds the parts."""
+    import torch
+    n_rows, n_feat = k * 16 * wg_per_part, 1152
+    Xb, y, w_star, X, y_d = _device_problem(n_rows, n_feat)
+    beta = torch.linspace(-1.0, 2.0, n_feat, device="cuda")
+    G = api.padded_rows(k, n_feat)
+    resid = torch.empty(n_rows, device="cuda")
+    ws = torch.empty(api.agc_ls_workspace_floats(n_rows, n_feat, k), device="cuda")
+    api.agc_ls_partial_gradients(X, y_d, beta, k, G, resid, ws)
+    torch.cuda.synchronize()
+    parts = ws[:k * wg_per_part * n_feat].cpu().numpy().reshape(k, wg_per_part, n_feat)
+    total = np.zeros((k, n_feat), dtype=np.float32)
+    for u in range(8):
+        s = np.zeros((k, n_feat), dtype=np.float32)
+        for q in range(wg_per_part * u // 8, wg_per_part * (u + 1) // 8):
+            s = s + parts[:, q]
+        total = total + s
+    assert np.array_equal(G.cpu().numpy(), total)
+
+
 def test_rejects_shapes_the_kernel_does_not_cover():
     import torch
     X = torch.zeros((64, 128), dtype=torch.bfloat16, device="cuda")
