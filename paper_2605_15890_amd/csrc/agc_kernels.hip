@@ -966,7 +966,8 @@ void k_decode(const DecWorker* __restrict__ workers, const DecUnit* __restrict__
             const uint32_t* part = reinterpret_cast<const uint32_t*>(&lds_chunk[x][wk.w * kUnitPieces]);
             uint32_t mask = wk.z;
             if (SCALES != 0) {  // the weights differ from lane to lane: one choice for the wave
-                const uint64_t no = __builtin_amdgcn_ballot_w64(!(halves_exactly(c1) & (TWO ? halves_exactly(c2) : true)));
+                const bool halves1 = halves_exactly(c1), halves2 = !TWO || halves_exactly(c2);
+                const uint64_t no = __builtin_amdgcn_ballot_w64(!(halves1 & halves2));
                 mask = mask == 4u && no == 0 ? 1u : mask;
             }
             if (mask & 0x1Fu) decode_any<0, 4, COORDS, TWO>(mask, part, c1, c2, acc, acc2);
