@@ -10,8 +10,8 @@ namespace agc {
 // (k_scale_pass_parts, k_quantize<.., PARTS>).  A wave that walks over all workers alone on its SIMD mostly waits
 // for itself; four waves per block hide that as long as the chip has room for them, and lose to the long form
 // (four blocks per workgroup, every row read once) once it is full.  With one or two workers there is nothing to
-// share.  A vector that ends inside a block has its last block in the gather driver, one worker after the other
-// while the chip waits; the parts shorten that chain too, so their lines lie further out.
+// share.  The lines of vectors that end inside a block lie further out, from when that block took the gather driver;
+// for the cyclic band the library does not ask by them any more (use_parts_of).
 //   band   > 0: cyclic band of that width, -W: window driver, 0: gather driver
 //   norm   Euclidean scale;  bucket: bucket-wise scales (no scale pass)
 // Measured: time of a whole step in the long form over that in this one, ten steps in a graph, 6000 shapes of
@@ -69,14 +69,22 @@ inline bool use_parts(int64_t d, int n, int k, int nnz, int band, bool norm, boo
     return blocks <= 1024;
 }
 
+// The rule that the library asks.  The block that a vector ends in passes through the ring like every other, so a
+// cyclic band goes by the lines of whole blocks.  By the lines of vectors that end inside a block | by those of whole
+// ones, us: max-abs, 64 workers x 327 681 73 | 63, 500 000 93 | 67, 32 x 393 000 44 | 37;  Euclidean 64 x 500 000
+// 100 | 69;  bucket-wise 64 x 500 000 77 | 51.  The windows keep theirs: up to them the parts are still the faster form
+// (W = 4, 32 x 196 001 33 and 39 us in the long form; W = 8, 32 x 98 001 31 and 45; 64 x 131 001 bucket-wise 51 and 55).
+inline bool use_parts_of(int64_t d, int n, int k, int nnz, int band, bool norm, bool bucket)
+{
+    return use_parts(band > 0 ? (d + 255) / 256 * 256 : d, n, k, nnz, band, norm, bucket);
+}
+
 // The quantize pass of long vectors: the group of four blocks that its first workgroup takes; the others follow
-// upwards and wrap around.  A vector that ends inside a block has that block in the gather driver, which takes
-// several times as long as the others: it must not be the last to start, so the pass starts 64 groups before the
-// end.  With no more groups than the chip holds at once (four workgroups on each of 256 compute units) all start
-// together and the order is left alone.  Whole step, upwards from 0 | from 64 groups before the end, us:
-// 64 workers x 2 000 000 257 | 238, 50 x 5 400 003 462 | 433, 32 x 11 700 000 549 | 535, 128 x 5 400 001 1193 | 1114,
-// 64 x 25 600 001 2423 | 2396.  Vectors of whole blocks take the same time from any group (32 x 11 700 224 521 | 522),
-// so nothing of G that the scale pass left in the memory-side cache is gained by the order.
+// upwards and wrap around.  With a general code the block that the vector ends in masks every row that it gathers and
+// takes longer than the others, and in any code its codes leave in pieces that do not fill their lines: it is not the last
+// to start.  With no more groups than the chip holds at once (four workgroups on each of 256 compute units) all start
+// together and the order is left alone.  Vectors of whole blocks take the same time from any group (32 x 11 700 224
+// 521 | 522 us), so nothing of G that the scale pass left in the memory-side cache is gained by the order.
 constexpr int64_t kChipGroups = 4 * 256;
 constexpr unsigned kEarlyGroups = 64;
 inline unsigned first_group(int64_t d, unsigned groups)

@@ -52,6 +52,8 @@ struct EpiMaxAbs {
     static constexpr int kPrefetchRows = AGC_SCALE_PREFETCH_ROWS;
     uint32_t* acc;  // this wave's LDS slice [n], bit patterns of non-negative floats
     int lane;
+    int nvalid;     // of the lane's coordinates in the present block
+    bool ragged;    // wave-uniform: the vector ends inside the present block and its driver leaves the rows unmasked
     static __device__ __forceinline__ float max_abs4(const float4& f)
     {
         return fmaxf(fmaxf(fabsf(f.x), fabsf(f.y)), fmaxf(fabsf(f.z), fabsf(f.w)));
@@ -59,7 +61,7 @@ struct EpiMaxAbs {
     template <bool EVEN>
     __device__ __forceinline__ void worker(int i, const float4& f)
     {
-        const uint32_t m = wave_max_nonneg_bits(max_abs4(f));
+        const uint32_t m = wave_max_nonneg_bits(max_abs4(ragged ? valid_coords(f, nvalid) : f));
         if (lane == 0) acc[i] = m;
     }
     template <bool EVEN, int V>
@@ -82,9 +84,12 @@ struct EpiSumSq {
     static constexpr int kPrefetchRows = AGC_SCALE_PREFETCH_ROWS;
     double* acc;  // this wave's LDS slice [n]
     int lane;
+    int nvalid;
+    bool ragged;  // as in EpiMaxAbs
     template <bool EVEN>
-    __device__ __forceinline__ void worker(int i, const float4& f)
+    __device__ __forceinline__ void worker(int i, const float4& whole)
     {
+        const float4 f = ragged ? valid_coords(whole, nvalid) : whole;
         const double x0 = f.x, x1 = f.y, x2 = f.z, x3 = f.w;
         const double s01 = x0 * x0 + x1 * x1;
         const double s23 = x2 * x2 + x3 * x3;
@@ -147,7 +152,7 @@ __global__ __launch_bounds__(kWave * WAVES) void k_scale_pass(const float* __res
         for (int i = threadIdx.x; i < a.n; i += kWave * WAVES) wg_max[i] = 0u;
         if (threadIdx.x == 0) wg_done = 0u;
         __syncthreads();  // the only barrier: at the start, where no wave has anything to wait for
-        EpiMaxAbs epi{accu, lane};
+        EpiMaxAbs epi{accu, lane, 4, false};
         // Layer-wise scales (Sec. II-B names the layer-wise granularity): layer l owns rows
         // l*kLayerSub .. l*kLayerSub+kLayerSub-1 of the slot array (several rows, so that the
         // workgroups that walk one layer at the same time do not all hit the same words).  The
@@ -189,6 +194,8 @@ __global__ __launch_bounds__(kWave * WAVES) void k_scale_pass(const float* __res
                     const int64_t b = base + (int64_t)u * kBlockCoords;
                     if (b < a.d) {
                         const LaneCoords lc = lane_coords(b, lane, a.d);
+                        epi.nvalid = lc.nvalid;
+                        epi.ragged = S != 0 && lc.wave_ragged;
                         encode_block<S>(G + b, a.ldg, a.n, a.k, B, lc, epi);
                         fold(layer_of(b));
                     }
@@ -224,7 +231,7 @@ __global__ __launch_bounds__(kWave * WAVES) void k_scale_pass(const float* __res
     }
     if (sq_has) {
         const LaneCoords lc = lane_coords(sq_base, lane, a.d);
-        EpiSumSq epi{accd, lane};
+        EpiSumSq epi{accd, lane, lc.nvalid, S != 0 && lc.wave_ragged};
         encode_block<S>(G + sq_base, a.ldg, a.n, a.k, B, lc, epi);
     } else {  // a block past the end of the vector (or of the layer's last segment) contributes nothing
         for (int i = lane; i < a.n; i += kWave) accd[i] = 0.0;
@@ -261,7 +268,7 @@ __global__ __launch_bounds__(kWave * (MODE == 1 ? kParts : kParts * kSegBlocks))
         const int64_t blk = blockIdx.x;
         const int64_t base = blk * kBlockCoords;
         const LaneCoords lc = lane_coords(base, lane, a.d);
-        EpiMaxAbs epi{lds_max, lane};
+        EpiMaxAbs epi{lds_max, lane, lc.nvalid, S != 0 && lc.wave_ragged};
         encode_block_part<S>(G + base, a.ldg, a.k, B, lc, i0, i1, epi);
         const int64_t slot = a.block_layer ? (int64_t)a.block_layer[blk] * kLayerSub + blk % kLayerSub : blk & (kMaxSlots - 1);
         for (int i = i0 + lane; i < i1; i += kWave) {  // written by this wave's lane 0
@@ -281,7 +288,7 @@ __global__ __launch_bounds__(kWave * (MODE == 1 ? kParts : kParts * kSegBlocks))
         }
         if (has) {
             const LaneCoords lc = lane_coords(base, lane, a.d);
-            EpiSumSq epi{lds_sq[b], lane};
+            EpiSumSq epi{lds_sq[b], lane, lc.nvalid, S != 0 && lc.wave_ragged};
             encode_block_part<S>(G + base, a.ldg, a.k, B, lc, i0, i1, epi);
         } else {
             for (int i = i0 + lane; i < i1; i += kWave) lds_sq[b][i] = 0.0;

@@ -145,6 +145,7 @@ struct EpiQuant {
     uint32_t ctr0;       // m >> 2 of this lane's coordinates
     int nvalid;
     bool wave_ragged;    // wave-uniform: some lane has coordinates >= d
+    bool drop;           // and its driver leaves the rows unmasked
     uint32_t keep2, keep3;  // second half of the Philox block, for the odd worker of the pair
     float* scales;          // bucket-wise scales: n x nb
     int64_t nb;
@@ -219,8 +220,9 @@ struct EpiQuant {
         }
     }
 
-    __device__ __forceinline__ float block_multiplier(int i, const float4& f, float num, float& scale)
+    __device__ __forceinline__ float block_multiplier(int i, const float4& whole, float num, float& scale)
     {
+        const float4 f = drop ? valid_coords(whole, nvalid) : whole;
         if (BUCKET == 1) {
             const float a = fmaxf(fmaxf(fabsf(f.x), fabsf(f.y)), fmaxf(fabsf(f.z), fabsf(f.w)));
             scale = __uint_as_float(wave_max_nonneg_bits(a));
@@ -465,7 +467,7 @@ __global__ __launch_bounds__(kQuantThreads) __attribute__((amdgpu_waves_per_eu(S
     EpiQuant<BUCKET, FUSE, MULTI, PARTS> epi{wq, a.key0, a.key1, a.step_lo, a.step_hi, lds_stage, stage_scales, lane, wave,
                                PARTS ? 0 : wave, a.n, wg,
                                groups_left >= 2 * kBlocks ? 2 * kBlocks : (int)groups_left, block, (uint32_t)((base + 4 * lane) >> 2),
-                               lc.nvalid, lc.wave_ragged, 0u, 0u, a.scales, a.nb, 0, {0.f, 0.f, 0.f, 0.f},
+                               lc.nvalid, lc.wave_ragged, S != 0 && lc.wave_ragged, 0u, 0u, a.scales, a.nb, 0, {0.f, 0.f, 0.f, 0.f},
                                load_uniform(wq + (i0 < a.n ? i0 : 0))};
     if constexpr (PARTS) {  // every workgroup has its block
         encode_block_part<S>(G + base, a.ldg, a.k, CsrView{row_ptr, col, val, a.win}, lc, i0, i1, epi);
