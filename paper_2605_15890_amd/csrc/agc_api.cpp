@@ -39,8 +39,10 @@ struct agc_ctx {
     agc::WindowRec* d_win = nullptr;   // monotone-interval codes only
     int band = 0;
     bool force_long = false;  // testing hook
+    int sketch_mode = 0;      // testing hook: 0 by the rule, 1 wherever the sketch can be made, 2 never
     // workspace
     agc::Workspace ws{};
+    agc::SketchDev sk{};      // planes is null where the rule never takes it
     // profiling
     bool profiling = false;
     std::vector<EventPair> events[AGC_NUM_KERNELS];
@@ -92,6 +94,35 @@ void free_layers(agc_ctx* c)
     c->ws.coef_layer = nullptr;
     c->ws.coef2_layer = nullptr;
     c->ws.n_layers = 0;
+}
+
+void free_sketch(agc_ctx* c)
+{
+    void* all[] = {c->sk.planes, c->sk.recs, c->sk.counts, c->sk.lo_scale, c->sk.lo_mult, c->sk.state, c->sk.done};
+    for (void* p : all)
+        if (p) (void)hipFree(p);
+    c->sk = agc::SketchDev{};
+}
+
+// Workspace of the one-read form.  Without the memory for it the two-read form runs: not an error.
+hipError_t alloc_sketch(agc_ctx* c)
+{
+    agc::SketchDev& sk = c->sk;
+    const size_t blocks = (size_t)(c->d + 255) / 256;
+    sk.cap = agc::sketch_cap(c->n);
+    sk.chunks = (c->n + 31) / 32;
+    hipError_t e = dev_alloc(&sk.planes, blocks * (size_t)sk.chunks * 256);
+    if (e == hipSuccess) e = dev_alloc(&sk.recs, blocks * (size_t)sk.cap);
+    if (e == hipSuccess) e = dev_alloc(&sk.counts, 4 * (size_t)c->ws.nseg);
+    if (e == hipSuccess) e = dev_alloc(&sk.lo_scale, (size_t)c->n);
+    if (e == hipSuccess) e = dev_alloc(&sk.lo_mult, (size_t)c->n);
+    if (e == hipSuccess) e = dev_alloc(&sk.state, 1);
+    if (e == hipSuccess) e = dev_alloc(&sk.done, (size_t)c->ws.nseg);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();  // not the caller's
+        free_sketch(c);
+    }
+    return e;
 }
 
 void free_code(agc_ctx* c)
@@ -191,6 +222,17 @@ agc::CodeDev code_dev(const agc_ctx* c)
     return agc::CodeDev{c->d_row_ptr, c->d_col, c->d_val, band, c->d_win, parts};
 }
 
+bool use_sketch(const agc_ctx* c, const agc::CodeDev& code, const uint8_t* bits)
+{
+    if (!c->sk.planes || c->ws.n_layers > 0 || c->sketch_mode == 2) return false;
+    double levels = 0.0;
+    for (int i = 0; i < c->n; ++i) {
+        if (bits[i] < 2) return false;  // a one-bit code has no level 0
+        levels += (double)((1 << (bits[i] - 1)) - 1);
+    }
+    return c->sketch_mode == 1 || agc::use_sketch(c->d, c->k, levels, code.band == 0 && code.parts, c->sk.cap);
+}
+
 }  // namespace
 
 extern "C" {
@@ -259,6 +301,8 @@ agc_status agc_create(agc_ctx** out, int n, int k, int64_t d, const agc_opts* op
         return fail(nullptr, e == hipErrorOutOfMemory ? AGC_ENOMEM : AGC_EHIP,
                     std::string("workspace allocation: ") + hipGetErrorString(e));
     }
+    if (!o.bucket && o.scale_mode == AGC_SCALE_L2 && agc::use_sketch(d, k, n, false, agc::sketch_cap(n)))
+        (void)alloc_sketch(c);  // some widths are few enough levels: two bits each
     *out = c;
     return AGC_OK;
 }
@@ -268,6 +312,7 @@ void agc_destroy(agc_ctx* c)
     if (!c) return;
     free_code(c);
     free_layers(c);
+    free_sketch(c);
     if (c->ws.part_max) (void)hipFree(c->ws.part_max);
     if (c->ws.part_sq) (void)hipFree(c->ws.part_sq);
     if (c->ws.group_sq) (void)hipFree(c->ws.group_sq);
@@ -518,7 +563,8 @@ agc_status encode_quantize_impl(agc_ctx* c, const float* G, int64_t ldg, const u
     }
     int sum_bits = 0;
     for (int i = 0; i < c->n; ++i) sum_bits += bits[i];
-    qs.parts = code.parts && sum_bits <= agc::kPartBits;
+    const agc::SketchDev* sk = use_sketch(c, code, bits) ? &c->sk : nullptr;
+    qs.parts = code.parts && sum_bits <= agc::kPartBits && !sk;
     qs.stage_fills = agc::stage_starts(qs.bits, c->n, qs.parts ? agc::kPartBits : agc::stage_limit(c->n, c->opts.bucket != 0),
                                        qs.stage_start, &qs.stage_bits);
     hipError_t e;
@@ -540,14 +586,19 @@ agc_status encode_quantize_impl(agc_ctx* c, const float* G, int64_t ldg, const u
         KernelTimer t{c, 0, stream};
         if ((st = t.begin()) != AGC_OK) return st;
         c->slots_dirty = maxabs;
-        e = agc::launch_scale_pass(G, ldg, c->n, c->k, c->d, code, c->opts.scale_mode, c->ws, stream);
+        if (sk) {
+            e = agc::launch_sketch_bounds(G, ldg, c->n, c->k, c->d, code, c->ws, *sk, qs, stream);
+            if (e == hipSuccess) e = agc::launch_sketch(G, ldg, c->n, c->k, c->d, code, c->ws, *sk, seed, step, stream);
+        } else {
+            e = agc::launch_scale_pass(G, ldg, c->n, c->k, c->d, code, c->opts.scale_mode, c->ws, stream);
+        }
         if (e != hipSuccess) return hip_fail(c, e, "scale pass launch");
         if ((st = t.end()) != AGC_OK) return st;
     }
     {
         KernelTimer t{c, 1, stream};
         if ((st = t.begin()) != AGC_OK) return st;
-        e = agc::launch_scale_finalize(c->n, c->opts.scale_mode, qs, sw, c->ws, scales, stream);
+        e = agc::launch_scale_finalize(c->n, c->opts.scale_mode, qs, sw, c->ws, sk, scales, stream);
         if (e != hipSuccess) return hip_fail(c, e, "scale finalize launch");
         c->slots_dirty = false;
         if ((st = t.end()) != AGC_OK) return st;
@@ -555,7 +606,11 @@ agc_status encode_quantize_impl(agc_ctx* c, const float* G, int64_t ldg, const u
     {
         KernelTimer t{c, 2, stream};
         if ((st = t.begin()) != AGC_OK) return st;
-        e = agc::launch_quantize(G, ldg, c->n, c->k, c->d, code, c->ws, qs, seed, step, ghat, stream);
+        if (sk) {
+            e = agc::launch_resolve(c->n, c->d, c->ws, *sk, qs, seed, step, ghat, stream);
+            if (e != hipSuccess) return hip_fail(c, e, "resolve launch");
+        }
+        e = agc::launch_quantize(G, ldg, c->n, c->k, c->d, code, c->ws, qs, seed, step, ghat, sk ? sk->done : nullptr, stream);
         if (e != hipSuccess) return hip_fail(c, e, "quantize launch");
         if ((st = t.end()) != AGC_OK) return st;
     }
@@ -751,6 +806,19 @@ agc_status agc_debug_force_long(agc_ctx* c, int on)
 {
     if (!c) return fail(nullptr, AGC_EINVAL, "null context");
     c->force_long = on != 0;
+    return AGC_OK;
+}
+
+agc_status agc_debug_sketch(agc_ctx* c, int mode)
+{
+    if (!c || mode < 0 || mode > 2) return fail(nullptr, AGC_EINVAL, "null context or unknown mode");
+    if (mode == 1 && (c->opts.bucket || c->opts.scale_mode != AGC_SCALE_L2))
+        return fail(c, AGC_EINVAL, "one scale of the whole vector, Euclidean");
+    if (mode == 1 && !c->sk.planes) {
+        const hipError_t e = alloc_sketch(c);
+        if (e != hipSuccess) return fail(c, AGC_ENOMEM, "workspace of the one-read form");
+    }
+    c->sketch_mode = mode;
     return AGC_OK;
 }
 

@@ -63,7 +63,7 @@ void k_stream_rows(const float* __restrict__ G, int64_t ldg, int k, int64_t nblo
         for (int r = 0; r < P; ++r)
 #pragma unroll
             for (int v = 0; v < V; ++v)
-                ring[r][v] = load_row4<false, true>(row + (int64_t)(r < k ? r : k - 1) * ldg + v * kBlockCoords, lc);
+                ring[r][v] = load_row4<true>(row + (int64_t)(r < k ? r : k - 1) * ldg + v * kBlockCoords, lc);
         for (int j0 = 0; j0 < k; j0 += P) {
 #pragma unroll
             for (int r = 0; r < P; ++r) {
@@ -75,7 +75,7 @@ void k_stream_rows(const float* __restrict__ G, int64_t ldg, int k, int64_t nblo
                 if (j + P < k) {
 #pragma unroll
                     for (int v = 0; v < V; ++v)
-                        ring[r][v] = load_row4<false, true>(row + (int64_t)(j + P) * ldg + v * kBlockCoords, lc);
+                        ring[r][v] = load_row4<true>(row + (int64_t)(j + P) * ldg + v * kBlockCoords, lc);
                 }
                 last = cur[0];
 #pragma unroll

@@ -75,6 +75,9 @@ constexpr int kDppQuadSwap2 = 0x4E;     // quad_perm [2,3,0,1]: partner l ^ 2
 constexpr int kDppHalfMirror = 0x141;   // l -> 7 - l within 8 lanes: a partner in the other quad
 constexpr int kDppRowMirror = 0x140;    // l -> 15 - l within 16 lanes: a partner in the other half
 
+constexpr int kDppQuadReverse = 0x1B;   // quad_perm [3,2,1,0]: l -> l ^ 3
+constexpr int kDppRowRor8 = 0x128;      // rotation of 16 lanes by eight: l -> l ^ 8
+
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_u32(uint32_t v)
 {
@@ -164,15 +167,27 @@ __device__ __forceinline__ float4 valid_coords(const float4& f, int nvalid)
     return make_float4(nvalid > 0 ? f.x : 0.f, nvalid > 1 ? f.y : 0.f, nvalid > 2 ? f.z : 0.f, nvalid > 3 ? f.w : 0.f);
 }
 
+// An epilogue behind a driver for the block that the vector ends in: it sees zeros for the coordinates >= d.  For
+// epilogues that count them (Epi::kWantsZeros).
+template <class Epi>
+struct DropPast {
+    static constexpr bool kStoresPerWorker = Epi::kStoresPerWorker;
+    static constexpr int kPrefetchRows = Epi::kPrefetchRows;
+    Epi& epi;
+    int nvalid;
+    template <bool EVEN>
+    __device__ __forceinline__ void worker(int i, const float4& f) { epi.template worker<EVEN>(i, valid_coords(f, nvalid)); }
+    __device__ __forceinline__ void worker_any(int i, const float4& f) { epi.worker_any(i, valid_coords(f, nvalid)); }
+};
+
 // `row` points at the block's first coordinate inside one row of G and is wave-uniform, so
 // the load is a scalar base plus a 32-bit lane offset.  Every lane loads (lanes past d re-read
-// the last float4), so there is no per-lane predicate; with RAGGED the coordinates >= d are
-// zeroed, without it the block lies inside the vector or the caller drops them from what it makes of the rows
-// (valid_coords).
+// the last float4, whose coordinates >= d are the row's padding), so there is no per-lane predicate; what comes of
+// them is dropped behind the driver (DropPast).
 // STREAM: the element is used once per pass (register-ring driver); a non-temporal load keeps it
 // from displacing anything in the caches (measured: 9 % off the scale pass).  The gather driver
 // re-reads rows and wants them cached.
-template <bool RAGGED, bool STREAM = false>
+template <bool STREAM>
 __device__ __forceinline__ float4 load_row4(const float* __restrict__ row, const LaneCoords& lc)
 {
     // scalar row pointer + zero-extended 32-bit lane offset: the form the hardware addresses
@@ -186,8 +201,7 @@ __device__ __forceinline__ float4 load_row4(const float* __restrict__ row, const
 #else
     const f32x4_t t = STREAM ? __builtin_nontemporal_load(src) : *src;
 #endif
-    const float4 v = make_float4(t.x, t.y, t.z, t.w);
-    return RAGGED ? valid_coords(v, lc.nvalid) : v;
+    return make_float4(t.x, t.y, t.z, t.w);
 }
 
 __device__ __forceinline__ float4 mul4(float a, const float4& g)
@@ -249,7 +263,7 @@ __device__ __forceinline__ Row load_row(const float* __restrict__ row, const Lan
     Row r;
     float4* p = reinterpret_cast<float4*>(&r);
 #pragma unroll
-    for (int t = 0; t < RowBlocks<Row>::value; ++t) p[t] = load_row4<false, true>(row + t * kBlockCoords, lc);
+    for (int t = 0; t < RowBlocks<Row>::value; ++t) p[t] = load_row4<true>(row + t * kBlockCoords, lc);
     return r;
 }
 
@@ -433,27 +447,26 @@ struct CsrView {
     const WindowRec* __restrict__ win;  // monotone-interval codes: one record per row + sentinel
 };
 
-template <bool RAGGED>
 __device__ __forceinline__ float4 encode_gather_one(const float* __restrict__ G, int64_t ldg,
                                                     const CsrView& B, int i, const LaneCoords& lc)
 {
     const int e0 = B.row_ptr[i], e1 = B.row_ptr[i + 1];
     float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
     if (e0 < e1) {
-        f = mul4(B.val[e0], load_row4<RAGGED>(G + (int64_t)B.col[e0] * ldg, lc));
+        f = mul4(B.val[e0], load_row4<false>(G + (int64_t)B.col[e0] * ldg, lc));
         for (int e = e0 + 1; e < e1; ++e)
-            f = fma4(B.val[e], load_row4<RAGGED>(G + (int64_t)B.col[e] * ldg, lc), f);
+            f = fma4(B.val[e], load_row4<false>(G + (int64_t)B.col[e] * ldg, lc), f);
     }
     return f;
 }
 
-template <bool RAGGED, class Epi>
+template <class Epi>
 __device__ __forceinline__ void encode_gather(const float* __restrict__ G, int64_t ldg, int n,
                                               const CsrView& B, const LaneCoords& lc, Epi& epi)
 {
     for (int i = 0; i < n; i += 2) {
-        epi.template worker<true>(i, encode_gather_one<RAGGED>(G, ldg, B, i, lc));
-        if (i + 1 < n) epi.template worker<false>(i + 1, encode_gather_one<RAGGED>(G, ldg, B, i + 1, lc));
+        epi.template worker<true>(i, encode_gather_one(G, ldg, B, i, lc));
+        if (i + 1 < n) epi.template worker<false>(i + 1, encode_gather_one(G, ldg, B, i + 1, lc));
     }
 }
 
@@ -573,7 +586,7 @@ __device__ __forceinline__ void window_request(float4 (&ring)[BatchShape<W>::R],
 #pragma unroll
         for (int r = 0; r < BT; ++r) {
             const int row = row0 + r < k ? row0 + r : k - 1;
-            ring[H * BT + r] = load_row4<false, true>(G + (int64_t)row * ldg, lc);
+            ring[H * BT + r] = load_row4<true>(G + (int64_t)row * ldg, lc);
         }
     }
 }
@@ -654,7 +667,7 @@ __device__ __forceinline__ void ring_part_step(float4 (&ring)[(RingShapeT<S, PF>
     constexpr int R = RingShapeT<S, PF>::R;
     const int j = j0 + r;
     if (j + P < m + S - 1) {
-        ring[(r + P) % R] = load_row4<false, true>(G + (int64_t)row * ldg, lc);
+        ring[(r + P) % R] = load_row4<true>(G + (int64_t)row * ldg, lc);
         row = row + 1 < k ? row + 1 : 0;
     }
     const int t = j - (S - 1);
@@ -697,7 +710,7 @@ __device__ __forceinline__ void encode_ring_part(const float* __restrict__ G, in
 #pragma unroll
     for (int r = 0; r < P; ++r) {
         if (r < m + S - 1) {
-            ring[r] = load_row4<false, true>(G + (int64_t)row * ldg, lc);
+            ring[r] = load_row4<true>(G + (int64_t)row * ldg, lc);
             row = row + 1 < k ? row + 1 : 0;
         }
     }
@@ -716,7 +729,7 @@ __device__ __forceinline__ void window_part_step(float4 (&ring)[(RingShapeT<W, P
     constexpr int P = RingShapeT<W, PF>::P;
     constexpr int R = RingShapeT<W, PF>::R;
     const int j = j0 + r;
-    if (j + P < k) ring[(r + P) % R] = load_row4<false, true>(G + (int64_t)(j + P) * ldg, lc);
+    if (j + P < k) ring[(r + P) % R] = load_row4<true>(G + (int64_t)(j + P) * ldg, lc);
     const int lo = j - (W - 1);
     while (i < i1 && cur.lo == lo) {
         const WindowCur nxt = load_window_rec(B.win + i + 1);  // the sentinel record ends the table
@@ -754,31 +767,41 @@ __device__ __forceinline__ void encode_window_part(const float* __restrict__ G, 
     for (int r = 0; r < R; ++r) ring[r] = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int r = 0; r < P; ++r)
-        if (first + r < k) ring[r] = load_row4<false, true>(G + (int64_t)(first + r) * ldg, lc);
+        if (first + r < k) ring[r] = load_row4<true>(G + (int64_t)(first + r) * ldg, lc);
     for (int j0 = first; i < i1; j0 += R)  // every worker is met: its lo is at most k - 1
         window_part_round<W, PF>(ring, G, ldg, k, B, lc, j0, i1, i, cur, epi, std::make_integer_sequence<int, R>{});
 }
 
-template <bool RAGGED, class Epi>
+template <class Epi>
 __device__ __forceinline__ void encode_gather_part(const float* __restrict__ G, int64_t ldg, const CsrView& B,
                                                    const LaneCoords& lc, int i0, int i1, Epi& epi)
 {
     for (int i = i0; i < i1; i += 2) {
-        epi.template worker<true>(i, encode_gather_one<RAGGED>(G, ldg, B, i, lc));
-        if (i + 1 < i1) epi.template worker<false>(i + 1, encode_gather_one<RAGGED>(G, ldg, B, i + 1, lc));
+        epi.template worker<true>(i, encode_gather_one(G, ldg, B, i, lc));
+        if (i + 1 < i1) epi.template worker<false>(i + 1, encode_gather_one(G, ldg, B, i + 1, lc));
     }
 }
 
 // workers i0..i1-1 of one block; nothing if the range is empty
 template <int S, class Epi>
+__device__ __forceinline__ void encode_part_any(const float* __restrict__ G, int64_t ldg, int k, const CsrView& B,
+                                                const LaneCoords& lc, int i0, int i1, Epi& epi)
+{
+    if constexpr (S > 0) encode_ring_part<S, Epi::kPrefetchRows>(G, ldg, k, B.val, lc, i0, i1, epi);
+    else if constexpr (S < 0) encode_window_part<-S, Epi::kPrefetchRows>(G, ldg, k, B, lc, i0, i1, epi);
+    else encode_gather_part(G, ldg, B, lc, i0, i1, epi);
+}
+template <int S, class Epi>
 __device__ __forceinline__ void encode_block_part(const float* __restrict__ G, int64_t ldg, int k, const CsrView& B,
                                                   const LaneCoords& lc, int i0, int i1, Epi& epi)
 {
     if (i0 >= i1) return;
-    if constexpr (S > 0) encode_ring_part<S, Epi::kPrefetchRows>(G, ldg, k, B.val, lc, i0, i1, epi);
-    else if constexpr (S < 0) encode_window_part<-S, Epi::kPrefetchRows>(G, ldg, k, B, lc, i0, i1, epi);
-    else if (lc.wave_ragged) encode_gather_part<true>(G, ldg, B, lc, i0, i1, epi);
-    else encode_gather_part<false>(G, ldg, B, lc, i0, i1, epi);
+    if (!Epi::kWantsZeros || !lc.wave_ragged) {
+        encode_part_any<S>(G, ldg, k, B, lc, i0, i1, epi);
+    } else {
+        DropPast<Epi> drop{epi, lc.nvalid};
+        encode_part_any<S>(G, ldg, k, B, lc, i0, i1, drop);
+    }
 }
 
 // Short vectors: how many waves share the workers of a block (each takes a run of an even number of them).
@@ -787,13 +810,13 @@ __host__ __device__ inline int part_size(int n) { return ((n + kParts - 1) / kPa
 
 // One block of 256 coordinates for all workers.  S > 0: cyclic band of width S; S < 0: monotone
 // intervals of at most -S columns; S == 0: any code.  All give identical bits.  The block that straddles d takes
-// the same driver as the others: lanes past d repeat the last float4, and with S != 0 the epilogues drop what comes of
-// coordinates >= d.  It used to take the gather driver, n rows one after the other while the chip waited.  Whole steps,
-// gather | as now, us: 256 workers x 1 000 000, Euclidean 738 | 393, max-abs 618 | 389, one pass 485 | 291;
+// the same driver as the others, in an instance of its own: with the test for it in the epilogues of all blocks, bucket-wise
+// steps were 2-5 % slower.  It used to take the gather driver, n rows one after the other while the chip waited.
+// Whole steps, gather | as now, us: 256 workers x 1 000 000, Euclidean 738 | 393, max-abs 618 | 389, one pass 485 | 291;
 // 64 x 2 000 000 234 | 191;  128 x 5 400 001 1119 | 1047;  32 x 11 700 001 559 | 546;  16 x 300 001 23.8 | 21.4.
 template <int S, class Epi>
-__device__ __forceinline__ void encode_block(const float* __restrict__ G, int64_t ldg, int n, int k,
-                                             const CsrView& B, const LaneCoords& lc, Epi& epi)
+__device__ __forceinline__ void encode_block_any(const float* __restrict__ G, int64_t ldg, int n, int k,
+                                                 const CsrView& B, const LaneCoords& lc, Epi& epi)
 {
     if constexpr (S > 0) {
         encode_ring<S, Epi::kPrefetchRows, float4>(G, ldg, k, B.val, lc, epi);
@@ -801,8 +824,18 @@ __device__ __forceinline__ void encode_block(const float* __restrict__ G, int64_
         if constexpr (Epi::kStoresPerWorker) encode_window_batched<-S>(G, ldg, k, B, lc, epi);
         else encode_window<-S, Epi::kPrefetchRows, float4>(G, ldg, k, B, lc, epi);
     } else {
-        if (!lc.wave_ragged) encode_gather<false>(G, ldg, n, B, lc, epi);
-        else encode_gather<true>(G, ldg, n, B, lc, epi);
+        encode_gather(G, ldg, n, B, lc, epi);
+    }
+}
+template <int S, class Epi>
+__device__ __forceinline__ void encode_block(const float* __restrict__ G, int64_t ldg, int n, int k,
+                                             const CsrView& B, const LaneCoords& lc, Epi& epi)
+{
+    if (!Epi::kWantsZeros || !lc.wave_ragged) {
+        encode_block_any<S>(G, ldg, n, k, B, lc, epi);
+    } else {
+        DropPast<Epi> drop{epi, lc.nvalid};
+        encode_block_any<S>(G, ldg, n, k, B, lc, drop);
     }
 }
 

@@ -92,6 +92,37 @@ inline unsigned first_group(int64_t d, unsigned groups)
     return d % 256 != 0 && groups > kChipGroups ? groups - kEarlyGroups : 0u;
 }
 
+// One read of G (agc_sketch.h): records a block has room for.  As many as leave four workgroups of a compute unit's 160 KB of
+// LDS (three and two with more workers, whose partial sums and signs take room themselves), and no more than an eighth of
+// the block's coded elements, beyond which a record of eight bytes each moves as much as a second read of G.
+inline int sketch_cap(int n)
+{
+    const int budget = n <= 96 ? 40 * 1024 : n <= 160 ? 53 * 1024 : 64 * 1024;
+    const int room = (budget - 32 * n - 4096 * ((n + 31) / 32)) / 32;
+    const int cap = room < 32 * n ? room : 32 * n;
+    return cap / 2 * 2;
+}
+
+// Records of a whole vector with levels 0..L_i, `levels` the sum of the L_i: its magnitudes sum to at most sqrt(d) times its
+// norm, and the sketch knows 0.7 of the norm (Gaussian values: 0.8 of this).
+inline double sketch_records(int64_t d, double levels) { return levels / 0.7 * __builtin_sqrt((double)d); }
+
+// Whether one read of G and the small kernels around it are faster than two reads.  Microseconds saved, fitted to whole
+// steps in graphs: half of one for every million elements of G that are not read again, less ten for three more
+// launches, 1.9 for every million coordinates (signs and tables by groups of blocks) and seven for every million records.
+// Two reads | one, us (and the fit's gain): cyclic, 4 bits 32 x 11.7 M 588 | 390 (152);  3 bits 64 x 25.6 M 2404 | 1580 (735),
+// 64 x 1 M 115 | 87 (17), 32 x 1 M 64 | 56 (3), 32 x 500 000 42 | 45 (-4), 16 x 2 M 69 | 64 (2), 8 x 4 M 70 | 71 (-1);
+// 6 bits 50 x 5.4 M 455 | 365 (64), 16 x 2 M 71 | 72 (-8);  8 bits 64 x 5.4 M 590 | 669 (-117), 4 x 25.6 M 199 | 243 (-44).
+// General codes whose blocks share their workers among waves gain less: 64 x 300 000 79 | 112, but 64 x 1 M 196 | 141.
+// A block of average magnitudes may fill three quarters of its room; the rest take k_quantize.
+//   gather_parts: gather driver with use_parts;  cap: sketch_cap
+inline bool use_sketch(int64_t d, int k, double levels, bool gather_parts, int cap)
+{
+    const double m = 1e-6 * (double)d, records = sketch_records(d, levels);
+    if (gather_parts || 256.0 * records > 0.75 * cap * (double)d) return false;
+    return 0.5 * k * m - 10.0 - 1.9 * m - 7e-6 * records > 2.0;
+}
+
 // Workgroups of the decode pass that a compute unit holds: six, which was measured to be best with one scale per
 // vector (walking over the tiles: five 0.162, four 0.166 against 0.148 ms for 64 workers x 25.6 M), or as many as
 // 160 KB of LDS has room for beside the weights of bucket- and layer-wise scales: five, four with two tracks and

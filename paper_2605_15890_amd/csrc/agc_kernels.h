@@ -159,6 +159,21 @@ struct Workspace {
     float* coef2_layer;   // [n_layers][n]
 };
 
+// What k_sketch leaves behind of its one read of G (agc_sketch.h), and the small tables around it.
+struct SketchDev {
+    uint32_t* planes;     // [block][worker, up to 32 * chunks][8] signs, in the order of the coordinates; null: not available
+    uint2* recs;          // [block][cap] coded values whose level depends on the scale
+    int* counts;          // [4 * groups of four blocks] records of the block; -1: there were more than cap
+    float* lo_scale;      // [n] lower bounds of the scales, and the largest multipliers that they leave
+    float* lo_mult;       // [n]
+    uint32_t* state;      // not 0: a bound did not hold, or a weight is not finite
+    uint32_t* done;       // [groups of four blocks] 1: k_resolve has made the group's codes
+    int cap;              // even
+    int chunks;           // ceil(n / 32)
+};
+// LDS of a k_sketch workgroup: [4][n] doubles, [4][chunks] KB of signs, [4][cap] records
+constexpr unsigned sketch_lds_bytes(int n, int cap) { return 32u * n + 4096u * ((n + 31) / 32) + 32u * cap; }
+
 constexpr int kMaxSlots = 256;  // rows of the max-abs array; a block folds into row (block mod kMaxSlots)
 constexpr int kMaxLayers = 256;  // layer-wise scales: a block's layer fits a byte
 constexpr int kLayerSub = 16;    // with layer-wise scales layer l owns rows l*kLayerSub .. +kLayerSub-1 of the array
@@ -223,13 +238,22 @@ hipError_t launch_scale_clear_slots(int n, const Workspace& ws, hipStream_t stre
 // sw.fuse != 0: the quantize pass that follows also forms the estimate (ghat) from the codes it
 // has just produced, in the same order and arithmetic as the decode kernel.
 hipError_t launch_scale_finalize(int n, int scale_mode, const QuantStreams& out, const StepWeights& sw,
-                                 const Workspace& ws, float* scales, hipStream_t stream);
+                                 const Workspace& ws, const SketchDev* sk, float* scales, hipStream_t stream);
+// One read of G (Euclidean scale of the whole vector): bounds from a sample, then the sketch; it leaves the partial results
+// of the scales like the scale pass.  launch_scale_finalize with the same sk checks the bounds.
+hipError_t launch_sketch_bounds(const float* G, int64_t ldg, int n, int k, int64_t d, const CodeDev& code,
+                                const Workspace& ws, const SketchDev& sk, const QuantStreams& out, hipStream_t stream);
+hipError_t launch_sketch(const float* G, int64_t ldg, int n, int k, int64_t d, const CodeDev& code, const Workspace& ws,
+                         const SketchDev& sk, uint64_t seed, uint64_t step, hipStream_t stream);
+// codes (and with ghat the estimate) of the sketch; launch_quantize with sk.done makes those of the groups it leaves
+hipError_t launch_resolve(int n, int64_t d, const Workspace& ws, const SketchDev& sk, const QuantStreams& out, uint64_t seed,
+                          uint64_t step, float* ghat, hipStream_t stream);
 // K2: fused encode + stochastic quantize + bit-pack.
 // ghat != nullptr: fused step (the table must have been written with sw.fuse != 0).
 // out: its bit-widths size the LDS staging area (the table holds them too).
 hipError_t launch_quantize(const float* G, int64_t ldg, int n, int k, int64_t d,
                            const CodeDev& code, const Workspace& ws, const QuantStreams& out, uint64_t seed,
-                           uint64_t step, float* ghat, hipStream_t stream);
+                           uint64_t step, float* ghat, const uint32_t* done, hipStream_t stream);
 // Bucket-wise scales (one per 256-coordinate block and worker): a table prologue, then ONE pass
 // over G that derives each block's scale from the block itself.  scales: n x nb, nb = ceil(d/256).
 hipError_t launch_quantize_bucket(const float* G, int64_t ldg, int n, int k, int64_t d, const CodeDev& code,

@@ -49,11 +49,10 @@ typedef __attribute__((address_space(1))) uint32_t global_word;
 // epilogue for the largest-magnitude scale: exact and order-free
 struct EpiMaxAbs {
     static constexpr bool kStoresPerWorker = false;
+    static constexpr bool kWantsZeros = true;
     static constexpr int kPrefetchRows = AGC_SCALE_PREFETCH_ROWS;
     uint32_t* acc;  // this wave's LDS slice [n], bit patterns of non-negative floats
     int lane;
-    int nvalid;     // of the lane's coordinates in the present block
-    bool ragged;    // wave-uniform: the vector ends inside the present block and its driver leaves the rows unmasked
     static __device__ __forceinline__ float max_abs4(const float4& f)
     {
         return fmaxf(fmaxf(fabsf(f.x), fabsf(f.y)), fmaxf(fabsf(f.z), fabsf(f.w)));
@@ -61,7 +60,7 @@ struct EpiMaxAbs {
     template <bool EVEN>
     __device__ __forceinline__ void worker(int i, const float4& f)
     {
-        const uint32_t m = wave_max_nonneg_bits(max_abs4(ragged ? valid_coords(f, nvalid) : f));
+        const uint32_t m = wave_max_nonneg_bits(max_abs4(f));
         if (lane == 0) acc[i] = m;
     }
     template <bool EVEN, int V>
@@ -81,15 +80,13 @@ struct EpiMaxAbs {
 // (x0^2+x1^2)+(x2^2+x3^2); exchange-add across the 64 lanes)
 struct EpiSumSq {
     static constexpr bool kStoresPerWorker = false;
+    static constexpr bool kWantsZeros = true;
     static constexpr int kPrefetchRows = AGC_SCALE_PREFETCH_ROWS;
     double* acc;  // this wave's LDS slice [n]
     int lane;
-    int nvalid;
-    bool ragged;  // as in EpiMaxAbs
     template <bool EVEN>
-    __device__ __forceinline__ void worker(int i, const float4& whole)
+    __device__ __forceinline__ void worker(int i, const float4& f)
     {
-        const float4 f = ragged ? valid_coords(whole, nvalid) : whole;
         const double x0 = f.x, x1 = f.y, x2 = f.z, x3 = f.w;
         const double s01 = x0 * x0 + x1 * x1;
         const double s23 = x2 * x2 + x3 * x3;
@@ -152,7 +149,7 @@ __global__ __launch_bounds__(kWave * WAVES) void k_scale_pass(const float* __res
         for (int i = threadIdx.x; i < a.n; i += kWave * WAVES) wg_max[i] = 0u;
         if (threadIdx.x == 0) wg_done = 0u;
         __syncthreads();  // the only barrier: at the start, where no wave has anything to wait for
-        EpiMaxAbs epi{accu, lane, 4, false};
+        EpiMaxAbs epi{accu, lane};
         // Layer-wise scales (Sec. II-B names the layer-wise granularity): layer l owns rows
         // l*kLayerSub .. l*kLayerSub+kLayerSub-1 of the slot array (several rows, so that the
         // workgroups that walk one layer at the same time do not all hit the same words).  The
@@ -194,8 +191,6 @@ __global__ __launch_bounds__(kWave * WAVES) void k_scale_pass(const float* __res
                     const int64_t b = base + (int64_t)u * kBlockCoords;
                     if (b < a.d) {
                         const LaneCoords lc = lane_coords(b, lane, a.d);
-                        epi.nvalid = lc.nvalid;
-                        epi.ragged = S != 0 && lc.wave_ragged;
                         encode_block<S>(G + b, a.ldg, a.n, a.k, B, lc, epi);
                         fold(layer_of(b));
                     }
@@ -231,7 +226,7 @@ __global__ __launch_bounds__(kWave * WAVES) void k_scale_pass(const float* __res
     }
     if (sq_has) {
         const LaneCoords lc = lane_coords(sq_base, lane, a.d);
-        EpiSumSq epi{accd, lane, lc.nvalid, S != 0 && lc.wave_ragged};
+        EpiSumSq epi{accd, lane};
         encode_block<S>(G + sq_base, a.ldg, a.n, a.k, B, lc, epi);
     } else {  // a block past the end of the vector (or of the layer's last segment) contributes nothing
         for (int i = lane; i < a.n; i += kWave) accd[i] = 0.0;
@@ -268,7 +263,7 @@ __global__ __launch_bounds__(kWave * (MODE == 1 ? kParts : kParts * kSegBlocks))
         const int64_t blk = blockIdx.x;
         const int64_t base = blk * kBlockCoords;
         const LaneCoords lc = lane_coords(base, lane, a.d);
-        EpiMaxAbs epi{lds_max, lane, lc.nvalid, S != 0 && lc.wave_ragged};
+        EpiMaxAbs epi{lds_max, lane};
         encode_block_part<S>(G + base, a.ldg, a.k, B, lc, i0, i1, epi);
         const int64_t slot = a.block_layer ? (int64_t)a.block_layer[blk] * kLayerSub + blk % kLayerSub : blk & (kMaxSlots - 1);
         for (int i = i0 + lane; i < i1; i += kWave) {  // written by this wave's lane 0
@@ -288,7 +283,7 @@ __global__ __launch_bounds__(kWave * (MODE == 1 ? kParts : kParts * kSegBlocks))
         }
         if (has) {
             const LaneCoords lc = lane_coords(base, lane, a.d);
-            EpiSumSq epi{lds_sq[b], lane, lc.nvalid, S != 0 && lc.wave_ragged};
+            EpiSumSq epi{lds_sq[b], lane};
             encode_block_part<S>(G + base, a.ldg, a.k, B, lc, i0, i1, epi);
         } else {
             for (int i = i0 + lane; i < i1; i += kWave) lds_sq[b][i] = 0.0;
@@ -448,10 +443,16 @@ __device__ __forceinline__ float unit_weight(float w, float scale, int b)
     return (float)(((double)w * (double)scale) / L);
 }
 
+// The lower bounds that the sketch was made with, to be checked (null: there is none).
+struct SketchCheck {
+    const float* lo_scale;
+    uint32_t* state;
+};
+
 // One workgroup per worker (and layer, with the Euclidean scale).
 template <int MODE, int CAP>
 __global__ __launch_bounds__(kWgThreads) void k_scale_finalize(int n, QuantList<CAP> in, Workspace ws, int64_t ngroup,
-                                                               float* scales)
+                                                               SketchCheck check, float* scales)
 {
     const int i = blockIdx.x;
     const int tid = threadIdx.x;
@@ -503,7 +504,11 @@ __global__ __launch_bounds__(kWgThreads) void k_scale_finalize(int n, QuantList<
         const int l = MODE == 0 ? (int)blockIdx.y : 0, per = MODE == 0 ? (int)gridDim.y : 1;
         scales[(int64_t)i * per + l] = scale;
         const int b = in.bits[i];
-        ws.wq[(int64_t)l * n + i] = worker_record(in, i, n, inv16_of(scale, b), unit_weight(in.w[i], scale, b));
+        const WorkerQ q = worker_record(in, i, n, inv16_of(scale, b), unit_weight(in.w[i], scale, b));
+        ws.wq[(int64_t)l * n + i] = q;
+        // a weight that is not finite makes NaN of zero levels too, which k_resolve does not add up
+        if (MODE == 0 && check.state && !(scale >= check.lo_scale[i] && fabsf(q.coef) < __builtin_inff()))
+            (void)__hip_atomic_fetch_or(check.state, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -547,15 +552,16 @@ static QuantList<CAP> quant_list(int n, const QuantStreams& out, const StepWeigh
 
 template <int CAP>
 static hipError_t launch_scale_finalize_cap(int n, int scale_mode, const QuantStreams& out, const StepWeights& sw,
-                                            const Workspace& ws, float* scales, hipStream_t stream)
+                                            const Workspace& ws, const SketchDev* sk, float* scales, hipStream_t stream)
 {
+    const SketchCheck check = sk ? SketchCheck{sk->lo_scale, sk->state} : SketchCheck{nullptr, nullptr};
     const QuantList<CAP> q = quant_list<CAP>(n, out, sw);
     const int layers = ws.n_layers;
     if (scale_mode == 1) {
         if (layers > 0)
             hipLaunchKernelGGL((k_scale_finalize_layers<CAP>), dim3(layers), dim3(kWgThreads), 0, stream, n, q, ws, scales);
         else
-            hipLaunchKernelGGL((k_scale_finalize<1, CAP>), dim3(n), dim3(kWgThreads), 0, stream, n, q, ws, (int64_t)0, scales);
+            hipLaunchKernelGGL((k_scale_finalize<1, CAP>), dim3(n), dim3(kWgThreads), 0, stream, n, q, ws, (int64_t)0, check, scales);
         return hipGetLastError();
     }
     const int64_t ngroup = layers > 0 ? ws.ngroup_layers : ws.ngroup;
@@ -563,18 +569,122 @@ static hipError_t launch_scale_finalize_cap(int n, int scale_mode, const QuantSt
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_scale_finalize<0, CAP>), dim3(n, layers > 0 ? layers : 1), dim3(kWgThreads), 0, stream, n, q, ws,
-                       ngroup, scales);
+                       ngroup, check, scales);
     return hipGetLastError();
 }
 
 // The host pays about 1.7 ns per byte of kernel arguments (64 bytes 2.5 us a launch, 4000 bytes 9.1 us), so the
 // lists come in three sizes.
 hipError_t launch_scale_finalize(int n, int scale_mode, const QuantStreams& out, const StepWeights& sw,
-                                 const Workspace& ws, float* scales, hipStream_t stream)
+                                 const Workspace& ws, const SketchDev* sk, float* scales, hipStream_t stream)
 {
-    if (n <= 16) return launch_scale_finalize_cap<16>(n, scale_mode, out, sw, ws, scales, stream);
-    if (n <= 64) return launch_scale_finalize_cap<64>(n, scale_mode, out, sw, ws, scales, stream);
-    return launch_scale_finalize_cap<kArgWorkers>(n, scale_mode, out, sw, ws, scales, stream);
+    if (n <= 16) return launch_scale_finalize_cap<16>(n, scale_mode, out, sw, ws, sk, scales, stream);
+    if (n <= 64) return launch_scale_finalize_cap<64>(n, scale_mode, out, sw, ws, sk, scales, stream);
+    return launch_scale_finalize_cap<kArgWorkers>(n, scale_mode, out, sw, ws, sk, scales, stream);
+}
+
+// ---- lower bounds of the Euclidean scales from a sample of the blocks (agc_sketch.h).  The sample's sum of squares
+// without its two largest blocks, scaled up to the vector, estimates the square of the scale from below; the bound is 0.7 of
+// its root.  A coordinate becomes a record with a probability in proportion to scale / bound, so a lower bound
+// costs records; a higher one costs the whole sketch when the scale falls below it.  With heavy tails (Student's t, three
+// degrees) one block in a sample of 131072 coordinates that holds an extreme value put the plain estimate 40 % too high in
+// about 5 % of the steps of 64 workers; two such blocks are rare.
+constexpr int kSampleParts = 16;  // waves that share the workers of a block: one block's latency is what counts
+constexpr int kMaxSamples = 512;
+
+template <int S>
+__global__ __launch_bounds__(kWave * kSampleParts) void k_sketch_sample(const float* __restrict__ G, const int* __restrict__ row_ptr,
+                                                                        const int* __restrict__ col, const float* __restrict__ val,
+                                                                        ScaleArgs a, int64_t block_step)
+{
+    __shared__ double lds_sq[kMaxWorkers];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int lane = threadIdx.x % kWave;
+    const int size = ((a.n + kSampleParts - 1) / kSampleParts + 1) / 2 * 2;
+    const int i0 = wave * size, i1 = i0 + size < a.n ? i0 + size : a.n;
+    const int64_t base = (int64_t)blockIdx.x * block_step * kBlockCoords;
+    const LaneCoords lc = lane_coords(base, lane, a.d);
+    EpiSumSq epi{lds_sq, lane};
+    encode_block_part<S>(G + base, a.ldg, a.k, CsrView{row_ptr, col, val, a.win}, lc, i0, i1, epi);
+    for (int i = i0 + lane; i < i1; i += kWave) a.part_sq[(int64_t)blockIdx.x * a.n + i] = lds_sq[i];  // of this wave's lane 0
+}
+
+struct BitList {
+    uint8_t bits[kArgWorkers];
+};
+
+__global__ __launch_bounds__(kWgThreads) void k_sketch_bounds(int n, BitList in, const double* part_sq, int samples,
+                                                              double times, SketchDev sk)
+{
+    __shared__ double sum[kWgThreads], top[kWgThreads], second[kWgThreads];
+    const int i = blockIdx.x, tid = threadIdx.x;
+    double s = 0.0, m1 = 0.0, m2 = 0.0;
+    for (int e = tid; e < samples; e += kWgThreads) {
+        const double v = part_sq[(int64_t)e * n + i];
+        s = s + v;
+        m2 = fmax(m2, fmin(m1, v));
+        m1 = fmax(m1, v);
+    }
+    sum[tid] = s;
+    top[tid] = m1;
+    second[tid] = m2;
+    __syncthreads();
+    for (int h = kWgThreads / 2; h > 0; h >>= 1) {
+        if (tid < h) {
+            sum[tid] = sum[tid] + sum[tid + h];
+            second[tid] = fmax(fmax(second[tid], second[tid + h]), fmin(top[tid], top[tid + h]));
+            top[tid] = fmax(top[tid], top[tid + h]);
+        }
+        __syncthreads();
+    }
+    if (tid == 0) {
+        const double rest = sum[0] - (samples >= 8 ? top[0] + second[0] : 0.0);
+        const float lo = (float)(0.7 * sqrt(fmax(rest, 0.0) * times));
+        const float mult = inv16_of(lo, in.bits[i]);
+        sk.lo_scale[i] = lo;
+        sk.lo_mult[i] = mult > 0.f ? mult : __builtin_inff();  // no bound, or a quotient beyond binary32
+        if (i == 0) sk.state[0] = 0u;
+    }
+}
+
+template <int S>
+static void launch_sketch_sample_s(const float* G, const CodeDev& code, const ScaleArgs& a, int samples, int64_t block_step,
+                                   hipStream_t stream)
+{
+    hipLaunchKernelGGL((k_sketch_sample<S>), dim3(samples), dim3(kWave * kSampleParts), 0, stream, G, code.row_ptr, code.col,
+                       code.val, a, block_step);
+}
+
+hipError_t launch_sketch_bounds(const float* G, int64_t ldg, int n, int k, int64_t d, const CodeDev& code,
+                                const Workspace& ws, const SketchDev& sk, const QuantStreams& out, hipStream_t stream)
+{
+    // one block in 64; the partial sums' array is their scratch, which has a row for every four blocks
+    const int64_t nblocks = (d + kBlockCoords - 1) / kBlockCoords;
+    const int samples = nblocks < 64 ? 1 : nblocks / 64 < kMaxSamples ? (int)(nblocks / 64) : kMaxSamples;
+    const int64_t step = nblocks / samples;
+    const ScaleArgs a{ldg, n, k, d, 0, nullptr, ws.part_sq, code.win, nullptr, nullptr, nullptr};
+    if (code.band < 0 && !code.win) return hipErrorInvalidValue;
+    switch (code.band) {
+        case 1: launch_sketch_sample_s<1>(G, code, a, samples, step, stream); break;
+        case 2: launch_sketch_sample_s<2>(G, code, a, samples, step, stream); break;
+        case 3: launch_sketch_sample_s<3>(G, code, a, samples, step, stream); break;
+        case 4: launch_sketch_sample_s<4>(G, code, a, samples, step, stream); break;
+        case 5: launch_sketch_sample_s<5>(G, code, a, samples, step, stream); break;
+        case 6: launch_sketch_sample_s<6>(G, code, a, samples, step, stream); break;
+        case 7: launch_sketch_sample_s<7>(G, code, a, samples, step, stream); break;
+        case 8: launch_sketch_sample_s<8>(G, code, a, samples, step, stream); break;
+        case -2: launch_sketch_sample_s<-2>(G, code, a, samples, step, stream); break;
+        case -4: launch_sketch_sample_s<-4>(G, code, a, samples, step, stream); break;
+        case -8: launch_sketch_sample_s<-8>(G, code, a, samples, step, stream); break;
+        default: launch_sketch_sample_s<0>(G, code, a, samples, step, stream); break;
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    BitList bits;
+    for (int i = 0; i < kArgWorkers; ++i) bits.bits[i] = i < n ? out.bits[i] : 0;
+    hipLaunchKernelGGL(k_sketch_bounds, dim3(n), dim3(kWgThreads), 0, stream, n, bits, ws.part_sq, samples,
+                       (double)nblocks / (double)samples, sk);
+    return hipGetLastError();
 }
 
 // =======================================================================================
@@ -612,7 +722,7 @@ hipError_t launch_quantize_bucket(const float* G, int64_t ldg, int n, int k, int
     if (e != hipSuccess) return e;
     QuantArgs a{ldg, n, k, d, (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32),
                 scales, (d + kBlockCoords - 1) / kBlockCoords, ghat, nullptr, out.stage_bits, out.stage_fills,
-                nullptr, 0u, out.parts};
+                nullptr, 0u, out.parts, nullptr};
     if (a.stage_fills > 1)
         return scale_mode == 0 ? launch_quantize_band2m(G, code, ws, a, stream)
                                : launch_quantize_band1m(G, code, ws, a, stream);
@@ -622,11 +732,11 @@ hipError_t launch_quantize_bucket(const float* G, int64_t ldg, int n, int k, int
 
 hipError_t launch_quantize(const float* G, int64_t ldg, int n, int k, int64_t d,
                            const CodeDev& code, const Workspace& ws, const QuantStreams& out, uint64_t seed,
-                           uint64_t step, float* ghat, hipStream_t stream)
+                           uint64_t step, float* ghat, const uint32_t* done, hipStream_t stream)
 {
     QuantArgs a{ldg, n, k, d, (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32),
                 nullptr, 0, ghat, nullptr, out.stage_bits, out.stage_fills,
-                ws.n_layers > 0 ? ws.block_layer : nullptr, 0u, out.parts};
+                ws.n_layers > 0 ? ws.block_layer : nullptr, 0u, out.parts, done};
     return a.stage_fills > 1 ? launch_quantize_band0m(G, code, ws, a, stream)
                              : launch_quantize_band0s(G, code, ws, a, stream);
 }

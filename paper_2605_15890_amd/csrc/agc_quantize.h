@@ -26,6 +26,7 @@ struct QuantArgs {
     const uint8_t* block_layer;  // layer-wise scales only: the layer of every block; wq is then [layer][n]
     unsigned wg_first;     // the workgroups take the groups of four blocks from here upwards and then from 0; 0 with parts
     bool parts;            // short vectors: one block per workgroup, its workers shared among the waves
+    const uint32_t* done;  // not null: groups of four blocks whose codes exist already (agc_sketch.h); never with parts
 };
 
 typedef __attribute__((address_space(1))) uint32_t global_u32;  // a pointer known to be device memory
@@ -106,6 +107,42 @@ __device__ __forceinline__ float grid_pos(float f, float inv)
     return fabsf(f) * inv;
 }
 
+// The waves of a workgroup write out a fill of its staging area, workers first..last, which they share.  A worker's 2 * kBlocks
+// * b pieces leave as one store of contiguous bytes through a buffer descriptor that covers exactly the bytes of the
+// stream that exist, so the hardware's range check drops the pieces past the end of the vector.  Pieces are handed back
+// zeroed.  wg_groups: 128-code groups of the workgroup's blocks that exist.  AHEAD: the next worker's record is requested
+// while this one's pieces leave, for a kernel that does little else.
+template <int kBlocks, bool AHEAD = false>
+__device__ __forceinline__ void store_fill(uint32_t* stage, const WorkerQ* wq, int first, int last, int wave, int lane,
+                                           int64_t wg, int wg_groups)
+{
+    u32x4_t* pieces = reinterpret_cast<u32x4_t*>(stage);
+    WorkerQ next{};
+    if (AHEAD) next = load_uniform(wq + (first + wave <= last ? first + wave : last));
+    for (int j = first + wave; j <= last; j += kQuantWaves) {
+        const WorkerQ w = AHEAD ? next : load_uniform(wq + j);
+        if (AHEAD && j + kQuantWaves <= last) next = load_uniform(wq + j + kQuantWaves);
+        const int b = (int)w.bits;
+        const int np = 2 * kBlocks * b;  // pieces of this worker in the area
+        const __amdgpu_buffer_rsrc_t rsrc = uniform_buffer(
+            (const char*)w.codes + (uint64_t)wg * (uint64_t)(32 * kBlocks * b), 16 * b * wg_groups);
+        const uint32_t at = w.stage_piece * (uint32_t)kBlocks / 4u;  // the table counts for four blocks
+        for (int off = 0; off < np; off += kWave) {
+            const int piece = off + lane;
+            u32x4_t v = u32x4_t{0u, 0u, 0u, 0u};
+            if (piece < np) {
+                u32x4_t* sp = pieces + (at + (uint32_t)piece);
+                v = *sp;
+                *sp = u32x4_t{0u, 0u, 0u, 0u};
+            }
+            // lanes with piece >= np lie at or past the worker's bytes >= valid_bytes: dropped by the range check
+#ifndef AGC_ABLATE_STORES
+            __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, 16 * piece, 0, kPayloadStorePolicy);
+#endif
+        }
+    }
+}
+
 // BUCKET 0: the worker's multiplier comes from the table (one scale per vector).
 // BUCKET 1 / 2: one scale per 256-coordinate block, derived here from the block itself (largest
 // magnitude / Euclidean norm), stored by lane 0, and turned into the multiplier with one binary32
@@ -130,6 +167,7 @@ template <int BUCKET, bool FUSE, bool MULTI, bool PARTS>
 struct EpiQuant {
     static constexpr int kBlocks = PARTS ? 1 : kQuantWaves;  // of the workgroup
     static constexpr bool kStoresPerWorker = MULTI;  // stores inside the worker loop (a flush between workers)
+    static constexpr bool kWantsZeros = BUCKET != 0;  // else codes4 drops the codes of coordinates >= d, and nothing else counts them
     static constexpr int kPrefetchRows = AGC_PREFETCH_ROWS;
     const WorkerQ* __restrict__ wq;
     uint32_t key0, key1, step_lo, step_hi;
@@ -145,7 +183,6 @@ struct EpiQuant {
     uint32_t ctr0;       // m >> 2 of this lane's coordinates
     int nvalid;
     bool wave_ragged;    // wave-uniform: some lane has coordinates >= d
-    bool drop;           // and its driver leaves the rows unmasked
     uint32_t keep2, keep3;  // second half of the Philox block, for the odd worker of the pair
     float* scales;          // bucket-wise scales: n x nb
     int64_t nb;
@@ -155,35 +192,11 @@ struct EpiQuant {
 
     // The workgroup writes out the fill that ends with worker `last`.  Every wave of the
     // workgroup calls this for the same workers in the same order (also a wave whose block lies
-    // past the end of the vector), so the barriers match.  The waves share the workers of the
-    // fill; a worker's 8b pieces leave as one store of 128*b contiguous bytes through a buffer
-    // descriptor that covers exactly the bytes of the stream that exist, so the hardware's range
-    // check drops the pieces past the end of the vector.  Pieces are handed back zeroed.
+    // past the end of the vector), so the barriers match.
     __device__ __forceinline__ void flush_fill(int last)
     {
         __syncthreads();
-        u32x4_t* pieces = reinterpret_cast<u32x4_t*>(stage);
-        for (int j = group_first + wave; j <= last; j += kQuantWaves) {
-            const WorkerQ w = load_uniform(wq + j);
-            const int b = (int)w.bits;
-            const int np = 2 * kBlocks * b;  // pieces of this worker in the area
-            const __amdgpu_buffer_rsrc_t rsrc = uniform_buffer(
-                (const char*)w.codes + (uint64_t)wg * (uint64_t)(32 * kBlocks * b), 16 * b * wg_groups);
-            const uint32_t first = w.stage_piece * (uint32_t)kBlocks / 4u;  // the table counts for four blocks
-            for (int off = 0; off < np; off += kWave) {
-                const int piece = off + lane;
-                u32x4_t v = u32x4_t{0u, 0u, 0u, 0u};
-                if (piece < np) {
-                    u32x4_t* sp = pieces + (first + (uint32_t)piece);
-                    v = *sp;
-                    *sp = u32x4_t{0u, 0u, 0u, 0u};
-                }
-                // lanes with piece >= np lie at or past the worker's bytes >= valid_bytes: dropped by the range check
-#ifndef AGC_ABLATE_STORES
-                __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, 16 * piece, 0, kPayloadStorePolicy);
-#endif
-            }
-        }
+        store_fill<kBlocks>(stage, wq, group_first, last, wave, lane, wg, wg_groups);
         group_first = last + 1;
         if (last + 1 < n) {
             __syncthreads();  // the area is reused by the next fill
@@ -220,9 +233,8 @@ struct EpiQuant {
         }
     }
 
-    __device__ __forceinline__ float block_multiplier(int i, const float4& whole, float num, float& scale)
+    __device__ __forceinline__ float block_multiplier(int i, const float4& f, float num, float& scale)
     {
-        const float4 f = drop ? valid_coords(whole, nvalid) : whole;
         if (BUCKET == 1) {
             const float a = fmaxf(fmaxf(fabsf(f.x), fabsf(f.y)), fmaxf(fabsf(f.z), fabsf(f.w)));
             scale = __uint_as_float(wave_max_nonneg_bits(a));
@@ -422,7 +434,8 @@ __device__ __forceinline__ float staged_estimate(const WorkerQ* __restrict__ wq,
     return acc;
 }
 
-template <int S, int BUCKET, bool FUSE, bool MULTI, bool PARTS>
+// LEFT: only the groups of blocks that k_resolve has left (an instance of its own: the test alone cost the others 0.3 us).
+template <int S, int BUCKET, bool FUSE, bool MULTI, bool PARTS, bool LEFT = false>
 // The compiler is told to plan for four waves per SIMD: with a register count just under the
 // five-wave limit it otherwise schedules for five and gives up instruction-level parallelism;
 // measured 1.45 ms against 1.51 ms on the metric workload (three: 1.51 ms).  The gather driver
@@ -445,6 +458,9 @@ __global__ __launch_bounds__(kQuantThreads) __attribute__((amdgpu_waves_per_eu(S
     unsigned wg_index = blockIdx.x + a.wg_first;  // < 2 * grid <= 2^24
     if (wg_index >= gridDim.x) wg_index -= gridDim.x;
     const int64_t wg = wg_index;
+    if constexpr (LEFT) {
+        if (load_uniform(a.done + wg) != 0u) return;
+    }
     const int64_t block = PARTS ? wg : wg * kQuantWaves + wave;
     const int64_t base = block * (int64_t)kBlockCoords;
     {
@@ -467,7 +483,7 @@ __global__ __launch_bounds__(kQuantThreads) __attribute__((amdgpu_waves_per_eu(S
     EpiQuant<BUCKET, FUSE, MULTI, PARTS> epi{wq, a.key0, a.key1, a.step_lo, a.step_hi, lds_stage, stage_scales, lane, wave,
                                PARTS ? 0 : wave, a.n, wg,
                                groups_left >= 2 * kBlocks ? 2 * kBlocks : (int)groups_left, block, (uint32_t)((base + 4 * lane) >> 2),
-                               lc.nvalid, lc.wave_ragged, S != 0 && lc.wave_ragged, 0u, 0u, a.scales, a.nb, 0, {0.f, 0.f, 0.f, 0.f},
+                               lc.nvalid, lc.wave_ragged, 0u, 0u, a.scales, a.nb, 0, {0.f, 0.f, 0.f, 0.f},
                                load_uniform(wq + (i0 < a.n ? i0 : 0))};
     if constexpr (PARTS) {  // every workgroup has its block
         encode_block_part<S>(G + base, a.ldg, a.k, CsrView{row_ptr, col, val, a.win}, lc, i0, i1, epi);
@@ -529,6 +545,17 @@ static hipError_t launch_quantize_s(const float* G, const CodeDev& code, const W
     const unsigned lds_bytes = 16u * (unsigned)stage_pieces(a.stage_bits, kQuantWaves) +
                                (BUCKET != 0 ? (unsigned)(sizeof(float) * kQuantWaves * a.n) : 0u);
     const dim3 g(grid), b(kQuantThreads);
+    if constexpr (BUCKET == 0) {
+        if (a.done) {
+            if (a.ghat)
+                hipLaunchKernelGGL((k_quantize<S, 0, true, MULTI, false, true>), g, b, lds_bytes, stream, G, code.row_ptr,
+                                   code.col, code.val, ws.wq, a);
+            else
+                hipLaunchKernelGGL((k_quantize<S, 0, false, MULTI, false, true>), g, b, lds_bytes, stream, G, code.row_ptr,
+                                   code.col, code.val, ws.wq, a);
+            return hipGetLastError();
+        }
+    }
     if (a.ghat)
         hipLaunchKernelGGL((k_quantize<S, BUCKET, true, MULTI, false>), g, b, lds_bytes, stream, G, code.row_ptr, code.col,
                            code.val, ws.wq, a);

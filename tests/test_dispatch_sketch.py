@@ -1,0 +1,56 @@
+"""The rule that decides between one read of G and two (csrc/agc_dispatch.h), compiled on its own with the host compiler:
+on either side of its line, at shapes where both forms were timed, and at the ends of its ranges.  CPU only."""
+import ctypes
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+DRIVER = r"""
+#include "agc_dispatch.h"
+extern "C" int one_read(int64_t d, int n, int k, double levels, int gather_parts)
+{
+    return agc::use_sketch(d, k, levels, gather_parts != 0, agc::sketch_cap(n));
+}
+extern "C" int cap(int n) { return agc::sketch_cap(n); }
+"""
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("sketch")
+    (tmp / "driver.cpp").write_text(DRIVER)
+    cxx = shutil.which("g++") or shutil.which("c++")
+    subprocess.run([cxx, "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-fPIC", "-shared",
+                    "-fsanitize=undefined", "-fno-sanitize-recover=undefined",
+                    "-I", os.path.join(ROOT, "paper_2605_15890_amd", "csrc"), str(tmp / "driver.cpp"),
+                    "-o", str(tmp / "librules.so")], check=True)
+    lib = ctypes.CDLL(str(tmp / "librules.so"))
+    lib.one_read.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_double, ctypes.c_int]
+    return lib
+
+
+@pytest.mark.parametrize("one,d,n,k,bits", [
+    (1, 25_600_000, 64, 64, 3), (1, 11_700_000, 32, 32, 4), (1, 5_400_003, 50, 50, 6), (1, 5_400_001, 10, 30, 3),
+    (1, 1_000_001, 64, 64, 3), (1, 3_000_000, 256, 256, 2), (1, 12_000_000, 64, 64, 6),
+    (0, 25_600_000, 4, 4, 8), (0, 5_400_000, 64, 64, 8), (0, 4_000_000, 8, 8, 3), (0, 500_000, 32, 32, 3),
+    (0, 2_000_000, 16, 16, 6), (0, 65536, 128, 128, 3), (0, 1_000_001, 128, 128, 6)])
+def test_one_read_where_that_was_measured_to_be_faster(rules, one, d, n, k, bits):
+    assert rules.one_read(d, n, k, float(n * (2 ** (bits - 1) - 1)), 0) == one
+    assert rules.one_read(d, n, k, float(n * (2 ** (bits - 1) - 1)), 1) == 0
+
+
+def test_ends_of_the_ranges(rules):
+    """No overflow (the driver is built with the sanitizer), room for a whole number of 16-byte pieces in 64 KB of LDS."""
+    for n in range(1, 257):
+        cap = rules.cap(n)
+        assert cap >= 32 and cap % 2 == 0 and cap <= 32 * n
+        assert 32 * n + 4096 * -(-n // 32) + 32 * cap <= 64 * 1024
+        for d in (1, 2 ** 33):
+            for k in (1, 65536):
+                for level in (1, 32767):
+                    one = rules.one_read(d, n, k, float(n * level), 0)
+                    assert not (d == 1 and one)

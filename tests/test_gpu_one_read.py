@@ -1,0 +1,195 @@
+"""The form with one read of G (Euclidean scale of the whole vector): forced at small sizes by its testing hook, every
+driver, one and several fills of the staging area, blocks and groups that end inside the vector, blocks with more records
+than there is room for, samples that mislead in either direction, values and weights that are not finite.  Codes, scales
+and estimates equal the oracle's bit for bit, twice in a row and from a replayed graph."""
+import numpy as np
+import pytest
+
+from oracle import agc_oracle as O
+from paper_2605_15890_amd import api
+
+from gpu_util import cyclic_csr, monotone_csr, random_csr, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+def _code(rng, kind, n, k, width):
+    return (cyclic_csr(rng, n, min(n, width)) if kind == "cyclic" else monotone_csr(rng, n, k, width) if kind == "interval"
+            else random_csr(rng, n, k, width))
+
+
+def _check(G_host, csr, k, bits, w, mask, unfused=False, graph=False, seed=77, step=9, oracle=None):
+    import torch
+    n, d = len(bits), G_host.shape[1]
+    ctx = api.Context(n, k, d, scale_mode=api.AGC_SCALE_L2, unfused_step=unfused)
+    ctx.agc_set_code(*csr)
+    ctx.agc_debug_sketch(1)
+    codes, scales, ghat = ctx.alloc_outputs(bits)
+    for t in codes:
+        t.fill_(0x5A)
+    ghat.fill_(float("nan"))
+    G = to_device(G_host)
+
+    def run():
+        ctx.agc_step(G, bits, w, mask, seed, step, codes, scales, ghat)
+    run()
+    if graph:
+        torch.cuda.synchronize()
+        side, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=side):
+            run()
+    for _ in range(3 if graph else 1):   # the next pass finds what the last one left behind
+        if graph:
+            ghat.fill_(float("nan"))
+            g.replay()
+            torch.cuda.synchronize()
+        else:
+            run()
+    torch.cuda.synchronize()
+    o_streams, o_scales, o_ghat = oracle or O.step(G_host, O.Csr(*csr, k), bits, w, mask, seed, step, api.AGC_SCALE_L2)
+    assert np.array_equal(scales.cpu().numpy().view(np.uint32).ravel(), o_scales.view(np.uint32).ravel())
+    for i in range(n):
+        assert np.array_equal(codes[i].cpu().numpy(), o_streams[i]), i
+    got = ghat.cpu().numpy()
+    nan = np.isnan(o_ghat)   # the payload of a NaN is nobody's contract
+    assert np.array_equal(np.isnan(got), nan) and np.array_equal(got.view(np.uint32)[~nan], o_ghat.view(np.uint32)[~nan])
+    ctx.close()
+
+
+def _draw(rng, n, most):
+    return (rng.integers(2, most + 1, n).astype(np.uint8), rng.uniform(0.2, 3.0, n).astype(np.float32),
+            (rng.random(n) < 0.7).astype(np.uint8))
+
+
+@pytest.mark.parametrize("kind,width", [("cyclic", s) for s in range(1, 9)] + [("interval", w) for w in (2, 4, 8)] + [("general", 5)])
+@pytest.mark.parametrize("d", [1, 255, 1024, 40000 + 77])
+def test_every_driver(kind, width, d):
+    rng = np.random.default_rng([d, width, len(kind)])
+    n = k = 13
+    bits, w, mask = _draw(rng, n, 6)
+    _check(rng.standard_normal((k, d)).astype(np.float32), _code(rng, kind, n, k, width), k, bits, w, mask)
+
+
+@pytest.mark.parametrize("n,most", [(1, 16), (2, 3), (7, 16), (8, 4), (9, 2), (31, 16), (32, 9), (33, 16), (64, 5), (97, 3),
+                                    (161, 2), (256, 2), (256, 6)])
+@pytest.mark.parametrize("law", ["normal", "heavy", "layered"])
+def test_workers_widths_and_fills(n, most, law):
+    """Wide codes overflow their blocks' room for records (all, or with layers of very different size some of them), the rest
+    of the group's blocks and of the vector do not."""
+    rng = np.random.default_rng([n, most])
+    k, d = n, 3 * 1024 * 12 + 300
+    csr = _code(rng, "cyclic" if n % 2 else "interval", n, k, 4)
+    bits, w, mask = _draw(rng, n, most)
+    G = rng.standard_normal((k, d))
+    if law == "heavy":
+        G = G * np.exp(2.0 * rng.standard_normal((k, d)))
+    elif law == "layered":
+        G = G * np.repeat(10.0 ** rng.uniform(-4, 1, 36 + 1), 1024)[:d]
+    _check(G.astype(np.float32), csr, k, bits, w, mask, unfused=n % 3 == 0, graph=n == 33)
+
+
+@pytest.mark.parametrize("where", ["sampled", "elsewhere", "nowhere", "sign", "large", "small"])
+def test_samples_that_mislead(where):
+    """70 segments, of which two are sampled, the first and the 36th.  All of the vector's norm in one of them: the bound lies
+    above the scale and everything takes the quantize pass.  In none of them: there is no bound."""
+    rng = np.random.default_rng(5)
+    n = k = 11
+    d = 70 * 1024
+    csr = cyclic_csr(rng, n, 3)
+    bits, w, mask = _draw(rng, n, 8)
+    G = np.zeros((k, d), np.float32)
+    at = {"sampled": slice(0, 1024), "elsewhere": slice(5000, 9000), "nowhere": slice(0, 0)}.get(where, slice(0, d))
+    G[:, at] = rng.standard_normal((k, G[:, at].shape[1]))
+    if where == "sign":
+        G = np.copysign(np.float32(0), rng.standard_normal((k, d))).astype(np.float32)
+        G[:, 3] = 1.0
+    G *= np.float32({"large": 1e18, "small": 1e-42}.get(where, 1.0))
+    _check(G, csr, k, bits, w, mask)
+
+
+def test_ties_take_the_secondary_draw():
+    """Every coordinate the same and sixteen bits wide: many draws tie with the low half of the grid position."""
+    rng = np.random.default_rng(6)
+    n = k = 4
+    bits, w, mask = np.full(n, 16, np.uint8), np.ones(n, np.float32), np.ones(n, np.uint8)
+    csr = cyclic_csr(rng, n, 1)
+    _check(np.full((k, 200 * 1024), 1e-3, np.float32) * np.float32(1 + 0.1 * rng.random((k, 1))), csr, k, bits, w, mask)
+
+
+@pytest.mark.parametrize("weight", [0.0, -0.0, -2.5, 1e-38, 3e38])
+def test_weights(weight):
+    rng = np.random.default_rng(8)
+    n = k = 6
+    bits, w, mask = _draw(rng, n, 4)
+    w[:3] = weight
+    mask[:] = 1
+    _check(rng.standard_normal((k, 5000)).astype(np.float32), cyclic_csr(rng, n, 2), k, bits, w, mask)
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("as_weight", [False, True])
+def test_what_is_not_finite_gives_what_two_reads_give(value, as_weight):
+    """Against the form with two reads, since the oracle defines nothing here: scales, codes and estimates."""
+    import torch
+    rng = np.random.default_rng(9)
+    n, k, d = 6, 6, 70 * 1024 + 5
+    csr = cyclic_csr(rng, n, 2)
+    bits, w, mask = _draw(rng, n, 4)
+    G = rng.standard_normal((k, d)).astype(np.float32)
+    if as_weight:
+        w[1] = value
+        mask[1] = 1
+    else:
+        G[2, 4321] = value
+    outs = []
+    for mode in (1, 2):
+        ctx = api.Context(n, k, d, scale_mode=api.AGC_SCALE_L2)
+        ctx.agc_set_code(*csr)
+        ctx.agc_debug_sketch(mode)
+        codes, scales, ghat = ctx.alloc_outputs(bits)
+        ctx.agc_step(to_device(G), bits, w, mask, 3, 4, codes, scales, ghat)
+        torch.cuda.synchronize()
+        outs.append([c.cpu().numpy() for c in codes] + [scales.cpu().numpy().view(np.uint32), ghat.cpu().numpy()])
+        ctx.close()
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b, equal_nan=a.dtype == np.float32)
+
+
+def test_the_rule_takes_it_and_layers_do_not():
+    """A vector long enough for the rule, ragged end, in a context whose layers are switched on and off."""
+    import torch
+    rng = np.random.default_rng(10)
+    n, k, d = 16, 16, (1 << 20) + 333
+    csr = cyclic_csr(rng, n, 3)
+    bits, w, mask = _draw(rng, n, 4)
+    G_host = rng.standard_normal((k, d)).astype(np.float32)
+    G = to_device(G_host)
+    outs = []
+    for mode in (0, 2):
+        ctx = api.Context(n, k, d, scale_mode=api.AGC_SCALE_L2)
+        ctx.agc_set_code(*csr)
+        ctx.agc_debug_sketch(mode)
+        for layers in (None, [512 * 256, d], None):
+            if layers:
+                ctx.agc_set_layers(np.array(layers, np.int64))
+            elif len(outs) % 3 == 2:
+                ctx.agc_set_layers([])
+            codes, scales, ghat = ctx.alloc_outputs(bits)
+            ghat.fill_(float("nan"))
+            ctx.agc_step(G, bits, w, mask, 3, 4, codes, scales, ghat)
+            torch.cuda.synchronize()
+            outs.append([c.cpu().numpy() for c in codes] + [scales.cpu().numpy().view(np.uint32).ravel(), ghat.cpu().numpy().view(np.uint32)])
+        ctx.close()
+    for a, b in zip(outs[:3], outs[3:]):
+        assert all(np.array_equal(x, y) for x, y in zip(a, b))
+    assert all(np.array_equal(x, y) for x, y in zip(outs[0], outs[2]))
+
+
+def test_the_hook_refuses_other_scales():
+    for kw in (dict(scale_mode=api.AGC_SCALE_MAXABS), dict(scale_mode=api.AGC_SCALE_L2, bucket=256)):
+        ctx = api.Context(2, 2, 4096, **kw)
+        with pytest.raises(api.AgcError):
+            ctx.agc_debug_sketch(1)
+        with pytest.raises(api.AgcError):
+            ctx.agc_debug_sketch(3)
+        ctx.close()
