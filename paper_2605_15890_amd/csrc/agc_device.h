@@ -76,6 +76,7 @@ constexpr int kDppHalfMirror = 0x141;   // l -> 7 - l within 8 lanes: a partner 
 constexpr int kDppRowMirror = 0x140;    // l -> 15 - l within 16 lanes: a partner in the other half
 
 constexpr int kDppQuadReverse = 0x1B;   // quad_perm [3,2,1,0]: l -> l ^ 3
+constexpr int kDppRowRor4 = 0x124;      // rotation of 16 lanes by four
 constexpr int kDppRowRor8 = 0x128;      // rotation of 16 lanes by eight: l -> l ^ 8
 
 template <int CTRL>
@@ -136,6 +137,44 @@ __device__ __forceinline__ double wave_butterfly_add(double v)
     const double r2 = readlane_f64(v, 32), r3 = readlane_f64(v, 48);
     const double a = r0 + r1, b = r2 + r3;
     return a + b;
+}
+
+// Exchanges that keep several workers' values apart in the lanes' low bits.  After the first one a lane goes on with one
+// of two workers (lanes with `second` with b); the sums of every worker are the same pairs as in wave_butterfly_add.
+template <int CTRL>
+__device__ __forceinline__ double exchange_pair(double a, double b, bool second)
+{
+    const double keep = second ? b : a, send = second ? a : b;
+    return keep + dpp_f64<CTRL>(send);
+}
+__device__ __forceinline__ double exchange_quads(double v)  // distances 4 and 8
+{
+    v = v + dpp_f64<kDppQuadReverse>(dpp_f64<kDppHalfMirror>(v));  // l ^ 7 ^ 3
+    return v + dpp_f64<kDppRowRor8>(v);
+}
+__device__ __forceinline__ double exchange_halves(double v)  // distances 16 and 32
+{
+    uint32_t lo = (uint32_t)(uint64_t)__double_as_longlong(v), hi = (uint32_t)((uint64_t)__double_as_longlong(v) >> 32);
+    const auto l16 = __builtin_amdgcn_permlane16_swap(lo, lo, false, false), h16 = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    v = __longlong_as_double((long long)(((uint64_t)h16[0] << 32) | l16[0])) + __longlong_as_double((long long)(((uint64_t)h16[1] << 32) | l16[1]));
+    lo = (uint32_t)(uint64_t)__double_as_longlong(v);
+    hi = (uint32_t)((uint64_t)__double_as_longlong(v) >> 32);
+    const auto l32 = __builtin_amdgcn_permlane32_swap(lo, lo, false, false), h32 = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    return __longlong_as_double((long long)(((uint64_t)h32[0] << 32) | l32[0])) + __longlong_as_double((long long)(((uint64_t)h32[1] << 32) | l32[1]));
+}
+// maxima over the wave of two workers' non-negative floats, the first's in the even lanes of the result, the second's in the
+// odd ones (bit patterns; the maximum does not care for the order, so rotations by 4 and 8 will do)
+__device__ __forceinline__ uint32_t pair_max_nonneg_bits(float a, float b, bool second)
+{
+    const uint32_t keep = __float_as_uint(second ? b : a), send = __float_as_uint(second ? a : b);
+    uint32_t v = max(keep, dpp_u32<kDppQuadSwap1>(send));
+    v = max(v, dpp_u32<kDppQuadSwap2>(v));
+    v = max(v, dpp_u32<kDppRowRor4>(v));
+    v = max(v, dpp_u32<kDppRowRor8>(v));
+    const auto r16 = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = max((uint32_t)r16[0], (uint32_t)r16[1]);
+    const auto r32 = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return max((uint32_t)r32[0], (uint32_t)r32[1]);
 }
 
 // ---------------------------------------------------------------------------------------

@@ -183,12 +183,16 @@ struct EpiQuant {
     uint32_t ctr0;       // m >> 2 of this lane's coordinates
     int nvalid;
     bool wave_ragged;    // wave-uniform: some lane has coordinates >= d
-    uint32_t keep2, keep3;  // second half of the Philox block, for the odd worker of the pair
+    uint32_t keep[4];       // the Philox block of a pair: two words of the even worker, two of the odd one
     float* scales;          // bucket-wise scales: n x nb
     int64_t nb;
     int group_first;        // first worker of the fill that is being staged
     float acc[4];           // fused step: this lane's four coordinates of the estimate
     WorkerQ pend;           // record of the worker that comes next, requested one worker early
+    // bucket-wise scales: the even worker of a pair, or held_i < 0
+    float4 held;
+    WorkerQ held_q;
+    int held_i;
 
     // The workgroup writes out the fill that ends with worker `last`.  Every wave of the
     // workgroup calls this for the same workers in the same order (also a wave whose block lies
@@ -233,6 +237,41 @@ struct EpiQuant {
         }
     }
 
+    // The scales of workers i and i + 1 in this block and the multipliers num / scale, both at once: the even lanes have
+    // the first worker's, the odd lanes the second's, after one exchange, so that the rest of the reduction, the square
+    // root and the division are paid once.  Whole steps, a worker at a time | in pairs, us: Euclidean 64 x 5.4 M 406 | 346,
+    // 32 x 11.7 M 419 | 374, max-abs 345 | 319 and 349 | 333, 16 x 1 M 23.5 | 23.3 (64 x 25.6 M 1469 | 1458: stores among
+    // reads bound that one).  num = L * 2^16 (2^15 for a one-bit worker) comes with the worker's record.
+    __device__ __forceinline__ void block_multipliers(int i, const float4& f0, const float4& f1, float num0, float num1,
+                                                      bool two, float (&scale)[2], float (&inv)[2])
+    {
+        const bool odd = lane & 1;
+        float s;
+        if (BUCKET == 1) {
+            const float a = fmaxf(fmaxf(fabsf(f0.x), fabsf(f0.y)), fmaxf(fabsf(f0.z), fabsf(f0.w)));
+            const float b = fmaxf(fmaxf(fabsf(f1.x), fabsf(f1.y)), fmaxf(fabsf(f1.z), fabsf(f1.w)));
+            s = __uint_as_float(pair_max_nonneg_bits(a, b, odd));
+        } else {
+            // squares are exact in binary64: the fused sums round as the plain ones do
+            const double x0 = f0.x, x1 = f0.y, x2 = f0.z, x3 = f0.w, y0 = f1.x, y1 = f1.y, y2 = f1.z, y3 = f1.w;
+            const double a = fma(x0, x0, x1 * x1) + fma(x2, x2, x3 * x3), b = fma(y0, y0, y1 * y1) + fma(y2, y2, y3 * y3);
+            double v = exchange_pair<kDppQuadSwap1>(a, b, odd);
+            v = v + dpp_f64<kDppQuadSwap2>(v);
+            s = (float)sqrt(exchange_halves(exchange_quads(v)));
+        }
+        // the block's scales wait in LDS next to the codes ([worker][block of the workgroup]) and
+        // leave with the last flush: 4-byte stores scattered over n rows cost far more than their bytes
+        if (lane < (two ? 2 : 1)) stage_scales[(i + lane) * kBlocks + blk] = s;
+        float q = (odd ? num1 : num0) / s;       // correctly rounded binary32 division
+        q = q <= 3.402823466e+38f ? q : 0.0f;    // scale == 0 gives +inf and ends here too
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            scale[t] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(s), t));
+            inv[t] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(q), t));
+        }
+    }
+
+    // the same for one worker
     __device__ __forceinline__ float block_multiplier(int i, const float4& f, float num, float& scale)
     {
         if (BUCKET == 1) {
@@ -244,12 +283,9 @@ struct EpiQuant {
             const double s23 = x2 * x2 + x3 * x3;
             scale = (float)sqrt(wave_butterfly_add(s01 + s23));
         }
-        // the block's scale waits in LDS next to the codes ([worker][block of the workgroup]) and
-        // leaves with the last flush: 4-byte stores scattered over n rows cost far more than their bytes
         if (lane == 0) stage_scales[i * kBlocks + blk] = scale;
-        // num = L * 2^16 (2^15 for a one-bit worker) comes with the worker's record
-        const float q = num / scale;  // correctly rounded binary32 division
-        return q <= 3.402823466e+38f ? q : 0.0f;  // scale == 0 gives +inf and ends here too
+        const float q = num / scale;
+        return q <= 3.402823466e+38f ? q : 0.0f;
     }
 
     // four rounding decisions; only the grid position differs between the regular grid
@@ -300,35 +336,58 @@ struct EpiQuant {
     template <bool EVEN>
     __device__ __forceinline__ void worker(int i, const float4& f)
     {
-        uint32_t wa, wb;
-        if (EVEN) {
-            uint32_t o[4];
-            philox4x32_10(ctr0, (uint32_t)i >> 1, step_lo, step_hi, key0, key1, o);
-            wa = o[0];
-            wb = o[1];
-            keep2 = o[2];
-            keep3 = o[3];
+        if (EVEN) draw(i);
+        if constexpr (BUCKET == 0) {
+            finish(i, f, EVEN ? keep[0] : keep[2], EVEN ? keep[1] : keep[3]);
         } else {
-            wa = keep2;
-            wb = keep3;
+            if (EVEN) hold(i, f);
+            else pair(i - 1, held, f, true);
+        }
+    }
+
+    // the worker's parity known only at run time (window driver); workers still come in
+    // ascending order, so an odd worker finds the second half of its pair's Philox block.  One worker at a time with
+    // bucket-wise scales too: pairs double the code at every ring position (W = 4, 32 workers x 262 144, Euclidean
+    // 27.8 us, in pairs 29.1, in pairs with the two workers in a loop 30.5)
+    __device__ __forceinline__ void worker_any(int i, const float4& f)
+    {
+        uint32_t wa = keep[2], wb = keep[3];
+        if ((i & 1) == 0) {  // wave-uniform
+            draw(i);
+            wa = keep[0];
+            wb = keep[1];
         }
         finish(i, f, wa, wb);
     }
 
-    // the worker's parity known only at run time (window driver); workers still come in
-    // ascending order, so an odd worker finds the second half of its pair's Philox block
-    __device__ __forceinline__ void worker_any(int i, const float4& f)
+    __device__ __forceinline__ void draw(int i)
     {
-        uint32_t wa = keep2, wb = keep3;
-        if ((i & 1) == 0) {  // wave-uniform
-            uint32_t o[4];
-            philox4x32_10(ctr0, (uint32_t)i >> 1, step_lo, step_hi, key0, key1, o);
-            wa = o[0];
-            wb = o[1];
-            keep2 = o[2];
-            keep3 = o[3];
-        }
-        finish(i, f, wa, wb);
+        philox4x32_10(ctr0, (uint32_t)i >> 1, step_lo, step_hi, key0, key1, keep);
+    }
+
+    // bucket-wise scales: the first worker of a pair waits for the second
+    __device__ __forceinline__ void hold(int i, const float4& f)
+    {
+        held = f;
+        held_q = pend;
+        held_i = i;
+        pend = load_uniform(wq + (i + 1 < n ? i + 1 : i));
+    }
+    __device__ __forceinline__ void pair(int i, const float4& f0, const float4& f1, bool two)
+    {
+        const WorkerQ q0 = held_q, q1 = pend;
+        held_i = -1;
+        pend = load_uniform(wq + (i + 2 < n ? i + 2 : n - 1));
+        float scale[2], inv[2];
+        block_multipliers(i, f0, f1, q0.inv16, q1.inv16, two, scale, inv);
+        emit(i, f0, q0, inv[0], scale[0], keep[0], keep[1]);
+        if (two) emit(i + 1, f1, q1, inv[1], scale[1], keep[2], keep[3]);
+    }
+    // after the last worker: one that is still waiting for another
+    __device__ __forceinline__ void finish_pairs()
+    {
+        if constexpr (BUCKET != 0)
+            if (held_i >= 0) pair(held_i, held, held, false);
     }
 
     __device__ __forceinline__ void finish(int i, const float4& f, uint32_t wa, uint32_t wb)
@@ -337,10 +396,15 @@ struct EpiQuant {
         // was requested while the previous one was quantized
         const WorkerQ q = pend;
         pend = load_uniform(wq + (i + 1 < n ? i + 1 : i));
-        const int b = (int)q.bits;
-        uint32_t c[4], lev[4];
         float scale = 0.f;
         const float inv = BUCKET == 0 ? q.inv16 : block_multiplier(i, f, q.inv16, scale);
+        emit(i, f, q, inv, scale, wa, wb);
+    }
+
+    __device__ __forceinline__ void emit(int i, const float4& f, const WorkerQ& q, float inv, float scale, uint32_t wa, uint32_t wb)
+    {
+        const int b = (int)q.bits;
+        uint32_t c[4], lev[4];
         codes4(i, f, inv, b, wa, wb, c, lev);
         if constexpr (FUSE && !PARTS) {
             if (q.arrived) {  // wave-uniform
@@ -483,10 +547,11 @@ __global__ __launch_bounds__(kQuantThreads) __attribute__((amdgpu_waves_per_eu(S
     EpiQuant<BUCKET, FUSE, MULTI, PARTS> epi{wq, a.key0, a.key1, a.step_lo, a.step_hi, lds_stage, stage_scales, lane, wave,
                                PARTS ? 0 : wave, a.n, wg,
                                groups_left >= 2 * kBlocks ? 2 * kBlocks : (int)groups_left, block, (uint32_t)((base + 4 * lane) >> 2),
-                               lc.nvalid, lc.wave_ragged, 0u, 0u, a.scales, a.nb, 0, {0.f, 0.f, 0.f, 0.f},
-                               load_uniform(wq + (i0 < a.n ? i0 : 0))};
+                               lc.nvalid, lc.wave_ragged, {0u, 0u, 0u, 0u}, a.scales, a.nb, 0, {0.f, 0.f, 0.f, 0.f},
+                               load_uniform(wq + (i0 < a.n ? i0 : 0)), make_float4(0.f, 0.f, 0.f, 0.f), WorkerQ{}, -1};
     if constexpr (PARTS) {  // every workgroup has its block
         encode_block_part<S>(G + base, a.ldg, a.k, CsrView{row_ptr, col, val, a.win}, lc, i0, i1, epi);
+        epi.finish_pairs();
         if constexpr (FUSE) {
             __syncthreads();
             const float g = staged_estimate<BUCKET>(wq, lds_stage, stage_scales, a.n);
@@ -501,6 +566,7 @@ __global__ __launch_bounds__(kQuantThreads) __attribute__((amdgpu_waves_per_eu(S
         return;
     }
     encode_block<S>(G + base, a.ldg, a.n, a.k, CsrView{row_ptr, col, val, a.win}, lc, epi);
+    epi.finish_pairs();
     if constexpr (!MULTI) epi.flush_fill(a.n - 1);  // the one fill: all workers, written out after the loop
     if constexpr (FUSE) {
         float* dst = a.ghat + base + 4 * lane;

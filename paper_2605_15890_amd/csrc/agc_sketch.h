@@ -36,24 +36,9 @@ struct SketchArgs {
 // The norm's exchange-add over the 64 lanes (wave_butterfly_add) for four workers at once: after the first exchange a
 // lane goes on with one of two workers only, after the second with one of four, so that the later ones are shared.  Every
 // worker's sums are the same pairs as alone.
-template <int CTRL>
-__device__ __forceinline__ double exchange_pair(double a, double b, bool second)  // lanes with `second` go on with b
-{
-    const double keep = second ? b : a, send = second ? a : b;
-    return keep + dpp_f64<CTRL>(send);
-}
 __device__ __forceinline__ double sum_rows_of_four(double v)  // lane l: worker l & 3, sum of its quad -> of the wave
 {
-    v = v + dpp_f64<kDppQuadReverse>(dpp_f64<kDppHalfMirror>(v));  // l ^ 7 ^ 3
-    v = v + dpp_f64<kDppRowRor8>(v);
-    uint32_t lo = (uint32_t)(uint64_t)__double_as_longlong(v), hi = (uint32_t)((uint64_t)__double_as_longlong(v) >> 32);
-    // rows of sixteen lanes 0 and 1, 2 and 3; then the halves of the wave
-    const auto l16 = __builtin_amdgcn_permlane16_swap(lo, lo, false, false), h16 = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-    v = __longlong_as_double((long long)(((uint64_t)h16[0] << 32) | l16[0])) + __longlong_as_double((long long)(((uint64_t)h16[1] << 32) | l16[1]));
-    lo = (uint32_t)(uint64_t)__double_as_longlong(v);
-    hi = (uint32_t)((uint64_t)__double_as_longlong(v) >> 32);
-    const auto l32 = __builtin_amdgcn_permlane32_swap(lo, lo, false, false), h32 = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-    return __longlong_as_double((long long)(((uint64_t)h32[0] << 32) | l32[0])) + __longlong_as_double((long long)(((uint64_t)h32[1] << 32) | l32[1]));
+    return exchange_halves(exchange_quads(v));
 }
 
 struct EpiSketch {
