@@ -94,7 +94,10 @@ typedef struct {
 /* Creates a context for n workers, k partitions, d coordinates on the current device and
  * allocates its workspace (scale partials: 4 bytes * 256 * n for the max-abs scale, whatever d is;
  * 8 bytes * n * ceil(d/1024) for the Euclidean one; none with bucket-wise scales; a few n-entry
- * tables).
+ * tables).  With the Euclidean scale of a long vector it also takes signs and records for one read of G
+ * instead of two: for every 256 coordinates 1 KB per 32 workers and 8 bytes for each of up to 32 * n, at most 1151,
+ * records (0.97 GB at 64 x 25.6 M), only beside a G of at most half the device's memory and within an eighth of
+ * what is free; without it two reads are made, with the same results.
  * opts may be NULL (AGC_SCALE_MAXABS, no 1-bit).  Limits: 1 <= n <= AGC_MAX_WORKERS,
  * 1 <= k <= 65536, 1 <= d <= 2^33. */
 agc_status agc_create(agc_ctx **out, int n_workers, int k_parts, int64_t d, const agc_opts *opts);
@@ -122,7 +125,7 @@ agc_status agc_set_code(agc_ctx *ctx, const int32_t *row_ptr, const int32_t *col
  * weight (float)(((double)w_i * scale_il) / L_i); draws and payload layout do not change.  With
  * layers set, scales_dev of the per-step calls holds n x n_layers floats, [worker][layer]
  * (agc_scales_per_worker), and agc_encode_quantize, agc_decode, agc_decode2 and agc_step (both
- * forms) work on them; the worker side still reads G twice.
+ * forms) work on them; the worker side reads G twice.
  *   layer_end  host, n_layers ends, strictly ascending, all but the last multiples of 256 (a
  *              256-coordinate block lies in one layer), the last equal to d
  * 1 <= n_layers <= AGC_MAX_LAYERS; n_layers == 0 returns to one scale per vector.  Needs a context

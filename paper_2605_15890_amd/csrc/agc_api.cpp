@@ -301,8 +301,12 @@ agc_status agc_create(agc_ctx** out, int n, int k, int64_t d, const agc_opts* op
         return fail(nullptr, e == hipErrorOutOfMemory ? AGC_ENOMEM : AGC_EHIP,
                     std::string("workspace allocation: ") + hipGetErrorString(e));
     }
-    if (!o.bucket && o.scale_mode == AGC_SCALE_L2 && agc::use_sketch(d, k, n, false, agc::sketch_cap(n)))
-        (void)alloc_sketch(c);  // some widths are few enough levels: two bits each
+    if (!o.bucket && o.scale_mode == AGC_SCALE_L2 && agc::use_sketch(d, k, n, false, agc::sketch_cap(n))) {
+        // some widths are few enough levels: two bits each
+        size_t free_bytes = 0, total_bytes = 0;
+        if (hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess) (void)hipGetLastError();
+        else if (agc::sketch_fits(n, k, d, free_bytes, total_bytes)) (void)alloc_sketch(c);
+    }
     *out = c;
     return AGC_OK;
 }

@@ -2,6 +2,7 @@
 // compiled and checked without a GPU.
 #pragma once
 
+#include <stddef.h>
 #include <stdint.h>
 
 namespace agc {
@@ -121,6 +122,21 @@ inline bool use_sketch(int64_t d, int k, double levels, bool gather_parts, int c
     const double m = 1e-6 * (double)d, records = sketch_records(d, levels);
     if (gather_parts || 256.0 * records > 0.75 * cap * (double)d) return false;
     return 0.5 * k * m - 10.0 - 1.9 * m - 7e-6 * records > 2.0;
+}
+
+// Bytes of the sketch's two large arrays, signs and records: 0.97 GB at 64 workers x 25.6 M, 15 % of G there and up to half of
+// G for four workers.
+inline int64_t sketch_bytes(int n, int64_t d)
+{
+    return (d + 255) / 256 * ((int64_t)((n + 31) / 32) * 1024 + 8 * (int64_t)sketch_cap(n));
+}
+// A context takes them only beside a G that leaves half of the card to the rest of the program (the context may be made
+// first), and no more than an eighth of what is free: a program that fills the card keeps the form with two reads and the
+// memory that it had.
+inline bool sketch_fits(int n, int k, int64_t d, size_t free_bytes, size_t total_bytes)
+{
+    const double bytes = (double)sketch_bytes(n, d);
+    return bytes + 4.0 * k * (double)d <= 0.5 * (double)total_bytes && bytes <= 0.125 * (double)free_bytes;
 }
 
 // Workgroups of the decode pass that a compute unit holds: six, which was measured to be best with one scale per

@@ -15,6 +15,11 @@ extern "C" int one_read(int64_t d, int n, int k, double levels, int gather_parts
 {
     return agc::use_sketch(d, k, levels, gather_parts != 0, agc::sketch_cap(n));
 }
+extern "C" int fits(int n, int k, int64_t d, size_t free_bytes, size_t total_bytes)
+{
+    return agc::sketch_fits(n, k, d, free_bytes, total_bytes);
+}
+extern "C" int64_t bytes(int n, int64_t d) { return agc::sketch_bytes(n, d); }
 extern "C" int cap(int n) { return agc::sketch_cap(n); }
 """
 
@@ -30,6 +35,8 @@ def rules(tmp_path_factory):
                     "-o", str(tmp / "librules.so")], check=True)
     lib = ctypes.CDLL(str(tmp / "librules.so"))
     lib.one_read.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_double, ctypes.c_int]
+    lib.fits.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_size_t, ctypes.c_size_t]
+    lib.bytes.argtypes, lib.bytes.restype = [ctypes.c_int, ctypes.c_int64], ctypes.c_int64
     return lib
 
 
@@ -54,3 +61,16 @@ def test_ends_of_the_ranges(rules):
                 for level in (1, 32767):
                     one = rules.one_read(d, n, k, float(n * level), 0)
                     assert not (d == 1 and one)
+
+
+def test_a_program_that_fills_the_card_keeps_its_memory(rules):
+    """A context may be made before the gradients: G counts whether it is there or not."""
+    total = 288 * 10 ** 9
+    need = rules.bytes(64, 25_600_000)
+    assert need == 100_000 * (2048 + 8 * rules.cap(64))
+    assert rules.fits(64, 64, 25_600_000, total, total) and rules.fits(64, 64, 25_600_000, 8 * need, total)
+    assert not rules.fits(64, 64, 25_600_000, 8 * need - 8, total)
+    assert rules.fits(64, 64, 480_000_000, total, total) and not rules.fits(64, 64, 1_000_000_000, total, total)
+    for n, k, d in ((1, 1, 2 ** 33), (256, 65536, 2 ** 33), (256, 4, 2 ** 33)):
+        assert not rules.fits(n, k, d, total, total)
+    assert not rules.fits(1, 1, 1, 0, 0)
