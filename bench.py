@@ -161,8 +161,9 @@ def tag_of(cfg, code, scale, bucket, two_pass, layers=0):
             + ("_two_pass" if two_pass else ""))
 
 
-def alg_bytes_of(n, k, d, bits, masks, bucket, two_pass):
-    """Algorithmic bytes per launch of each kernel: what the method must move."""
+def alg_bytes_of(n, k, d, bits, masks, bucket, two_pass, one_read=False):
+    """Algorithmic bytes per launch of each kernel: what the method must move.  one_read: the Euclidean scale of
+    the whole vector, whose worker side can do with one read of G."""
     nb = (d + 255) // 256 if bucket else 0
     sum_b = float(np.sum(bits))
     arrived_b = float(np.mean([np.sum(bits[m.astype(bool)]) for m in masks]))
@@ -170,7 +171,7 @@ def alg_bytes_of(n, k, d, bits, masks, bucket, two_pass):
     return {
         "scale_pass": 0.0 if bucket else 4.0 * k * d,
         "scale_finalize": 0.0,
-        "quantize": 4.0 * k * d + d * sum_b / 8.0 + 4.0 * n * nb + (0.0 if two_pass else 4.0 * d),
+        "quantize": (0.0 if one_read else 4.0 * k * d) + d * sum_b / 8.0 + 4.0 * n * nb + (0.0 if two_pass else 4.0 * d),
         "decode": (d * arrived_b / 8.0 + 4.0 * d + 4.0 * n_arr * nb) if two_pass else 0.0,
     }
 
@@ -217,7 +218,8 @@ def time_variant(api, I, cfg, G, bufs, p, bits, code, w, scale, bucket, two_pass
     ctx.close()
     del scales
     ms_per_step = (t1 - t0) * 1e3 / K
-    alg = alg_bytes_of(n, k, d, bits, masks[W:W + K], bucket, two_pass)
+    alg = alg_bytes_of(n, k, d, bits, masks[W:W + K], bucket, two_pass,
+                       one_read=scale == "l2" and not bucket and not layers)
     kernels = {}
     for name, (ms, cnt) in prof.items():
         if cnt == 0:
