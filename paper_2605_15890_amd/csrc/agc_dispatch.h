@@ -81,11 +81,11 @@ inline bool use_parts_of(int64_t d, int n, int k, int nnz, int band, bool norm, 
 }
 
 // The quantize pass of long vectors: the group of four blocks that its first workgroup takes; the others follow
-// upwards and wrap around.  With a general code the block that the vector ends in masks every row that it gathers and
-// takes longer than the others, and in any code its codes leave in pieces that do not fill their lines: it is not the last
-// to start.  With no more groups than the chip holds at once (four workgroups on each of 256 compute units) all start
-// together and the order is left alone.  Vectors of whole blocks take the same time from any group (32 x 11 700 224
-// 521 | 522 us), so nothing of G that the scale pass left in the memory-side cache is gained by the order.
+// upwards and wrap around.  The codes of the block that the vector ends in leave in pieces that do not fill their lines and
+// are masked lane by lane, so it takes longer than the others: it is not the last to start.  With no more groups than
+// the chip holds at once (four workgroups on each of 256 compute units) all start together and the order is left alone.
+// Vectors of whole blocks take the same time from any group (32 x 11 700 224 521 | 522 us), so nothing of G that the
+// scale pass left in the memory-side cache is gained by the order.
 constexpr int64_t kChipGroups = 4 * 256;
 constexpr unsigned kEarlyGroups = 64;
 inline unsigned first_group(int64_t d, unsigned groups)

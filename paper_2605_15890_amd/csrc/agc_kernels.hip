@@ -589,24 +589,68 @@ hipError_t launch_scale_finalize(int n, int scale_mode, const QuantStreams& out,
 // costs records; a higher one costs the whole sketch when the scale falls below it.  With heavy tails (Student's t, three
 // degrees) one block in a sample of 131072 coordinates that holds an extreme value put the plain estimate 40 % too high in
 // about 5 % of the steps of 64 workers; two such blocks are rare.
-constexpr int kSampleParts = 16;  // waves that share the workers of a block: one block's latency is what counts
+constexpr int kSampleWaves = 16;  // waves that share a block: its latency is what counts
 constexpr int kMaxSamples = 512;
+constexpr int kSampleRows = 128;  // rows of a block that 160 KB of LDS have room for
 
-template <int S>
-__global__ __launch_bounds__(kWave * kSampleParts) void k_sketch_sample(const float* __restrict__ G, const int* __restrict__ row_ptr,
+// A worker's combination from rows in LDS, [k][lane]
+__device__ __forceinline__ float4 encode_staged_one(const float4* rows, const CsrView& B, int i, int lane)
+{
+    const int e0 = B.row_ptr[i], e1 = B.row_ptr[i + 1];
+    float4 f = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int e = e0; e < e1; ++e) f = fma4(B.val[e], rows[B.col[e] * kWave + lane], f);
+    return f;
+}
+
+// What bounds it: latency, one block per workgroup and all workgroups resident at once.  S > 0: the register ring.  Other codes
+// with STAGED: all rows of the block are requested at once and wait in LDS, where each wave takes its workers' from; else
+// rows are gathered from memory (more rows than LDS holds).  64 workers x 25.6 M, window of 8: the window driver, whose
+// unrolled code comes cold into the instruction cache, took 20.9 us, with 4 | 8 | 12 rows requested ahead 19.6 | 38.9 |
+// 39.0, staged 11.2;  50 x 5.4 M 19.9 | 8.4;  10 workers of 30 partitions, gathered 8.4, staged 5.9.  The ring of a cyclic band
+// is the faster one: 64 x 1 M 5.6, staged 7.1, 32 x 11.7 M 6.2 and 8.0.  Code entries one a lane instead of scalar loads,
+// a worker ahead: 13.2 for 11.2.
+template <int S, bool STAGED>
+__global__ __launch_bounds__(kWave * kSampleWaves) void k_sketch_sample(const float* __restrict__ G, const int* __restrict__ row_ptr,
                                                                         const int* __restrict__ col, const float* __restrict__ val,
                                                                         ScaleArgs a, int64_t block_step)
 {
+    extern __shared__ __attribute__((aligned(16))) float4 lds_rows[];  // STAGED: [k][64]
     __shared__ double lds_sq[kMaxWorkers];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = threadIdx.x % kWave;
-    const int size = ((a.n + kSampleParts - 1) / kSampleParts + 1) / 2 * 2;
-    const int i0 = wave * size, i1 = i0 + size < a.n ? i0 + size : a.n;
     const int64_t base = (int64_t)blockIdx.x * block_step * kBlockCoords;
     const LaneCoords lc = lane_coords(base, lane, a.d);
+    const CsrView B{row_ptr, col, val, nullptr};
     EpiSumSq epi{lds_sq, lane};
-    encode_block_part<S>(G + base, a.ldg, a.k, CsrView{row_ptr, col, val, a.win}, lc, i0, i1, epi);
-    for (int i = i0 + lane; i < i1; i += kWave) a.part_sq[(int64_t)blockIdx.x * a.n + i] = lds_sq[i];  // of this wave's lane 0
+    if constexpr (S > 0) {
+        const int size = ((a.n + kSampleWaves - 1) / kSampleWaves + 1) / 2 * 2;
+        const int i0 = wave * size, i1 = i0 + size < a.n ? i0 + size : a.n;
+        encode_block_part<S>(G + base, a.ldg, a.k, B, lc, i0, i1, epi);
+        for (int i = i0 + lane; i < i1; i += kWave) a.part_sq[(int64_t)blockIdx.x * a.n + i] = lds_sq[i];  // of this wave's lane 0
+        return;
+    }
+    if constexpr (STAGED) {
+        for (int j0 = wave; j0 < a.k; j0 += 4 * kSampleWaves) {
+            float4 r[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int j = j0 + t * kSampleWaves;
+                r[t] = load_row4<true>(G + base + (int64_t)(j < a.k ? j : a.k - 1) * a.ldg, lc);
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int j = j0 + t * kSampleWaves;
+                if (j < a.k) lds_rows[j * kWave + lane] = r[t];
+            }
+        }
+        __syncthreads();
+    }
+    for (int i = wave; i < a.n; i += kSampleWaves) {
+        const float4 f = STAGED ? encode_staged_one(lds_rows, B, i, lane) : encode_gather_one(G + base, a.ldg, B, i, lc);
+        epi.worker<true>(i, valid_coords(f, lc.nvalid));
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < a.n; i += kWave * kSampleWaves) a.part_sq[(int64_t)blockIdx.x * a.n + i] = lds_sq[i];
 }
 
 struct BitList {
@@ -647,12 +691,12 @@ __global__ __launch_bounds__(kWgThreads) void k_sketch_bounds(int n, BitList in,
     }
 }
 
-template <int S>
+template <int S, bool STAGED>
 static void launch_sketch_sample_s(const float* G, const CodeDev& code, const ScaleArgs& a, int samples, int64_t block_step,
                                    hipStream_t stream)
 {
-    hipLaunchKernelGGL((k_sketch_sample<S>), dim3(samples), dim3(kWave * kSampleParts), 0, stream, G, code.row_ptr, code.col,
-                       code.val, a, block_step);
+    hipLaunchKernelGGL((k_sketch_sample<S, STAGED>), dim3(samples), dim3(kWave * kSampleWaves),
+                       STAGED ? sizeof(float4) * kWave * a.k : 0, stream, G, code.row_ptr, code.col, code.val, a, block_step);
 }
 
 hipError_t launch_sketch_bounds(const float* G, int64_t ldg, int n, int k, int64_t d, const CodeDev& code,
@@ -663,20 +707,18 @@ hipError_t launch_sketch_bounds(const float* G, int64_t ldg, int n, int k, int64
     const int samples = nblocks < 64 ? 1 : nblocks / 64 < kMaxSamples ? (int)(nblocks / 64) : kMaxSamples;
     const int64_t step = nblocks / samples;
     const ScaleArgs a{ldg, n, k, d, 0, nullptr, ws.part_sq, code.win, nullptr, nullptr, nullptr};
-    if (code.band < 0 && !code.win) return hipErrorInvalidValue;
     switch (code.band) {
-        case 1: launch_sketch_sample_s<1>(G, code, a, samples, step, stream); break;
-        case 2: launch_sketch_sample_s<2>(G, code, a, samples, step, stream); break;
-        case 3: launch_sketch_sample_s<3>(G, code, a, samples, step, stream); break;
-        case 4: launch_sketch_sample_s<4>(G, code, a, samples, step, stream); break;
-        case 5: launch_sketch_sample_s<5>(G, code, a, samples, step, stream); break;
-        case 6: launch_sketch_sample_s<6>(G, code, a, samples, step, stream); break;
-        case 7: launch_sketch_sample_s<7>(G, code, a, samples, step, stream); break;
-        case 8: launch_sketch_sample_s<8>(G, code, a, samples, step, stream); break;
-        case -2: launch_sketch_sample_s<-2>(G, code, a, samples, step, stream); break;
-        case -4: launch_sketch_sample_s<-4>(G, code, a, samples, step, stream); break;
-        case -8: launch_sketch_sample_s<-8>(G, code, a, samples, step, stream); break;
-        default: launch_sketch_sample_s<0>(G, code, a, samples, step, stream); break;
+        case 1: launch_sketch_sample_s<1, false>(G, code, a, samples, step, stream); break;
+        case 2: launch_sketch_sample_s<2, false>(G, code, a, samples, step, stream); break;
+        case 3: launch_sketch_sample_s<3, false>(G, code, a, samples, step, stream); break;
+        case 4: launch_sketch_sample_s<4, false>(G, code, a, samples, step, stream); break;
+        case 5: launch_sketch_sample_s<5, false>(G, code, a, samples, step, stream); break;
+        case 6: launch_sketch_sample_s<6, false>(G, code, a, samples, step, stream); break;
+        case 7: launch_sketch_sample_s<7, false>(G, code, a, samples, step, stream); break;
+        case 8: launch_sketch_sample_s<8, false>(G, code, a, samples, step, stream); break;
+        default:
+            if (k <= kSampleRows) launch_sketch_sample_s<0, true>(G, code, a, samples, step, stream);
+            else launch_sketch_sample_s<0, false>(G, code, a, samples, step, stream);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

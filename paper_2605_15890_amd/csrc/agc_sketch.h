@@ -13,7 +13,7 @@
 // The results are those of the two-read form bit for bit, whatever the sample said.
 //
 // Measured, 64 workers x 25.6 M, three bits on average, Euclidean, interval code, whole step 2416 us with two reads (scale pass
-// 984, quantize pass 1420), 1573 with one: sample and bounds 21 + 5, k_sketch 1210-1240, groups and finalize 13,
+// 984, quantize pass 1420), 1565 with one: sample and bounds 11 + 5, k_sketch 1210-1240, groups and finalize 13,
 // k_resolve 310, the quantize pass that finds nothing left 10.
 #pragma once
 

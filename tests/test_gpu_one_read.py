@@ -88,6 +88,15 @@ def test_workers_widths_and_fills(n, most, law):
     _check(G.astype(np.float32), csr, k, bits, w, mask, unfused=n % 3 == 0, graph=n == 33)
 
 
+@pytest.mark.parametrize("kind,n,k,width", [("general", 5, 1, 1), ("general", 5, 17, 17), ("general", 33, 127, 9), ("general", 3, 128, 128),
+                                            ("general", 7, 129, 70), ("interval", 128, 128, 8), ("interval", 140, 150, 4)])
+def test_rows_that_the_sample_holds_and_more(kind, n, k, width):
+    """Up to 128 rows of a sampled block wait in LDS, more are gathered; rows of the code shorter and longer than a wave."""
+    rng = np.random.default_rng([n, k])
+    for d in (300, 64 * 256 + 77):
+        _check(rng.standard_normal((k, d)).astype(np.float32), _code(rng, kind, n, k, width), k, *_draw(rng, n, 4))
+
+
 @pytest.mark.parametrize("where", ["sampled", "elsewhere", "nowhere", "sign", "large", "small"])
 def test_samples_that_mislead(where):
     """70 segments, of which two are sampled, the first and the 36th.  All of the vector's norm in one of them: the bound lies
