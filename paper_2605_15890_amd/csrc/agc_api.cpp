@@ -40,6 +40,7 @@ struct agc_ctx {
     int band = 0;
     bool force_long = false;  // testing hook
     int sketch_mode = 0;      // testing hook: 0 by the rule, 1 wherever the sketch can be made, 2 never
+    bool sketch_last = false; // the last worker-side call made one
     // workspace
     agc::Workspace ws{};
     agc::SketchDev sk{};      // planes is null where the rule never takes it
@@ -568,6 +569,7 @@ agc_status encode_quantize_impl(agc_ctx* c, const float* G, int64_t ldg, const u
     int sum_bits = 0;
     for (int i = 0; i < c->n; ++i) sum_bits += bits[i];
     const agc::SketchDev* sk = use_sketch(c, code, bits) ? &c->sk : nullptr;
+    c->sketch_last = sk != nullptr;
     qs.parts = code.parts && sum_bits <= agc::kPartBits && !sk;
     qs.stage_fills = agc::stage_starts(qs.bits, c->n, qs.parts ? agc::kPartBits : agc::stage_limit(c->n, c->opts.bucket != 0),
                                        qs.stage_start, &qs.stage_bits);
@@ -823,6 +825,25 @@ agc_status agc_debug_sketch(agc_ctx* c, int mode)
         if (e != hipSuccess) return fail(c, AGC_ENOMEM, "workspace of the one-read form");
     }
     c->sketch_mode = mode;
+    return AGC_OK;
+}
+
+agc_status agc_debug_sketch_last(agc_ctx* c, int64_t out[4])
+{
+    if (!c || !out) return fail(nullptr, AGC_EINVAL, "null context or out");
+    for (int t = 0; t < 4; ++t) out[t] = 0;
+    hipError_t e = hipDeviceSynchronize();
+    if (e != hipSuccess) return hip_fail(c, e, "hipDeviceSynchronize");
+    if (!c->sketch_last || !c->sk.planes) return AGC_OK;
+    std::vector<uint32_t> done((size_t)c->ws.nseg);
+    uint32_t state = 0;
+    e = hipMemcpy(done.data(), c->sk.done, done.size() * sizeof(uint32_t), hipMemcpyDeviceToHost);
+    if (e == hipSuccess) e = hipMemcpy(&state, c->sk.state, sizeof state, hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return hip_fail(c, e, "reading the sketch's counters");
+    out[0] = 1;
+    out[1] = c->ws.nseg;
+    for (uint32_t v : done) out[2] += v == 0u;
+    out[3] = state != 0u;
     return AGC_OK;
 }
 

@@ -194,6 +194,27 @@ def test_the_rule_takes_it_and_layers_do_not():
     assert all(np.array_equal(x, y) for x, y in zip(outs[0], outs[2]))
 
 
+def test_the_hook_tells_the_form():
+    rng = np.random.default_rng(11)
+    n, d = 5, 40 * 1024 + 9
+    bits, w, mask = np.full(n, 2, np.uint8), np.ones(n, np.float32), np.ones(n, np.uint8)
+    G = rng.standard_normal((n, d)).astype(np.float32)
+    G[:, 7 * 1024: 8 * 1024] *= 1e4   # four of the 161 blocks hold the norm: more records than there is room for
+    ctx = api.Context(n, n, d, scale_mode=api.AGC_SCALE_L2)
+    ctx.agc_set_code(*cyclic_csr(rng, n, 2))
+    codes, scales, ghat = ctx.alloc_outputs(bits)
+    none = dict(one_read=False, groups=0, left=0, bound_failed=False)
+    assert ctx.agc_debug_sketch_last() == none
+    ctx.agc_debug_sketch(1)
+    ctx.agc_step(to_device(G), bits, w, mask, 1, 2, codes, scales, ghat)
+    last = ctx.agc_debug_sketch_last()
+    assert last["one_read"] and last["groups"] == 41 and not last["bound_failed"] and last["left"] == 1
+    ctx.agc_debug_sketch(2)
+    ctx.agc_step(to_device(G), bits, w, mask, 1, 2, codes, scales, ghat)
+    assert ctx.agc_debug_sketch_last() == none
+    ctx.close()
+
+
 def test_the_hook_refuses_other_scales():
     for kw in (dict(scale_mode=api.AGC_SCALE_MAXABS), dict(scale_mode=api.AGC_SCALE_L2, bucket=256)):
         ctx = api.Context(2, 2, 4096, **kw)
