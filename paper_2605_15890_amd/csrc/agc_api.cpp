@@ -593,7 +593,7 @@ agc_status encode_quantize_impl(agc_ctx* c, const float* G, int64_t ldg, const u
         if ((st = t.begin()) != AGC_OK) return st;
         c->slots_dirty = maxabs;
         if (sk) {
-            e = agc::launch_sketch_bounds(G, ldg, c->n, c->k, c->d, code, c->ws, *sk, qs, stream);
+            e = agc::launch_sketch_bounds(G, ldg, c->n, c->k, c->d, code, c->ws, *sk, qs, seed, step, stream);
             if (e == hipSuccess) e = agc::launch_sketch(G, ldg, c->n, c->k, c->d, code, c->ws, *sk, seed, step, stream);
         } else {
             e = agc::launch_scale_pass(G, ldg, c->n, c->k, c->d, code, c->opts.scale_mode, c->ws, stream);

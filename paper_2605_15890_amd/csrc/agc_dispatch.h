@@ -139,6 +139,34 @@ inline bool sketch_fits(int n, int k, int64_t d, size_t free_bytes, size_t total
     return bytes + 4.0 * k * (double)d <= 0.5 * (double)total_bytes && bytes <= 0.125 * (double)free_bytes;
 }
 
+// The blocks that the bounds of the scales are estimated from: one of each of `samples` runs of equal length (up to one
+// block), drawn anew for every step.  At a fixed distance, up to 8.4 M coordinates a power of two, the sample saw the same columns of
+// every row of a gradient made of matrices, in every step: with the first 256 of 4096, 8192 or 16 384 columns 20 times as
+// large the bounds did not hold, at a twentieth they lay so low that no block had room for its records, and a step took 9-15 and
+// 10-34 % longer than with two reads (50 workers x 5.4 M, 64 x 5.4 M, 32 x 2 M, 64 x 1 M).
+struct SampleRuns {
+    int64_t length, longer;  // blocks of a run; the first `longer` runs have one more
+    uint64_t salt;
+};
+// SplitMix64's output function (Steele, Lea, Flood 2014)
+constexpr uint64_t mix64(uint64_t x)
+{
+    x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
+    x = (x ^ (x >> 27)) * 0x94D049BB133111EBull;
+    return x ^ (x >> 31);
+}
+inline SampleRuns sample_runs(int64_t nblocks, int samples, uint64_t seed, uint64_t step)
+{
+    return SampleRuns{nblocks / samples, nblocks % samples,
+                      mix64(seed + mix64(step + 0x9E3779B97F4A7C15ull))};
+}
+constexpr int64_t sample_block(const SampleRuns& r, int64_t e)  // device too
+{
+    const int64_t first = e * r.length + (e < r.longer ? e : r.longer);
+    const uint64_t length = (uint64_t)(r.length + (e < r.longer ? 1 : 0));  // < 2^32
+    return first + (int64_t)(((mix64(r.salt + 0x9E3779B97F4A7C15ull * (uint64_t)e) >> 32) * length) >> 32);
+}
+
 // Workgroups of the decode pass that a compute unit holds: six, which was measured to be best with one scale per
 // vector (walking over the tiles: five 0.162, four 0.166 against 0.148 ms for 64 workers x 25.6 M), or as many as
 // 160 KB of LDS has room for beside the weights of bucket- and layer-wise scales: five, four with two tracks and

@@ -242,7 +242,8 @@ hipError_t launch_scale_finalize(int n, int scale_mode, const QuantStreams& out,
 // One read of G (Euclidean scale of the whole vector): bounds from a sample, then the sketch; it leaves the partial results
 // of the scales like the scale pass.  launch_scale_finalize with the same sk checks the bounds.
 hipError_t launch_sketch_bounds(const float* G, int64_t ldg, int n, int k, int64_t d, const CodeDev& code,
-                                const Workspace& ws, const SketchDev& sk, const QuantStreams& out, hipStream_t stream);
+                                const Workspace& ws, const SketchDev& sk, const QuantStreams& out, uint64_t seed,
+                                uint64_t step, hipStream_t stream);
 hipError_t launch_sketch(const float* G, int64_t ldg, int n, int k, int64_t d, const CodeDev& code, const Workspace& ws,
                          const SketchDev& sk, uint64_t seed, uint64_t step, hipStream_t stream);
 // codes (and with ghat the estimate) of the sketch; launch_quantize with sk.done makes those of the groups it leaves

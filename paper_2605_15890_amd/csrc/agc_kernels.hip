@@ -612,13 +612,13 @@ __device__ __forceinline__ float4 encode_staged_one(const float4* rows, const Cs
 template <int S, bool STAGED>
 __global__ __launch_bounds__(kWave * kSampleWaves) void k_sketch_sample(const float* __restrict__ G, const int* __restrict__ row_ptr,
                                                                         const int* __restrict__ col, const float* __restrict__ val,
-                                                                        ScaleArgs a, int64_t block_step)
+                                                                        ScaleArgs a, SampleRuns runs)
 {
     extern __shared__ __attribute__((aligned(16))) float4 lds_rows[];  // STAGED: [k][64]
     __shared__ double lds_sq[kMaxWorkers];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = threadIdx.x % kWave;
-    const int64_t base = (int64_t)blockIdx.x * block_step * kBlockCoords;
+    const int64_t base = sample_block(runs, blockIdx.x) * kBlockCoords;
     const LaneCoords lc = lane_coords(base, lane, a.d);
     const CsrView B{row_ptr, col, val, nullptr};
     EpiSumSq epi{lds_sq, lane};
@@ -692,33 +692,34 @@ __global__ __launch_bounds__(kWgThreads) void k_sketch_bounds(int n, BitList in,
 }
 
 template <int S, bool STAGED>
-static void launch_sketch_sample_s(const float* G, const CodeDev& code, const ScaleArgs& a, int samples, int64_t block_step,
+static void launch_sketch_sample_s(const float* G, const CodeDev& code, const ScaleArgs& a, int samples, const SampleRuns& runs,
                                    hipStream_t stream)
 {
     hipLaunchKernelGGL((k_sketch_sample<S, STAGED>), dim3(samples), dim3(kWave * kSampleWaves),
-                       STAGED ? sizeof(float4) * kWave * a.k : 0, stream, G, code.row_ptr, code.col, code.val, a, block_step);
+                       STAGED ? sizeof(float4) * kWave * a.k : 0, stream, G, code.row_ptr, code.col, code.val, a, runs);
 }
 
 hipError_t launch_sketch_bounds(const float* G, int64_t ldg, int n, int k, int64_t d, const CodeDev& code,
-                                const Workspace& ws, const SketchDev& sk, const QuantStreams& out, hipStream_t stream)
+                                const Workspace& ws, const SketchDev& sk, const QuantStreams& out, uint64_t seed,
+                                uint64_t step, hipStream_t stream)
 {
     // one block in 64; the partial sums' array is their scratch, which has a row for every four blocks
     const int64_t nblocks = (d + kBlockCoords - 1) / kBlockCoords;
     const int samples = nblocks < 64 ? 1 : nblocks / 64 < kMaxSamples ? (int)(nblocks / 64) : kMaxSamples;
-    const int64_t step = nblocks / samples;
+    const SampleRuns runs = sample_runs(nblocks, samples, seed, step);
     const ScaleArgs a{ldg, n, k, d, 0, nullptr, ws.part_sq, code.win, nullptr, nullptr, nullptr};
     switch (code.band) {
-        case 1: launch_sketch_sample_s<1, false>(G, code, a, samples, step, stream); break;
-        case 2: launch_sketch_sample_s<2, false>(G, code, a, samples, step, stream); break;
-        case 3: launch_sketch_sample_s<3, false>(G, code, a, samples, step, stream); break;
-        case 4: launch_sketch_sample_s<4, false>(G, code, a, samples, step, stream); break;
-        case 5: launch_sketch_sample_s<5, false>(G, code, a, samples, step, stream); break;
-        case 6: launch_sketch_sample_s<6, false>(G, code, a, samples, step, stream); break;
-        case 7: launch_sketch_sample_s<7, false>(G, code, a, samples, step, stream); break;
-        case 8: launch_sketch_sample_s<8, false>(G, code, a, samples, step, stream); break;
+        case 1: launch_sketch_sample_s<1, false>(G, code, a, samples, runs, stream); break;
+        case 2: launch_sketch_sample_s<2, false>(G, code, a, samples, runs, stream); break;
+        case 3: launch_sketch_sample_s<3, false>(G, code, a, samples, runs, stream); break;
+        case 4: launch_sketch_sample_s<4, false>(G, code, a, samples, runs, stream); break;
+        case 5: launch_sketch_sample_s<5, false>(G, code, a, samples, runs, stream); break;
+        case 6: launch_sketch_sample_s<6, false>(G, code, a, samples, runs, stream); break;
+        case 7: launch_sketch_sample_s<7, false>(G, code, a, samples, runs, stream); break;
+        case 8: launch_sketch_sample_s<8, false>(G, code, a, samples, runs, stream); break;
         default:
-            if (k <= kSampleRows) launch_sketch_sample_s<0, true>(G, code, a, samples, step, stream);
-            else launch_sketch_sample_s<0, false>(G, code, a, samples, step, stream);
+            if (k <= kSampleRows) launch_sketch_sample_s<0, true>(G, code, a, samples, runs, stream);
+            else launch_sketch_sample_s<0, false>(G, code, a, samples, runs, stream);
     }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

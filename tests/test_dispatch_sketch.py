@@ -20,6 +20,10 @@ extern "C" int fits(int n, int k, int64_t d, size_t free_bytes, size_t total_byt
     return agc::sketch_fits(n, k, d, free_bytes, total_bytes);
 }
 extern "C" int64_t bytes(int n, int64_t d) { return agc::sketch_bytes(n, d); }
+extern "C" int64_t block(int64_t nblocks, int samples, uint64_t seed, uint64_t step, int64_t e)
+{
+    return agc::sample_block(agc::sample_runs(nblocks, samples, seed, step), e);
+}
 extern "C" int cap(int n) { return agc::sketch_cap(n); }
 """
 
@@ -37,6 +41,8 @@ def rules(tmp_path_factory):
     lib.one_read.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_double, ctypes.c_int]
     lib.fits.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_size_t, ctypes.c_size_t]
     lib.bytes.argtypes, lib.bytes.restype = [ctypes.c_int, ctypes.c_int64], ctypes.c_int64
+    lib.block.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_int64]
+    lib.block.restype = ctypes.c_int64
     return lib
 
 
@@ -74,3 +80,26 @@ def test_a_program_that_fills_the_card_keeps_its_memory(rules):
     for n, k, d in ((1, 1, 2 ** 33), (256, 65536, 2 ** 33), (256, 4, 2 ** 33)):
         assert not rules.fits(n, k, d, total, total)
     assert not rules.fits(1, 1, 1, 0, 0)
+
+
+@pytest.mark.parametrize("nblocks,samples", [(1, 1), (63, 1), (4096, 64), (21094, 329), (32768, 512), (100_000, 512), (2 ** 25, 512)])
+def test_samples_spread_over_the_vector_and_over_the_columns_of_matrices(rules, nblocks, samples):
+    """One block of each of equal runs, other ones with every seed and step; with rows of 16 to 64 blocks all columns are met
+    (for each of them the number of samples in 40 steps is a sum of nearly independent draws: eight standard deviations)."""
+    draws = [[rules.block(nblocks, samples, 2 ** 64 - 1 - t % 3, t, e) for e in range(samples)] for t in range(40)]
+    for blocks in draws:
+        at = 0
+        for e, b in enumerate(blocks):
+            length = nblocks // samples + (e < nblocks % samples)
+            assert at <= b < at + length
+            at += length
+        assert at == nblocks
+    if samples >= 64:
+        assert len({tuple(b) for b in draws}) == 40
+        for width in (16, 32, 64):
+            count = [0] * width
+            for blocks in draws:
+                for b in blocks:
+                    count[b % width] += 1
+            mean = 40 * samples / width
+            assert all(abs(c - mean) < 8 * mean ** 0.5 for c in count)

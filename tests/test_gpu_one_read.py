@@ -194,6 +194,27 @@ def test_the_rule_takes_it_and_layers_do_not():
     assert all(np.array_equal(x, y) for x, y in zip(outs[0], outs[2]))
 
 
+@pytest.mark.parametrize("width", [4096, 16384])
+@pytest.mark.parametrize("first,width_of_codes", [(20.0, 2), (0.05, 4)])
+def test_gradients_made_of_matrices_do_not_mislead_the_sample(width, first, width_of_codes):
+    """The first 256 columns of every row much larger or smaller than the others: neither fails the bounds nor puts them so low
+    that blocks overflow."""
+    rng = np.random.default_rng(12)
+    n, d = 12, 1 << 20
+    bits, w, mask = np.full(n, width_of_codes, np.uint8), np.ones(n, np.float32), np.ones(n, np.uint8)
+    G_host = rng.standard_normal((n, d), dtype=np.float32).reshape(n, -1, width)
+    G_host[:, :, :256] *= np.float32(first)
+    G = to_device(G_host.reshape(n, d))
+    ctx = api.Context(n, n, d, scale_mode=api.AGC_SCALE_L2)
+    ctx.agc_set_code(*cyclic_csr(rng, n, 2))
+    ctx.agc_debug_sketch(1)
+    codes, scales, ghat = ctx.alloc_outputs(bits)
+    for step in range(6):
+        ctx.agc_step(G, bits, w, mask, 2, step, codes, scales, ghat)
+        assert ctx.agc_debug_sketch_last() == dict(one_read=True, groups=1024, left=0, bound_failed=False), step
+    ctx.close()
+
+
 def test_the_hook_tells_the_form():
     rng = np.random.default_rng(11)
     n, d = 5, 40 * 1024 + 9
