@@ -99,7 +99,7 @@ void free_layers(agc_ctx* c)
 
 void free_sketch(agc_ctx* c)
 {
-    void* all[] = {c->sk.planes, c->sk.recs, c->sk.counts, c->sk.lo_scale, c->sk.lo_mult, c->sk.state, c->sk.done};
+    void* all[] = {c->sk.planes, c->sk.recs, c->sk.counts, c->sk.lo_scale, c->sk.lo_mult, c->sk.state, c->sk.left};
     for (void* p : all)
         if (p) (void)hipFree(p);
     c->sk = agc::SketchDev{};
@@ -117,8 +117,8 @@ hipError_t alloc_sketch(agc_ctx* c)
     if (e == hipSuccess) e = dev_alloc(&sk.counts, 4 * (size_t)c->ws.nseg);
     if (e == hipSuccess) e = dev_alloc(&sk.lo_scale, (size_t)c->n);
     if (e == hipSuccess) e = dev_alloc(&sk.lo_mult, (size_t)c->n);
-    if (e == hipSuccess) e = dev_alloc(&sk.state, 1);
-    if (e == hipSuccess) e = dev_alloc(&sk.done, (size_t)c->ws.nseg);
+    if (e == hipSuccess) e = dev_alloc(&sk.state, 2);
+    if (e == hipSuccess) e = dev_alloc(&sk.left, (size_t)c->ws.nseg);
     if (e != hipSuccess) {
         (void)hipGetLastError();  // not the caller's
         free_sketch(c);
@@ -616,7 +616,7 @@ agc_status encode_quantize_impl(agc_ctx* c, const float* G, int64_t ldg, const u
             e = agc::launch_resolve(c->n, c->d, c->ws, *sk, qs, seed, step, ghat, stream);
             if (e != hipSuccess) return hip_fail(c, e, "resolve launch");
         }
-        e = agc::launch_quantize(G, ldg, c->n, c->k, c->d, code, c->ws, qs, seed, step, ghat, sk ? sk->done : nullptr, stream);
+        e = agc::launch_quantize(G, ldg, c->n, c->k, c->d, code, c->ws, qs, seed, step, ghat, sk, stream);
         if (e != hipSuccess) return hip_fail(c, e, "quantize launch");
         if ((st = t.end()) != AGC_OK) return st;
     }
@@ -835,15 +835,13 @@ agc_status agc_debug_sketch_last(agc_ctx* c, int64_t out[4])
     hipError_t e = hipDeviceSynchronize();
     if (e != hipSuccess) return hip_fail(c, e, "hipDeviceSynchronize");
     if (!c->sketch_last || !c->sk.planes) return AGC_OK;
-    std::vector<uint32_t> done((size_t)c->ws.nseg);
-    uint32_t state = 0;
-    e = hipMemcpy(done.data(), c->sk.done, done.size() * sizeof(uint32_t), hipMemcpyDeviceToHost);
-    if (e == hipSuccess) e = hipMemcpy(&state, c->sk.state, sizeof state, hipMemcpyDeviceToHost);
+    uint32_t state[2] = {0, 0};
+    e = hipMemcpy(state, c->sk.state, sizeof state, hipMemcpyDeviceToHost);
     if (e != hipSuccess) return hip_fail(c, e, "reading the sketch's counters");
     out[0] = 1;
     out[1] = c->ws.nseg;
-    for (uint32_t v : done) out[2] += v == 0u;
-    out[3] = state != 0u;
+    out[2] = state[0] != 0u ? c->ws.nseg : (int64_t)state[1];
+    out[3] = state[0] != 0u;
     return AGC_OK;
 }
 

@@ -166,8 +166,8 @@ struct SketchDev {
     int* counts;          // [4 * groups of four blocks] records of the block; -1: there were more than cap
     float* lo_scale;      // [n] lower bounds of the scales, and the largest multipliers that they leave
     float* lo_mult;       // [n]
-    uint32_t* state;      // not 0: a bound did not hold, or a weight is not finite
-    uint32_t* done;       // [groups of four blocks] 1: k_resolve has made the group's codes
+    uint32_t* state;      // [2] not 0: a bound did not hold, or a weight is not finite;  length of the list
+    uint32_t* left;       // [groups of four blocks] list of those that k_resolve leaves to k_quantize, in any order
     int cap;              // even
     int chunks;           // ceil(n / 32)
 };
@@ -246,7 +246,7 @@ hipError_t launch_sketch_bounds(const float* G, int64_t ldg, int n, int k, int64
                                 uint64_t step, hipStream_t stream);
 hipError_t launch_sketch(const float* G, int64_t ldg, int n, int k, int64_t d, const CodeDev& code, const Workspace& ws,
                          const SketchDev& sk, uint64_t seed, uint64_t step, hipStream_t stream);
-// codes (and with ghat the estimate) of the sketch; launch_quantize with sk.done makes those of the groups it leaves
+// codes (and with ghat the estimate) of the sketch; launch_quantize with sk makes those of the groups it leaves
 hipError_t launch_resolve(int n, int64_t d, const Workspace& ws, const SketchDev& sk, const QuantStreams& out, uint64_t seed,
                           uint64_t step, float* ghat, hipStream_t stream);
 // K2: fused encode + stochastic quantize + bit-pack.
@@ -254,7 +254,7 @@ hipError_t launch_resolve(int n, int64_t d, const Workspace& ws, const SketchDev
 // out: its bit-widths size the LDS staging area (the table holds them too).
 hipError_t launch_quantize(const float* G, int64_t ldg, int n, int k, int64_t d,
                            const CodeDev& code, const Workspace& ws, const QuantStreams& out, uint64_t seed,
-                           uint64_t step, float* ghat, const uint32_t* done, hipStream_t stream);
+                           uint64_t step, float* ghat, const SketchDev* sk, hipStream_t stream);
 // Bucket-wise scales (one per 256-coordinate block and worker): a table prologue, then ONE pass
 // over G that derives each block's scale from the block itself.  scales: n x nb, nb = ceil(d/256).
 hipError_t launch_quantize_bucket(const float* G, int64_t ldg, int n, int k, int64_t d, const CodeDev& code,

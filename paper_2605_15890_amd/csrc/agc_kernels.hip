@@ -687,7 +687,7 @@ __global__ __launch_bounds__(kWgThreads) void k_sketch_bounds(int n, BitList in,
         const float mult = inv16_of(lo, in.bits[i]);
         sk.lo_scale[i] = lo;
         sk.lo_mult[i] = mult > 0.f ? mult : __builtin_inff();  // no bound, or a quotient beyond binary32
-        if (i == 0) sk.state[0] = 0u;
+        if (i == 0) sk.state[0] = sk.state[1] = 0u;
     }
 }
 
@@ -765,7 +765,7 @@ hipError_t launch_quantize_bucket(const float* G, int64_t ldg, int n, int k, int
     if (e != hipSuccess) return e;
     QuantArgs a{ldg, n, k, d, (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32),
                 scales, (d + kBlockCoords - 1) / kBlockCoords, ghat, nullptr, out.stage_bits, out.stage_fills,
-                nullptr, 0u, out.parts, nullptr};
+                nullptr, 0u, out.parts, nullptr, nullptr};
     if (a.stage_fills > 1)
         return scale_mode == 0 ? launch_quantize_band2m(G, code, ws, a, stream)
                                : launch_quantize_band1m(G, code, ws, a, stream);
@@ -775,11 +775,11 @@ hipError_t launch_quantize_bucket(const float* G, int64_t ldg, int n, int k, int
 
 hipError_t launch_quantize(const float* G, int64_t ldg, int n, int k, int64_t d,
                            const CodeDev& code, const Workspace& ws, const QuantStreams& out, uint64_t seed,
-                           uint64_t step, float* ghat, const uint32_t* done, hipStream_t stream)
+                           uint64_t step, float* ghat, const SketchDev* sk, hipStream_t stream)
 {
     QuantArgs a{ldg, n, k, d, (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32),
                 nullptr, 0, ghat, nullptr, out.stage_bits, out.stage_fills,
-                ws.n_layers > 0 ? ws.block_layer : nullptr, 0u, out.parts, done};
+                ws.n_layers > 0 ? ws.block_layer : nullptr, 0u, out.parts, sk ? sk->state : nullptr, sk ? sk->left : nullptr};
     return a.stage_fills > 1 ? launch_quantize_band0m(G, code, ws, a, stream)
                              : launch_quantize_band0s(G, code, ws, a, stream);
 }

@@ -26,7 +26,10 @@ struct QuantArgs {
     const uint8_t* block_layer;  // layer-wise scales only: the layer of every block; wq is then [layer][n]
     unsigned wg_first;     // the workgroups take the groups of four blocks from here upwards and then from 0; 0 with parts
     bool parts;            // short vectors: one block per workgroup, its workers shared among the waves
-    const uint32_t* done;  // not null: groups of four blocks whose codes exist already (agc_sketch.h); never with parts
+    // not null: only the groups of four blocks that k_resolve has left (agc_sketch.h): all of them if left_state[0] is not 0,
+    // else the first left_state[1] of the list; never with parts
+    const uint32_t* left_state;
+    const uint32_t* left;
 };
 
 typedef __attribute__((address_space(1))) uint32_t global_u32;  // a pointer known to be device memory
@@ -521,10 +524,19 @@ __global__ __launch_bounds__(kQuantThreads) __attribute__((amdgpu_waves_per_eu(S
     const int lane = threadIdx.x % kWave;
     unsigned wg_index = blockIdx.x + a.wg_first;  // < 2 * grid <= 2^24
     if (wg_index >= gridDim.x) wg_index -= gridDim.x;
-    const int64_t wg = wg_index;
     if constexpr (LEFT) {
-        if (load_uniform(a.done + wg) != 0u) return;
+        // Workgroups go to the eight dies in turn.  The groups that are left may lie a multiple of eight apart (the first columns of
+        // matrices), so the first workgroups take them from a list; while each looked after its own group, one die did all of
+        // the work: 64 x 25.6 M, rows of 16384 whose first 256 values are 20 times the others, six bits, whole step
+        // LEFT_BEFORE | LEFT_AFTER us.
+        struct State { uint32_t all, count; };
+        const State s = load_uniform(reinterpret_cast<const State*>(a.left_state));
+        if (s.all == 0u) {
+            if (blockIdx.x >= s.count) return;
+            wg_index = load_uniform(a.left + blockIdx.x);
+        }
     }
+    const int64_t wg = wg_index;
     const int64_t block = PARTS ? wg : wg * kQuantWaves + wave;
     const int64_t base = block * (int64_t)kBlockCoords;
     {
@@ -612,7 +624,7 @@ static hipError_t launch_quantize_s(const float* G, const CodeDev& code, const W
                                (BUCKET != 0 ? (unsigned)(sizeof(float) * kQuantWaves * a.n) : 0u);
     const dim3 g(grid), b(kQuantThreads);
     if constexpr (BUCKET == 0) {
-        if (a.done) {
+        if (a.left) {
             if (a.ghat)
                 hipLaunchKernelGGL((k_quantize<S, 0, true, MULTI, false, true>), g, b, lds_bytes, stream, G, code.row_ptr,
                                    code.col, code.val, ws.wq, a);

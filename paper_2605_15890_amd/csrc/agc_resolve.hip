@@ -94,11 +94,12 @@ __global__ __launch_bounds__(kWgThreads) void k_resolve(const WorkerQ* __restric
     const bool has_block = base < a.d;
     struct Counts { int c[4]; };
     const Counts counts = load_uniform(reinterpret_cast<const Counts*>(a.sk.counts + 4 * wg));
-    if (load_uniform(a.sk.state) != 0u || (counts.c[0] | counts.c[1] | counts.c[2] | counts.c[3]) < 0) {
-        if (threadIdx.x == 0) a.sk.done[wg] = 0u;  // left to k_quantize
+    if (load_uniform(a.sk.state) != 0u) return;  // all are left to k_quantize
+    if ((counts.c[0] | counts.c[1] | counts.c[2] | counts.c[3]) < 0) {
+        if (threadIdx.x == 0)
+            a.sk.left[__hip_atomic_fetch_add(a.sk.state + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)] = (uint32_t)wg;
         return;
     }
-    if (threadIdx.x == 0) a.sk.done[wg] = 1u;
     const int np = stage_pieces(a.stage_bits, kQuantWaves);
     u32x4_t* pieces = reinterpret_cast<u32x4_t*>(lds_stage);
     for (int p = threadIdx.x; p < np; p += kQuantThreads) pieces[p] = u32x4_t{0u, 0u, 0u, 0u};

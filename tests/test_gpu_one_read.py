@@ -215,6 +215,38 @@ def test_gradients_made_of_matrices_do_not_mislead_the_sample(width, first, widt
     ctx.close()
 
 
+def test_groups_left_over_are_spread_over_the_chip():
+    """The same number of blocks with more records than there is room for, one in every 64 of the vector or one in every four
+    of its first sixteenth: the kernels behind the scales take the same time (on one of the eight dies alone the former
+    would take several times as long as on all)."""
+    rng = np.random.default_rng(13)
+    n, d = 32, 1 << 23
+    bits, w, mask = np.full(n, 8, np.uint8), np.ones(n, np.float32), np.ones(n, np.uint8)
+    ctx = api.Context(n, n, d, scale_mode=api.AGC_SCALE_L2)
+    ctx.agc_set_code(*cyclic_csr(rng, n, 2))
+    ctx.agc_debug_sketch(1)
+    codes, scales, ghat = ctx.alloc_outputs(bits)
+    G = to_device(rng.standard_normal((n, d), dtype=np.float32))
+    G.view(n, -1, 256)[:, ::64] *= 20
+    took = []
+    for _ in range(2):
+        best = float("inf")
+        for step in range(12):
+            ctx.agc_profile_enable(step >= 2)
+            ctx.agc_profile_read()
+            ctx.agc_step(G, bits, w, mask, 2, step, codes, scales, ghat)
+            last = ctx.agc_debug_sketch_last()
+            assert last["left"] == 512 and not last["bound_failed"], last
+            if step >= 2:
+                best = min(best, ctx.agc_profile_read()["quantize"][0])
+        took.append(best)
+        blocks = G.view(n, -1, 256)
+        blocks[:, ::64] /= 20
+        blocks[:, :2048:4] *= 20
+    ctx.close()
+    assert took[0] < 1.35 * took[1], took
+
+
 def test_the_hook_tells_the_form():
     rng = np.random.default_rng(11)
     n, d = 5, 40 * 1024 + 9
