@@ -144,6 +144,14 @@ inline bool sketch_fits(int n, int k, int64_t d, size_t free_bytes, size_t total
 // every row of a gradient made of matrices, in every step: with the first 256 of 4096, 8192 or 16 384 columns 20 times as
 // large the bounds did not hold, at a twentieth they lay so low that no block had room for its records, and a step took 9-15 and
 // 10-34 % longer than with two reads (50 workers x 5.4 M, 64 x 5.4 M, 32 x 2 M, 64 x 1 M).
+// One block in 32, and at most 512.  The bound leaves the two largest out, so of a norm that lies in a 32nd of the vector one
+// block in 64 saw nothing at 1 M coordinates: 64 x 1 M 131 us with two reads, 139 with one block in 64, 116 with one in 32;
+// 32 x 2 M 125 | 122 | 106.  Values that are alike everywhere 108.4 | 108.4 and 108.8 | 109.0, one block in 16 110.5 and 111.8.
+constexpr int kMaxSamples = 512;
+inline int sample_count(int64_t nblocks)
+{
+    return nblocks < 32 ? 1 : nblocks / 32 < kMaxSamples ? (int)(nblocks / 32) : kMaxSamples;
+}
 struct SampleRuns {
     int64_t length, longer;  // blocks of a run; the first `longer` runs have one more
     uint64_t salt;

@@ -24,6 +24,7 @@ extern "C" int64_t block(int64_t nblocks, int samples, uint64_t seed, uint64_t s
 {
     return agc::sample_block(agc::sample_runs(nblocks, samples, seed, step), e);
 }
+extern "C" int count(int64_t nblocks) { return agc::sample_count(nblocks); }
 extern "C" int cap(int n) { return agc::sketch_cap(n); }
 """
 
@@ -41,6 +42,7 @@ def rules(tmp_path_factory):
     lib.one_read.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_double, ctypes.c_int]
     lib.fits.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_size_t, ctypes.c_size_t]
     lib.bytes.argtypes, lib.bytes.restype = [ctypes.c_int, ctypes.c_int64], ctypes.c_int64
+    lib.count.argtypes = [ctypes.c_int64]
     lib.block.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_int64]
     lib.block.restype = ctypes.c_int64
     return lib
@@ -82,10 +84,12 @@ def test_a_program_that_fills_the_card_keeps_its_memory(rules):
     assert not rules.fits(1, 1, 1, 0, 0)
 
 
-@pytest.mark.parametrize("nblocks,samples", [(1, 1), (63, 1), (4096, 64), (21094, 329), (32768, 512), (100_000, 512), (2 ** 25, 512)])
+@pytest.mark.parametrize("nblocks,samples", [(1, 1), (63, 1), (64, 2), (4096, 128), (10_547, 329), (32768, 512), (100_000, 512),
+                                             (2 ** 25, 512)])
 def test_samples_spread_over_the_vector_and_over_the_columns_of_matrices(rules, nblocks, samples):
     """One block of each of equal runs, other ones with every seed and step; with rows of 16 to 64 blocks all columns are met
     (for each of them the number of samples in 40 steps is a sum of nearly independent draws: eight standard deviations)."""
+    assert rules.count(nblocks) == samples and samples <= -(-nblocks // 4)   # rows of the scratch
     draws = [[rules.block(nblocks, samples, 2 ** 64 - 1 - t % 3, t, e) for e in range(samples)] for t in range(40)]
     for blocks in draws:
         at = 0

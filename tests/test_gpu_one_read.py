@@ -215,6 +215,23 @@ def test_gradients_made_of_matrices_do_not_mislead_the_sample(width, first, widt
     ctx.close()
 
 
+def test_a_norm_in_one_part_of_the_vector_is_seen():
+    """All but a millionth of it in a 32nd: two of the sampled blocks are left out of the bound, and it must not be two of two."""
+    rng = np.random.default_rng(14)
+    n, d = 12, 1 << 20
+    bits, w, mask = np.full(n, 2, np.uint8), np.ones(n, np.float32), np.ones(n, np.uint8)
+    G = to_device(rng.standard_normal((n, d), dtype=np.float32))
+    G[:, d // 3: d // 3 + d // 32] *= 200
+    ctx = api.Context(n, n, d, scale_mode=api.AGC_SCALE_L2)
+    ctx.agc_set_code(*cyclic_csr(rng, n, 2))
+    ctx.agc_debug_sketch(1)
+    codes, scales, ghat = ctx.alloc_outputs(bits)
+    for step in range(6):
+        ctx.agc_step(G, bits, w, mask, 2, step, codes, scales, ghat)
+        assert ctx.agc_debug_sketch_last() == dict(one_read=True, groups=1024, left=0, bound_failed=False), step
+    ctx.close()
+
+
 def test_groups_left_over_are_spread_over_the_chip():
     """The same number of blocks with more records than there is room for, one in every 64 of the vector or one in every four
     of its first sixteenth: the kernels behind the scales take the same time (on one of the eight dies alone the former
