@@ -231,7 +231,7 @@ bool use_sketch(const agc_ctx* c, const agc::CodeDev& code, const uint8_t* bits)
         if (bits[i] < 2) return false;  // a one-bit code has no level 0
         levels += (double)((1 << (bits[i] - 1)) - 1);
     }
-    return c->sketch_mode == 1 || agc::use_sketch(c->d, c->k, levels, code.band == 0 && code.parts, c->sk.cap);
+    return c->sketch_mode == 1 || agc::use_sketch(c->d, c->n, c->k, levels, code.band == 0, code.parts, c->sk.cap);
 }
 
 }  // namespace
@@ -302,7 +302,7 @@ agc_status agc_create(agc_ctx** out, int n, int k, int64_t d, const agc_opts* op
         return fail(nullptr, e == hipErrorOutOfMemory ? AGC_ENOMEM : AGC_EHIP,
                     std::string("workspace allocation: ") + hipGetErrorString(e));
     }
-    if (!o.bucket && o.scale_mode == AGC_SCALE_L2 && agc::use_sketch(d, k, n, false, agc::sketch_cap(n))) {
+    if (!o.bucket && o.scale_mode == AGC_SCALE_L2 && agc::use_sketch(d, n, k, n, false, false, agc::sketch_cap(n))) {
         // some widths are few enough levels: two bits each
         size_t free_bytes = 0, total_bytes = 0;
         if (hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess) (void)hipGetLastError();

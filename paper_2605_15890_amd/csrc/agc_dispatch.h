@@ -109,19 +109,26 @@ inline int sketch_cap(int n)
 inline double sketch_records(int64_t d, double levels) { return levels / 0.7 * __builtin_sqrt((double)d); }
 
 // Whether one read of G and the small kernels around it are faster than two reads.  Microseconds saved, fitted to whole
-// steps in graphs: half of one for every million elements of G that are not read again, less ten for three more
-// launches, 1.9 for every million coordinates (signs and tables by groups of blocks) and seven for every million records.
-// Two reads | one, us (and the fit's gain): cyclic, 4 bits 32 x 11.7 M 588 | 390 (152);  3 bits 64 x 25.6 M 2404 | 1580 (735),
-// 64 x 1 M 115 | 87 (17), 32 x 1 M 64 | 56 (3), 32 x 500 000 42 | 45 (-4), 16 x 2 M 69 | 64 (2), 8 x 4 M 70 | 71 (-1);
-// 6 bits 50 x 5.4 M 455 | 365 (64), 16 x 2 M 71 | 72 (-8);  8 bits 64 x 5.4 M 590 | 669 (-117), 4 x 25.6 M 199 | 243 (-44).
-// General codes whose blocks share their workers among waves gain less: 64 x 300 000 79 | 112, but 64 x 1 M 196 | 141.
-// A block of average magnitudes may fill three quarters of its room; the rest take k_quantize.
-//   gather_parts: gather driver with use_parts;  cap: sketch_cap
-inline bool use_sketch(int64_t d, int k, double levels, bool gather_parts, int cap)
+// steps of 1126 shapes (4..64 workers, 15..250 M elements, three to eight bits) with Gaussian, heavy-tailed and layered values:
+// 0.58 of one for every million elements of G that are not read again, less nine for three more launches, 2.8 for every
+// million coordinates (signs and tables by groups of blocks) and six for every million records.
+// Two reads | one, us (and the fit's gain): cyclic, 4 bits 32 x 11.7 M 588 | 390 (169);  3 bits 64 x 25.6 M 2404 | 1580 (861),
+// 64 x 1 M 132 | 108 (24), 32 x 1 M 64 | 56 (7), 32 x 500 000 42 | 45 (-2), 16 x 2 M 69 | 64 (3), 8 x 4 M 70 | 71 (-2);
+// 6 bits 50 x 5.4 M 480 | 435 (26), 16 x 2 M 71 | 72 (-2);  8 bits 64 x 5.4 M 590 | 669 (-18), 4 x 25.6 M 199 | 243 (-43).
+// A block of average magnitudes may fill three quarters of its room; the rest take k_quantize, and where the norm lies in a few
+// layers, fuller ones do too.  That second pass costs the latency of a wave that walks over all workers and rows however
+// few blocks it has; with sixty layers of magnitudes up to 1000 apart it was needed at 1 % of the shapes with up to 0.2 of the
+// room in use on average, at 31 % with 0.25-0.3 and at 84 % with 0.3-0.4.  Without its price 46 of 1886 accepted steps were
+// slower than with two reads, cyclic 59 x 700 353 115 | 149, window 59 x 965 376 138 | 165, gathered 48 of 123 partitions x
+// 359 951 164 | 211; with it five of 1671, by up to 3 %.  The gather driver's times vary more than the fit knows,
+// and its blocks that share their workers among waves gain nothing (64 x 300 000 79 | 112).
+inline bool use_sketch(int64_t d, int n, int k, double levels, bool gather, bool parts, int cap)
 {
     const double m = 1e-6 * (double)d, records = sketch_records(d, levels);
-    if (gather_parts || 256.0 * records > 0.75 * cap * (double)d) return false;
-    return 0.5 * k * m - 10.0 - 1.9 * m - 7e-6 * records > 2.0;
+    const double full = 256.0 * records / ((double)cap * (double)d);
+    if ((gather && parts) || full > 0.75) return false;
+    const double again = full > 0.2 ? (gather ? 0.5 : 0.25) * (n + k) : 0.0;
+    return (0.58 * k - 2.8) * m - 9.0 - 6e-6 * records - again > (gather ? 20.0 : 2.0);
 }
 
 // Bytes of the sketch's two large arrays, signs and records: 0.97 GB at 64 workers x 25.6 M, 15 % of G there and up to half of

@@ -11,9 +11,9 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 DRIVER = r"""
 #include "agc_dispatch.h"
-extern "C" int one_read(int64_t d, int n, int k, double levels, int gather_parts)
+extern "C" int one_read(int64_t d, int n, int k, double levels, int gather, int parts)
 {
-    return agc::use_sketch(d, k, levels, gather_parts != 0, agc::sketch_cap(n));
+    return agc::use_sketch(d, n, k, levels, gather != 0, parts != 0, agc::sketch_cap(n));
 }
 extern "C" int fits(int n, int k, int64_t d, size_t free_bytes, size_t total_bytes)
 {
@@ -39,7 +39,7 @@ def rules(tmp_path_factory):
                     "-I", os.path.join(ROOT, "paper_2605_15890_amd", "csrc"), str(tmp / "driver.cpp"),
                     "-o", str(tmp / "librules.so")], check=True)
     lib = ctypes.CDLL(str(tmp / "librules.so"))
-    lib.one_read.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_double, ctypes.c_int]
+    lib.one_read.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_double, ctypes.c_int, ctypes.c_int]
     lib.fits.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_size_t, ctypes.c_size_t]
     lib.bytes.argtypes, lib.bytes.restype = [ctypes.c_int, ctypes.c_int64], ctypes.c_int64
     lib.count.argtypes = [ctypes.c_int64]
@@ -54,8 +54,21 @@ def rules(tmp_path_factory):
     (0, 25_600_000, 4, 4, 8), (0, 5_400_000, 64, 64, 8), (0, 4_000_000, 8, 8, 3), (0, 500_000, 32, 32, 3),
     (0, 2_000_000, 16, 16, 6), (0, 65536, 128, 128, 3), (0, 1_000_001, 128, 128, 6)])
 def test_one_read_where_that_was_measured_to_be_faster(rules, one, d, n, k, bits):
-    assert rules.one_read(d, n, k, float(n * (2 ** (bits - 1) - 1)), 0) == one
-    assert rules.one_read(d, n, k, float(n * (2 ** (bits - 1) - 1)), 1) == 0
+    assert rules.one_read(d, n, k, float(n * (2 ** (bits - 1) - 1)), 0, 0) == one
+    assert rules.one_read(d, n, k, float(n * (2 ** (bits - 1) - 1)), 1, 1) == 0
+
+
+@pytest.mark.parametrize("one,d,n,k,levels,gather", [
+    # sixty layers of very different magnitude: these took the second pass for up to a seventh of the groups, and longer than two reads
+    (0, 700_353, 59, 59, 857, 0), (0, 965_376, 59, 59, 1217, 0), (0, 1_271_552, 58, 58, 1038, 0), (0, 1_294_221, 60, 60, 1184, 0),
+    (0, 359_951, 48, 123, 896, 1), (0, 583_808, 31, 74, 623, 1), (0, 886_016, 44, 73, 914, 1), (0, 1_647_104, 14, 35, 1018, 1),
+    # and these did not, or gained more than that pass takes
+    (1, 1_050_112, 41, 41, 150, 0), (1, 4_071_000, 31, 31, 330, 0), (1, 2_586_889, 45, 45, 480, 0), (1, 5_400_003, 50, 50, 4078, 0),
+    (1, 25_600_000, 64, 64, 8128, 0), (1, 4_924_838, 34, 78, 1060, 1), (1, 541_184, 45, 127, 190, 1),
+    # few workers: signs and tables by coordinates outweigh the rows
+    (0, 19_554_560, 6, 6, 96, 0), (0, 25_600_000, 5, 5, 40, 0)])
+def test_one_read_takes_the_second_pass_into_account(rules, one, d, n, k, levels, gather):
+    assert rules.one_read(d, n, k, float(levels), gather, 0) == one
 
 
 def test_ends_of_the_ranges(rules):
@@ -67,7 +80,7 @@ def test_ends_of_the_ranges(rules):
         for d in (1, 2 ** 33):
             for k in (1, 65536):
                 for level in (1, 32767):
-                    one = rules.one_read(d, n, k, float(n * level), 0)
+                    one = rules.one_read(d, n, k, float(n * level), 0, 0)
                     assert not (d == 1 and one)
 
 
