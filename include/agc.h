@@ -12,8 +12,9 @@
  *     aborts; agc_last_error() gives a message for the last failure on a context;
  *   - "host" pointers are ordinary process memory, "device" pointers are HIP device memory
  *     of the GPU that was current when the context was created;
- *   - the caller owns every buffer it passes; the library owns only the workspace it
- *     allocates in agc_create() and allocates nothing in the per-step calls;
+ *   - the caller owns every buffer it passes; the library owns only the workspace and the tables it
+ *     allocates in agc_create(), agc_set_code() and agc_set_layers() and allocates nothing in the
+ *     per-step calls;
  *   - per-step calls validate their arguments synchronously, enqueue kernels on the given
  *     HIP stream (a hipStream_t passed as void*, NULL = the default stream) and return
  *     without waiting and without any host<->device copy: the small host arrays (bits, w,
@@ -94,10 +95,7 @@ typedef struct {
 /* Creates a context for n workers, k partitions, d coordinates on the current device and
  * allocates its workspace (scale partials: 4 bytes * 256 * n for the max-abs scale, whatever d is;
  * 8 bytes * n * ceil(d/1024) for the Euclidean one; none with bucket-wise scales; a few n-entry
- * tables).  With the Euclidean scale of a long vector it also takes signs and records for one read of G
- * instead of two: for every 256 coordinates 1 KB per 32 workers and 8 bytes for each of up to 32 * n, at most 1151,
- * records (0.97 GB at 64 x 25.6 M), only beside a G of at most half the device's memory and within an eighth of
- * what is free; without it two reads are made, with the same results.
+ * tables).  agc_set_code() takes more with the Euclidean scale of a long vector.
  * opts may be NULL (AGC_SCALE_MAXABS, no 1-bit).  Limits: 1 <= n <= AGC_MAX_WORKERS,
  * 1 <= k <= 65536, 1 <= d <= 2^33. */
 agc_status agc_create(agc_ctx **out, int n_workers, int k_parts, int64_t d, const agc_opts *opts);
@@ -112,7 +110,13 @@ void agc_destroy(agc_ctx *ctx);
  * ascending columns whose two ends never decrease from one worker to the next (the shape
  * agc_build_code produces), they take the same kind of path without the wrap-around; any other B
  * takes the generic gather path, which re-reads shared rows through the caches.  All three give
- * identical bits (agc_code_path tells which one a context runs). */
+ * identical bits (agc_code_path tells which one a context runs).
+ * With one Euclidean scale per vector and sizes at which it is faster, the call also takes the workspace for reading G
+ * once instead of twice: for every 256 coordinates 1 KB of signs per 32 workers and 8 bytes for each of up to 32 * n, at
+ * most 1118, coded values (0.97 GB at 64 x 25.6 M).  It is taken beside a G of at most half the device's memory, within an
+ * eighth of what hipMemGetInfo reports as free (what a caching allocator holds is not), and whatever the bit-widths of
+ * the steps will be; layers give it back.  Without it two reads are made, with the same results
+ * (agc_debug_sketch_last tells which). */
 agc_status agc_set_code(agc_ctx *ctx, const int32_t *row_ptr, const int32_t *col, const float *val);
 
 /* Layer-wise scales (Sec. II-B: the quantizer "at layer-wise or bucket-wise granularity"): the d

@@ -26,8 +26,8 @@ extern "C" {
 agc_status agc_debug_force_long(agc_ctx *ctx, int on);
 
 /* Testing hook: the form with one read of G (Euclidean scale of the whole vector, no one-bit workers).  mode 0: by the
- * library's rule; 1: wherever it can be made, at any length (allocates its workspace); 2: never.  Results are the same
- * bits.  AGC_EINVAL without a context, for another mode, and for mode 1 in a context with another kind of scale. */
+ * library's rule; 1: wherever it can be made, at any length (allocates its workspace); 2: never (gives it back).  Waits for the
+ * device.  Results are the same bits.  AGC_EINVAL without a context, for another mode, and for mode 1 in a context with another kind of scale. */
 agc_status agc_debug_sketch(agc_ctx *ctx, int mode);
 
 /* Which form the last worker-side call on this context took (agc_encode_quantize, agc_step).  Waits for the device.

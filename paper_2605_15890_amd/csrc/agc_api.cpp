@@ -43,7 +43,7 @@ struct agc_ctx {
     bool sketch_last = false; // the last worker-side call made one
     // workspace
     agc::Workspace ws{};
-    agc::SketchDev sk{};      // planes is null where the rule never takes it
+    agc::SketchDev sk{};      // planes is null where no step can use it (update_sketch)
     // profiling
     bool profiling = false;
     std::vector<EventPair> events[AGC_NUM_KERNELS];
@@ -223,9 +223,29 @@ agc::CodeDev code_dev(const agc_ctx* c)
     return agc::CodeDev{c->d_row_ptr, c->d_col, c->d_val, band, c->d_win, parts};
 }
 
+// Takes the workspace of the one-read form where a step of this context may use it, some bit-widths provided (those of two
+// bits have the fewest levels), and gives it back where none can: no code and hence no worker side, another kind of scale, layers.
+// Not called in the per-step calls.  Kernels that use it must have ended.
+hipError_t update_sketch(agc_ctx* c)
+{
+    bool want = c->sketch_mode == 1;
+    if (!want && c->sketch_mode == 0 && c->has_code) {
+        const agc::CodeDev code = code_dev(c);
+        size_t free_bytes = 0, total_bytes = 0;
+        want = agc::use_sketch(c->d, c->n, c->k, c->n, code.band == 0, code.parts, agc::sketch_cap(c->n));
+        if (want && !c->sk.planes) {
+            if (hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess) (void)hipGetLastError();
+            want = agc::sketch_fits(c->n, c->k, c->d, free_bytes, total_bytes);
+        }
+    }
+    want = want && !c->opts.bucket && c->opts.scale_mode == AGC_SCALE_L2 && c->ws.n_layers == 0;
+    if (!want) free_sketch(c);
+    return want && !c->sk.planes ? alloc_sketch(c) : hipSuccess;
+}
+
 bool use_sketch(const agc_ctx* c, const agc::CodeDev& code, const uint8_t* bits)
 {
-    if (!c->sk.planes || c->ws.n_layers > 0 || c->sketch_mode == 2) return false;
+    if (!c->sk.planes) return false;
     double levels = 0.0;
     for (int i = 0; i < c->n; ++i) {
         if (bits[i] < 2) return false;  // a one-bit code has no level 0
@@ -301,12 +321,6 @@ agc_status agc_create(agc_ctx** out, int n, int k, int64_t d, const agc_opts* op
         agc_destroy(c);
         return fail(nullptr, e == hipErrorOutOfMemory ? AGC_ENOMEM : AGC_EHIP,
                     std::string("workspace allocation: ") + hipGetErrorString(e));
-    }
-    if (!o.bucket && o.scale_mode == AGC_SCALE_L2 && agc::use_sketch(d, n, k, n, false, false, agc::sketch_cap(n))) {
-        // some widths are few enough levels: two bits each
-        size_t free_bytes = 0, total_bytes = 0;
-        if (hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess) (void)hipGetLastError();
-        else if (agc::sketch_fits(n, k, d, free_bytes, total_bytes)) (void)alloc_sketch(c);
     }
     *out = c;
     return AGC_OK;
@@ -404,6 +418,7 @@ agc_status agc_set_code(agc_ctx* c, const int32_t* row_ptr, const int32_t* col, 
     c->nnz = nnz;
     c->band = band;
     c->has_code = true;
+    (void)update_sketch(c);  // without the memory for it two reads are made
     return AGC_OK;
 }
 
@@ -417,6 +432,7 @@ agc_status agc_set_layers(agc_ctx* c, int n_layers, const int64_t* layer_end)
     if (e != hipSuccess) return hip_fail(c, e, "hipDeviceSynchronize");
     if (n_layers == 0) {
         free_layers(c);
+        (void)update_sketch(c);
         return AGC_OK;
     }
     if (c->opts.bucket) return fail(c, AGC_EINVAL, "layer-wise scales need bucket == 0");
@@ -530,6 +546,7 @@ agc_status agc_set_layers(agc_ctx* c, int n_layers, const int64_t* layer_end)
     c->ws.coef_layer = d_c1;
     c->ws.coef2_layer = d_c2;
     c->ws.n_layers = n_layers;
+    (void)update_sketch(c);
     return AGC_OK;
 }
 
@@ -820,12 +837,11 @@ agc_status agc_debug_sketch(agc_ctx* c, int mode)
     if (!c || mode < 0 || mode > 2) return fail(nullptr, AGC_EINVAL, "null context or unknown mode");
     if (mode == 1 && (c->opts.bucket || c->opts.scale_mode != AGC_SCALE_L2))
         return fail(c, AGC_EINVAL, "one scale of the whole vector, Euclidean");
-    if (mode == 1 && !c->sk.planes) {
-        const hipError_t e = alloc_sketch(c);
-        if (e != hipSuccess) return fail(c, AGC_ENOMEM, "workspace of the one-read form");
-    }
+    hipError_t e = hipDeviceSynchronize();
+    if (e != hipSuccess) return hip_fail(c, e, "hipDeviceSynchronize");
     c->sketch_mode = mode;
-    return AGC_OK;
+    e = update_sketch(c);
+    return e != hipSuccess && mode == 1 ? fail(c, AGC_ENOMEM, "workspace of the one-read form") : AGC_OK;
 }
 
 agc_status agc_debug_sketch_last(agc_ctx* c, int64_t out[4])

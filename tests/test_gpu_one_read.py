@@ -264,6 +264,34 @@ def test_groups_left_over_are_spread_over_the_chip():
     assert took[0] < 1.35 * took[1], took
 
 
+def test_memory_is_held_only_where_a_step_can_use_it():
+    """Signs and records come with the code (a program that only decodes sets none), go with layers and come back without them."""
+    import torch
+    rng = np.random.default_rng(15)
+    n, d = 64, 1 << 22
+    need = (d // 256) * (2 * 1024 + 8 * 900)   # more than 900 records a block
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+    before = free()
+    ctx = api.Context(n, n, d, scale_mode=api.AGC_SCALE_L2)
+    assert before - free() < need // 4
+    ctx.agc_set_code(*cyclic_csr(rng, n, 4))
+    with_code = free()
+    assert before - with_code > need
+    ctx.agc_set_layers(np.array([d // 2, d], np.int64))
+    assert before - free() < need // 4
+    ctx.agc_set_layers([])
+    assert before - free() > need
+    ctx.agc_debug_sketch(2)
+    assert before - free() < need // 4
+    ctx.agc_debug_sketch(0)
+    assert before - free() > need
+    ctx.close()
+    assert before - free() < need // 4
+
+
 def test_the_hook_tells_the_form():
     rng = np.random.default_rng(11)
     n, d = 5, 40 * 1024 + 9
