@@ -95,10 +95,13 @@ inline unsigned first_group(int64_t d, unsigned groups)
 
 // One read of G (agc_sketch.h): records a block has room for.  As many as leave four workgroups of a compute unit's 160 KB of
 // LDS (three and two with more workers, whose partial sums and signs take room themselves), and no more than an eighth of
-// the block's coded elements, beyond which a record of eight bytes each moves as much as a second read of G.
+// the block's coded elements, which as records of eight bytes each, written and read, move half of a second read of G.
+// LDS is handed out in units of 1280 bytes: at 53 760 bytes three workgroups of 256 threads run on a compute unit, at 53 764 two
+// (768 of them 358 and 673 us).  Whole steps with 53 * 1024 bytes | 42 units, us: 128 workers x 4 M 617 | 566, 100 x 4 M
+// 565 | 512, 144 x 4 M 717 | 657, 160 x 3 M 623 | 573, 128 x 8 M six bits 1647 | 1642.
 inline int sketch_cap(int n)
 {
-    const int budget = n <= 96 ? 40 * 1024 : n <= 160 ? 53 * 1024 : 64 * 1024;
+    const int budget = n <= 96 ? 40 * 1024 : n <= 160 ? 42 * 1280 : 64 * 1024;
     const int room = (budget - 32 * n - 4096 * ((n + 31) / 32)) / 32;
     const int cap = room < 32 * n ? room : 32 * n;
     return cap / 2 * 2;

@@ -76,7 +76,9 @@ def test_ends_of_the_ranges(rules):
     for n in range(1, 257):
         cap = rules.cap(n)
         assert cap >= 32 and cap % 2 == 0 and cap <= 32 * n
-        assert 32 * n + 4096 * -(-n // 32) + 32 * cap <= 64 * 1024
+        lds = 32 * n + 4096 * -(-n // 32) + 32 * cap
+        assert lds <= 64 * 1024
+        assert 128 * 1280 // (-(-lds // 1280) * 1280) >= (4 if n <= 96 else 3 if n <= 160 else 2)   # of a compute unit's LDS
         for d in (1, 2 ** 33):
             for k in (1, 65536):
                 for level in (1, 32767):
