@@ -219,7 +219,7 @@ agc::CodeDev code_dev(const agc_ctx* c)
 {
     const int band = c->opts.force_generic ? 0 : c->band;
     const bool parts = !c->force_long &&
-                       agc::use_parts_of(c->d, c->n, c->k, c->nnz, band, c->opts.scale_mode == AGC_SCALE_L2, c->opts.bucket != 0);
+                       agc::use_parts(c->d, c->n, c->k, c->nnz, band, c->opts.scale_mode == AGC_SCALE_L2, c->opts.bucket != 0);
     return agc::CodeDev{c->d_row_ptr, c->d_col, c->d_val, band, c->d_win, parts};
 }
 

@@ -11,15 +11,16 @@ namespace agc {
 // (k_scale_pass_parts, k_quantize<.., PARTS>).  A wave that walks over all workers alone on its SIMD mostly waits
 // for itself; four waves per block hide that as long as the chip has room for them, and lose to the long form
 // (four blocks per workgroup, every row read once) once it is full.  With one or two workers there is nothing to
-// share.  The lines of vectors that end inside a block lie further out, from when that block took the gather driver;
-// for the cyclic band the library does not ask by them any more (use_parts_of).
+// share.  The windows of vectors that end inside a block have lines further out (up to them the parts are still the faster
+// form: W = 4, 32 workers x 196 001 33 and 39 us in the long form; W = 8, 32 x 98 001 31 and 45; 64 x 131 001 bucket-wise 51 and
+// 55); a cyclic band has the same for all, us beyond its line in parts | long: max-abs 64 x 327 681 73 | 63, 64 x 500 000 93 | 67,
+// 32 x 393 000 44 | 37;  Euclidean 64 x 500 000 100 | 69;  bucket-wise 64 x 500 000 77 | 51.
 //   band   > 0: cyclic band of that width, -W: window driver, 0: gather driver
 //   norm   Euclidean scale;  bucket: bucket-wise scales (no scale pass)
 // Measured: time of a whole step in the long form over that in this one, ten steps in a graph, 6000 shapes of
 // 3..256 workers.  Largest and smallest up to the line | beyond it:
 //   band    4-7 workers           1.26 .. 0.99 | 262144 coordinates 1.07 .. 0.93
 //           8 and more            2.09 .. 1.00 | 393216: 0.99 .. 0.77, 524288: 0.91 .. 0.65
-//           16, ending inside     2.76 .. 0.98 | 786432: 1.15 .. 0.80
 // (tenth percentile and median up to the line | beyond it)
 //   window, W <= 4                whole, 4-15 workers 0.97 and 1.08 | 0.93 and 1.00;  16-47 1.08 and 1.21 | 0.93 and
 //           1.02;  48 and more 1.15 and 1.45 | 1.05 and 1.2;  ending inside, 16 and more 1.25 and 1.6 | 0.96 and 1.1
@@ -39,9 +40,7 @@ inline bool use_parts(int64_t d, int n, int k, int nnz, int band, bool norm, boo
     const bool ragged = d % 256 != 0;
     if (n < 4) return n == 3 && blocks <= 256;
     if (band > 0) {
-        if (n < 8) return blocks <= 768;
-        if (ragged && n >= 16) return blocks <= (bucket && n < 48 ? 1536 : 2048);
-        return blocks <= (norm && !bucket && !ragged ? 768 : 1024);
+        return blocks <= (n < 8 || (norm && !bucket) ? 768 : 1024);
     }
     if (band < 0 && band >= -4) {
         if (n >= 96 || (n >= 32 && ragged)) return blocks <= 1024;
@@ -70,20 +69,12 @@ inline bool use_parts(int64_t d, int n, int k, int nnz, int band, bool norm, boo
     return blocks <= 1024;
 }
 
-// The rule that the library asks.  The block that a vector ends in passes through the ring like every other, so a
-// cyclic band goes by the lines of whole blocks.  By the lines of vectors that end inside a block | by those of whole
-// ones, us: max-abs, 64 workers x 327 681 73 | 63, 500 000 93 | 67, 32 x 393 000 44 | 37;  Euclidean 64 x 500 000
-// 100 | 69;  bucket-wise 64 x 500 000 77 | 51.  The windows keep theirs: up to them the parts are still the faster form
-// (W = 4, 32 x 196 001 33 and 39 us in the long form; W = 8, 32 x 98 001 31 and 45; 64 x 131 001 bucket-wise 51 and 55).
-inline bool use_parts_of(int64_t d, int n, int k, int nnz, int band, bool norm, bool bucket)
-{
-    return use_parts(band > 0 ? (d + 255) / 256 * 256 : d, n, k, nnz, band, norm, bucket);
-}
-
 // The quantize pass of long vectors: the group of four blocks that its first workgroup takes; the others follow
 // upwards and wrap around.  The codes of the block that the vector ends in leave in pieces that do not fill their lines and
 // are masked lane by lane, so it takes longer than the others: it is not the last to start.  With no more groups than
 // the chip holds at once (four workgroups on each of 256 compute units) all start together and the order is left alone.
+// Whole step, upwards from 0 | from 64 groups before the end, three runs each, us: 128 workers x 5 400 001 1096-1100 |
+// 1090-1093;  64 x 25 600 001, 64 x 2 000 003, 50 x 5 400 003, 32 x 11 700 003, 4 x 25 600 003 within the runs' difference (1 %).
 // Vectors of whole blocks take the same time from any group (32 x 11 700 224 521 | 522 us), so nothing of G that the
 // scale pass left in the memory-side cache is gained by the order.
 constexpr int64_t kChipGroups = 4 * 256;

@@ -55,7 +55,11 @@ def rules(tmp_path_factory):
     # cyclic band: whole vectors of 2^19 coordinates took 0.62 to 0.87 of the time in the long form
     (0, 524288, 16, 16, 48, 3, 0, 0), (0, 524288, 64, 64, 192, 3, 1, 0), (0, 524288, 32, 32, 256, 8, 0, 1),
     (0, 393216, 128, 128, 384, 3, 0, 0), (0, 262144, 32, 32, 96, 3, 1, 0),
-    (1, 262144, 32, 32, 96, 3, 0, 0), (1, 196608, 32, 32, 96, 3, 1, 0), (1, 500000, 64, 64, 192, 3, 1, 0),
+    (1, 262144, 32, 32, 96, 3, 0, 0), (1, 196608, 32, 32, 96, 3, 1, 0),
+    # a band that ends inside a block: as one of whole blocks (64 x 500000 Euclidean 100 us in parts, 69 in the long form)
+    (0, 500000, 64, 64, 192, 3, 1, 0), (0, 500000, 64, 64, 192, 3, 0, 1), (0, 327681, 64, 64, 192, 3, 0, 0),
+    (1, 262143, 64, 64, 192, 3, 0, 0), (0, 262145, 64, 64, 192, 3, 0, 0), (1, 196607, 64, 64, 192, 3, 1, 0),
+    (0, 196609, 64, 64, 192, 3, 1, 0), (1, 196607, 5, 5, 10, 2, 0, 1), (0, 196609, 5, 5, 10, 2, 0, 1),
     (1, 65536, 48, 48, 144, 3, 0, 0), (1, 4096, 4, 4, 8, 2, 0, 0), (0, 262144, 4, 4, 8, 2, 0, 0),
     # one or two workers share nothing
     (0, 200000, 1, 1, 1, 1, 0, 0), (0, 262144, 2, 2, 4, 2, 0, 0), (0, 4096, 2, 2, 4, 2, 1, 0),
