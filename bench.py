@@ -161,9 +161,9 @@ def tag_of(cfg, code, scale, bucket, two_pass, layers=0):
             + ("_two_pass" if two_pass else ""))
 
 
-def alg_bytes_of(n, k, d, bits, masks, bucket, two_pass, one_read=False):
-    """Algorithmic bytes per launch of each kernel: what the method must move.  one_read: the Euclidean scale of
-    the whole vector, whose worker side can do with one read of G."""
+def alg_bytes_of(n, k, d, bits, masks, bucket, two_pass, second_read=1.0):
+    """Algorithmic bytes per launch of each kernel: what the method must move.  second_read: the part of G that is read
+    once more behind the scales (all of it, unless the library chose the form with one read)."""
     nb = (d + 255) // 256 if bucket else 0
     sum_b = float(np.sum(bits))
     arrived_b = float(np.mean([np.sum(bits[m.astype(bool)]) for m in masks]))
@@ -171,7 +171,7 @@ def alg_bytes_of(n, k, d, bits, masks, bucket, two_pass, one_read=False):
     return {
         "scale_pass": 0.0 if bucket else 4.0 * k * d,
         "scale_finalize": 0.0,
-        "quantize": (0.0 if one_read else 4.0 * k * d) + d * sum_b / 8.0 + 4.0 * n * nb + (0.0 if two_pass else 4.0 * d),
+        "quantize": second_read * 4.0 * k * d + d * sum_b / 8.0 + 4.0 * n * nb + (0.0 if two_pass else 4.0 * d),
         "decode": (d * arrived_b / 8.0 + 4.0 * d + 4.0 * n_arr * nb) if two_pass else 0.0,
     }
 
@@ -215,11 +215,12 @@ def time_variant(api, I, cfg, G, bufs, p, bits, code, w, scale, bucket, two_pass
     prof = ctx.agc_profile_read()
     ctx.agc_profile_enable(False)
     path = ctx.agc_code_path()
+    form = ctx.agc_debug_sketch_last()
     ctx.close()
     del scales
     ms_per_step = (t1 - t0) * 1e3 / K
     alg = alg_bytes_of(n, k, d, bits, masks[W:W + K], bucket, two_pass,
-                       one_read=scale == "l2" and not bucket and not layers)
+                       second_read=form["left"] / form["groups"] if form["one_read"] else 1.0)
     kernels = {}
     for name, (ms, cnt) in prof.items():
         if cnt == 0:
