@@ -69,8 +69,9 @@ __device__ __forceinline__ void or_signs_any(int b, uint32_t* part, uint32_t sig
     }
 }
 
-// What bounds it: 0.92 GB in and out at 64 workers x 25.6 M (205 MB of signs, 614 MB of codes, 102 MB of estimate) in 0.31 ms,
-// 3 TB/s; latency is most of the rest: waves wait 0.57 of their time.  Signs lane by lane, with an LDS atomic for every
+// What bounds it: 0.95 GB in and out at 64 workers x 25.6 M (205 MB of signs, 30 of records, 614 of codes, 102 of estimate) in
+// 0.31 ms, 3 TB/s; latency is most of the rest: waves wait 0.47 of their time, vector ALU 0.35 busy (counters of the interval
+// code).  Signs lane by lane, with an LDS atomic for every
 // word that two lanes share, took 0.80 ms; whole words per lane 0.41; with the fill's end looked up in LDS instead of worker
 // by worker in memory 0.31.
 //

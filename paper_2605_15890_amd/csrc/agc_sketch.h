@@ -2,19 +2,24 @@
 // needs the whole vector, and reading G twice is most of a step (64 workers x 25.6 M: 2 x 6.55 GB of 13.8).  But with a
 // small magnitude against the scale nearly every coordinate ends at level 0 whatever the scale is exactly: for the
 // Euclidean norm the levels sum to at most L * sqrt(d) of d coordinates.  So:
-//   1. a sample of the vector gives a lower bound of every scale (launch_sketch_bounds);
+//   1. a sample of the vector, at places drawn anew for every step, gives a lower bound of every scale (launch_sketch_bounds);
 //   2. k_sketch reads G once.  It forms the partial results of the scales and, with the bound in place of the scale,
 //      the largest grid position a coordinate can have.  Where the draw lies above that, the level is 0 for every
 //      scale from the bound upwards and only the sign is kept, one bit; the others are written down whole ("records": the
 //      coded value, its draw, worker and place);
 //   3. when the scales are known and none fell below its bound, k_resolve (agc_resolve.hip) makes the codes and the estimate
 //      of signs and records, by the arithmetic of k_quantize, operation by operation;
-//   4. groups of blocks with more records than there is room for, or all if a bound did not hold, take k_quantize.
+//   4. groups of blocks with more records than there is room for, listed by k_resolve, or all if a bound did not hold, take
+//      k_quantize.
 // The results are those of the two-read form bit for bit, whatever the sample said.
 //
 // Measured, 64 workers x 25.6 M, three bits on average, Euclidean, interval code, whole step 2416 us with two reads (scale pass
 // 984, quantize pass 1420), 1565 with one: sample and bounds 11 + 5, k_sketch 1210-1240, groups and finalize 13,
-// k_resolve 310, the quantize pass that finds nothing left 10.
+// k_resolve 310, the quantize pass that finds nothing left 7.  A step whose bounds do not hold pays for both forms (some 2670).
+// Values that are not alike everywhere, two reads | one: rows of 16384 with the first 256 values 20 times the others, six bits,
+// 64 x 25.6 M 2500 | 1950, 50 x 5.4 M 480 | 437, 64 x 5.4 M three bits 541 | 402; sixty layers of magnitudes up to 1000 apart,
+// eight bits, 64 x 25.6 M 2552 | 2108.  What stays slower: at 64 x 1 M the second pass takes 27 us for however few blocks, so a
+// norm in a 64th of the vector or less, 132 | 139, and such rows, 132 | 141, lose what alike values gain, 132 | 108.
 #pragma once
 
 #include "agc_device.h"
