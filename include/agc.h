@@ -116,7 +116,8 @@ void agc_destroy(agc_ctx *ctx);
  * most 1118, coded values (0.97 GB at 64 x 25.6 M).  It is taken beside a G of at most half the device's memory, within an
  * eighth of what hipMemGetInfo reports as free (what a caching allocator holds is not), and whatever the bit-widths of
  * the steps will be; layers give it back.  Without it two reads are made, with the same results
- * (agc_debug_sketch_last tells which). */
+ * (agc_debug_sketch_last tells which).  Likewise with one largest-magnitude scale per vector, G of 4 GB and more and up to 128
+ * workers, where 8 bytes are held for each of up to 32 * k coded values (1.9 GB at 64 x 25.6 M). */
 agc_status agc_set_code(agc_ctx *ctx, const int32_t *row_ptr, const int32_t *col, const float *val);
 
 /* Layer-wise scales (Sec. II-B: the quantizer "at layer-wise or bucket-wise granularity"): the d

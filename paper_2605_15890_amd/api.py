@@ -23,7 +23,7 @@ EXPORTS = [
     "agc_create", "agc_destroy", "agc_set_code", "agc_code_path", "agc_code_bytes", "agc_last_error",
     "agc_encode_quantize", "agc_decode", "agc_step", "agc_profile_enable", "agc_profile_read",
     "agc_scales_per_worker", "agc_set_layers", "agc_decode2", "agc_decode_noalloc", "agc_adam_update", "agc_second_moment_decoder",
-    "agc_calibration_copy", "agc_debug_force_long", "agc_debug_sketch", "agc_debug_sketch_last", "agc_debug_stream_rows", "agc_ls_workspace_floats", "agc_ls_partial_gradients", "agc_gd_update",
+    "agc_calibration_copy", "agc_debug_force_long", "agc_debug_sketch", "agc_debug_sketch_last", "agc_debug_sketch_max", "agc_debug_stream_rows", "agc_ls_workspace_floats", "agc_ls_partial_gradients", "agc_gd_update",
     "agc_phi_coef_balanced", "agc_alloc_bits", "agc_alloc_bits_dp", "agc_alloc_objective",
     "agc_build_code", "agc_build_cyclic_code", "agc_build_cyclic_code_opt", "agc_check_unbiased",
 ]
@@ -111,6 +111,8 @@ def load():
     L.agc_debug_force_long.restype = C.c_int
     L.agc_debug_sketch.argtypes = [_vp, C.c_int]
     L.agc_debug_sketch.restype = C.c_int
+    L.agc_debug_sketch_max.argtypes = [_vp, C.c_int]
+    L.agc_debug_sketch_max.restype = C.c_int
     L.agc_debug_sketch_last.argtypes = [_vp, C.POINTER(C.c_int64)]
     L.agc_debug_sketch_last.restype = C.c_int
     L.agc_profile_enable.argtypes = [_vp, C.c_int]
@@ -407,6 +409,9 @@ class Context:
 
     def agc_debug_sketch(self, mode):
         self._check(self.lib.agc_debug_sketch(self.h, int(mode)))
+
+    def agc_debug_sketch_max(self, mode):
+        self._check(self.lib.agc_debug_sketch_max(self.h, int(mode)))
 
     def agc_debug_sketch_last(self):
         out = (C.c_int64 * 4)()

@@ -105,19 +105,30 @@ void free_sketch(agc_ctx* c)
     c->sk = agc::SketchDev{};
 }
 
+int sketch_room(const agc_ctx* c)
+{
+    return c->opts.scale_mode == AGC_SCALE_L2 ? agc::sketch_cap(c->n) : agc::sketch_max_cap(c->n, c->k);
+}
+
 // Workspace of the one-read form.  Without the memory for it the two-read form runs: not an error.
 hipError_t alloc_sketch(agc_ctx* c)
 {
     agc::SketchDev& sk = c->sk;
     const size_t blocks = (size_t)(c->d + 255) / 256;
-    sk.cap = agc::sketch_cap(c->n);
+    sk.cap = sketch_room(c);
+    sk.limit = agc::sketch_max_limit(c->k, agc::sample_count((int64_t)blocks));
     sk.chunks = (c->n + 31) / 32;
+    sk.blocks = 4 * c->ws.nseg;
     hipError_t e = dev_alloc(&sk.planes, blocks * (size_t)sk.chunks * 256);
     if (e == hipSuccess) e = dev_alloc(&sk.recs, blocks * (size_t)sk.cap);
-    if (e == hipSuccess) e = dev_alloc(&sk.counts, 4 * (size_t)c->ws.nseg);
-    if (e == hipSuccess) e = dev_alloc(&sk.lo_scale, (size_t)c->n);
-    if (e == hipSuccess) e = dev_alloc(&sk.lo_mult, (size_t)c->n);
-    if (e == hipSuccess) e = dev_alloc(&sk.state, 2);
+    if (e == hipSuccess) e = dev_alloc(&sk.counts, (size_t)sk.blocks);
+    if (c->opts.scale_mode == AGC_SCALE_L2) {
+        if (e == hipSuccess) e = dev_alloc(&sk.lo_scale, (size_t)c->n);
+        if (e == hipSuccess) e = dev_alloc(&sk.lo_mult, (size_t)c->n);
+    }
+    if (e == hipSuccess) e = dev_alloc(&sk.state, 3);
+    if (e == hipSuccess) e = hipMemset(sk.state, 0, 3 * sizeof(uint32_t));
+    if (e == hipSuccess) e = hipDeviceSynchronize();  // the next step may run on any stream
     if (e == hipSuccess) e = dev_alloc(&sk.left, (size_t)c->ws.nseg);
     if (e != hipSuccess) {
         (void)hipGetLastError();  // not the caller's
@@ -232,13 +243,15 @@ hipError_t update_sketch(agc_ctx* c)
     if (!want && c->sketch_mode == 0 && c->has_code) {
         const agc::CodeDev code = code_dev(c);
         size_t free_bytes = 0, total_bytes = 0;
-        want = agc::use_sketch(c->d, c->n, c->k, c->n, code.band == 0, code.parts, agc::sketch_cap(c->n));
+        want = c->opts.scale_mode == AGC_SCALE_L2
+                   ? agc::use_sketch(c->d, c->n, c->k, c->n, code.band == 0, code.parts, agc::sketch_cap(c->n))
+                   : agc::use_sketch_max(c->d, c->n, c->k, c->n);
         if (want && !c->sk.planes) {
             if (hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess) (void)hipGetLastError();
-            want = agc::sketch_fits(c->n, c->k, c->d, free_bytes, total_bytes);
+            want = agc::sketch_fits(c->n, c->k, c->d, free_bytes, total_bytes, sketch_room(c));
         }
     }
-    want = want && !c->opts.bucket && c->opts.scale_mode == AGC_SCALE_L2 && c->ws.n_layers == 0;
+    want = want && !c->opts.bucket && c->ws.n_layers == 0;
     if (!want) free_sketch(c);
     return want && !c->sk.planes ? alloc_sketch(c) : hipSuccess;
 }
@@ -251,6 +264,7 @@ bool use_sketch(const agc_ctx* c, const agc::CodeDev& code, const uint8_t* bits)
         if (bits[i] < 2) return false;  // a one-bit code has no level 0
         levels += (double)((1 << (bits[i] - 1)) - 1);
     }
+    if (c->opts.scale_mode == AGC_SCALE_MAXABS) return c->sketch_mode == 1 || agc::use_sketch_max(c->d, c->n, c->k, levels);
     return c->sketch_mode == 1 || agc::use_sketch(c->d, c->n, c->k, levels, code.band == 0, code.parts, c->sk.cap);
 }
 
@@ -609,11 +623,15 @@ agc_status encode_quantize_impl(agc_ctx* c, const float* G, int64_t ldg, const u
         KernelTimer t{c, 0, stream};
         if ((st = t.begin()) != AGC_OK) return st;
         c->slots_dirty = maxabs;
-        if (sk) {
+        if (sk && maxabs) {
+            e = agc::launch_sketch_bounds_max(G, ldg, c->n, c->k, c->d, code, c->ws, *sk, qs, seed, step, stream);
+            if (e == hipSuccess) e = agc::launch_scale_pass(G, ldg, c->n, c->k, c->d, code, c->opts.scale_mode, c->ws, sk, stream);
+            if (e == hipSuccess) e = agc::launch_sketch_max(G, ldg, c->n, c->k, c->d, code, c->ws, *sk, qs, seed, step, stream);
+        } else if (sk) {
             e = agc::launch_sketch_bounds(G, ldg, c->n, c->k, c->d, code, c->ws, *sk, qs, seed, step, stream);
             if (e == hipSuccess) e = agc::launch_sketch(G, ldg, c->n, c->k, c->d, code, c->ws, *sk, seed, step, stream);
         } else {
-            e = agc::launch_scale_pass(G, ldg, c->n, c->k, c->d, code, c->opts.scale_mode, c->ws, stream);
+            e = agc::launch_scale_pass(G, ldg, c->n, c->k, c->d, code, c->opts.scale_mode, c->ws, nullptr, stream);
         }
         if (e != hipSuccess) return hip_fail(c, e, "scale pass launch");
         if ((st = t.end()) != AGC_OK) return st;
@@ -841,6 +859,19 @@ agc_status agc_debug_sketch(agc_ctx* c, int mode)
     if (e != hipSuccess) return hip_fail(c, e, "hipDeviceSynchronize");
     c->sketch_mode = mode;
     e = update_sketch(c);
+    return e != hipSuccess && mode == 1 ? fail(c, AGC_ENOMEM, "workspace of the one-read form") : AGC_OK;
+}
+
+agc_status agc_debug_sketch_max(agc_ctx* c, int mode)
+{
+    if (!c || mode < 0 || mode > 2) return fail(nullptr, AGC_EINVAL, "null context or unknown mode");
+    if (c->opts.bucket || c->opts.scale_mode != AGC_SCALE_MAXABS)
+        return fail(c, AGC_EINVAL, "one scale of the whole vector, largest magnitude");
+    hipError_t e = hipDeviceSynchronize();
+    if (e != hipSuccess) return hip_fail(c, e, "hipDeviceSynchronize");
+    c->sketch_mode = mode;
+    e = update_sketch(c);
+    c->sk.limit = mode == 1 ? UINT32_MAX : agc::sketch_max_limit(c->k, agc::sample_count((c->d + 255) / 256));
     return e != hipSuccess && mode == 1 ? fail(c, AGC_ENOMEM, "workspace of the one-read form") : AGC_OK;
 }
 

@@ -878,4 +878,43 @@ __device__ __forceinline__ void encode_block(const float* __restrict__ G, int64_
     }
 }
 
+// epilogue for the largest-magnitude scale: exact and order-free
+struct EpiMaxAbs {
+    static constexpr bool kStoresPerWorker = false;
+    static constexpr bool kWantsZeros = true;
+    static constexpr int kPrefetchRows = AGC_SCALE_PREFETCH_ROWS;
+    uint32_t* acc;  // this wave's LDS slice [n], bit patterns of non-negative floats
+    int lane;
+    static __device__ __forceinline__ float max_abs4(const float4& f)
+    {
+        return fmaxf(fmaxf(fabsf(f.x), fabsf(f.y)), fmaxf(fabsf(f.z), fabsf(f.w)));
+    }
+    template <bool EVEN>
+    __device__ __forceinline__ void worker(int i, const float4& f)
+    {
+        const uint32_t m = wave_max_nonneg_bits(max_abs4(f));
+        if (lane == 0) acc[i] = m;
+    }
+    template <bool EVEN, int V>
+    __device__ __forceinline__ void worker(int i, const RowN<V>& f)  // V blocks, one reduction
+    {
+        float a = max_abs4(f.v[0]);
+#pragma unroll
+        for (int t = 1; t < V; ++t) a = fmaxf(a, max_abs4(f.v[t]));
+        const uint32_t m = wave_max_nonneg_bits(a);
+        if (lane == 0) acc[i] = m;
+    }
+    template <class Row>
+    __device__ __forceinline__ void worker_any(int i, const Row& f) { worker<true>(i, f); }
+};
+
+// multiplier of the grid positions: L_i * 2^16 / scale (2^15 / scale for a one-bit worker)
+__device__ __forceinline__ float inv16_of(float scale, int bits)
+{
+    if (!(scale > 0.f)) return 0.f;
+    const double num = bits >= 2 ? (double)((1 << (bits - 1)) - 1) * 65536.0 : 32768.0;
+    const float q = (float)(num / (double)scale);
+    return (q <= 3.402823466e+38f) ? q : 0.f;
+}
+
 }  // namespace agc

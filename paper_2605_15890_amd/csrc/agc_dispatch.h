@@ -125,19 +125,54 @@ inline bool use_sketch(int64_t d, int n, int k, double levels, bool gather, bool
     return (0.58 * k - 2.8) * m - 9.0 - 6e-6 * records - again > (gather ? 20.0 : 2.0);
 }
 
-// Bytes of the sketch's two large arrays, signs and records: 0.97 GB at 64 workers x 25.6 M, 15 % of G there and up to half of
-// G for four workers.
-inline int64_t sketch_bytes(int n, int64_t d)
+// One read of G for the largest magnitude (k_sketch_max).  Records a block has room for: half as many bytes, written and read, as
+// a second read of its rows, and no more than half of its coded elements.
+inline int sketch_max_cap(int n, int k)
 {
-    return (d + 255) / 256 * ((int64_t)((n + 31) / 32) * 1024 + 8 * (int64_t)sketch_cap(n));
+    const int room = 32 * k < 128 * n ? 32 * k : 128 * n;
+    return (room + 255) / 256 * 256;
 }
+// G of 4 GB and more, where what the sample, its bounds and three kernels that find nothing to do take (30 us) is little beside
+// what they save or fail to save.  Whether they save anything depends on the values, and the sample decides that on the device
+// (sketch_max_limit); the wider the codes, the fewer the values with which they do.  Whole steps, two reads | one, us: heavy tails (t,
+// three degrees), three bits on average, cyclic 64 workers x 25.6 M 2347 | 1823, 32 x 25.6 M 1150 | 862, 16 x 25.6 M 610 | 528,
+// 8 x 25.6 M 332 | 345, 64 x 6.4 M 609 | 532;  windows of 8 and more, 10 workers and 30 partitions x 25.6 M 1099 | 777;  gathered
+// 64 x 25.6 M 7166 | 4084;  sixty layers of magnitudes up to 1000 apart 64 x 25.6 M 2350 | 2100-2250, 40 x 25.6 M 1457 | 1387.
+// Values that are alike everywhere, which the sample refuses: 64 x 25.6 M 2347 | 2375, 64 x 6.4 M 607 | 627, 10 of 30 x 5.4 M
+// 247 | 265.  Four bits on average, forced: heavy tails 2411 | 2534, layers 2414 | 2742.
+// The vector fills the chip several times over, since the bounds rise with what has been read.  With more than 128 workers too few
+// workgroups fit a compute unit: 128 x 8.5 M 1599 | 1362, 256 x 5.3 M 2094 | 2177.
+inline bool use_sketch_max(int64_t d, int n, int k, double levels)
+{
+    return k >= 12 && n <= 128 && d >= 20480 * 256 && (int64_t)k * d >= (int64_t)1 << 30 && levels <= 16.0 * n;
+}
+// Of how many of the sampled blocks the sketch may have more records than there is room for.  What it saves, in us for a million
+// coordinates, is about 0.37 k - 3, less 0.75 k where every block overflows: 64 workers with 0.30 of the blocks left over
+// 2352 | 2172, with 0.35 2350 | 2247;  40 with 0.30 1457 | 1387;  20 with 0.33 740 | 767.
+inline uint32_t sketch_max_limit(int k, int samples)
+{
+    const double share = 0.45 - 4.0 / k;
+    return share > 0.0 ? (uint32_t)(share * samples) : 0u;
+}
+
+// Bytes of the sketch's two large arrays, signs and records: 0.97 GB at 64 workers x 25.6 M, 15 % of G there and up to half of
+// G for four workers;  for the largest magnitude 1.9 GB, 28 %.
+inline int64_t sketch_bytes(int n, int64_t d, int cap)
+{
+    return (d + 255) / 256 * ((int64_t)((n + 31) / 32) * 1024 + 8 * (int64_t)cap);
+}
+inline int64_t sketch_bytes(int n, int64_t d) { return sketch_bytes(n, d, sketch_cap(n)); }
 // A context takes them only beside a G that leaves half of the card to the rest of the program (the context may be made
 // first), and no more than an eighth of what is free: a program that fills the card keeps the form with two reads and the
 // memory that it had.
+inline bool sketch_fits(int n, int k, int64_t d, size_t free_bytes, size_t total_bytes, int cap)
+{
+    const double bytes = (double)sketch_bytes(n, d, cap);
+    return bytes + 4.0 * k * (double)d <= 0.5 * (double)total_bytes && bytes <= 0.125 * (double)free_bytes;
+}
 inline bool sketch_fits(int n, int k, int64_t d, size_t free_bytes, size_t total_bytes)
 {
-    const double bytes = (double)sketch_bytes(n, d);
-    return bytes + 4.0 * k * (double)d <= 0.5 * (double)total_bytes && bytes <= 0.125 * (double)free_bytes;
+    return sketch_fits(n, k, d, free_bytes, total_bytes, sketch_cap(n));
 }
 
 // The blocks that the bounds of the scales are estimated from: one of each of `samples` runs of equal length (up to one

@@ -166,13 +166,19 @@ struct SketchDev {
     int* counts;          // [4 * groups of four blocks] records of the block; -1: there were more than cap
     float* lo_scale;      // [n] lower bounds of the scales, and the largest multipliers that they leave
     float* lo_mult;       // [n]
-    uint32_t* state;      // [2] not 0: a bound did not hold, or a weight is not finite;  length of the list
+    uint32_t* state;      // [3] not 0: a bound did not hold, or a weight is not finite, or there is no sketch;  length of the
+                          // list;  largest magnitude: sampled blocks that would overflow, 0 between steps
+    uint32_t limit;       // largest magnitude: with more of them G is read twice after all
     uint32_t* left;       // [groups of four blocks] list of those that k_resolve leaves to k_quantize, in any order
+    int64_t blocks;       // entries of counts
     int cap;              // even
     int chunks;           // ceil(n / 32)
 };
 // LDS of a k_sketch workgroup: [4][n] doubles, [4][chunks] KB of signs, [4][cap] records
 constexpr unsigned sketch_lds_bytes(int n, int cap) { return 32u * n + 4096u * ((n + 31) / 32) + 32u * cap; }
+
+// LDS of a k_sketch_max workgroup: for each of its waves a ring of 512 records, [chunks] KB of signs, [n] maxima and multipliers
+constexpr unsigned sketch_max_lds_bytes(int n) { return 4u * (4096u + 1024u * ((n + 31) / 32) + 8u * ((n + 1) / 2 * 2)); }
 
 constexpr int kMaxSlots = 256;  // rows of the max-abs array; a block folds into row (block mod kMaxSlots)
 constexpr int kMaxLayers = 256;  // layer-wise scales: a block's layer fits a byte
@@ -184,6 +190,10 @@ struct QuantStreams {      // host arrays of the encode call
     uint16_t stage_start[kArgWorkers];  // stage_starts() of the bit-widths
     int stage_fills, stage_bits;        // and what it returns: fills, the fullest one in bits
     bool parts;                         // the quantize pass shares the workers of a block among the waves
+};
+
+struct BitList {           // bit-widths as a kernel argument
+    uint8_t bits[kArgWorkers];
 };
 
 struct StepWeights {       // decode side of a fused step
@@ -230,7 +240,7 @@ struct DecodeList {        // the same as kernel arguments of the decode's prolo
 // with layer-wise scales; Euclidean: per-segment sums of squares).  scale_mode: 0 Euclidean, 1 max-abs.
 hipError_t launch_scale_pass(const float* G, int64_t ldg, int n, int k, int64_t d,
                              const CodeDev& code, int scale_mode, const Workspace& ws,
-                             hipStream_t stream);
+                             const SketchDev* sk, hipStream_t stream);
 // all rows of the max-abs slot array back to zero
 hipError_t launch_scale_clear_slots(int n, const Workspace& ws, hipStream_t stream);
 // K1f: partials -> scales[n] and the per-worker table of the quantize pass (with layer-wise scales:
@@ -246,6 +256,11 @@ hipError_t launch_sketch_bounds(const float* G, int64_t ldg, int n, int k, int64
                                 uint64_t step, hipStream_t stream);
 hipError_t launch_sketch(const float* G, int64_t ldg, int n, int k, int64_t d, const CodeDev& code, const Workspace& ws,
                          const SketchDev& sk, uint64_t seed, uint64_t step, hipStream_t stream);
+hipError_t launch_sketch_bounds_max(const float* G, int64_t ldg, int n, int k, int64_t d, const CodeDev& code, const Workspace& ws,
+                             const SketchDev& sk, const QuantStreams& out, uint64_t seed, uint64_t step, hipStream_t stream);
+// One read of G for the largest magnitude of the whole vector; the scales' partial results are in the first row of ws.part_max.
+hipError_t launch_sketch_max(const float* G, int64_t ldg, int n, int k, int64_t d, const CodeDev& code, const Workspace& ws,
+                             const SketchDev& sk, const QuantStreams& out, uint64_t seed, uint64_t step, hipStream_t stream);
 // codes (and with ghat the estimate) of the sketch; launch_quantize with sk makes those of the groups it leaves
 hipError_t launch_resolve(int n, int64_t d, const Workspace& ws, const SketchDev& sk, const QuantStreams& out, uint64_t seed,
                           uint64_t step, float* ghat, hipStream_t stream);

@@ -41,44 +41,17 @@ struct ScaleArgs {
     const uint8_t* block_layer;  // layer-wise scales only (max-abs): the layer of every block
     const int* seg_first;        // layer-wise Euclidean scales only: the segments of the layers
     const uint8_t* seg_blocks;
+    const uint32_t* full;        // COND: nothing to do where this word is at most `limit` (the sketch serves the step)
+    uint32_t limit;
 };
 
 // the same 32-bit word seen as device memory (store without address-space checks)
 typedef __attribute__((address_space(1))) uint32_t global_word;
 
-// epilogue for the largest-magnitude scale: exact and order-free
-struct EpiMaxAbs {
-    static constexpr bool kStoresPerWorker = false;
-    static constexpr bool kWantsZeros = true;
-    static constexpr int kPrefetchRows = AGC_SCALE_PREFETCH_ROWS;
-    uint32_t* acc;  // this wave's LDS slice [n], bit patterns of non-negative floats
-    int lane;
-    static __device__ __forceinline__ float max_abs4(const float4& f)
-    {
-        return fmaxf(fmaxf(fabsf(f.x), fabsf(f.y)), fmaxf(fabsf(f.z), fabsf(f.w)));
-    }
-    template <bool EVEN>
-    __device__ __forceinline__ void worker(int i, const float4& f)
-    {
-        const uint32_t m = wave_max_nonneg_bits(max_abs4(f));
-        if (lane == 0) acc[i] = m;
-    }
-    template <bool EVEN, int V>
-    __device__ __forceinline__ void worker(int i, const RowN<V>& f)  // V blocks, one reduction
-    {
-        float a = max_abs4(f.v[0]);
-#pragma unroll
-        for (int t = 1; t < V; ++t) a = fmaxf(a, max_abs4(f.v[t]));
-        const uint32_t m = wave_max_nonneg_bits(a);
-        if (lane == 0) acc[i] = m;
-    }
-    template <class Row>
-    __device__ __forceinline__ void worker_any(int i, const Row& f) { worker<true>(i, f); }
-};
-
 // epilogue for the Euclidean scale: levels 0 and 1 of the binary64 summation tree (lane value
 // (x0^2+x1^2)+(x2^2+x3^2); exchange-add across the 64 lanes)
 struct EpiSumSq {
+    typedef double Part, Sum;
     static constexpr bool kStoresPerWorker = false;
     static constexpr bool kWantsZeros = true;
     static constexpr int kPrefetchRows = AGC_SCALE_PREFETCH_ROWS;
@@ -121,7 +94,7 @@ constexpr int64_t kTwoBlockMin = 2 * 2 * 256 * 4 * 5;
 // cost far more than their bytes on this memory system; even the atomics, performed in memory,
 // cost 22 us at one per wave and worker).  The finalize kernel reads the rows and hands them back
 // zeroed.
-template <int S, int MODE, int WAVES, int V>
+template <int S, int MODE, int WAVES, int V, bool COND = false>
 __global__ __launch_bounds__(kWave * WAVES) void k_scale_pass(const float* __restrict__ G,
                                                               const int* __restrict__ row_ptr,
                                                               const int* __restrict__ col,
@@ -131,6 +104,9 @@ __global__ __launch_bounds__(kWave * WAVES) void k_scale_pass(const float* __res
     static_assert(MODE == 1 || (WAVES == kSegBlocks && V == 1), "the norm's tree fixes four blocks per workgroup");
     static_assert(V == 1 || V == 2 || V == 4, "one, two or four blocks per wave");
     __shared__ double lds_acc[WAVES][kMaxWorkers];
+    if constexpr (COND) {
+        if (load_uniform(a.full) <= a.limit) return;
+    }
     // the wave index is the same for all lanes: tell the compiler, so that everything derived
     // from it (block base, pointers) lives in scalar registers
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -325,8 +301,9 @@ static void launch_scale_max(const float* G, const CodeDev& code, const ScaleArg
     constexpr int W = (V > 1 && S >= 7) ? 4 : AGC_SCALE_WAVES;
     const int64_t nblocks = (a.d + kBlockCoords - 1) / kBlockCoords;
     const int64_t per_wg = (int64_t)W * V;
-    hipLaunchKernelGGL((k_scale_pass<S, 1, W, V>), dim3((unsigned)((nblocks + per_wg - 1) / per_wg)), dim3(kWave * W),
-                       0, stream, G, code.row_ptr, code.col, code.val, a);
+    const dim3 g((unsigned)((nblocks + per_wg - 1) / per_wg)), b(kWave * W);
+    if (a.full) hipLaunchKernelGGL((k_scale_pass<S, 1, W, V, true>), g, b, 0, stream, G, code.row_ptr, code.col, code.val, a);
+    else hipLaunchKernelGGL((k_scale_pass<S, 1, W, V>), g, b, 0, stream, G, code.row_ptr, code.col, code.val, a);
 }
 
 template <int S>
@@ -357,12 +334,12 @@ static hipError_t launch_scale_pass_s(const float* G, const CodeDev& code, const
 
 hipError_t launch_scale_pass(const float* G, int64_t ldg, int n, int k, int64_t d,
                              const CodeDev& code, int scale_mode, const Workspace& ws,
-                             hipStream_t stream)
+                             const SketchDev* sk, hipStream_t stream)
 {
     const bool layers = ws.n_layers > 0;
     ScaleArgs a{ldg, n, k, d, layers && scale_mode == 0 ? ws.nseg_layers : ws.nseg, ws.part_max, ws.part_sq, code.win,
                 layers && scale_mode == 1 ? ws.block_layer : nullptr,
-                layers && scale_mode == 0 ? ws.seg_first : nullptr, layers && scale_mode == 0 ? ws.seg_blocks : nullptr};
+                layers && scale_mode == 0 ? ws.seg_first : nullptr, layers && scale_mode == 0 ? ws.seg_blocks : nullptr, sk ? sk->state + 2 : nullptr, sk ? sk->limit : 0u};
     if (code.band < 0 && !code.win) return hipErrorInvalidValue;  // the window driver reads the records
     switch (code.band) {
         case 1: return launch_scale_pass_s<1>(G, code, a, scale_mode, stream);
@@ -383,14 +360,6 @@ hipError_t launch_scale_pass(const float* G, int64_t ldg, int n, int k, int64_t 
 // =======================================================================================
 // K1f  scale finalize: one workgroup per worker
 // =======================================================================================
-__device__ __forceinline__ float inv16_of(float scale, int bits)
-{
-    if (!(scale > 0.f)) return 0.f;
-    const double num = bits >= 2 ? (double)((1 << (bits - 1)) - 1) * 65536.0 : 32768.0;
-    const float q = (float)(num / (double)scale);
-    return (q <= 3.402823466e+38f) ? q : 0.f;
-}
-
 // acc = acc + rows b0, b0 + 1, .. of part, BATCH of them or up to s1; past s1 the last row is read again
 template <int BATCH>
 __device__ __forceinline__ void add_rows(const double* part, int n, int64_t b0, int64_t s1, double& acc)
@@ -443,10 +412,11 @@ __device__ __forceinline__ float unit_weight(float w, float scale, int b)
     return (float)(((double)w * (double)scale) / L);
 }
 
-// The lower bounds that the sketch was made with, to be checked (null: there is none).
+// What the finalize kernel checks of a sketch (state null: there is none).
 struct SketchCheck {
-    const float* lo_scale;
+    const float* lo_scale;  // Euclidean: the lower bounds that it was made with
     uint32_t* state;
+    uint32_t limit;         // largest magnitude: with state[2] above this there is no sketch
 };
 
 // One workgroup per worker (and layer, with the Euclidean scale).
@@ -507,7 +477,12 @@ __global__ __launch_bounds__(kWgThreads) void k_scale_finalize(int n, QuantList<
         const WorkerQ q = worker_record(in, i, n, inv16_of(scale, b), unit_weight(in.w[i], scale, b));
         ws.wq[(int64_t)l * n + i] = q;
         // a weight that is not finite makes NaN of zero levels too, which k_resolve does not add up
-        if (MODE == 0 && check.state && !(scale >= check.lo_scale[i] && fabsf(q.coef) < __builtin_inff()))
+        bool none = false;
+        if (MODE == 1 && check.state && i == 0) {
+            none = check.state[2] > check.limit;
+            check.state[2] = 0u;  // the next step's
+        }
+        if (check.state && !(!none && (MODE == 1 || scale >= check.lo_scale[i]) && fabsf(q.coef) < __builtin_inff()))
             (void)__hip_atomic_fetch_or(check.state, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
@@ -554,7 +529,7 @@ template <int CAP>
 static hipError_t launch_scale_finalize_cap(int n, int scale_mode, const QuantStreams& out, const StepWeights& sw,
                                             const Workspace& ws, const SketchDev* sk, float* scales, hipStream_t stream)
 {
-    const SketchCheck check = sk ? SketchCheck{sk->lo_scale, sk->state} : SketchCheck{nullptr, nullptr};
+    const SketchCheck check = sk ? SketchCheck{sk->lo_scale, sk->state, sk->limit} : SketchCheck{nullptr, nullptr, 0u};
     const QuantList<CAP> q = quant_list<CAP>(n, out, sw);
     const int layers = ws.n_layers;
     if (scale_mode == 1) {
@@ -603,6 +578,26 @@ __device__ __forceinline__ float4 encode_staged_one(const float4* rows, const Cs
     return f;
 }
 
+// all rows of a block into LDS, requested together
+__device__ __forceinline__ void stage_rows(const float* __restrict__ G, int64_t ldg, int k, const LaneCoords& lc, int wave, int lane,
+                                           float4* rows)
+{
+    for (int j0 = wave; j0 < k; j0 += 4 * kSampleWaves) {
+        float4 r[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int j = j0 + t * kSampleWaves;
+            r[t] = load_row4<true>(G + (int64_t)(j < k ? j : k - 1) * ldg, lc);
+        }
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int j = j0 + t * kSampleWaves;
+            if (j < k) rows[j * kWave + lane] = r[t];
+        }
+    }
+    __syncthreads();
+}
+
 // What bounds it: latency, one block per workgroup and all workgroups resident at once.  S > 0: the register ring.  Other codes
 // with STAGED: all rows of the block are requested at once and wait in LDS, where each wave takes its workers' from; else
 // rows are gathered from memory (more rows than LDS holds).  64 workers x 25.6 M, window of 8: the window driver, whose
@@ -610,53 +605,74 @@ __device__ __forceinline__ float4 encode_staged_one(const float4* rows, const Cs
 // 39.0, staged 11.2;  50 x 5.4 M 19.9 | 8.4;  10 workers of 30 partitions, gathered 8.4, staged 5.9.  The ring of a cyclic band
 // is the faster one: 64 x 1 M 5.6, staged 7.1, 32 x 11.7 M 6.2 and 8.0.  Code entries one a lane instead of scalar loads,
 // a worker ahead: 13.2 for 11.2.
-template <int S, bool STAGED>
+// What the sample keeps of a block and worker for the largest-magnitude scale: the largest magnitude and the sum of all
+struct EpiTopSum {
+    typedef float2 Part;
+    typedef float Sum;
+    static constexpr bool kStoresPerWorker = false;
+    static constexpr bool kWantsZeros = true;
+    static constexpr int kPrefetchRows = AGC_SCALE_PREFETCH_ROWS;
+    float2* acc;
+    int lane;
+    template <bool EVEN>
+    __device__ __forceinline__ void worker(int i, const float4& f)
+    {
+        const uint32_t m = wave_max_nonneg_bits(EpiMaxAbs::max_abs4(f));
+        float s = (fabsf(f.x) + fabsf(f.y)) + (fabsf(f.z) + fabsf(f.w));
+        s += __uint_as_float(dpp_u32<kDppQuadSwap1>(__float_as_uint(s)));
+        s += __uint_as_float(dpp_u32<kDppQuadSwap2>(__float_as_uint(s)));
+        s += __uint_as_float(dpp_u32<kDppHalfMirror>(__float_as_uint(s)));
+        s += __uint_as_float(dpp_u32<kDppRowMirror>(__float_as_uint(s)));
+        const uint32_t v = __float_as_uint(s);
+        s = (__uint_as_float(__builtin_amdgcn_readlane(v, 0)) + __uint_as_float(__builtin_amdgcn_readlane(v, 16))) +
+            (__uint_as_float(__builtin_amdgcn_readlane(v, 32)) + __uint_as_float(__builtin_amdgcn_readlane(v, 48)));
+        if (lane == 0) acc[i] = make_float2(__uint_as_float(m), s);
+    }
+    __device__ __forceinline__ void worker_any(int i, const float4& f) { worker<true>(i, f); }
+};
+
+constexpr int kBoundRows = 16;  // rows of the array of running maxima that the sample is folded into
+
+// sums: [sample][worker], sums of squares or of magnitudes; maxima go to the first rows of a.part_max
+template <int S, bool STAGED, class Epi>
 __global__ __launch_bounds__(kWave * kSampleWaves) void k_sketch_sample(const float* __restrict__ G, const int* __restrict__ row_ptr,
                                                                         const int* __restrict__ col, const float* __restrict__ val,
-                                                                        ScaleArgs a, SampleRuns runs)
+                                                                        ScaleArgs a, SampleRuns runs, typename Epi::Sum* sums)
 {
     extern __shared__ __attribute__((aligned(16))) float4 lds_rows[];  // STAGED: [k][64]
-    __shared__ double lds_sq[kMaxWorkers];
+    __shared__ typename Epi::Part lds_part[kMaxWorkers];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int lane = threadIdx.x % kWave;
     const int64_t base = sample_block(runs, blockIdx.x) * kBlockCoords;
     const LaneCoords lc = lane_coords(base, lane, a.d);
     const CsrView B{row_ptr, col, val, nullptr};
-    EpiSumSq epi{lds_sq, lane};
+    Epi epi{lds_part, lane};
+    auto hand_in = [&](int i) {
+        if constexpr (std::is_same<Epi, EpiTopSum>::value) {
+            (void)__hip_atomic_fetch_max(a.part_max + (blockIdx.x % kBoundRows) * a.n + i, __float_as_uint(lds_part[i].x),
+                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            sums[(int64_t)blockIdx.x * a.n + i] = lds_part[i].y;
+        } else {
+            sums[(int64_t)blockIdx.x * a.n + i] = lds_part[i];
+        }
+    };
     if constexpr (S > 0) {
         const int size = ((a.n + kSampleWaves - 1) / kSampleWaves + 1) / 2 * 2;
         const int i0 = wave * size, i1 = i0 + size < a.n ? i0 + size : a.n;
         encode_block_part<S>(G + base, a.ldg, a.k, B, lc, i0, i1, epi);
-        for (int i = i0 + lane; i < i1; i += kWave) a.part_sq[(int64_t)blockIdx.x * a.n + i] = lds_sq[i];  // of this wave's lane 0
+        for (int i = i0 + lane; i < i1; i += kWave) hand_in(i);  // of this wave's lane 0
         return;
     }
     if constexpr (STAGED) {
-        for (int j0 = wave; j0 < a.k; j0 += 4 * kSampleWaves) {
-            float4 r[4];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int j = j0 + t * kSampleWaves;
-                r[t] = load_row4<true>(G + base + (int64_t)(j < a.k ? j : a.k - 1) * a.ldg, lc);
-            }
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int j = j0 + t * kSampleWaves;
-                if (j < a.k) lds_rows[j * kWave + lane] = r[t];
-            }
-        }
-        __syncthreads();
+        stage_rows(G + base, a.ldg, a.k, lc, wave, lane, lds_rows);
     }
     for (int i = wave; i < a.n; i += kSampleWaves) {
         const float4 f = STAGED ? encode_staged_one(lds_rows, B, i, lane) : encode_gather_one(G + base, a.ldg, B, i, lc);
-        epi.worker<true>(i, valid_coords(f, lc.nvalid));
+        epi.template worker<true>(i, valid_coords(f, lc.nvalid));
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < a.n; i += kWave * kSampleWaves) a.part_sq[(int64_t)blockIdx.x * a.n + i] = lds_sq[i];
+    for (int i = threadIdx.x; i < a.n; i += kWave * kSampleWaves) hand_in(i);
 }
-
-struct BitList {
-    uint8_t bits[kArgWorkers];
-};
 
 __global__ __launch_bounds__(kWgThreads) void k_sketch_bounds(int n, BitList in, const double* part_sq, int samples,
                                                               double times, SketchDev sk)
@@ -692,12 +708,77 @@ __global__ __launch_bounds__(kWgThreads) void k_sketch_bounds(int n, BitList in,
     }
 }
 
-template <int S, bool STAGED>
-static void launch_sketch_sample_s(const float* G, const CodeDev& code, const ScaleArgs& a, int samples, const SampleRuns& runs,
-                                   hipStream_t stream)
+// The same for the largest-magnitude scale, whose bounds always hold, and whether the sketch is worth making: of how many of the
+// sampled blocks it would have more records than there is room for.  A coordinate becomes one with a probability of
+// L |f| / bound.  The bounds rise as k_sketch_max goes on (heavy tails: to three and more times those of the sample), so a block
+// may have a quarter more than the room.  The bounds go to the first row of the array of running maxima.
+constexpr int kBoundsWgs = 16;
+constexpr int kBoundsThreads = 1024;
+__global__ __launch_bounds__(kBoundsThreads) void k_sketch_bounds_max(int n, BitList in, const float* __restrict__ sums, int samples,
+                                                                      uint32_t* part_max, SketchDev sk)
 {
-    hipLaunchKernelGGL((k_sketch_sample<S, STAGED>), dim3(samples), dim3(kWave * kSampleWaves),
-                       STAGED ? sizeof(float4) * kWave * a.k : 0, stream, G, code.row_ptr, code.col, code.val, a, runs);
+    __shared__ float per_sum[kMaxWorkers];  // expected records for each of a block's sum of magnitudes
+    const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+    if (tid < n) {
+        uint32_t m[kBoundRows];
+#pragma unroll
+        for (int t = 0; t < kBoundRows; ++t) m[t] = __hip_atomic_load(part_max + t * n + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int t = 1; t < kBoundRows; ++t) m[0] = max(m[0], m[t]);
+        per_sum[tid] = m[0] != 0u ? (float)((1 << (in.bits[tid] - 1)) - 1) / __uint_as_float(m[0]) : 0.f;
+        if (blockIdx.x == 0) (void)__hip_atomic_fetch_max(part_max + tid, m[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    uint32_t full = 0u;
+    for (int e = blockIdx.x + wave * kBoundsWgs; e < samples; e += kBoundsWgs * (kBoundsThreads / kWave)) {
+        float records = 0.f;
+        for (int j = lane; j < n; j += kWave) {
+            const float r = sums[(int64_t)e * n + j] * per_sum[j];
+            records += r < (float)kBlockCoords ? r : (float)kBlockCoords;
+        }
+#pragma unroll
+        for (int h = 1; h < kWave; h *= 2) records += __shfl_xor(records, h);
+        full += records > 1.25f * (float)sk.cap ? 1u : 0u;
+    }
+    if (lane == 0 && full != 0u) (void)__hip_atomic_fetch_add(sk.state + 2, full, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (blockIdx.x == 0 && tid == 0) sk.state[0] = sk.state[1] = 0u;
+}
+
+template <int S, bool STAGED, class Epi>
+static void launch_sketch_sample_s(const float* G, const CodeDev& code, const ScaleArgs& a, int samples, const SampleRuns& runs,
+                                   typename Epi::Sum* sums, hipStream_t stream)
+{
+    hipLaunchKernelGGL((k_sketch_sample<S, STAGED, Epi>), dim3(samples), dim3(kWave * kSampleWaves),
+                       STAGED ? sizeof(float4) * kWave * a.k : 0, stream, G, code.row_ptr, code.col, code.val, a, runs, sums);
+}
+
+template <class Epi>
+static hipError_t launch_sketch_sample(const float* G, int64_t ldg, int n, int k, int64_t d, const CodeDev& code, int samples,
+                                       uint64_t seed, uint64_t step, uint32_t* part_max, typename Epi::Sum* sums, hipStream_t stream)
+{
+    const SampleRuns runs = sample_runs((d + kBlockCoords - 1) / kBlockCoords, samples, seed, step);
+    const ScaleArgs a{ldg, n, k, d, 0, part_max, nullptr, code.win, nullptr, nullptr, nullptr, nullptr, 0u};
+    switch (code.band) {
+        case 1: launch_sketch_sample_s<1, false, Epi>(G, code, a, samples, runs, sums, stream); break;
+        case 2: launch_sketch_sample_s<2, false, Epi>(G, code, a, samples, runs, sums, stream); break;
+        case 3: launch_sketch_sample_s<3, false, Epi>(G, code, a, samples, runs, sums, stream); break;
+        case 4: launch_sketch_sample_s<4, false, Epi>(G, code, a, samples, runs, sums, stream); break;
+        case 5: launch_sketch_sample_s<5, false, Epi>(G, code, a, samples, runs, sums, stream); break;
+        case 6: launch_sketch_sample_s<6, false, Epi>(G, code, a, samples, runs, sums, stream); break;
+        case 7: launch_sketch_sample_s<7, false, Epi>(G, code, a, samples, runs, sums, stream); break;
+        case 8: launch_sketch_sample_s<8, false, Epi>(G, code, a, samples, runs, sums, stream); break;
+        default:
+            if (k <= kSampleRows) launch_sketch_sample_s<0, true, Epi>(G, code, a, samples, runs, sums, stream);
+            else launch_sketch_sample_s<0, false, Epi>(G, code, a, samples, runs, sums, stream);
+    }
+    return hipGetLastError();
+}
+
+static BitList bit_list(int n, const QuantStreams& out)
+{
+    BitList bits;
+    for (int i = 0; i < kArgWorkers; ++i) bits.bits[i] = i < n ? out.bits[i] : 0;
+    return bits;
 }
 
 hipError_t launch_sketch_bounds(const float* G, int64_t ldg, int n, int k, int64_t d, const CodeDev& code,
@@ -707,27 +788,24 @@ hipError_t launch_sketch_bounds(const float* G, int64_t ldg, int n, int k, int64
     // the partial sums' array is their scratch, which has a row for every four blocks
     const int64_t nblocks = (d + kBlockCoords - 1) / kBlockCoords;
     const int samples = sample_count(nblocks);
-    const SampleRuns runs = sample_runs(nblocks, samples, seed, step);
-    const ScaleArgs a{ldg, n, k, d, 0, nullptr, ws.part_sq, code.win, nullptr, nullptr, nullptr};
-    switch (code.band) {
-        case 1: launch_sketch_sample_s<1, false>(G, code, a, samples, runs, stream); break;
-        case 2: launch_sketch_sample_s<2, false>(G, code, a, samples, runs, stream); break;
-        case 3: launch_sketch_sample_s<3, false>(G, code, a, samples, runs, stream); break;
-        case 4: launch_sketch_sample_s<4, false>(G, code, a, samples, runs, stream); break;
-        case 5: launch_sketch_sample_s<5, false>(G, code, a, samples, runs, stream); break;
-        case 6: launch_sketch_sample_s<6, false>(G, code, a, samples, runs, stream); break;
-        case 7: launch_sketch_sample_s<7, false>(G, code, a, samples, runs, stream); break;
-        case 8: launch_sketch_sample_s<8, false>(G, code, a, samples, runs, stream); break;
-        default:
-            if (k <= kSampleRows) launch_sketch_sample_s<0, true>(G, code, a, samples, runs, stream);
-            else launch_sketch_sample_s<0, false>(G, code, a, samples, runs, stream);
-    }
-    const hipError_t e = hipGetLastError();
+    const hipError_t e = launch_sketch_sample<EpiSumSq>(G, ldg, n, k, d, code, samples, seed, step, nullptr, ws.part_sq, stream);
     if (e != hipSuccess) return e;
-    BitList bits;
-    for (int i = 0; i < kArgWorkers; ++i) bits.bits[i] = i < n ? out.bits[i] : 0;
-    hipLaunchKernelGGL(k_sketch_bounds, dim3(n), dim3(kWgThreads), 0, stream, n, bits, ws.part_sq, samples,
+    hipLaunchKernelGGL(k_sketch_bounds, dim3(n), dim3(kWgThreads), 0, stream, n, bit_list(n, out), ws.part_sq, samples,
                        (double)nblocks / (double)samples, sk);
+    return hipGetLastError();
+}
+
+hipError_t launch_sketch_bounds_max(const float* G, int64_t ldg, int n, int k, int64_t d, const CodeDev& code,
+                                    const Workspace& ws, const SketchDev& sk, const QuantStreams& out, uint64_t seed,
+                                    uint64_t step, hipStream_t stream)
+{
+    // the records' array is scratch: four bytes for a worker and sample, of which there are no more than blocks, in a room of
+    // at least 2048 bytes a block (256 records)
+    const int samples = sample_count((d + kBlockCoords - 1) / kBlockCoords);
+    float* sums = reinterpret_cast<float*>(sk.recs);
+    const hipError_t e = launch_sketch_sample<EpiTopSum>(G, ldg, n, k, d, code, samples, seed, step, ws.part_max, sums, stream);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_sketch_bounds_max, dim3(kBoundsWgs), dim3(kBoundsThreads), 0, stream, n, bit_list(n, out), sums, samples, ws.part_max, sk);
     return hipGetLastError();
 }
 
