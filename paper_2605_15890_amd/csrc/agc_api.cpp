@@ -99,7 +99,7 @@ void free_layers(agc_ctx* c)
 
 void free_sketch(agc_ctx* c)
 {
-    void* all[] = {c->sk.planes, c->sk.recs, c->sk.counts, c->sk.lo_scale, c->sk.lo_mult, c->sk.state, c->sk.left};
+    void* all[] = {c->sk.planes, c->sk.recs, c->sk.counts, c->sk.lo_scale, c->sk.lo_mult, c->sk.state, c->sk.left, c->sk.table};
     for (void* p : all)
         if (p) (void)hipFree(p);
     c->sk = agc::SketchDev{};
@@ -130,6 +130,7 @@ hipError_t alloc_sketch(agc_ctx* c)
     if (e == hipSuccess) e = hipMemset(sk.state, 0, 3 * sizeof(uint32_t));
     if (e == hipSuccess) e = hipDeviceSynchronize();  // the next step may run on any stream
     if (e == hipSuccess) e = dev_alloc(&sk.left, (size_t)c->ws.nseg);
+    if (e == hipSuccess) e = dev_alloc(&sk.table, (size_t)c->n);
     if (e != hipSuccess) {
         (void)hipGetLastError();  // not the caller's
         free_sketch(c);
@@ -604,6 +605,7 @@ agc_status encode_quantize_impl(agc_ctx* c, const float* G, int64_t ldg, const u
     qs.parts = code.parts && sum_bits <= agc::kPartBits && !sk;
     qs.stage_fills = agc::stage_starts(qs.bits, c->n, qs.parts ? agc::kPartBits : agc::stage_limit(c->n, c->opts.bucket != 0),
                                        qs.stage_start, &qs.stage_bits);
+    if (sk) (void)agc::stage_starts(qs.bits, c->n, agc::resolve_limit(c->n, ghat != nullptr), qs.resolve_start, &qs.resolve_bits);
     hipError_t e;
     if (c->opts.bucket) {  // one pass: every block finds its own scale
         KernelTimer t{c, 2, stream};

@@ -93,6 +93,24 @@ inline int stage_starts(const uint8_t* bits, int n, int limit, uint16_t* start, 
     return fills;
 }
 
+// The same area of k_resolve, in fills of its own.  LDS of a workgroup: the area in pieces of 16 bytes, a record of 16 bytes and four
+// blocks' signs for every worker, and with the estimate a sum and a claim for each of its 1024 coordinates.
+constexpr int resolve_pieces(int stage_bits) { return 8 * stage_bits + 1; }
+constexpr unsigned resolve_lds_bytes(int n, int stage_bits, bool fuse)
+{
+    return 16u * (unsigned)(resolve_pieces(stage_bits) + n) + 16u * (unsigned)(8 * n + 8) + (fuse ? 8192u : 0u);
+}
+// Bits of a fill: what leaves room for six workgroups on a compute unit, which is what its registers allow too (k_resolve, us,
+// five | six | seven at 64 workers x 25.6 M: heavy tails, largest magnitude 404 | 374 | 425, Euclidean 245 | 232 | 282;  50 x 5.4 M,
+// 300 bits, without estimate 86 | 84 | 78), but no less than 48, where that many do not fit.
+constexpr int kResolveWgs = 6;
+constexpr int resolve_limit(int n, bool fuse)
+{
+    const int room = 160 * 1024 / kResolveWgs / 1280 * 1280, rest = (int)resolve_lds_bytes(n, 0, fuse);
+    const int bits = (room - rest) / 128;
+    return bits < 48 ? 48 : bits;
+}
+
 // Short vectors (use_parts): the codes of one block wait in LDS in a single fill, 32 bytes per bit of width: all
 // 256 workers at four bits or 64 at sixteen.
 constexpr int kPartBits = 1024;
@@ -169,6 +187,8 @@ struct SketchDev {
     uint32_t* state;      // [3] not 0: a bound did not hold, or a weight is not finite, or there is no sketch;  length of the
                           // list;  largest magnitude: sampled blocks that would overflow, 0 between steps
     uint32_t limit;       // largest magnitude: with more of them G is read twice after all
+    uint4* table;         // [n] what k_resolve needs to know of a worker: multiplier, weight, bits with 256 arrived and 512 end of a
+                          // fill, first word in the staging area
     uint32_t* left;       // [groups of four blocks] list of those that k_resolve leaves to k_quantize, in any order
     int64_t blocks;       // entries of counts
     int cap;              // even
@@ -189,6 +209,8 @@ struct QuantStreams {      // host arrays of the encode call
     uint8_t bits[kArgWorkers];
     uint16_t stage_start[kArgWorkers];  // stage_starts() of the bit-widths
     int stage_fills, stage_bits;        // and what it returns: fills, the fullest one in bits
+    uint16_t resolve_start[kArgWorkers];  // and for the fills of k_resolve, where it runs
+    int resolve_bits;
     bool parts;                         // the quantize pass shares the workers of a block among the waves
 };
 
@@ -207,7 +229,7 @@ struct QuantList {         // both as kernel arguments of the table kernels, for
     void* codes[CAP];
     float w[CAP];
     uint8_t bits[CAP];
-    uint16_t stage_start[CAP];
+    uint16_t stage_start[CAP], resolve_start[CAP];
     uint8_t arrived[CAP];
     int fuse;
 };

@@ -417,6 +417,7 @@ struct SketchCheck {
     const float* lo_scale;  // Euclidean: the lower bounds that it was made with
     uint32_t* state;
     uint32_t limit;         // largest magnitude: with state[2] above this there is no sketch
+    uint4* table;           // k_resolve's
 };
 
 // One workgroup per worker (and layer, with the Euclidean scale).
@@ -477,6 +478,10 @@ __global__ __launch_bounds__(kWgThreads) void k_scale_finalize(int n, QuantList<
         const WorkerQ q = worker_record(in, i, n, inv16_of(scale, b), unit_weight(in.w[i], scale, b));
         ws.wq[(int64_t)l * n + i] = q;
         // a weight that is not finite makes NaN of zero levels too, which k_resolve does not add up
+        if (check.state) {
+            const uint32_t ends = i == n - 1 || in.resolve_start[i + 1] == 0 ? 512u : 0u;
+            check.table[i] = make_uint4(__float_as_uint(q.inv16), __float_as_uint(q.coef), q.bits | (q.arrived << 8) | ends, 32u * in.resolve_start[i]);
+        }
         bool none = false;
         if (MODE == 1 && check.state && i == 0) {
             none = check.state[2] > check.limit;
@@ -519,6 +524,7 @@ static QuantList<CAP> quant_list(int n, const QuantStreams& out, const StepWeigh
         q.codes[i] = out.codes[i];
         q.bits[i] = out.bits[i];
         q.stage_start[i] = out.stage_start[i];
+        q.resolve_start[i] = out.resolve_start[i];
         q.w[i] = sw.fuse ? sw.w[i] : 0.f;
         q.arrived[i] = sw.fuse ? sw.arrived[i] : (uint8_t)0;
     }
@@ -529,7 +535,7 @@ template <int CAP>
 static hipError_t launch_scale_finalize_cap(int n, int scale_mode, const QuantStreams& out, const StepWeights& sw,
                                             const Workspace& ws, const SketchDev* sk, float* scales, hipStream_t stream)
 {
-    const SketchCheck check = sk ? SketchCheck{sk->lo_scale, sk->state, sk->limit} : SketchCheck{nullptr, nullptr, 0u};
+    const SketchCheck check = sk ? SketchCheck{sk->lo_scale, sk->state, sk->limit, sk->table} : SketchCheck{nullptr, nullptr, 0u, nullptr};
     const QuantList<CAP> q = quant_list<CAP>(n, out, sw);
     const int layers = ws.n_layers;
     if (scale_mode == 1) {

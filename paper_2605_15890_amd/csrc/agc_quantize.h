@@ -113,18 +113,14 @@ __device__ __forceinline__ float grid_pos(float f, float inv)
 // The waves of a workgroup write out a fill of its staging area, workers first..last, which they share.  A worker's 2 * kBlocks
 // * b pieces leave as one store of contiguous bytes through a buffer descriptor that covers exactly the bytes of the
 // stream that exist, so the hardware's range check drops the pieces past the end of the vector.  Pieces are handed back
-// zeroed.  wg_groups: 128-code groups of the workgroup's blocks that exist.  AHEAD: the next worker's record is requested
-// while this one's pieces leave, for a kernel that does little else.
-template <int kBlocks, bool AHEAD = false>
+// zeroed.  wg_groups: 128-code groups of the workgroup's blocks that exist.
+template <int kBlocks>
 __device__ __forceinline__ void store_fill(uint32_t* stage, const WorkerQ* wq, int first, int last, int wave, int lane,
                                            int64_t wg, int wg_groups)
 {
     u32x4_t* pieces = reinterpret_cast<u32x4_t*>(stage);
-    WorkerQ next{};
-    if (AHEAD) next = load_uniform(wq + (first + wave <= last ? first + wave : last));
     for (int j = first + wave; j <= last; j += kQuantWaves) {
-        const WorkerQ w = AHEAD ? next : load_uniform(wq + j);
-        if (AHEAD && j + kQuantWaves <= last) next = load_uniform(wq + j + kQuantWaves);
+        const WorkerQ w = load_uniform(wq + j);
         const int b = (int)w.bits;
         const int np = 2 * kBlocks * b;  // pieces of this worker in the area
         const __amdgpu_buffer_rsrc_t rsrc = uniform_buffer(

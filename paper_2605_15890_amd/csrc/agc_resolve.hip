@@ -14,7 +14,7 @@ struct ResolveArgs {
     SketchDev sk;
 };
 
-constexpr int kClaims = 128;  // claim words of a wave; a coordinate's is its low seven bits
+constexpr int kClaims = kBlockCoords;  // claim words of a wave, one for every coordinate of its block
 
 // Sign bits of 32 codes -> the words of the stream that hold them, at the top bits of the codes.  Word w of 32 codes of B
 // bits (of sixteen, where B is even: half a wave each) holds the signs from code 32 w / B on; they are spread
@@ -41,50 +41,95 @@ __device__ __forceinline__ uint32_t sign_word(uint32_t signs)
     const uint32_t x = (signs >> first) & (count >= 32 ? ~0u : (1u << count) - 1u);
     return spread_bits<B, count, 16>(x) << at;
 }
-template <int B, int... Ws>
-__device__ __forceinline__ void or_sign_words(uint32_t* dst, uint32_t signs, std::integer_sequence<int, Ws...>)
+template <int B, int N, int... Ws>
+__device__ __forceinline__ void sign_words(uint32_t (&v)[N], uint32_t signs, std::integer_sequence<int, Ws...>)
 {
-    ((dst[Ws] |= sign_word<B, Ws>(signs)), ...);
+    ((v[Ws] |= sign_word<B, Ws>(signs)), ...);
 }
-// the signs of one worker for the workgroup's 1024 coordinates; part: the worker's words in the staging area
+// One worker's codes of the workgroup's 1024 coordinates: levels from the staging area, signs ORed in, stored to its stream.
+// signs: 32 codes' worth, those of run lane mod 32.  Widths that are even: sixteen codes are whole words, which a lane takes from
+// the area, completes and stores, half a wave the first sixteen of every run and the other half the second, so that the wave
+// stores one run of bytes.  Odd ones: half the wave completes 32 codes each in the area, and the wave stores 16-byte pieces.
+// Runs past the end of the stream lie past `bytes` and are dropped by the range check, which never parts what a lane stores.
 template <int B>
-__device__ __forceinline__ void or_signs(uint32_t* part, uint32_t signs, int lane)
+__device__ __forceinline__ void store_worker(uint32_t* part, uint32_t signs, int lane, bool clear, __amdgpu_buffer_rsrc_t out)
 {
     if constexpr (B % 2 == 0) {
-        or_sign_words<B>(part + (lane & 31) * B + (lane >> 5) * (B / 2), signs >> (16 * (lane >> 5)),
-                         std::make_integer_sequence<int, B / 2>{});
-    } else if (lane < 32) {
-        or_sign_words<B>(part + lane * B, signs, std::make_integer_sequence<int, B>{});
+        constexpr int W = B / 2;
+        uint32_t* at = part + (lane & 31) * B + (lane >> 5) * W;
+        uint32_t v[W];
+#pragma unroll
+        for (int t = 0; t < W; ++t) v[t] = at[t];
+        sign_words<B>(v, signs >> (16 * (lane >> 5)), std::make_integer_sequence<int, W>{});
+        if (clear) {
+#pragma unroll
+            for (int t = 0; t < W; ++t) at[t] = 0u;
+        }
+        const int off = (lane & 31) * (4 * B) + (lane >> 5) * (2 * B);
+        typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+        typedef uint32_t u32x3_t __attribute__((ext_vector_type(3)));
+        int t = 0;
+        if constexpr (W >= 4) {
+            __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{v[0], v[1], v[2], v[3]}, out, off, 0, kPayloadStorePolicy);
+            t = 4;
+        }
+        if constexpr (W >= 4 ? W % 4 == 1 : W == 1) __builtin_amdgcn_raw_buffer_store_b32(v[W - 1], out, off + 4 * t, 0, kPayloadStorePolicy);
+        if constexpr (W >= 4 ? W % 4 == 2 : W == 2) __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{v[W - 2], v[W - 1]}, out, off + 4 * t, 0, kPayloadStorePolicy);
+        if constexpr (W >= 4 ? W % 4 == 3 : W == 3) __builtin_amdgcn_raw_buffer_store_b96(u32x3_t{v[W - 3], v[W - 2], v[W - 1]}, out, off + 4 * t, 0, kPayloadStorePolicy);
+        if constexpr (W == 8) __builtin_amdgcn_raw_buffer_store_b128(u32x4_t{v[4], v[5], v[6], v[7]}, out, off + 16, 0, kPayloadStorePolicy);
+    } else {
+        if (lane < 32) {
+            uint32_t* at = part + lane * B;
+            uint32_t v[B];
+#pragma unroll
+            for (int t = 0; t < B; ++t) v[t] = at[t];
+            sign_words<B>(v, signs, std::make_integer_sequence<int, B>{});
+#pragma unroll
+            for (int t = 0; t < B; ++t) at[t] = v[t];
+        }
+        asm volatile("" ::: "memory");  // lanes read what others have written
+        u32x4_t* pieces = reinterpret_cast<u32x4_t*>(part);
+#pragma unroll
+        for (int p0 = 0; p0 < 8 * B; p0 += kWave) {
+            const int p = p0 + lane;
+            if (p < 8 * B) {
+                __builtin_amdgcn_raw_buffer_store_b128(pieces[p], out, 16 * p, 0, kPayloadStorePolicy);
+                if (clear) pieces[p] = u32x4_t{0u, 0u, 0u, 0u};
+            }
+        }
+        asm volatile("" ::: "memory");
     }
 }
 template <int LO, int HI>
-__device__ __forceinline__ void or_signs_any(int b, uint32_t* part, uint32_t signs, int lane)  // b is wave-uniform
-{
+__device__ __forceinline__ void store_worker_any(int b, uint32_t* part, uint32_t signs, int lane, bool clear, __amdgpu_buffer_rsrc_t out)
+{  // b is wave-uniform
     if constexpr (LO == HI) {
-        or_signs<LO>(part, signs, lane);
+        store_worker<LO>(part, signs, lane, clear, out);
     } else {
         constexpr int mid = LO == 2 && HI > 4 ? (HI > 8 ? 8 : 4) : (LO + HI) / 2;
-        if (b <= mid) or_signs_any<LO, mid>(b, part, signs, lane);
-        else or_signs_any<mid + 1, HI>(b, part, signs, lane);
+        if (b <= mid) store_worker_any<LO, mid>(b, part, signs, lane, clear, out);
+        else store_worker_any<mid + 1, HI>(b, part, signs, lane, clear, out);
     }
 }
 
-// What bounds it: 0.95 GB in and out at 64 workers x 25.6 M (205 MB of signs, 30 of records, 614 of codes, 102 of estimate) in
-// 0.31 ms, 3 TB/s; latency is most of the rest: waves wait 0.47 of their time, vector ALU 0.35 busy (counters of the interval
-// code).  Signs lane by lane, with an LDS atomic for every
-// word that two lanes share, took 0.80 ms; whole words per lane 0.41; with the fill's end looked up in LDS instead of worker
-// by worker in memory 0.31.
+// What bounds it: latency; a workgroup is one chain of requests, LDS operations and barriers, and what counts is how many
+// share a compute unit.  64 workers x 25.6 M, interval code, Euclidean: 0.95 GB in and out (205 MB of signs, 30 of records, 614 of
+// codes, 102 of estimate) in 232 us, 4.1 TB/s;  largest magnitude with heavy tails, 450 records a block: 1.28 GB in 374.
+// All workers' codes in one fill, four workgroups a compute unit, records one chunk ahead, every width completed in LDS and claims for
+// two coordinates each: 317 and 450 us, 104 for 84 at 50 workers x 5.4 M without estimate.  Signs worker by worker from
+// memory instead of LDS left room for eight workgroups and took 364 and 491.
 //
 // A group of four blocks per workgroup.  A wave first ORs the levels of its block's records into the staging area of
-// k_quantize, one record per lane; then the waves share the workers, add their signs and write them out.  The estimate is
+// k_quantize, one record per lane; then the waves share the workers, add their signs and store them.  The estimate is
 // summed in LDS, where only levels above zero change it (the running sums start at +0, and finite weights times a zero
 // level leave them as they are).  Records are ordered by worker and a worker has a coordinate once, so the sums take
 // their terms in ascending order of workers if, of the lanes that hold the same coordinate, the lowest goes
 // first: lanes claim the coordinate with their number by an atomic minimum, in rounds.
+constexpr int kChunksAhead = 4;  // of 64 records
 template <bool FUSE>
-__global__ __launch_bounds__(kWgThreads) void k_resolve(const WorkerQ* __restrict__ wq, ResolveArgs a)
+__global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_waves_per_eu(kResolveWgs, 8))) void k_resolve(const WorkerQ* __restrict__ wq, ResolveArgs a)
 {
-    // stage_pieces(a.stage_bits, 4) pieces, then [n] records of 16 bytes, then (FUSE) [4][256] sums and [4][kClaims] claims, then
+    // resolve_pieces(a.stage_bits) pieces, then [n] records of 16 bytes, then (FUSE) [4][256] sums and [4][kClaims] claims, then
     // [4][8 * n + 8] signs
     extern __shared__ __attribute__((aligned(16))) uint32_t lds_stage[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -92,23 +137,34 @@ __global__ __launch_bounds__(kWgThreads) void k_resolve(const WorkerQ* __restric
     const int64_t wg = blockIdx.x;
     const int64_t block = wg * kQuantWaves + wave;
     const int64_t base = block * (int64_t)kBlockCoords;
-    const bool has_block = base < a.d;
+    if (load_uniform(a.sk.state) != 0u) return;  // all are left to k_quantize
     struct Counts { int c[4]; };
     const Counts counts = load_uniform(reinterpret_cast<const Counts*>(a.sk.counts + 4 * wg));
-    if (load_uniform(a.sk.state) != 0u) return;  // all are left to k_quantize
+    // what does not depend on the counts is requested before they are looked at: the first records, signs and the table
+    typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+    typedef const __attribute__((address_space(1))) u32x2_t* global_u32x2_t;
+    const bool has_block = base < a.d;
+    const global_u32x2_t recs = (global_u32x2_t)(a.sk.recs + (has_block ? block : 0) * (int64_t)a.sk.cap);
+    auto record = [&](int from, int end) { return __builtin_nontemporal_load(recs + (from + lane < end ? from + lane : 0)); };
+    u32x2_t rec[kChunksAhead];
+#pragma unroll
+    for (int t = 0; t < kChunksAhead; ++t) rec[t] = record(t * kWave, a.sk.cap);
+    // the signs of the wave's block: [worker][8] words, two pieces of 16 bytes a worker
+    const __attribute__((address_space(1))) u32x4_t* planes =
+        (const __attribute__((address_space(1))) u32x4_t*)a.sk.planes + (has_block ? block : 0) * (int64_t)(a.sk.chunks * kWave);
+    u32x4_t sign[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) sign[t] = __builtin_nontemporal_load(planes + (t * kWave + lane < 2 * a.n ? t * kWave + lane : 0));
     if ((counts.c[0] | counts.c[1] | counts.c[2] | counts.c[3]) < 0) {
         if (threadIdx.x == 0)
             a.sk.left[__hip_atomic_fetch_add(a.sk.state + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)] = (uint32_t)wg;
         return;
     }
-    const int np = stage_pieces(a.stage_bits, kQuantWaves);
+    const int np = resolve_pieces(a.stage_bits);
     u32x4_t* pieces = reinterpret_cast<u32x4_t*>(lds_stage);
+    u32x4_t* table = pieces + np;  // multiplier, weight, bits with arrived and end of a fill, first word of the worker in the area
+    if ((int)threadIdx.x < a.n) table[threadIdx.x] = reinterpret_cast<const u32x4_t*>(a.sk.table)[threadIdx.x];  // n <= 256
     for (int p = threadIdx.x; p < np; p += kQuantThreads) pieces[p] = u32x4_t{0u, 0u, 0u, 0u};
-    u32x4_t* table = pieces + np;  // multiplier, weight, bits with arrived and flush, first word of the worker in the area
-    for (int i = threadIdx.x; i < a.n; i += kQuantThreads) {
-        const WorkerQ q = wq[i];
-        table[i] = u32x4_t{__float_as_uint(q.inv16), __float_as_uint(q.coef), q.bits | (q.arrived << 8) | (q.flush << 9), 4u * q.stage_piece};
-    }
     float* sums = reinterpret_cast<float*>(table + a.n) + wave * kBlockCoords;
     uint32_t* claims = reinterpret_cast<uint32_t*>(table + a.n) + kQuantWaves * kBlockCoords + wave * kClaims;
     if (FUSE) {
@@ -117,29 +173,21 @@ __global__ __launch_bounds__(kWgThreads) void k_resolve(const WorkerQ* __restric
         for (int t = 0; t < kClaims; t += kWave) claims[t + lane] = 0xFFFFFFFFu;
     }
     const int sign_stride = 8 * a.n + 8;  // dwords of a block; the eight keep the four blocks in different banks
-    uint32_t* signs = lds_stage + 4 * np + 4 * a.n + (FUSE ? kQuantWaves * (kBlockCoords + kClaims) : 0);
-    if (has_block) {
-        const u32x4_t* planes = reinterpret_cast<const u32x4_t*>(a.sk.planes) + block * (int64_t)(a.sk.chunks * kWave);
+    uint32_t* signs = lds_stage + 4 * (np + a.n) + (FUSE ? kQuantWaves * (kBlockCoords + kClaims) : 0);
+    {
         u32x4_t* to = reinterpret_cast<u32x4_t*>(signs + wave * sign_stride);
-        for (int p = lane; p < 2 * a.n; p += kWave) to[p] = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4_t*)planes + p);
-    } else {
-        for (int p = lane; p < 8 * a.n; p += kWave) signs[wave * sign_stride + p] = 0u;
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+            if (t * kWave + lane < 2 * a.n) to[t * kWave + lane] = has_block ? sign[t] : u32x4_t{0u, 0u, 0u, 0u};
+        for (int p = 2 * kWave + lane; p < 2 * a.n; p += kWave) to[p] = has_block ? __builtin_nontemporal_load(planes + p) : u32x4_t{0u, 0u, 0u, 0u};
     }
+    const uint32_t* my_signs = signs + ((lane & 31) >> 3) * sign_stride + (lane & 7);
     __syncthreads();
     const int64_t groups_left = (a.d + 127) / 128 - 2 * kQuantWaves * wg;
     const int wg_groups = groups_left >= 2 * kQuantWaves ? 2 * kQuantWaves : (int)groups_left;
     const uint32_t ctr_base = (uint32_t)(base >> 2);
     const int count = wave == 0 ? counts.c[0] : wave == 1 ? counts.c[1] : wave == 2 ? counts.c[2] : counts.c[3];
-    const uint2* recs = a.sk.recs + block * (int64_t)a.sk.cap;
-    int ptr = 0;
-    auto record = [&](int from) {
-        const int p = from + lane;
-        typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-        const u32x2_t v = __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x2_t*)(recs + (p < count ? p : 0)));
-        return make_uint2(v.x, v.y);
-    };
-    uint2 rec = make_uint2(0u, 0u);
-    if (count > 0) rec = record(0);
+    int ptr = 0;  // first record of the chunk in rec[0]
     int i = 0;
     while (i < a.n) {  // one turn per fill of the staging area
         const int first = i;
@@ -152,18 +200,16 @@ __global__ __launch_bounds__(kWgThreads) void k_resolve(const WorkerQ* __restric
         }
         // records of the fill's workers
         while (ptr < count) {
-            const uint2 ahead = record(ptr + kWave < count ? ptr + kWave : ptr);
-            const uint32_t worker = (rec.y >> 8) & 255u;
-            const bool mine = lane < count - ptr && (int)worker < i;
-            const uint64_t m = __builtin_amdgcn_ballot_w64(mine);
-            if (m == 0) break;
-            const u32x4_t t = table[worker];
-            const uint32_t b = t.z & 255u, coord = rec.y & 255u;
+            const uint32_t value = rec[0].x, what = rec[0].y;
+            const uint32_t worker = (what >> 8) & 255u;
+            const bool valid = lane < count - ptr, mine = valid && (int)worker < i && (int)worker >= first;
+            if (__builtin_amdgcn_ballot_w64(mine) == 0) break;  // all of the chunk's are for later fills
+            const u32x4_t t = table[mine ? worker : 0u];
+            const uint32_t b = t.z & 255u, coord = what & 255u;
             const uint32_t L = (1u << (b - 1u)) - 1u;
-            const float f = __uint_as_float(rec.x);
-            const float T = grid_pos<false>(f, __uint_as_float(t.x));
+            const float T = grid_pos<false>(__uint_as_float(value), __uint_as_float(t.x));
             bool tie;
-            uint32_t level = round_primary(T, rec.y >> 16, L, tie);
+            uint32_t level = round_primary(T, what >> 16, L, tie);
             if (__any(tie && mine)) {
                 uint32_t r2[4];
                 philox4x32_10(ctr_base + (coord >> 2), 0x80000000u | worker, a.step_lo, a.step_hi, a.key0, a.key1, r2);
@@ -180,46 +226,49 @@ __global__ __launch_bounds__(kWgThreads) void k_resolve(const WorkerQ* __restric
             }
             if constexpr (FUSE) {
                 add = add && (t.z & 256u) != 0u;
-                const float v = __uint_as_float(__float_as_uint((float)level) | (rec.x & 0x80000000u));
+                const float v = __uint_as_float(__float_as_uint((float)level) | (value & 0x80000000u));
                 const float coef = __uint_as_float(t.y);
-                uint32_t* claim = claims + (coord & (kClaims - 1));
+                uint32_t* claim = claims + coord;
                 while (__any(add)) {  // the lowest lane that is left always succeeds
                     if (add) atomicMin(claim, (uint32_t)lane);
                     asm volatile("" ::: "memory");  // lanes read what others have written; LDS serves a wave in order
-                    const bool go = add && *claim == (uint32_t)lane;
+                    const uint32_t winner = *claim;
+                    const float so_far = sums[coord];  // requested together; who does not win reads it again
+                    const bool go = add && winner == (uint32_t)lane;
                     if (go) {
-                        sums[coord] = fmaf(coef, v, sums[coord]);
+                        sums[coord] = fmaf(coef, v, so_far);
                         *claim = 0xFFFFFFFFu;
                     }
                     asm volatile("" ::: "memory");
                     add = add && !go;
                 }
             }
-            const int taken = __builtin_popcountll(m);
-            ptr += taken;
-            rec = taken == kWave ? ahead : record(ptr);
+            if (__any(valid && (int)worker >= i)) break;  // the rest of the chunk is for later fills
+#pragma unroll
+            for (int u = 0; u + 1 < kChunksAhead; ++u) rec[u] = rec[u + 1];
+            ptr += kWave;
+            rec[kChunksAhead - 1] = record(ptr + (kChunksAhead - 1) * kWave, count);
         }
         __syncthreads();
-        const uint32_t* my_signs = signs + ((lane & 31) >> 3) * sign_stride + (lane & 7);
-        const int j0 = first + wave < a.n ? first + wave : a.n - 1;
-        u32x4_t t_next = table[j0];
-        uint32_t s_next = my_signs[8 * j0];
-        for (int j = first + wave; j < i; j += kQuantWaves) {  // as store_fill shares them
-            const uint32_t b = __builtin_amdgcn_readfirstlane(t_next.z & 255u);
-            uint32_t* part = lds_stage + __builtin_amdgcn_readfirstlane(t_next.w);
+        const bool more = i < a.n;
+        uint32_t s_next = my_signs[8 * (first + wave < i ? first + wave : i - 1)];
+        WorkerQ w_next = load_uniform(wq + (first + wave < i ? first + wave : i - 1));
+        for (int j = first + wave; j < i; j += kQuantWaves) {
+            const WorkerQ w = w_next;
+            w_next = load_uniform(wq + (j + kQuantWaves < i ? j + kQuantWaves : i - 1));
+            uint32_t* part = lds_stage + __builtin_amdgcn_readfirstlane((int)table[j].w);
             const uint32_t s = s_next;
-            const int ahead = j + kQuantWaves < a.n ? j + kQuantWaves : a.n - 1;
-            t_next = table[ahead];
-            s_next = my_signs[8 * ahead];
-            or_signs_any<2, 16>((int)b, part, s, lane);
+            s_next = my_signs[8 * (j + kQuantWaves < i ? j + kQuantWaves : i - 1)];
+            const int b = (int)w.bits;
+            const __amdgpu_buffer_rsrc_t out = uniform_buffer((const char*)w.codes + (uint64_t)wg * (uint64_t)(32 * kQuantWaves * b), 16 * b * wg_groups);
+            store_worker_any<2, 16>(b, part, s, lane, more, out);
         }
-        asm volatile("" ::: "memory");  // lanes read what others have written
-        store_fill<kQuantWaves, true>(lds_stage, wq, first, i - 1, wave, lane, wg, wg_groups);
-        if (i < a.n) __syncthreads();  // the area is reused by the next fill
+        if (more) __syncthreads();  // the area is reused by the next fill
     }
     if constexpr (FUSE) {
         if (has_block) {
             const int64_t left = a.d - base - 4 * lane;
+            asm volatile("" ::: "memory");  // lanes read what others have written
             const u32x4_t s = *reinterpret_cast<const u32x4_t*>(sums + 4 * lane);
             float* dst = a.ghat + base + 4 * lane;
             if (left >= 4) *reinterpret_cast<u32x4_t*>(dst) = s;
@@ -233,12 +282,10 @@ hipError_t launch_resolve(int n, int64_t d, const Workspace& ws, const SketchDev
                           uint64_t step, float* ghat, hipStream_t stream)
 {
     const ResolveArgs a{n, d, (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32), ghat,
-                        out.stage_bits, sk};
-    if (out.stage_bits < 1 || out.stage_bits > kStageBits) return hipErrorInvalidValue;
+                        out.resolve_bits, sk};
+    if (out.resolve_bits < 1 || out.resolve_bits > resolve_limit(n, ghat != nullptr)) return hipErrorInvalidValue;
     const dim3 g((unsigned)((d + 1023) / 1024)), b(kQuantThreads);
-    const unsigned lds = 16u * (unsigned)(stage_pieces(out.stage_bits, kQuantWaves) + n) +
-                         (ghat ? 4u * (unsigned)(kQuantWaves * (kBlockCoords + kClaims)) : 0u) +
-                         4u * (unsigned)(kQuantWaves * (8 * n + 8));
+    const unsigned lds = resolve_lds_bytes(n, out.resolve_bits, ghat != nullptr);
     if (ghat) hipLaunchKernelGGL((k_resolve<true>), g, b, lds, stream, ws.wq, a);
     else hipLaunchKernelGGL((k_resolve<false>), g, b, lds, stream, ws.wq, a);
     return hipGetLastError();
