@@ -37,6 +37,7 @@ struct agc_ctx {
     int* d_col = nullptr;
     float* d_val = nullptr;
     agc::WindowRec* d_win = nullptr;   // monotone-interval codes only
+    agc::StreamRec* d_stream = nullptr;  // long monotone intervals only
     int band = 0;
     bool force_long = false;  // testing hook
     int sketch_mode = 0;      // testing hook: 0 by the rule, 1 wherever the sketch can be made, 2 never
@@ -144,7 +145,9 @@ void free_code(agc_ctx* c)
     if (c->d_col) (void)hipFree(c->d_col);
     if (c->d_val) (void)hipFree(c->d_val);
     if (c->d_win) (void)hipFree(c->d_win);
+    if (c->d_stream) (void)hipFree(c->d_stream);
     c->d_win = nullptr;
+    c->d_stream = nullptr;
     c->d_row_ptr = nullptr;
     c->d_col = nullptr;
     c->d_val = nullptr;
@@ -232,7 +235,36 @@ agc::CodeDev code_dev(const agc_ctx* c)
     const int band = c->opts.force_generic ? 0 : c->band;
     const bool parts = !c->force_long &&
                        agc::use_parts(c->d, c->n, c->k, c->nnz, band, c->opts.scale_mode == AGC_SCALE_L2, c->opts.bucket != 0);
-    return agc::CodeDev{c->d_row_ptr, c->d_col, c->d_val, band, c->d_win, parts};
+    return agc::CodeDev{c->d_row_ptr, c->d_col, c->d_val, band, c->d_win, parts, c->opts.force_generic ? nullptr : c->d_stream};
+}
+
+// The entries of a code whose rows are runs of consecutive ascending columns with neither end decreasing from worker to worker,
+// in the order of encode_stream, and a sentinel; empty if the code is not one, or too many workers are open at a time.
+std::vector<agc::StreamRec> stream_records(int n, const int32_t* row_ptr, const int32_t* col, const float* val)
+{
+    std::vector<agc::StreamRec> out;
+    for (int i = 0; i < n; ++i) {
+        const int e0 = row_ptr[i], e1 = row_ptr[i + 1];
+        if (e0 == e1) return {};
+        for (int e = e0 + 1; e < e1; ++e)
+            if (col[e] != col[e - 1] + 1) return {};
+        if (i > 0 && (col[e0] < col[row_ptr[i - 1]] || col[e1 - 1] < col[e0 - 1])) return {};
+    }
+    int lowest = 0, next = 0;  // workers lowest..next-1 are open
+    for (int j = n > 0 ? col[0] : 0; lowest < n; ++j) {
+        while (next < n && col[row_ptr[next]] == j) ++next;
+        const int first = lowest, end = next;
+        for (int i = first; i < end; ++i) {
+            if (i - lowest >= agc::kStreamSlots) return {};
+            const int e = row_ptr[i] + (j - col[row_ptr[i]]);
+            const int last = e + 1 == row_ptr[i + 1];
+            out.push_back(agc::StreamRec{j, val[e], i - lowest, last});
+            lowest += last;
+        }
+        if (lowest == next && next < n) j = col[row_ptr[next]] - 1;  // columns that no worker holds
+    }
+    out.push_back(agc::StreamRec{INT32_MAX, 0.f, 0, 0});
+    return out;
 }
 
 // Takes the workspace of the one-read form where a step of this context may use it, some bit-widths provided (those of two
@@ -426,6 +458,14 @@ agc_status agc_set_code(agc_ctx* c, const int32_t* row_ptr, const int32_t* col, 
         e = dev_alloc(&c->d_win, win.size());
         if (e == hipSuccess) e = hipMemcpy(c->d_win, win.data(), sizeof(agc::WindowRec) * win.size(), hipMemcpyHostToDevice);
     }
+    if (e == hipSuccess && band == 0 && nnz > 0) {
+        const std::vector<agc::StreamRec> entries = stream_records(c->n, row_ptr, col, val);
+        if (!entries.empty()) {
+            e = dev_alloc(&c->d_stream, entries.size());
+            if (e == hipSuccess)
+                e = hipMemcpy(c->d_stream, entries.data(), sizeof(agc::StreamRec) * entries.size(), hipMemcpyHostToDevice);
+        }
+    }
     if (e != hipSuccess) {
         free_code(c);
         return hip_fail(c, e, "uploading the code matrix");
@@ -605,7 +645,12 @@ agc_status encode_quantize_impl(agc_ctx* c, const float* G, int64_t ldg, const u
     qs.parts = code.parts && sum_bits <= agc::kPartBits && !sk;
     qs.stage_fills = agc::stage_starts(qs.bits, c->n, qs.parts ? agc::kPartBits : agc::stage_limit(c->n, c->opts.bucket != 0),
                                        qs.stage_start, &qs.stage_bits);
-    if (sk) (void)agc::stage_starts(qs.bits, c->n, agc::resolve_limit(c->n, ghat != nullptr), qs.resolve_start, &qs.resolve_bits);
+    if (sk) {
+        uint16_t start[agc::kArgWorkers];
+        const int limit = agc::resolve_limit(c->n, ghat != nullptr);
+        qs.resolve_cap = agc::stage_cap(qs.bits, c->n, limit);
+        (void)agc::stage_starts(qs.bits, c->n, limit, start, &qs.resolve_bits);
+    }
     hipError_t e;
     if (c->opts.bucket) {  // one pass: every block finds its own scale
         KernelTimer t{c, 2, stream};

@@ -296,13 +296,13 @@ __device__ __forceinline__ Row zero_row()
 }
 
 // streaming load of a lane's part of a row whose blocks lie wholly inside the vector
-template <class Row>
+template <class Row, bool STREAM = true>
 __device__ __forceinline__ Row load_row(const float* __restrict__ row, const LaneCoords& lc)
 {
     Row r;
     float4* p = reinterpret_cast<float4*>(&r);
 #pragma unroll
-    for (int t = 0; t < RowBlocks<Row>::value; ++t) p[t] = load_row4<true>(row + t * kBlockCoords, lc);
+    for (int t = 0; t < RowBlocks<Row>::value; ++t) p[t] = load_row4<STREAM>(row + t * kBlockCoords, lc);
     return r;
 }
 
@@ -484,6 +484,8 @@ struct CsrView {
     const int* __restrict__ col;
     const float* __restrict__ val;
     const WindowRec* __restrict__ win;  // monotone-interval codes: one record per row + sentinel
+    const StreamRec* __restrict__ stream = nullptr;  // long monotone intervals: one record per entry + sentinel
+    bool keep = false;                               // and G is small enough to be found in the caches again
 };
 
 __device__ __forceinline__ float4 encode_gather_one(const float* __restrict__ G, int64_t ldg,
@@ -693,6 +695,82 @@ __device__ __forceinline__ void encode_window_batched(const float* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------------------
+// Encode driver 4: monotone intervals of any length of which few are open at a time (a worker is open from its first column to
+// its last).  Rows stream once; a row is added to every open worker's sum as it arrives and is then dropped, so the
+// registers hold the sums of the open workers and the rows that are on their way.  A sum starts at -0, which
+// makes the first fused multiply-add the rounded product, sign of zero included.  The lowest open worker is always the first
+// to be complete.
+// Up to 256 MB of G, which the memory-side cache holds, rows are loaded to be kept for the pass or step that follows, above
+// that non-temporally.  Whole steps, us, the general driver (one row of one worker after the other) | this one kept | this one
+// non-temporal: 10 workers and 30 partitions x 400 000 41.6 | 33.6 | 39.7, 900 000 49.2 | 43.3 | 45, 1.5 M 64.0 | 63.8 | 68,
+// 2.5 M 126 | 109 | 110, 5.4 M 238-241 | 243 | 231;  24 and 70 x 5.4 M 539 | 555 | 512;  64 and 64 x 12.8 M 1607 | - | 1226.  Two
+// rows ahead; with four, six and eight 10 x 5.4 M takes 244, 247 and 252: more waves fit with fewer registers.
+// ---------------------------------------------------------------------------------------
+constexpr int kStreamDriver = -64;  // the S of kernels with this driver
+constexpr int64_t kKeepElements = (int64_t)1 << 26;
+constexpr int kStreamAhead = 2;     // rows requested ahead
+
+__device__ __forceinline__ float4 minus_zero(const float4&) { return make_float4(-0.f, -0.f, -0.f, -0.f); }
+template <int V>
+__device__ __forceinline__ RowN<V> minus_zero(const RowN<V>& r)
+{
+    RowN<V> z;
+#pragma unroll
+    for (int t = 0; t < V; ++t) z.v[t] = minus_zero(r.v[t]);
+    return z;
+}
+
+template <class Row, bool STREAM, class Epi>
+__device__ __forceinline__ void encode_stream_rows(const float* __restrict__ G, int64_t ldg, int k, const CsrView& B, const LaneCoords& lc,
+                                                   Epi& epi)
+{
+    Row ring[kStreamAhead], open[kStreamSlots];
+    const float* next_row = G;
+    int left = k;  // rows not requested yet
+#pragma unroll
+    for (int r = 0; r < kStreamAhead; ++r) {
+        ring[r] = load_row<Row, STREAM>(next_row, lc);  // past the last row the last row is read again
+        left -= 1;
+        next_row += left > 0 ? ldg : 0;
+    }
+#pragma unroll
+    for (int t = 0; t < kStreamSlots; ++t) open[t] = minus_zero(ring[0]);
+    const StreamRec* rec = B.stream;
+    StreamRec cur = load_uniform(rec);
+    int i = 0;
+    for (int j0 = 0; j0 < k; j0 += kStreamAhead) {
+#pragma unroll
+        for (int r = 0; r < kStreamAhead; ++r) {
+            while (cur.col == j0 + r) {
+                const StreamRec nxt = load_uniform(++rec);
+#pragma unroll
+                for (int t = 0; t < kStreamSlots; ++t)
+                    if (cur.slot == t) open[t] = fma4(cur.val, ring[r], open[t]);  // wave-uniform
+                if (cur.last) {
+                    epi.worker_any(i, open[0]);
+                    ++i;
+#pragma unroll
+                    for (int t = 0; t + 1 < kStreamSlots; ++t) open[t] = open[t + 1];
+                    open[kStreamSlots - 1] = minus_zero(ring[0]);
+                }
+                cur = nxt;
+            }
+            ring[r] = load_row<Row, STREAM>(next_row, lc);
+            left -= 1;
+            next_row += left > 0 ? ldg : 0;
+        }
+    }
+}
+
+template <class Row, class Epi>
+__device__ __forceinline__ void encode_stream(const float* __restrict__ G, int64_t ldg, int k, const CsrView& B, const LaneCoords& lc,
+                                              Epi& epi)
+{
+    if (B.keep) encode_stream_rows<Row, false>(G, ldg, k, B, lc, epi);
+    else encode_stream_rows<Row, true>(G, ldg, k, B, lc, epi);
+}
+
+// ---------------------------------------------------------------------------------------
 // The same drivers for a range of workers i0..i1-1 (i0 even, i0 < i1), for passes that give the waves of a
 // workgroup a part of the workers each.  The cyclic band loads the rows that wrap around once more.
 // ---------------------------------------------------------------------------------------
@@ -857,7 +935,9 @@ template <int S, class Epi>
 __device__ __forceinline__ void encode_block_any(const float* __restrict__ G, int64_t ldg, int n, int k,
                                                  const CsrView& B, const LaneCoords& lc, Epi& epi)
 {
-    if constexpr (S > 0) {
+    if constexpr (S == kStreamDriver) {
+        encode_stream<float4>(G, ldg, k, B, lc, epi);
+    } else if constexpr (S > 0) {
         encode_ring<S, Epi::kPrefetchRows, float4>(G, ldg, k, B.val, lc, epi);
     } else if constexpr (S < 0) {  // monotone intervals of at most -S columns
         if constexpr (Epi::kStoresPerWorker) encode_window_batched<-S>(G, ldg, k, B, lc, epi);

@@ -23,6 +23,17 @@ struct WindowRec {
 };
 static_assert(sizeof(WindowRec) == 64, "one record is 64 bytes");
 
+// Entry of a code whose rows are long intervals, in the order in which the columns' rows of G arrive (encode_stream): columns
+// ascending, workers ascending within a column.  The last one is a sentinel whose column matches no row.
+struct StreamRec {
+    int col;
+    float val;
+    int slot;             // which of the open workers: 0..kStreamSlots - 1, counted from the lowest
+    int last;             // the worker's last entry: it is formed, and the others move down a slot
+};
+static_assert(sizeof(StreamRec) == 16, "one record is one 16-byte scalar load");
+constexpr int kStreamSlots = 2;
+
 struct CodeDev {          // the code matrix B on the device
     const int* row_ptr;   // [n+1]
     const int* col;       // [nnz]
@@ -30,6 +41,7 @@ struct CodeDev {          // the code matrix B on the device
     int band;             // 0: generic CSR; s>0: cyclic band with s entries per row; -W: monotone intervals
     const WindowRec* win; // [n+1], monotone-interval codes only (else null)
     bool parts;           // use_parts() of this code
+    const StreamRec* stream;  // [nnz+1], band 0 and long monotone intervals with at most kStreamSlots workers open at a time (else null)
 };
 
 // what the quantize pass needs to know about worker i, read with one scalar 32-byte load
@@ -209,8 +221,7 @@ struct QuantStreams {      // host arrays of the encode call
     uint8_t bits[kArgWorkers];
     uint16_t stage_start[kArgWorkers];  // stage_starts() of the bit-widths
     int stage_fills, stage_bits;        // and what it returns: fills, the fullest one in bits
-    uint16_t resolve_start[kArgWorkers];  // and for the fills of k_resolve, where it runs
-    int resolve_bits;
+    int resolve_cap, resolve_bits;      // the same for the fills of k_resolve, where it runs: most bits of a fill, and of the fullest one
     bool parts;                         // the quantize pass shares the workers of a block among the waves
 };
 
@@ -229,7 +240,7 @@ struct QuantList {         // both as kernel arguments of the table kernels, for
     void* codes[CAP];
     float w[CAP];
     uint8_t bits[CAP];
-    uint16_t stage_start[CAP], resolve_start[CAP];
+    uint16_t stage_start[CAP];
     uint8_t arrived[CAP];
     int fuse;
 };

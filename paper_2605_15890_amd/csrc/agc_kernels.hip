@@ -38,6 +38,7 @@ struct ScaleArgs {
     uint32_t* part_max;
     double* part_sq;
     const WindowRec* win;  // monotone-interval codes only
+    const StreamRec* stream;     // long monotone intervals only
     const uint8_t* block_layer;  // layer-wise scales only (max-abs): the layer of every block
     const int* seg_first;        // layer-wise Euclidean scales only: the segments of the layers
     const uint8_t* seg_blocks;
@@ -114,7 +115,7 @@ __global__ __launch_bounds__(kWave * WAVES) void k_scale_pass(const float* __res
     const int64_t seg = blockIdx.x;
     const int64_t blk = seg * WAVES + wave;  // max-abs: index of the wave's run of V blocks
     const int64_t base = blk * (int64_t)(V * kBlockCoords);
-    const CsrView B{row_ptr, col, val, a.win};
+    const CsrView B{row_ptr, col, val, a.win, a.stream, (int64_t)a.k * a.d <= kKeepElements};
 
     double* accd = lds_acc[wave];
     uint32_t* accu = reinterpret_cast<uint32_t*>(lds_acc[wave]);
@@ -159,7 +160,8 @@ __global__ __launch_bounds__(kWave * WAVES) void k_scale_pass(const float* __res
             }
             if (together) {
                 const LaneCoords lc = lane_coords(base, lane, a.d);  // every lane whole, in all V blocks
-                if constexpr (S > 0) encode_ring<S, AGC_SCALE_PREFETCH_ROWS2, RowN<V>>(G + base, a.ldg, a.k, val, lc, epi);
+                if constexpr (S == kStreamDriver) encode_stream<RowN<V>>(G + base, a.ldg, a.k, B, lc, epi);
+                else if constexpr (S > 0) encode_ring<S, AGC_SCALE_PREFETCH_ROWS2, RowN<V>>(G + base, a.ldg, a.k, val, lc, epi);
                 else if constexpr (S < 0) encode_window<-S, AGC_SCALE_PREFETCH_ROWS2, RowN<V>>(G + base, a.ldg, a.k, B, lc, epi);
                 fold(layer_of(base));
             } else {
@@ -310,8 +312,9 @@ template <int S>
 static hipError_t launch_scale_pass_s(const float* G, const CodeDev& code, const ScaleArgs& a,
                                       int scale_mode, hipStream_t stream)
 {
-    if (code.parts) {
-        if (scale_mode == 0)
+    if (S != kStreamDriver && code.parts) {
+        if constexpr (S == kStreamDriver) {
+        } else if (scale_mode == 0)
             hipLaunchKernelGGL((k_scale_pass_parts<S, 0>), dim3((unsigned)a.nseg), dim3(kWave * kParts * kSegBlocks), 0,
                                stream, G, code.row_ptr, code.col, code.val, a);
         else
@@ -337,7 +340,7 @@ hipError_t launch_scale_pass(const float* G, int64_t ldg, int n, int k, int64_t 
                              const SketchDev* sk, hipStream_t stream)
 {
     const bool layers = ws.n_layers > 0;
-    ScaleArgs a{ldg, n, k, d, layers && scale_mode == 0 ? ws.nseg_layers : ws.nseg, ws.part_max, ws.part_sq, code.win,
+    ScaleArgs a{ldg, n, k, d, layers && scale_mode == 0 ? ws.nseg_layers : ws.nseg, ws.part_max, ws.part_sq, code.win, code.stream,
                 layers && scale_mode == 1 ? ws.block_layer : nullptr,
                 layers && scale_mode == 0 ? ws.seg_first : nullptr, layers && scale_mode == 0 ? ws.seg_blocks : nullptr, sk ? sk->state + 2 : nullptr, sk ? sk->limit : 0u};
     if (code.band < 0 && !code.win) return hipErrorInvalidValue;  // the window driver reads the records
@@ -353,7 +356,9 @@ hipError_t launch_scale_pass(const float* G, int64_t ldg, int n, int k, int64_t 
         case -2: return launch_scale_pass_s<-2>(G, code, a, scale_mode, stream);
         case -4: return launch_scale_pass_s<-4>(G, code, a, scale_mode, stream);
         case -8: return launch_scale_pass_s<-8>(G, code, a, scale_mode, stream);
-        default: return launch_scale_pass_s<0>(G, code, a, scale_mode, stream);
+        default:
+            return code.stream && !code.parts ? launch_scale_pass_s<kStreamDriver>(G, code, a, scale_mode, stream)
+                                              : launch_scale_pass_s<0>(G, code, a, scale_mode, stream);
     }
 }
 
@@ -418,6 +423,7 @@ struct SketchCheck {
     uint32_t* state;
     uint32_t limit;         // largest magnitude: with state[2] above this there is no sketch
     uint4* table;           // k_resolve's
+    int fill_cap;           // and most bits of its fills
 };
 
 // One workgroup per worker (and layer, with the Euclidean scale).
@@ -479,8 +485,13 @@ __global__ __launch_bounds__(kWgThreads) void k_scale_finalize(int n, QuantList<
         ws.wq[(int64_t)l * n + i] = q;
         // a weight that is not finite makes NaN of zero levels too, which k_resolve does not add up
         if (check.state) {
-            const uint32_t ends = i == n - 1 || in.resolve_start[i + 1] == 0 ? 512u : 0u;
-            check.table[i] = make_uint4(__float_as_uint(q.inv16), __float_as_uint(q.coef), q.bits | (q.arrived << 8) | ends, 32u * in.resolve_start[i]);
+            int start = 0;  // of the worker in its fill, as stage_starts places it; not an argument: other steps would pay for its bytes
+            for (int j = 0; j < i; ++j) {
+                start += in.bits[j];
+                if (start + in.bits[j + 1] > check.fill_cap) start = 0;
+            }
+            const uint32_t ends = i == n - 1 || start + b + in.bits[i + 1] > check.fill_cap ? 512u : 0u;
+            check.table[i] = make_uint4(__float_as_uint(q.inv16), __float_as_uint(q.coef), q.bits | (q.arrived << 8) | ends, 32u * (uint32_t)start);
         }
         bool none = false;
         if (MODE == 1 && check.state && i == 0) {
@@ -524,7 +535,6 @@ static QuantList<CAP> quant_list(int n, const QuantStreams& out, const StepWeigh
         q.codes[i] = out.codes[i];
         q.bits[i] = out.bits[i];
         q.stage_start[i] = out.stage_start[i];
-        q.resolve_start[i] = out.resolve_start[i];
         q.w[i] = sw.fuse ? sw.w[i] : 0.f;
         q.arrived[i] = sw.fuse ? sw.arrived[i] : (uint8_t)0;
     }
@@ -535,7 +545,8 @@ template <int CAP>
 static hipError_t launch_scale_finalize_cap(int n, int scale_mode, const QuantStreams& out, const StepWeights& sw,
                                             const Workspace& ws, const SketchDev* sk, float* scales, hipStream_t stream)
 {
-    const SketchCheck check = sk ? SketchCheck{sk->lo_scale, sk->state, sk->limit, sk->table} : SketchCheck{nullptr, nullptr, 0u, nullptr};
+    const SketchCheck check = sk ? SketchCheck{sk->lo_scale, sk->state, sk->limit, sk->table, out.resolve_cap}
+                                 : SketchCheck{nullptr, nullptr, 0u, nullptr, 0};
     const QuantList<CAP> q = quant_list<CAP>(n, out, sw);
     const int layers = ws.n_layers;
     if (scale_mode == 1) {
@@ -763,7 +774,7 @@ static hipError_t launch_sketch_sample(const float* G, int64_t ldg, int n, int k
                                        uint64_t seed, uint64_t step, uint32_t* part_max, typename Epi::Sum* sums, hipStream_t stream)
 {
     const SampleRuns runs = sample_runs((d + kBlockCoords - 1) / kBlockCoords, samples, seed, step);
-    const ScaleArgs a{ldg, n, k, d, 0, part_max, nullptr, code.win, nullptr, nullptr, nullptr, nullptr, 0u};
+    const ScaleArgs a{ldg, n, k, d, 0, part_max, nullptr, code.win, nullptr, nullptr, nullptr, nullptr, nullptr, 0u};
     switch (code.band) {
         case 1: launch_sketch_sample_s<1, false, Epi>(G, code, a, samples, runs, sums, stream); break;
         case 2: launch_sketch_sample_s<2, false, Epi>(G, code, a, samples, runs, sums, stream); break;
@@ -849,7 +860,7 @@ hipError_t launch_quantize_bucket(const float* G, int64_t ldg, int n, int k, int
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     QuantArgs a{ldg, n, k, d, (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32),
-                scales, (d + kBlockCoords - 1) / kBlockCoords, ghat, nullptr, out.stage_bits, out.stage_fills,
+                scales, (d + kBlockCoords - 1) / kBlockCoords, ghat, nullptr, nullptr, out.stage_bits, out.stage_fills,
                 nullptr, 0u, out.parts, nullptr, nullptr};
     if (a.stage_fills > 1)
         return scale_mode == 0 ? launch_quantize_band2m(G, code, ws, a, stream)
@@ -863,7 +874,7 @@ hipError_t launch_quantize(const float* G, int64_t ldg, int n, int k, int64_t d,
                            uint64_t step, float* ghat, const SketchDev* sk, hipStream_t stream)
 {
     QuantArgs a{ldg, n, k, d, (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32),
-                nullptr, 0, ghat, nullptr, out.stage_bits, out.stage_fills,
+                nullptr, 0, ghat, nullptr, nullptr, out.stage_bits, out.stage_fills,
                 ws.n_layers > 0 ? ws.block_layer : nullptr, 0u, out.parts, sk ? sk->state : nullptr, sk ? sk->left : nullptr};
     return a.stage_fills > 1 ? launch_quantize_band0m(G, code, ws, a, stream)
                              : launch_quantize_band0s(G, code, ws, a, stream);

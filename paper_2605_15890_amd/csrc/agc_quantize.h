@@ -21,6 +21,7 @@ struct QuantArgs {
     int64_t nb;
     float* ghat;    // fused step only
     const WindowRec* win;  // monotone-interval codes only; filled in by the launcher
+    const StreamRec* stream;  // long monotone intervals only; likewise
     int stage_bits;        // bit-widths of the fullest fill of the staging area: at most stage_limit(), kPartBits with parts
     int stage_fills;       // how many fills the workers need: 1 unless the widths sum to more than that; always 1 with parts
     const uint8_t* block_layer;  // layer-wise scales only: the layer of every block; wq is then [layer][n]
@@ -506,7 +507,7 @@ template <int S, int BUCKET, bool FUSE, bool MULTI, bool PARTS, bool LEFT = fals
 #ifndef AGC_K2_WAVES
 #define AGC_K2_WAVES 4
 #endif
-__global__ __launch_bounds__(kQuantThreads) __attribute__((amdgpu_waves_per_eu(S == 0 ? 1 : AGC_K2_WAVES, S == 0 ? 8 : AGC_K2_WAVES))) void k_quantize(const float* __restrict__ G,
+__global__ __launch_bounds__(kQuantThreads) __attribute__((amdgpu_waves_per_eu(S == 0 || S == kStreamDriver ? 1 : AGC_K2_WAVES, S == 0 || S == kStreamDriver ? 8 : AGC_K2_WAVES))) void k_quantize(const float* __restrict__ G,
                                                          const int* __restrict__ row_ptr,
                                                          const int* __restrict__ col,
                                                          const float* __restrict__ val,
@@ -573,7 +574,7 @@ __global__ __launch_bounds__(kQuantThreads) __attribute__((amdgpu_waves_per_eu(S
         else epi.flush_fill(a.n - 1);
         return;
     }
-    encode_block<S>(G + base, a.ldg, a.n, a.k, CsrView{row_ptr, col, val, a.win}, lc, epi);
+    encode_block<S>(G + base, a.ldg, a.n, a.k, CsrView{row_ptr, col, val, a.win, a.stream, (int64_t)a.k * a.d <= kKeepElements}, lc, epi);
     epi.finish_pairs();
     if constexpr (!MULTI) epi.flush_fill(a.n - 1);  // the one fill: all workers, written out after the loop
     if constexpr (FUSE) {
@@ -597,12 +598,13 @@ static hipError_t launch_quantize_s(const float* G, const CodeDev& code, const W
 {
     QuantArgs a = args;
     a.win = code.win;
-    if (S < 0 && !a.win) return hipErrorInvalidValue;  // the window driver reads the records
+    a.stream = code.stream;
+    if (S < 0 && S != kStreamDriver && !a.win) return hipErrorInvalidValue;  // the window driver reads the records
     const int64_t nblocks = (a.d + kBlockCoords - 1) / kBlockCoords;
     const unsigned grid = (unsigned)((nblocks + kQuantWaves - 1) / kQuantWaves);
     if (a.stage_bits < 1 || a.stage_bits > (a.parts ? kPartBits : kStageBits)) return hipErrorInvalidValue;
     if (MULTI ? a.stage_fills < 2 : a.stage_fills != 1) return hipErrorInvalidValue;
-    if constexpr (!MULTI) {
+    if constexpr (!MULTI && S != kStreamDriver) {
         if (a.parts) {
             const unsigned lds = 16u * (unsigned)stage_pieces(a.stage_bits, 1) + (BUCKET != 0 ? 4u * (unsigned)a.n : 0u);
             const dim3 g((unsigned)nblocks), b(kWave * kParts);
@@ -655,7 +657,9 @@ static inline hipError_t launch_quantize_band(const float* G, const CodeDev& cod
         case -2: return launch_quantize_s<-2, BUCKET, MULTI>(G, code, ws, a, stream);
         case -4: return launch_quantize_s<-4, BUCKET, MULTI>(G, code, ws, a, stream);
         case -8: return launch_quantize_s<-8, BUCKET, MULTI>(G, code, ws, a, stream);
-        default: return launch_quantize_s<0, BUCKET, MULTI>(G, code, ws, a, stream);
+        default:
+            return code.stream && !a.parts ? launch_quantize_s<kStreamDriver, BUCKET, MULTI>(G, code, ws, a, stream)
+                                           : launch_quantize_s<0, BUCKET, MULTI>(G, code, ws, a, stream);
     }
 }
 

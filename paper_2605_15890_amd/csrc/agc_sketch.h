@@ -34,6 +34,7 @@ struct SketchArgs {
     int64_t d;
     uint32_t key0, key1, step_lo, step_hi;
     const WindowRec* win;  // monotone-interval codes only
+    const StreamRec* stream;  // long monotone intervals only
     double* part_sq;       // Euclidean scale: [segment][worker]
     uint32_t* run_max;     // largest magnitude: [worker]
     SketchDev sk;
@@ -207,7 +208,7 @@ __device__ __forceinline__ void store_plane(const SketchArgs& a, int64_t block, 
 // One wave per block of 256 coordinates, four blocks of a segment of the norm's tree per workgroup.
 // LDS: [4][n] doubles, [4][4 * chunks][64] dwords of signs, [4][cap] records.
 template <int S>
-__global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_waves_per_eu(S == 0 ? 1 : 4, S == 0 ? 8 : 4))) void k_sketch(
+__global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_waves_per_eu(S == 0 || S == kStreamDriver ? 1 : 4, S == 0 || S == kStreamDriver ? 8 : 4))) void k_sketch(
     const float* __restrict__ G, const int* __restrict__ row_ptr, const int* __restrict__ col,
     const float* __restrict__ val, const float* __restrict__ lo_mult, SketchArgs a)
 {
@@ -224,7 +225,7 @@ __global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_waves_per_eu(S ==
         const LaneCoords lc = lane_coords(base, lane, a.d);
         EpiSketch epi{{a.key0, a.key1, a.step_lo, a.step_hi, plane, a.n, lane, (uint32_t)((base + 4 * lane) >> 2)},
                       lo_mult, acc, recs, a.sk.cap, 0, 0.0, 0.0, load_uniform(lo_mult)};
-        encode_block<S>(G + base, a.ldg, a.n, a.k, CsrView{row_ptr, col, val, a.win}, lc, epi);
+        encode_block<S>(G + base, a.ldg, a.n, a.k, CsrView{row_ptr, col, val, a.win, a.stream, (int64_t)a.k * a.d <= kKeepElements}, lc, epi);
         epi.finish();
         // what this wave's lanes have left in LDS leaves in long runs, by the store policy of the payload
         store_plane(a, block, plane, lane);
@@ -355,7 +356,7 @@ __device__ __forceinline__ void raise_bounds(const SketchArgs& a, const uint32_t
 // nothing left 7.  One kernel with both passes: 2384 us for 2374 where values are alike (its registers and LDS are the
 // sketch's), and with the first blocks of all in place of a sample 2123.
 template <int S>
-__global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_waves_per_eu(S == 0 ? 1 : 4, S == 0 ? 8 : 4))) void k_sketch_max(
+__global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_waves_per_eu(S == 0 || S == kStreamDriver ? 1 : 4, S == 0 || S == kStreamDriver ? 8 : 4))) void k_sketch_max(
     const float* __restrict__ G, const int* __restrict__ row_ptr, const int* __restrict__ col,
     const float* __restrict__ val, const uint32_t* __restrict__ full, SketchArgs a, BitList in)
 {
@@ -383,7 +384,7 @@ __global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_waves_per_eu(S ==
     const LaneCoords lc = lane_coords(base, lane, a.d);
     EpiSketchMax epi{{a.key0, a.key1, a.step_lo, a.step_hi, plane, a.n, lane, (uint32_t)((base + 4 * lane) >> 2)},
                      mult, acc, ring, a.sk.recs + block * (int64_t)a.sk.cap, a.sk.cap, 0, 0, 0.f, mult[0]};
-    encode_block<S>(G + base, a.ldg, a.n, a.k, CsrView{row_ptr, col, val, a.win}, lc, epi);
+    encode_block<S>(G + base, a.ldg, a.n, a.k, CsrView{row_ptr, col, val, a.win, a.stream, (int64_t)a.k * a.d <= kKeepElements}, lc, epi);
     epi.finish();
     store_plane(a, block, plane, lane);
     if (lane == 0) a.sk.counts[block] = epi.count <= a.sk.cap ? epi.count : -1;

@@ -7,7 +7,7 @@ hipError_t launch_sketch_max(const float* G, int64_t ldg, int n, int k, int64_t 
                              const SketchDev& sk, const QuantStreams& out, uint64_t seed, uint64_t step, hipStream_t stream)
 {
     const SketchArgs a{ldg, n, k, d, (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32),
-                       code.win, nullptr, ws.part_max, sk};
+                       code.win, code.stream, nullptr, ws.part_max, sk};
     if (code.band < 0 && !code.win) return hipErrorInvalidValue;  // the window driver reads the records
     BitList bits;
     for (int i = 0; i < kArgWorkers; ++i) bits.bits[i] = i < n ? out.bits[i] : 0;
@@ -23,7 +23,7 @@ hipError_t launch_sketch_max(const float* G, int64_t ldg, int n, int k, int64_t 
         case -2: return launch_sketch_max_s<-2>(G, code, a, bits, stream);
         case -4: return launch_sketch_max_s<-4>(G, code, a, bits, stream);
         case -8: return launch_sketch_max_s<-8>(G, code, a, bits, stream);
-        default: return launch_sketch_max_s<0>(G, code, a, bits, stream);
+        default: return code.stream ? launch_sketch_max_s<kStreamDriver>(G, code, a, bits, stream) : launch_sketch_max_s<0>(G, code, a, bits, stream);
     }
 }
 
