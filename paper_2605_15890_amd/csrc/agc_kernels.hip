@@ -426,8 +426,8 @@ struct SketchCheck {
     int fill_cap;           // and most bits of its fills
 };
 
-// One workgroup per worker (and layer, with the Euclidean scale).
-template <int MODE, int CAP>
+// One workgroup per worker (and layer, with the Euclidean scale).  SK: behind a sketch.
+template <int MODE, int CAP, bool SK>
 __global__ __launch_bounds__(kWgThreads) void k_scale_finalize(int n, QuantList<CAP> in, Workspace ws, int64_t ngroup,
                                                                SketchCheck check, float* scales)
 {
@@ -477,6 +477,20 @@ __global__ __launch_bounds__(kWgThreads) void k_scale_finalize(int n, QuantList<
         }
         scale = (float)sqrt(total);  // thread 0 holds the total, and it alone goes on
     }
+    // the worker's place in its fill of k_resolve, as stage_starts finds it; not an argument, whose bytes every other step
+    // would pay for.  The widths wait in lanes (one after the other from memory: 10 us for the kernel instead of 6).
+    int start = 0;
+    if (SK && tid < kWave) {
+#pragma unroll
+        for (int c = 0; c < (CAP + kWave - 1) / kWave; ++c) {
+            const int w = c * kWave + tid < n ? (int)in.bits[c * kWave + tid] : 0;
+            for (int j = 0; j < kWave && c * kWave + j <= i; ++j) {  // before worker j: does it open a fill?
+                const int wj = __builtin_amdgcn_readlane(w, j);
+                if (start + wj > check.fill_cap) start = 0;
+                if (c * kWave + j < i) start += wj;
+            }
+        }
+    }
     if (tid == 0) {
         const int l = MODE == 0 ? (int)blockIdx.y : 0, per = MODE == 0 ? (int)gridDim.y : 1;
         scales[(int64_t)i * per + l] = scale;
@@ -484,21 +498,16 @@ __global__ __launch_bounds__(kWgThreads) void k_scale_finalize(int n, QuantList<
         const WorkerQ q = worker_record(in, i, n, inv16_of(scale, b), unit_weight(in.w[i], scale, b));
         ws.wq[(int64_t)l * n + i] = q;
         // a weight that is not finite makes NaN of zero levels too, which k_resolve does not add up
-        if (check.state) {
-            int start = 0;  // of the worker in its fill, as stage_starts places it; not an argument: other steps would pay for its bytes
-            for (int j = 0; j < i; ++j) {
-                start += in.bits[j];
-                if (start + in.bits[j + 1] > check.fill_cap) start = 0;
-            }
+        if (SK) {
             const uint32_t ends = i == n - 1 || start + b + in.bits[i + 1] > check.fill_cap ? 512u : 0u;
             check.table[i] = make_uint4(__float_as_uint(q.inv16), __float_as_uint(q.coef), q.bits | (q.arrived << 8) | ends, 32u * (uint32_t)start);
         }
         bool none = false;
-        if (MODE == 1 && check.state && i == 0) {
+        if (SK && MODE == 1 && i == 0) {
             none = check.state[2] > check.limit;
             check.state[2] = 0u;  // the next step's
         }
-        if (check.state && !(!none && (MODE == 1 || scale >= check.lo_scale[i]) && fabsf(q.coef) < __builtin_inff()))
+        if (SK && !(!none && (MODE == 1 || scale >= check.lo_scale[i]) && fabsf(q.coef) < __builtin_inff()))
             (void)__hip_atomic_fetch_or(check.state, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
@@ -552,16 +561,19 @@ static hipError_t launch_scale_finalize_cap(int n, int scale_mode, const QuantSt
     if (scale_mode == 1) {
         if (layers > 0)
             hipLaunchKernelGGL((k_scale_finalize_layers<CAP>), dim3(layers), dim3(kWgThreads), 0, stream, n, q, ws, scales);
-        else
-            hipLaunchKernelGGL((k_scale_finalize<1, CAP>), dim3(n), dim3(kWgThreads), 0, stream, n, q, ws, (int64_t)0, check, scales);
+        else {
+            if (sk) hipLaunchKernelGGL((k_scale_finalize<1, CAP, true>), dim3(n), dim3(kWgThreads), 0, stream, n, q, ws, (int64_t)0, check, scales);
+            else hipLaunchKernelGGL((k_scale_finalize<1, CAP, false>), dim3(n), dim3(kWgThreads), 0, stream, n, q, ws, (int64_t)0, check, scales);
+        }
         return hipGetLastError();
     }
     const int64_t ngroup = layers > 0 ? ws.ngroup_layers : ws.ngroup;
     hipLaunchKernelGGL(k_scale_groups, dim3((unsigned)ngroup), dim3(kWgThreads), 0, stream, n, ws, ngroup);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_scale_finalize<0, CAP>), dim3(n, layers > 0 ? layers : 1), dim3(kWgThreads), 0, stream, n, q, ws,
-                       ngroup, check, scales);
+    const dim3 g(n, layers > 0 ? layers : 1), b(kWgThreads);
+    if (sk) hipLaunchKernelGGL((k_scale_finalize<0, CAP, true>), g, b, 0, stream, n, q, ws, ngroup, check, scales);
+    else hipLaunchKernelGGL((k_scale_finalize<0, CAP, false>), g, b, 0, stream, n, q, ws, ngroup, check, scales);
     return hipGetLastError();
 }
 
