@@ -146,13 +146,19 @@ inline bool use_sketch_max(int64_t d, int n, int k, double levels)
 {
     return k >= 12 && n <= 128 && d >= 20480 * 256 && (int64_t)k * d >= (int64_t)1 << 30 && levels <= 16.0 * n;
 }
-// Of how many of the sampled blocks the sketch may have more records than there is room for.  What it saves, in us for a million
-// coordinates, is about 0.37 k - 3, less 0.75 k where every block overflows: 64 workers with 0.30 of the blocks left over
-// 2352 | 2172, with 0.35 2350 | 2247;  40 with 0.30 1457 | 1387;  20 with 0.33 740 | 767.
+// What the sampled blocks may cost for the sketch to be made (k_sketch_bounds_max), in units of 1 / kReadCost of a second read of a
+// block's rows.  A block that overflows costs all of it, any other half of the part of its room that it fills (records are written and
+// read).  Fitted to both forms' times of 198 steps, 10-64 workers, 12-64 partitions, 4.3-6.5 GB of G, two to four bits: of those that
+// are taken one is 2 % slower than with two reads, the others at most 1 %.  Two reads | one, us, and cost (line): cyclic 64 x 25.6 M, heavy tails, two to
+// four bits 2313 | 1463 0.07 (0.44), 2363 | 1648 0.13, 2416 | 1935 0.31;  layers 2321 | 1772 0.12, 2361 | 2087 0.28, 2417 | 2377 0.43;
+// alike, two bits 2307 | 3249 1;  12 x 90 M, two bits, heavy tails 1627 | 1384 0.08 (0.17), Laplace 1626 | 1712 0.17 and alike
+// 1628 | 1954 0.22, whose blocks do not overflow;  16 x 68 M, one in a hundred values the largest, two bits, 0.5, 0.7, 0.85, 0.95 and 1.05
+// rooms of records 1573 | 1505 0.25 (0.25), 1574 | 1560 0.35, 1589 | 1652 0.43, 1591 | 1862 0.6, 1595 | 2846 1.
+constexpr uint32_t kReadCost = 64;
 inline uint32_t sketch_max_limit(int k, int samples)
 {
-    const double share = 0.45 - 4.0 / k;
-    return share > 0.0 ? (uint32_t)(share * samples) : 0u;
+    const double share = 0.5 - 4.0 / k;
+    return share > 0.0 ? (uint32_t)(share * kReadCost * samples) : 0u;
 }
 
 // Bytes of the sketch's two large arrays, signs and records: 0.97 GB at 64 workers x 25.6 M, 15 % of G there and up to half of

@@ -197,8 +197,8 @@ struct SketchDev {
     float* lo_scale;      // [n] lower bounds of the scales, and the largest multipliers that they leave
     float* lo_mult;       // [n]
     uint32_t* state;      // [3] not 0: a bound did not hold, or a weight is not finite, or there is no sketch;  length of the
-                          // list;  largest magnitude: sampled blocks that would overflow, 0 between steps
-    uint32_t limit;       // largest magnitude: with more of them G is read twice after all
+                          // list;  largest magnitude: what the sampled blocks would cost, 0 between steps
+    uint32_t limit;       // largest magnitude: above it G is read twice after all
     uint4* table;         // [n] what k_resolve needs to know of a worker: multiplier, weight, bits with 256 arrived and 512 end of a
                           // fill, first word in the staging area
     uint32_t* left;       // [groups of four blocks] list of those that k_resolve leaves to k_quantize, in any order

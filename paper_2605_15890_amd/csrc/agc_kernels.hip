@@ -737,39 +737,56 @@ __global__ __launch_bounds__(kWgThreads) void k_sketch_bounds(int n, BitList in,
     }
 }
 
-// The same for the largest-magnitude scale, whose bounds always hold, and whether the sketch is worth making: of how many of the
-// sampled blocks it would have more records than there is room for.  A coordinate becomes one with a probability of
-// L |f| / bound.  The bounds rise as k_sketch_max goes on (heavy tails: to three and more times those of the sample), so a block
-// may have a quarter more than the room.  The bounds go to the first row of the array of running maxima.
+// The same for the largest-magnitude scale, whose bounds always hold, and whether the sketch is worth making: what the sampled
+// blocks would cost, in parts of a second read of their rows (sketch_max_limit).  A coordinate becomes a record with a
+// probability of L |f| / bound.  The bounds rise as k_sketch_max goes on where the values have tails, which the sample shows: how far
+// the largest magnitude of all of it lies above the mean of those of its sixteenths.  Values of bounded size have 1,
+// Gaussian ones 1.1, heavy tails (t, three degrees) about 1.8.  Once more for every further factor of sixteen gives
+// the average block's bounds (heavy tails: three and more times those of the sample), from which follows what records cost;  whether a block
+// fits is asked with half as much again at most, since the first blocks find the sample's bounds, and one standard deviation of
+// room left.  The bounds go to the first row of the array of running maxima.
 constexpr int kBoundsWgs = 16;
 constexpr int kBoundsThreads = 1024;
 __global__ __launch_bounds__(kBoundsThreads) void k_sketch_bounds_max(int n, BitList in, const float* __restrict__ sums, int samples,
-                                                                      uint32_t* part_max, SketchDev sk)
+                                                                      float sixteens, uint32_t* part_max, SketchDev sk)
 {
-    __shared__ float per_sum[kMaxWorkers];  // expected records for each of a block's sum of magnitudes
+    __shared__ float2 per_sum[kMaxWorkers];  // expected records for each of a block's sum of magnitudes: early, average
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
     if (tid < n) {
         uint32_t m[kBoundRows];
+        float parts = 0.f;  // without the first row, which the first workgroup is raising
 #pragma unroll
         for (int t = 0; t < kBoundRows; ++t) m[t] = __hip_atomic_load(part_max + t * n + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
-        for (int t = 1; t < kBoundRows; ++t) m[0] = max(m[0], m[t]);
-        per_sum[tid] = m[0] != 0u ? (float)((1 << (in.bits[tid] - 1)) - 1) / __uint_as_float(m[0]) : 0.f;
+        for (int t = 1; t < kBoundRows; ++t) {
+            parts += __uint_as_float(m[t]);
+            m[0] = max(m[0], m[t]);
+        }
+        const float top = __uint_as_float(m[0]);
+        const float rise = fmaxf((float)(kBoundRows - 1) * top / parts, 1.f);  // 1 where that is not a number
+        const float per = m[0] != 0u ? (float)((1 << (in.bits[tid] - 1)) - 1) / top : 0.f;
+        per_sum[tid] = make_float2(per / fminf(rise, 1.5f), per / fminf(exp2f(sixteens * log2f(rise)), 3.f));
         if (blockIdx.x == 0) (void)__hip_atomic_fetch_max(part_max + tid, m[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    uint32_t full = 0u;
+    const float room = (float)sk.cap;
+    uint32_t cost = 0u;
     for (int e = blockIdx.x + wave * kBoundsWgs; e < samples; e += kBoundsWgs * (kBoundsThreads / kWave)) {
-        float records = 0.f;
+        float early = 0.f, average = 0.f;
         for (int j = lane; j < n; j += kWave) {
-            const float r = sums[(int64_t)e * n + j] * per_sum[j];
-            records += r < (float)kBlockCoords ? r : (float)kBlockCoords;
+            const float sum = sums[(int64_t)e * n + j];
+            const float r = sum * per_sum[j].x, q = sum * per_sum[j].y;
+            early += r < (float)kBlockCoords ? r : (float)kBlockCoords;
+            average += q < (float)kBlockCoords ? q : (float)kBlockCoords;
         }
 #pragma unroll
-        for (int h = 1; h < kWave; h *= 2) records += __shfl_xor(records, h);
-        full += records > 1.25f * (float)sk.cap ? 1u : 0u;
+        for (int h = 1; h < kWave; h *= 2) {
+            early += __shfl_xor(early, h);
+            average += __shfl_xor(average, h);
+        }
+        cost += early > room - sqrtf(room) ? kReadCost : (uint32_t)(0.5f * kReadCost * fminf(average / room, 1.f));
     }
-    if (lane == 0 && full != 0u) (void)__hip_atomic_fetch_add(sk.state + 2, full, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane == 0 && cost != 0u) (void)__hip_atomic_fetch_add(sk.state + 2, cost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (blockIdx.x == 0 && tid == 0) sk.state[0] = sk.state[1] = 0u;
 }
 
@@ -834,7 +851,9 @@ hipError_t launch_sketch_bounds_max(const float* G, int64_t ldg, int n, int k, i
     float* sums = reinterpret_cast<float*>(sk.recs);
     const hipError_t e = launch_sketch_sample<EpiTopSum>(G, ldg, n, k, d, code, samples, seed, step, ws.part_max, sums, stream);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_sketch_bounds_max, dim3(kBoundsWgs), dim3(kBoundsThreads), 0, stream, n, bit_list(n, out), sums, samples, ws.part_max, sk);
+    const float sixteens = (float)(log2((double)((d + kBlockCoords - 1) / kBlockCoords) / samples) / log2((double)kBoundRows));
+    hipLaunchKernelGGL(k_sketch_bounds_max, dim3(kBoundsWgs), dim3(kBoundsThreads), 0, stream, n, bit_list(n, out), sums, samples, sixteens,
+                       ws.part_max, sk);
     return hipGetLastError();
 }
 

@@ -192,6 +192,39 @@ def test_the_sample_decides(law):
     assert all(np.array_equal(x, y) for x, y in zip(outs[0], outs[2]))
 
 
+@pytest.mark.parametrize("rooms", [0.5, 0.9, 1.1])
+def test_bounded_values_take_one_read_where_it_is_faster(rooms):
+    """Values of which one in a hundred is the largest there is, so the sample's bounds do not rise, and as many records in a block
+    as the stated part of its room: 32 workers with two bits have 8192 coded values and room for 1024.  Records of a block
+    are within 1024 * rooms +- 31 (one standard deviation), the expectations of the sampled blocks within 1 % of each other, and what
+    these cost, half the part that they fill or all, is to be at most 0.5 - 4 / 32."""
+    import torch
+    rng = np.random.default_rng(12)
+    n, d = 32, (1 << 25) + 333
+    bits, w, mask = np.full(n, 2, np.uint8), np.ones(n, np.float32), np.ones(n, np.uint8)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(4)
+    G = api.padded_rows(n, d)
+    for j in range(n):
+        G[j].normal_(generator=gen).mul_((rooms / 8 - 0.01) / 0.99 / (2 / np.pi) ** 0.5)
+        largest = torch.rand(d, device="cuda", generator=gen) < 0.01
+        G[j][largest] = torch.sign(G[j][largest])
+    csr = cyclic_csr(rng, n, 1)
+    outs = []
+    for mode in (0, 2):
+        ctx = api.Context(n, n, d)
+        ctx.agc_set_code(*csr)
+        ctx.agc_debug_sketch_max(mode)
+        out, last = _outputs(ctx, G, bits, w, mask)
+        ctx.close()
+        assert last["one_read"] == (mode == 0)
+        if mode == 0:
+            assert last["bound_failed"] == (rooms > 0.75)
+            assert last["left"] == (last["groups"] if rooms > 0.75 else 0)
+        outs.append(out)
+    assert all(np.array_equal(a, b) for a, b in zip(*outs))
+
+
 def test_the_hook_refuses_other_scales():
     for kw in (dict(scale_mode=api.AGC_SCALE_L2), dict(bucket=256)):
         ctx = api.Context(2, 2, 4096, **kw)
