@@ -238,35 +238,6 @@ agc::CodeDev code_dev(const agc_ctx* c)
     return agc::CodeDev{c->d_row_ptr, c->d_col, c->d_val, band, c->d_win, parts, c->opts.force_generic ? nullptr : c->d_stream};
 }
 
-// The entries of a code whose rows are runs of consecutive ascending columns with neither end decreasing from worker to worker,
-// in the order of encode_stream, and a sentinel; empty if the code is not one, or too many workers are open at a time.
-std::vector<agc::StreamRec> stream_records(int n, const int32_t* row_ptr, const int32_t* col, const float* val)
-{
-    std::vector<agc::StreamRec> out;
-    for (int i = 0; i < n; ++i) {
-        const int e0 = row_ptr[i], e1 = row_ptr[i + 1];
-        if (e0 == e1) return {};
-        for (int e = e0 + 1; e < e1; ++e)
-            if (col[e] != col[e - 1] + 1) return {};
-        if (i > 0 && (col[e0] < col[row_ptr[i - 1]] || col[e1 - 1] < col[e0 - 1])) return {};
-    }
-    int lowest = 0, next = 0;  // workers lowest..next-1 are open
-    for (int j = n > 0 ? col[0] : 0; lowest < n; ++j) {
-        while (next < n && col[row_ptr[next]] == j) ++next;
-        const int first = lowest, end = next;
-        for (int i = first; i < end; ++i) {
-            if (i - lowest >= agc::kStreamSlots) return {};
-            const int e = row_ptr[i] + (j - col[row_ptr[i]]);
-            const int last = e + 1 == row_ptr[i + 1];
-            out.push_back(agc::StreamRec{j, val[e], i - lowest, last});
-            lowest += last;
-        }
-        if (lowest == next && next < n) j = col[row_ptr[next]] - 1;  // columns that no worker holds
-    }
-    out.push_back(agc::StreamRec{INT32_MAX, 0.f, 0, 0});
-    return out;
-}
-
 // Takes the workspace of the one-read form where a step of this context may use it, some bit-widths provided (those of two
 // bits have the fewest levels), and gives it back where none can: no code and hence no worker side, another kind of scale, layers.
 // Not called in the per-step calls.  Kernels that use it must have ended.
@@ -459,7 +430,7 @@ agc_status agc_set_code(agc_ctx* c, const int32_t* row_ptr, const int32_t* col, 
         if (e == hipSuccess) e = hipMemcpy(c->d_win, win.data(), sizeof(agc::WindowRec) * win.size(), hipMemcpyHostToDevice);
     }
     if (e == hipSuccess && band == 0 && nnz > 0) {
-        const std::vector<agc::StreamRec> entries = stream_records(c->n, row_ptr, col, val);
+        const std::vector<agc::StreamRec> entries = agc::stream_records(c->n, c->k, row_ptr, col, val);
         if (!entries.empty()) {
             e = dev_alloc(&c->d_stream, entries.size());
             if (e == hipSuccess)

@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "agc_dispatch.h"
+#include "agc_stream.h"
 
 namespace agc {
 
@@ -23,17 +24,6 @@ struct WindowRec {
 };
 static_assert(sizeof(WindowRec) == 64, "one record is 64 bytes");
 
-// Entry of a code whose rows are long intervals, in the order in which the columns' rows of G arrive (encode_stream): columns
-// ascending, workers ascending within a column.  The last one is a sentinel whose column matches no row.
-struct StreamRec {
-    int col;
-    float val;
-    int slot;             // which of the open workers: 0..kStreamSlots - 1, counted from the lowest
-    int last;             // the worker's last entry: it is formed, and the others move down a slot
-};
-static_assert(sizeof(StreamRec) == 16, "one record is one 16-byte scalar load");
-constexpr int kStreamSlots = 2;
-
 struct CodeDev {          // the code matrix B on the device
     const int* row_ptr;   // [n+1]
     const int* col;       // [nnz]
@@ -41,7 +31,7 @@ struct CodeDev {          // the code matrix B on the device
     int band;             // 0: generic CSR; s>0: cyclic band with s entries per row; -W: monotone intervals
     const WindowRec* win; // [n+1], monotone-interval codes only (else null)
     bool parts;           // use_parts() of this code
-    const StreamRec* stream;  // [nnz+1], band 0 and long monotone intervals with at most kStreamSlots workers open at a time (else null)
+    const StreamRec* stream;  // [nnz+1], codes that stream_records takes (else null)
 };
 
 // what the quantize pass needs to know about worker i, read with one scalar 32-byte load
