@@ -312,7 +312,7 @@ template <int S>
 static hipError_t launch_scale_pass_s(const float* G, const CodeDev& code, const ScaleArgs& a,
                                       int scale_mode, hipStream_t stream)
 {
-    if (S != kStreamDriver && code.parts) {
+    if (S != kStreamDriver && code.parts && !a.full) {
         if constexpr (S == kStreamDriver) {
         } else if (scale_mode == 0)
             hipLaunchKernelGGL((k_scale_pass_parts<S, 0>), dim3((unsigned)a.nseg), dim3(kWave * kParts * kSegBlocks), 0,
@@ -357,7 +357,7 @@ hipError_t launch_scale_pass(const float* G, int64_t ldg, int n, int k, int64_t 
         case -4: return launch_scale_pass_s<-4>(G, code, a, scale_mode, stream);
         case -8: return launch_scale_pass_s<-8>(G, code, a, scale_mode, stream);
         default:
-            return code.stream && !code.parts ? launch_scale_pass_s<kStreamDriver>(G, code, a, scale_mode, stream)
+            return code.stream && (sk || !code.parts) ? launch_scale_pass_s<kStreamDriver>(G, code, a, scale_mode, stream)
                                               : launch_scale_pass_s<0>(G, code, a, scale_mode, stream);
     }
 }

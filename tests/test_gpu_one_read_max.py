@@ -61,11 +61,12 @@ def _draw(rng, n, most):
 @pytest.mark.parametrize("kind,width", [("cyclic", s) for s in range(1, 9)] + [("interval", w) for w in (2, 4, 8)] + [("general", 5)])
 @pytest.mark.parametrize("d", [1, 255, 1024, 40000 + 77])
 def test_every_driver(kind, width, d):
-    """Few values that are not zero, so that the records fit whatever the sample saw."""
+    """Few values that are not zero, so that the records fit whatever the sample saw: a block has 266 / width +- 16 / sqrt(width)
+    (one standard deviation) of them, each coded by at most `width` workers, and room for 512 records."""
     rng = np.random.default_rng([d, width, len(kind)])
     n = k = 13
     bits, w, mask = _draw(rng, n, 9)
-    G = rng.standard_normal((k, d)) * (rng.random((k, d)) < 0.02)
+    G = rng.standard_normal((k, d)) * (rng.random((k, d)) < 0.08 / width)
     last = _check(G.astype(np.float32), _code(rng, kind, n, k, width), k, bits, w, mask, graph=width == 4)
     assert last["left"] == 0
 
@@ -86,6 +87,25 @@ def test_workers_widths_and_fills(n, most, law):
     last = _check(G.astype(np.float32), csr, k, bits, w, mask, unfused=n % 3 == 0)
     if law == "sparse":
         assert last["left"] == 0
+
+
+@pytest.mark.parametrize("kind,width,n", [("cyclic", s, 13) for s in range(1, 9)] + [("interval", w, 13) for w in (2, 4, 8)]
+                         + [("general", 5, 13), ("cyclic", 4, 70), ("interval", 4, 97), ("general", 5, 70), ("cyclic", 2, 161)])
+def test_scales_that_the_sample_has_not_seen(kind, width, n):
+    """The largest value of every row lies in one block, which in one of three trials at least is not one of the two that are sampled:
+    the scales can only come from the sketch itself, whose bounds lay far below them (every value that is not 0 a record) in the
+    blocks that began before that one was done."""
+    rng = np.random.default_rng([n, width, len(kind)])
+    d, k = 64 * 256 + 77, n
+    bits, w, mask = _draw(rng, n, 9)
+    csr = _code(rng, kind, n, k, width)
+    G = (1e-3 * rng.standard_normal((k, d))).astype(np.float32)
+    left = []
+    for block in (0, 31, 64):
+        one = G.copy()
+        one[:, 256 * block + 5] = rng.uniform(40.0, 50.0, k)
+        left.append(_check(one, csr, k, bits, w, mask)["left"])
+    assert max(left) > 0
 
 
 @pytest.mark.parametrize("records", [0, 1, 2, 255, 256, 257, 511, 512, 513, 768])
