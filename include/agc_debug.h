@@ -27,19 +27,19 @@ agc_status agc_debug_force_long(agc_ctx *ctx, int on);
 
 /* Testing hook: the form with one read of G (Euclidean scale of the whole vector, no one-bit workers).  mode 0: by the
  * library's rule; 1: wherever it can be made, at any length (allocates its workspace); 2: never (gives it back).  Waits for the
- * device.  Results are the same bits.  AGC_EINVAL without a context, for another mode, and for mode 1 in a context with another kind of scale. */
+ * device.  Results are the same bits.  AGC_EINVAL without a context, for another mode, and for mode 1 in a context with another kind of
+ * scale, where the other modes change nothing. */
 agc_status agc_debug_sketch(agc_ctx *ctx, int mode);
 
 /* The same for the largest-magnitude scale of the whole vector; mode 1 also keeps the sample from deciding for two reads.
- * Results are the same bits.  AGC_EINVAL without a context, for
- * another mode, and in a context with another kind of scale. */
+ * Results are the same bits.  AGC_EINVAL without a context, for another mode, and in a context with another kind of scale. */
 agc_status agc_debug_sketch_max(agc_ctx *ctx, int mode);
 
 /* Which form the last worker-side call on this context took (agc_encode_quantize, agc_step).  Waits for the device.
  *   out[0] 1: one read of G; 0: two, a scale of another kind, or no such call yet, and the rest is 0
  *   out[1] groups of four 256-coordinate blocks, out[2] how many of them G was read for once more after all (more coded
  *          values than there is room for), out[3] 1: all of them, because a scale lay below the bound that the sample gave,
- *          the sample showed that too many blocks would have more than there is room for (largest magnitude), or a weight is not finite
+ *          the sample showed that the coded values would cost more than they save (largest magnitude), or a weight is not finite
  * AGC_EINVAL without a context or out. */
 agc_status agc_debug_sketch_last(agc_ctx *ctx, int64_t out[4]);
 

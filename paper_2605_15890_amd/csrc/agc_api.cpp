@@ -117,7 +117,6 @@ hipError_t alloc_sketch(agc_ctx* c)
     agc::SketchDev& sk = c->sk;
     const size_t blocks = (size_t)(c->d + 255) / 256;
     sk.cap = sketch_room(c);
-    sk.limit = agc::sketch_max_limit(c->k, agc::sample_count((int64_t)blocks));
     sk.chunks = (c->n + 31) / 32;
     sk.blocks = 4 * c->ws.nseg;
     hipError_t e = dev_alloc(&sk.planes, blocks * (size_t)sk.chunks * 256);
@@ -257,7 +256,9 @@ hipError_t update_sketch(agc_ctx* c)
     }
     want = want && !c->opts.bucket && c->ws.n_layers == 0;
     if (!want) free_sketch(c);
-    return want && !c->sk.planes ? alloc_sketch(c) : hipSuccess;
+    const hipError_t e = want && !c->sk.planes ? alloc_sketch(c) : hipSuccess;
+    c->sk.limit = c->sketch_mode == 1 ? UINT32_MAX : agc::sketch_max_limit(c->k, agc::sample_count((c->d + 255) / 256));
+    return e;
 }
 
 bool use_sketch(const agc_ctx* c, const agc::CodeDev& code, const uint8_t* bits)
@@ -871,10 +872,11 @@ agc_status agc_debug_force_long(agc_ctx* c, int on)
 agc_status agc_debug_sketch(agc_ctx* c, int mode)
 {
     if (!c || mode < 0 || mode > 2) return fail(nullptr, AGC_EINVAL, "null context or unknown mode");
-    if (mode == 1 && (c->opts.bucket || c->opts.scale_mode != AGC_SCALE_L2))
-        return fail(c, AGC_EINVAL, "one scale of the whole vector, Euclidean");
+    const bool other = c->opts.bucket || c->opts.scale_mode != AGC_SCALE_L2;
+    if (mode == 1 && other) return fail(c, AGC_EINVAL, "one scale of the whole vector, Euclidean");
     hipError_t e = hipDeviceSynchronize();
     if (e != hipSuccess) return hip_fail(c, e, "hipDeviceSynchronize");
+    if (other) return AGC_OK;
     c->sketch_mode = mode;
     e = update_sketch(c);
     return e != hipSuccess && mode == 1 ? fail(c, AGC_ENOMEM, "workspace of the one-read form") : AGC_OK;
@@ -889,7 +891,6 @@ agc_status agc_debug_sketch_max(agc_ctx* c, int mode)
     if (e != hipSuccess) return hip_fail(c, e, "hipDeviceSynchronize");
     c->sketch_mode = mode;
     e = update_sketch(c);
-    c->sk.limit = mode == 1 ? UINT32_MAX : agc::sketch_max_limit(c->k, agc::sample_count((c->d + 255) / 256));
     return e != hipSuccess && mode == 1 ? fail(c, AGC_ENOMEM, "workspace of the one-read form") : AGC_OK;
 }
 

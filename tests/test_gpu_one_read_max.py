@@ -245,6 +245,31 @@ def test_bounded_values_take_one_read_where_it_is_faster(rooms):
     assert all(np.array_equal(a, b) for a, b in zip(*outs))
 
 
+def test_the_hook_keeps_its_mode():
+    """Forced by the hook, the sample does not decide, also with the workspace that is taken again after layers; the hook of the other
+    kind of scale changes nothing.  Back by the rule, a vector this short is read twice."""
+    rng = np.random.default_rng(13)
+    n, d = 16, 64 * 256
+    bits, w, mask = np.full(n, 8, np.uint8), np.ones(n, np.float32), np.ones(n, np.uint8)
+    csr, G = cyclic_csr(rng, n, 2), to_device(rng.standard_normal((n, d)).astype(np.float32))   # alike: every block overflows
+    ctx = api.Context(n, n, d)
+    ctx.agc_set_code(*csr)
+    ctx.agc_debug_sketch_max(1)
+    outs = []
+    for between in (lambda: None, lambda: (ctx.agc_set_layers(np.array([256, d], np.int64)), ctx.agc_set_layers(np.array([], np.int64))),
+                    lambda: ctx.agc_debug_sketch(0), lambda: ctx.agc_debug_sketch(2), lambda: ctx.agc_set_code(*csr)):
+        between()
+        out, last = _outputs(ctx, G, bits, w, mask)
+        assert last["one_read"] and not last["bound_failed"] and last["left"] > 0
+        outs.append(out)
+    ctx.agc_debug_sketch_max(0)
+    out, last = _outputs(ctx, G, bits, w, mask)
+    assert not last["one_read"]
+    for other in outs:
+        assert all(np.array_equal(a, b) for a, b in zip(out, other))
+    ctx.close()
+
+
 def test_the_hook_refuses_other_scales():
     for kw in (dict(scale_mode=api.AGC_SCALE_L2), dict(bucket=256)):
         ctx = api.Context(2, 2, 4096, **kw)
