@@ -633,8 +633,8 @@ agc_status encode_quantize_impl(agc_ctx* c, const float* G, int64_t ldg, const u
         return t.end();
     }
     const bool maxabs = c->opts.scale_mode == AGC_SCALE_MAXABS;
-    if (maxabs && c->slots_dirty) {  // the finalize hands the running maxima back zeroed; restore that after a failure
-        e = agc::launch_scale_clear_slots(c->n, c->ws, stream);
+    if (maxabs && c->slots_dirty) {  // the finalize hands them back zeroed; restore that after a failure
+        e = agc::launch_scale_clear_slots(c->n, c->ws, c->sk.state, stream);
         if (e != hipSuccess) return hip_fail(c, e, "clearing the scale workspace");
         c->slots_dirty = false;
     }

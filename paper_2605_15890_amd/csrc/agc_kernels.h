@@ -264,8 +264,8 @@ struct DecodeList {        // the same as kernel arguments of the decode's prolo
 hipError_t launch_scale_pass(const float* G, int64_t ldg, int n, int k, int64_t d,
                              const CodeDev& code, int scale_mode, const Workspace& ws,
                              const SketchDev* sk, hipStream_t stream);
-// all rows of the max-abs slot array back to zero
-hipError_t launch_scale_clear_slots(int n, const Workspace& ws, hipStream_t stream);
+// all rows of the max-abs slot array, and the sketch's state[2] if there is one, back to zero
+hipError_t launch_scale_clear_slots(int n, const Workspace& ws, uint32_t* state, hipStream_t stream);
 // K1f: partials -> scales[n] and the per-worker table of the quantize pass (with layer-wise scales:
 // scales[n][n_layers] and one table per layer).
 // sw.fuse != 0: the quantize pass that follows also forms the estimate (ghat) from the codes it

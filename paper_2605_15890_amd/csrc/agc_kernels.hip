@@ -276,19 +276,20 @@ __global__ __launch_bounds__(kWave * (MODE == 1 ? kParts : kParts * kSegBlocks))
     }
 }
 
-// rows of the max-abs slot array back to zero (context creation does it with a memset; this
-// kernel serves a call that follows one whose launches failed half-way)
-__global__ __launch_bounds__(kWgThreads) void k_scale_clear_slots(uint32_t* slots, int count)
+// What the finalize kernel hands back zeroed: rows of the max-abs slot array, and the sketch's cost of the sampled blocks (state
+// null: there is none).  Creation does it with a memset; this kernel serves a call that follows one whose launches failed half-way.
+__global__ __launch_bounds__(kWgThreads) void k_scale_clear_slots(uint32_t* slots, int count, uint32_t* state)
 {
     const int t = blockIdx.x * kWgThreads + threadIdx.x;
     if (t < count) slots[t] = 0u;
+    if (t == 0 && state) state[2] = 0u;
 }
 
-hipError_t launch_scale_clear_slots(int n, const Workspace& ws, hipStream_t stream)
+hipError_t launch_scale_clear_slots(int n, const Workspace& ws, uint32_t* state, hipStream_t stream)
 {
     const int count = n * ws.max_rows;
     hipLaunchKernelGGL(k_scale_clear_slots, dim3((count + kWgThreads - 1) / kWgThreads), dim3(kWgThreads), 0, stream,
-                       ws.part_max, count);
+                       ws.part_max, count, state);
     return hipGetLastError();
 }
 
