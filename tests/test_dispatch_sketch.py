@@ -26,6 +26,15 @@ extern "C" int64_t block(int64_t nblocks, int samples, uint64_t seed, uint64_t s
 }
 extern "C" int count(int64_t nblocks) { return agc::sample_count(nblocks); }
 extern "C" int cap(int n) { return agc::sketch_cap(n); }
+extern "C" int one_read_max(int64_t d, int n, int k, double levels) { return agc::use_sketch_max(d, n, k, levels); }
+extern "C" int max_cap(int n, int k) { return agc::sketch_max_cap(n, k); }
+extern "C" unsigned max_limit(int k, int samples) { return agc::sketch_max_limit(k, samples); }
+extern "C" unsigned read_cost() { return agc::kReadCost; }
+extern "C" int64_t max_bytes(int n, int k, int64_t d) { return agc::sketch_bytes(n, d, agc::sketch_max_cap(n, k)); }
+extern "C" int max_fits(int n, int k, int64_t d, size_t free_bytes, size_t total_bytes)
+{
+    return agc::sketch_fits(n, k, d, free_bytes, total_bytes, agc::sketch_max_cap(n, k));
+}
 """
 
 
@@ -42,6 +51,10 @@ def rules(tmp_path_factory):
     lib.one_read.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_double, ctypes.c_int, ctypes.c_int]
     lib.fits.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_size_t, ctypes.c_size_t]
     lib.bytes.argtypes, lib.bytes.restype = [ctypes.c_int, ctypes.c_int64], ctypes.c_int64
+    lib.one_read_max.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_int, ctypes.c_double]
+    lib.max_bytes.argtypes, lib.max_bytes.restype = [ctypes.c_int, ctypes.c_int, ctypes.c_int64], ctypes.c_int64
+    lib.max_fits.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int64, ctypes.c_size_t, ctypes.c_size_t]
+    lib.max_limit.restype = lib.read_cost.restype = ctypes.c_uint
     lib.count.argtypes = [ctypes.c_int64]
     lib.block.argtypes = [ctypes.c_int64, ctypes.c_int, ctypes.c_uint64, ctypes.c_uint64, ctypes.c_int64]
     lib.block.restype = ctypes.c_int64
@@ -97,6 +110,40 @@ def test_a_program_that_fills_the_card_keeps_its_memory(rules):
     for n, k, d in ((1, 1, 2 ** 33), (256, 65536, 2 ** 33), (256, 4, 2 ** 33)):
         assert not rules.fits(n, k, d, total, total)
     assert not rules.fits(1, 1, 1, 0, 0)
+
+
+@pytest.mark.parametrize("one,d,n,k,levels", [
+    (1, 25_600_000, 64, 64, 192), (1, 27_000_000, 40, 40, 160), (1, 90_000_000, 12, 12, 36), (1, 36_000_000, 10, 30, 40),
+    (1, 25_600_000, 64, 64, 1024), (0, 25_600_000, 64, 64, 1025),                        # wide codes
+    (1, 1 << 24, 64, 64, 192), (0, (1 << 24) - 1, 64, 64, 192), (0, 12_800_000, 64, 64, 192),   # less than 4 GB
+    (1, 20480 * 256, 128, 205, 384), (0, 20480 * 256 - 1, 128, 256, 384),                # too short
+    (0, 8_500_000, 129, 129, 387), (0, 98_000_000, 11, 11, 33), (0, 2 ** 33, 1, 1, 1), (1, 2 ** 33, 128, 65536, 128)])
+def test_one_read_of_the_largest_magnitude(rules, one, d, n, k, levels):
+    assert rules.one_read_max(d, n, k, float(levels)) == one
+
+
+@pytest.mark.parametrize("k,cost,one", [  # of steps in both forms
+    (64, 0.13, 1), (64, 0.31, 1), (64, 0.43, 1), (64, 1.0, 0), (40, 0.28, 1), (24, 0.28, 1), (12, 0.08, 1), (12, 0.17, 0), (12, 0.22, 0),
+    (16, 0.25, 1), (16, 0.43, 0), (16, 0.6, 0), (30, 0.02, 1)])
+def test_what_the_sampled_blocks_may_cost(rules, k, cost, one):
+    for samples in (163, 512):
+        assert (int(cost * rules.read_cost() * samples) <= rules.max_limit(k, samples)) == one
+
+
+def test_ends_of_the_ranges_of_the_largest_magnitude(rules):
+    """Records leave the ring of 512 in halves of it, and their array holds the sample's sums, four bytes a worker and block."""
+    for k in (1, 2, 7, 8, 9, 11, 12, 13, 64, 65535, 65536):
+        assert rules.max_limit(k, 1) <= rules.read_cost() // 2 and rules.max_limit(k, 512) < 2 ** 15
+        assert (rules.max_limit(k, 512) == 0) == (k <= 8)
+        for n in range(1, 257):
+            cap = rules.max_cap(n, k)
+            assert cap >= 256 and cap % 256 == 0 and cap - 256 < min(32 * k, 128 * n) <= cap and 8 * cap >= 4 * n
+            assert cap <= 256 * n
+    need = rules.max_bytes(64, 64, 25_600_000)
+    assert need == 100_000 * (2048 + 8 * 2048)
+    total = 288 * 10 ** 9
+    assert rules.max_fits(64, 64, 25_600_000, 8 * need, total) and not rules.max_fits(64, 64, 25_600_000, 8 * need - 8, total)
+    assert not rules.max_fits(256, 65536, 2 ** 33, total, total) and not rules.max_fits(1, 1, 1, 0, 0)
 
 
 @pytest.mark.parametrize("nblocks,samples", [(1, 1), (63, 1), (64, 2), (4096, 128), (10_547, 329), (32768, 512), (100_000, 512),

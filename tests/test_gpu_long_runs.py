@@ -74,7 +74,7 @@ def test_long_runs(name, mode, d, form):
 
 @pytest.mark.parametrize("mode", [api.AGC_SCALE_MAXABS, api.AGC_SCALE_L2])
 def test_forty_workers_in_several_fills(mode):
-    """More codes than one fill of the staging area holds, two blocks a wave, rows non-temporal and kept."""
+    """More codes than one fill of the staging area holds, rows non-temporal and kept."""
     import torch
     rng = np.random.default_rng(3)
     runs = [(i // 4 * 10, 1) if i % 4 else (max(0, i // 4 * 10 - 10), 11 if i else 1) for i in range(40)]
@@ -97,3 +97,62 @@ def test_forty_workers_in_several_fills(mode):
             outs.append([c.cpu().numpy() for c in codes] + [scales.cpu().numpy().view(np.uint32), ghat.cpu().numpy().view(np.uint32)])
             ctx.close()
         assert all(np.array_equal(a, b) for a, b in zip(*outs))
+
+
+def _both_drivers(csr, k, G, bits, w, mask, layers=None):
+    """Codes, scales and estimate of the streaming driver and of the general one, and the form that the first took."""
+    import torch
+    outs, last = [], None
+    for generic in (False, True):
+        ctx = api.Context(len(bits), k, G.shape[1], force_generic=generic)
+        ctx.agc_set_code(*csr)
+        if layers is not None:
+            ctx.agc_set_layers(np.array(layers, np.int64))
+        elif generic:
+            ctx.agc_debug_sketch_max(2)
+        codes, scales, ghat = ctx.alloc_outputs(bits)
+        ctx.agc_step(G, bits, w, mask, 5, 6, codes, scales, ghat)
+        torch.cuda.synchronize()
+        last = last or ctx.agc_debug_sketch_last()
+        outs.append([*codes, scales.view(torch.int32), ghat.view(torch.int32)])
+        ctx.close()
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
+    return last
+
+
+@pytest.mark.parametrize("d", [20480 * 256, 20481 * 256 + 77, 20482 * 256 - 3])
+@pytest.mark.parametrize("layers", [False, True])
+def test_two_blocks_a_wave(d, layers):
+    """From 20480 blocks a wave of the scale pass takes two: whole pairs, a single block and a piece of one at the end, and layers that
+    end between the two blocks of a pair.  Against the general driver, which takes one."""
+    import torch
+    rng = np.random.default_rng([d, layers])
+    runs, k = CODES["two_rows_of_two"]
+    csr, n = _runs(rng, runs), len(runs)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(2)
+    G = api.padded_rows(k, d)
+    G.normal_(generator=gen)
+    G[:, 5::1001] = -0.0
+    w, mask = rng.uniform(0.2, 3.0, n).astype(np.float32), np.ones(n, np.uint8)
+    last = _both_drivers(csr, k, G, np.full(n, 5, np.uint8), w, mask, [256 * 7, 256 * 8, 256 * 1025, d] if layers else None)
+    assert not last["one_read"]
+
+
+@pytest.mark.parametrize("law", ["heavy", "alike"])
+def test_one_read_of_long_runs_by_the_rule(law):
+    """A length that the rule takes: the sketch of the streaming driver, and, where the sample refuses it, the scale pass that
+    depends on that, two blocks a wave."""
+    import torch
+    rng = np.random.default_rng(8)
+    runs, k = CODES["one_row_shared"]
+    csr, n, d = _runs(rng, runs), len(runs), (1 << 30) // 30 + 77
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(2)
+    G = api.padded_rows(k, d)
+    for j in range(k):
+        G[j].normal_(generator=gen)
+        if law == "heavy":
+            G[j].pow_(7)
+    last = _both_drivers(csr, k, G, np.full(n, 5, np.uint8), np.ones(n, np.float32), np.ones(n, np.uint8))
+    assert last["one_read"] and last["bound_failed"] == (law == "alike")
