@@ -37,7 +37,7 @@ struct agc_ctx {
     int* d_col = nullptr;
     float* d_val = nullptr;
     agc::WindowRec* d_win = nullptr;   // monotone-interval codes only
-    agc::StreamRec* d_stream = nullptr;  // long monotone intervals only
+    agc::StreamRec* d_stream = nullptr;  // codes that stream_records takes
     int band = 0;
     bool force_long = false;  // testing hook
     int sketch_mode = 0;      // testing hook: 0 by the rule, 1 wherever the sketch can be made, 2 never
@@ -118,10 +118,9 @@ hipError_t alloc_sketch(agc_ctx* c)
     const size_t blocks = (size_t)(c->d + 255) / 256;
     sk.cap = sketch_room(c);
     sk.chunks = (c->n + 31) / 32;
-    sk.blocks = 4 * c->ws.nseg;
     hipError_t e = dev_alloc(&sk.planes, blocks * (size_t)sk.chunks * 256);
     if (e == hipSuccess) e = dev_alloc(&sk.recs, blocks * (size_t)sk.cap);
-    if (e == hipSuccess) e = dev_alloc(&sk.counts, (size_t)sk.blocks);
+    if (e == hipSuccess) e = dev_alloc(&sk.counts, 4 * (size_t)c->ws.nseg);
     if (c->opts.scale_mode == AGC_SCALE_L2) {
         if (e == hipSuccess) e = dev_alloc(&sk.lo_scale, (size_t)c->n);
         if (e == hipSuccess) e = dev_alloc(&sk.lo_mult, (size_t)c->n);

@@ -484,7 +484,7 @@ struct CsrView {
     const int* __restrict__ col;
     const float* __restrict__ val;
     const WindowRec* __restrict__ win;  // monotone-interval codes: one record per row + sentinel
-    const StreamRec* __restrict__ stream = nullptr;  // long monotone intervals: one record per entry + sentinel
+    const StreamRec* __restrict__ stream = nullptr;  // codes that stream_records takes: one record per entry + sentinel
     bool keep = false;                               // and G is small enough to be found in the caches again
 };
 

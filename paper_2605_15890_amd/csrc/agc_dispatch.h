@@ -126,7 +126,7 @@ inline bool use_sketch(int64_t d, int n, int k, double levels, bool gather, bool
 }
 
 // One read of G for the largest magnitude (k_sketch_max).  Records a block has room for: half as many bytes, written and read, as
-// a second read of its rows, and no more than half of its coded elements.
+// a second read of its rows, and no more than half of its coded elements, rounded up to halves of the ring that they wait in.
 inline int sketch_max_cap(int n, int k)
 {
     const int room = 32 * k < 128 * n ? 32 * k : 128 * n;

@@ -192,7 +192,6 @@ struct SketchDev {
     uint4* table;         // [n] what k_resolve needs to know of a worker: multiplier, weight, bits with 256 arrived and 512 end of a
                           // fill, first word in the staging area
     uint32_t* left;       // [groups of four blocks] list of those that k_resolve leaves to k_quantize, in any order
-    int64_t blocks;       // entries of counts
     int cap;              // even
     int chunks;           // ceil(n / 32)
 };
@@ -218,6 +217,12 @@ struct QuantStreams {      // host arrays of the encode call
 struct BitList {           // bit-widths as a kernel argument
     uint8_t bits[kArgWorkers];
 };
+inline BitList bit_list(int n, const QuantStreams& out)
+{
+    BitList bits;
+    for (int i = 0; i < kArgWorkers; ++i) bits.bits[i] = i < n ? out.bits[i] : 0;
+    return bits;
+}
 
 struct StepWeights {       // decode side of a fused step
     float w[kArgWorkers];

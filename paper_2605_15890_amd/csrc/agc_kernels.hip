@@ -38,7 +38,7 @@ struct ScaleArgs {
     uint32_t* part_max;
     double* part_sq;
     const WindowRec* win;  // monotone-interval codes only
-    const StreamRec* stream;     // long monotone intervals only
+    const StreamRec* stream;     // codes that stream_records takes
     const uint8_t* block_layer;  // layer-wise scales only (max-abs): the layer of every block
     const int* seg_first;        // layer-wise Euclidean scales only: the segments of the layers
     const uint8_t* seg_blocks;
@@ -418,7 +418,7 @@ __device__ __forceinline__ float unit_weight(float w, float scale, int b)
     return (float)(((double)w * (double)scale) / L);
 }
 
-// What the finalize kernel checks of a sketch (state null: there is none).
+// What the finalize kernel checks of a sketch, with SK.
 struct SketchCheck {
     const float* lo_scale;  // Euclidean: the lower bounds that it was made with
     uint32_t* state;
@@ -556,7 +556,7 @@ static hipError_t launch_scale_finalize_cap(int n, int scale_mode, const QuantSt
                                             const Workspace& ws, const SketchDev* sk, float* scales, hipStream_t stream)
 {
     const SketchCheck check = sk ? SketchCheck{sk->lo_scale, sk->state, sk->limit, sk->table, out.resolve_cap}
-                                 : SketchCheck{nullptr, nullptr, 0u, nullptr, 0};
+                                 : SketchCheck{};
     const QuantList<CAP> q = quant_list<CAP>(n, out, sw);
     const int layers = ws.n_layers;
     if (scale_mode == 1) {
@@ -628,13 +628,6 @@ __device__ __forceinline__ void stage_rows(const float* __restrict__ G, int64_t 
     __syncthreads();
 }
 
-// What bounds it: latency, one block per workgroup and all workgroups resident at once.  S > 0: the register ring.  Other codes
-// with STAGED: all rows of the block are requested at once and wait in LDS, where each wave takes its workers' from; else
-// rows are gathered from memory (more rows than LDS holds).  64 workers x 25.6 M, window of 8: the window driver, whose
-// unrolled code comes cold into the instruction cache, took 20.9 us, with 4 | 8 | 12 rows requested ahead 19.6 | 38.9 |
-// 39.0, staged 11.2;  50 x 5.4 M 19.9 | 8.4;  10 workers of 30 partitions, gathered 8.4, staged 5.9.  The ring of a cyclic band
-// is the faster one: 64 x 1 M 5.6, staged 7.1, 32 x 11.7 M 6.2 and 8.0.  Code entries one a lane instead of scalar loads,
-// a worker ahead: 13.2 for 11.2.
 // What the sample keeps of a block and worker for the largest-magnitude scale: the largest magnitude and the sum of all
 struct EpiTopSum {
     typedef float2 Part;
@@ -663,6 +656,14 @@ struct EpiTopSum {
 
 constexpr int kBoundRows = 16;  // rows of the array of running maxima that the sample is folded into
 
+// What bounds it: latency, one block per workgroup and all workgroups resident at once.  S > 0: the register ring.  Other codes
+// with STAGED: all rows of the block are requested at once and wait in LDS, where each wave takes its workers' from; else
+// rows are gathered from memory (more rows than LDS holds).  64 workers x 25.6 M, window of 8: the window driver, whose
+// unrolled code comes cold into the instruction cache, took 20.9 us, with 4 | 8 | 12 rows requested ahead 19.6 | 38.9 |
+// 39.0, staged 11.2;  50 x 5.4 M 19.9 | 8.4;  10 workers of 30 partitions, gathered 8.4, staged 5.9.  The ring of a cyclic band
+// is the faster one: 64 x 1 M 5.6, staged 7.1, 32 x 11.7 M 6.2 and 8.0.  Code entries one a lane instead of scalar loads,
+// a worker ahead: 13.2 for 11.2.
+//
 // sums: [sample][worker], sums of squares or of magnitudes; maxima go to the first rows of a.part_max
 template <int S, bool STAGED, class Epi>
 __global__ __launch_bounds__(kWave * kSampleWaves) void k_sketch_sample(const float* __restrict__ G, const int* __restrict__ row_ptr,
@@ -819,13 +820,6 @@ static hipError_t launch_sketch_sample(const float* G, int64_t ldg, int n, int k
             else launch_sketch_sample_s<0, false, Epi>(G, code, a, samples, runs, sums, stream);
     }
     return hipGetLastError();
-}
-
-static BitList bit_list(int n, const QuantStreams& out)
-{
-    BitList bits;
-    for (int i = 0; i < kArgWorkers; ++i) bits.bits[i] = i < n ? out.bits[i] : 0;
-    return bits;
 }
 
 hipError_t launch_sketch_bounds(const float* G, int64_t ldg, int n, int k, int64_t d, const CodeDev& code,

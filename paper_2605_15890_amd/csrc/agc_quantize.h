@@ -21,7 +21,7 @@ struct QuantArgs {
     int64_t nb;
     float* ghat;    // fused step only
     const WindowRec* win;  // monotone-interval codes only; filled in by the launcher
-    const StreamRec* stream;  // long monotone intervals only; likewise
+    const StreamRec* stream;  // codes that stream_records takes; likewise
     int stage_bits;        // bit-widths of the fullest fill of the staging area: at most stage_limit(), kPartBits with parts
     int stage_fills;       // how many fills the workers need: 1 unless the widths sum to more than that; always 1 with parts
     const uint8_t* block_layer;  // layer-wise scales only: the layer of every block; wq is then [layer][n]

@@ -34,7 +34,7 @@ struct SketchArgs {
     int64_t d;
     uint32_t key0, key1, step_lo, step_hi;
     const WindowRec* win;  // monotone-interval codes only
-    const StreamRec* stream;  // long monotone intervals only
+    const StreamRec* stream;  // codes that stream_records takes
     double* part_sq;       // Euclidean scale: [segment][worker]
     uint32_t* run_max;     // largest magnitude: [worker]
     SketchDev sk;

@@ -9,8 +9,7 @@ hipError_t launch_sketch_max(const float* G, int64_t ldg, int n, int k, int64_t 
     const SketchArgs a{ldg, n, k, d, (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32),
                        code.win, code.stream, nullptr, ws.part_max, sk};
     if (code.band < 0 && !code.win) return hipErrorInvalidValue;  // the window driver reads the records
-    BitList bits;
-    for (int i = 0; i < kArgWorkers; ++i) bits.bits[i] = i < n ? out.bits[i] : 0;
+    const BitList bits = bit_list(n, out);
     switch (code.band) {
         case 1: return launch_sketch_max_s<1>(G, code, a, bits, stream);
         case 2: return launch_sketch_max_s<2>(G, code, a, bits, stream);
