@@ -753,7 +753,9 @@ __global__ __launch_bounds__(kBoundsThreads) void k_sketch_bounds_max(int n, Bit
                                                                       float sixteens, uint32_t* part_max, SketchDev sk)
 {
     __shared__ float2 per_sum[kMaxWorkers];  // expected records for each of a block's sum of magnitudes: early, average
+    __shared__ uint32_t lds_cost;            // one addition to memory a workgroup: one a wave took 3 us
     const int tid = threadIdx.x, wave = tid / kWave, lane = tid % kWave;
+    if (tid == 0) lds_cost = 0u;
     if (tid < n) {
         uint32_t m[kBoundRows];
         float parts = 0.f;  // without the first row, which the first workgroup is raising
@@ -764,14 +766,16 @@ __global__ __launch_bounds__(kBoundsThreads) void k_sketch_bounds_max(int n, Bit
             parts += __uint_as_float(m[t]);
             m[0] = max(m[0], m[t]);
         }
+        // the chip's own reciprocal, logarithm and exponential: a decision, no result
         const float top = __uint_as_float(m[0]);
-        const float rise = fmaxf((float)(kBoundRows - 1) * top / parts, 1.f);  // 1 where that is not a number
-        const float per = m[0] != 0u ? (float)((1 << (in.bits[tid] - 1)) - 1) / top : 0.f;
-        per_sum[tid] = make_float2(per / fminf(rise, 1.5f), per / fminf(exp2f(sixteens * log2f(rise)), 3.f));
+        const float rise = fmaxf((float)(kBoundRows - 1) * top * __builtin_amdgcn_rcpf(parts), 1.f);  // 1 where that is not a number
+        const float per = m[0] != 0u ? (float)((1 << (in.bits[tid] - 1)) - 1) * __builtin_amdgcn_rcpf(top) : 0.f;
+        per_sum[tid] = make_float2(per * __builtin_amdgcn_rcpf(fminf(rise, 1.5f)),
+                                   per * __builtin_amdgcn_rcpf(fminf(__builtin_amdgcn_exp2f(sixteens * __builtin_amdgcn_logf(rise)), 3.f)));
         if (blockIdx.x == 0) (void)__hip_atomic_fetch_max(part_max + tid, m[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    const float room = (float)sk.cap;
+    const float room = (float)sk.cap, most = room - sqrtf(room), unit = 0.5f * kReadCost / room;
     uint32_t cost = 0u;
     for (int e = blockIdx.x + wave * kBoundsWgs; e < samples; e += kBoundsWgs * (kBoundsThreads / kWave)) {
         float early = 0.f, average = 0.f;
@@ -786,9 +790,11 @@ __global__ __launch_bounds__(kBoundsThreads) void k_sketch_bounds_max(int n, Bit
             early += __shfl_xor(early, h);
             average += __shfl_xor(average, h);
         }
-        cost += early > room - sqrtf(room) ? kReadCost : (uint32_t)(0.5f * kReadCost * fminf(average / room, 1.f));
+        cost += early > most ? kReadCost : (uint32_t)(unit * fminf(average, room));
     }
-    if (lane == 0 && cost != 0u) (void)__hip_atomic_fetch_add(sk.state + 2, cost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane == 0) atomicAdd(&lds_cost, cost);
+    __syncthreads();
+    if (tid == 0 && lds_cost != 0u) (void)__hip_atomic_fetch_add(sk.state + 2, lds_cost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (blockIdx.x == 0 && tid == 0) sk.state[0] = sk.state[1] = 0u;
 }
 
