@@ -210,7 +210,8 @@ struct QuantStreams {      // host arrays of the encode call
     uint8_t bits[kArgWorkers];
     uint16_t stage_start[kArgWorkers];  // stage_starts() of the bit-widths
     int stage_fills, stage_bits;        // and what it returns: fills, the fullest one in bits
-    int resolve_cap, resolve_bits;      // the same for the fills of k_resolve, where it runs: most bits of a fill, and of the fullest one
+    uint16_t resolve_start[kArgWorkers];  // the same for the fills of k_resolve, where it runs
+    int resolve_bits;
     bool parts;                         // the quantize pass shares the workers of a block among the waves
 };
 
@@ -239,6 +240,13 @@ struct QuantList {         // both as kernel arguments of the table kernels, for
     uint8_t arrived[CAP];
     int fuse;
 };
+
+template <int CAP, bool SK>
+struct ResolveStarts {     // and what the finalize kernel needs behind a sketch: stage_starts() of the fills of k_resolve
+    uint16_t start[CAP];
+};
+template <int CAP>
+struct ResolveStarts<CAP, false> {};
 
 struct DecodeStreams {     // the arrived workers of a decode call, in ascending order (host side)
     int n_arrived;

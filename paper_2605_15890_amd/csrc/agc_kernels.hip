@@ -424,17 +424,20 @@ struct SketchCheck {
     uint32_t* state;
     uint32_t limit;         // largest magnitude: with state[2] above this there is no sketch
     uint4* table;           // k_resolve's
-    int fill_cap;           // and most bits of its fills
 };
 
-// One workgroup per worker (and layer, with the Euclidean scale).  SK: behind a sketch.
+// One workgroup per worker (and layer, with the Euclidean scale).  SK: behind a sketch; the places of k_resolve are arguments of these
+// instances alone.  Found here from the widths of the workers before, the kernel took 1.3 us longer (64 workers; 64 x 1 M, Euclidean,
+// whole step 90.2 us, 87.0 with the arguments).
 template <int MODE, int CAP, bool SK>
-__global__ __launch_bounds__(kWgThreads) void k_scale_finalize(int n, QuantList<CAP> in, Workspace ws, int64_t ngroup,
-                                                               SketchCheck check, float* scales)
+__global__ __launch_bounds__(kWgThreads) void k_scale_finalize(int n, QuantList<CAP> in, ResolveStarts<CAP, SK> places, Workspace ws,
+                                                               int64_t ngroup, SketchCheck check, float* scales)
 {
     const int i = blockIdx.x;
     const int tid = threadIdx.x;
     float scale;
+    uint32_t cost = 0u;  // of the sampled blocks
+    if (SK && MODE == 1 && i == 0 && tid == 0) cost = check.state[2];
     if (MODE == 1) {
         __shared__ uint32_t red[kWgThreads];
         // this worker's column of the slot array: read it with loads that see the atomics of the
@@ -478,20 +481,6 @@ __global__ __launch_bounds__(kWgThreads) void k_scale_finalize(int n, QuantList<
         }
         scale = (float)sqrt(total);  // thread 0 holds the total, and it alone goes on
     }
-    // the worker's place in its fill of k_resolve, as stage_starts finds it; not an argument, whose bytes every other step
-    // would pay for.  The widths wait in lanes (one after the other from memory: 10 us for the kernel instead of 6).
-    int start = 0;
-    if (SK && tid < kWave) {
-#pragma unroll
-        for (int c = 0; c < (CAP + kWave - 1) / kWave; ++c) {
-            const int w = c * kWave + tid < n ? (int)in.bits[c * kWave + tid] : 0;
-            for (int j = 0; j < kWave && c * kWave + j <= i; ++j) {  // before worker j: does it open a fill?
-                const int wj = __builtin_amdgcn_readlane(w, j);
-                if (start + wj > check.fill_cap) start = 0;
-                if (c * kWave + j < i) start += wj;
-            }
-        }
-    }
     if (tid == 0) {
         const int l = MODE == 0 ? (int)blockIdx.y : 0, per = MODE == 0 ? (int)gridDim.y : 1;
         scales[(int64_t)i * per + l] = scale;
@@ -499,15 +488,13 @@ __global__ __launch_bounds__(kWgThreads) void k_scale_finalize(int n, QuantList<
         const WorkerQ q = worker_record(in, i, n, inv16_of(scale, b), unit_weight(in.w[i], scale, b));
         ws.wq[(int64_t)l * n + i] = q;
         // a weight that is not finite makes NaN of zero levels too, which k_resolve does not add up
-        if (SK) {
-            const uint32_t ends = i == n - 1 || start + b + in.bits[i + 1] > check.fill_cap ? 512u : 0u;
-            check.table[i] = make_uint4(__float_as_uint(q.inv16), __float_as_uint(q.coef), q.bits | (q.arrived << 8) | ends, 32u * (uint32_t)start);
+        if constexpr (SK) {
+            const uint32_t ends = i == n - 1 || places.start[i + 1] == 0 ? 512u : 0u;
+            check.table[i] = make_uint4(__float_as_uint(q.inv16), __float_as_uint(q.coef), q.bits | (q.arrived << 8) | ends,
+                                        32u * places.start[i]);
         }
-        bool none = false;
-        if (SK && MODE == 1 && i == 0) {
-            none = check.state[2] > check.limit;
-            check.state[2] = 0u;  // the next step's
-        }
+        if (SK && MODE == 1 && i == 0) check.state[2] = 0u;  // the next step's
+        const bool none = MODE == 1 && cost > check.limit;
         if (SK && !(!none && (MODE == 1 || scale >= check.lo_scale[i]) && fabsf(q.coef) < __builtin_inff()))
             (void)__hip_atomic_fetch_or(check.state, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -555,16 +542,17 @@ template <int CAP>
 static hipError_t launch_scale_finalize_cap(int n, int scale_mode, const QuantStreams& out, const StepWeights& sw,
                                             const Workspace& ws, const SketchDev* sk, float* scales, hipStream_t stream)
 {
-    const SketchCheck check = sk ? SketchCheck{sk->lo_scale, sk->state, sk->limit, sk->table, out.resolve_cap}
-                                 : SketchCheck{};
+    const SketchCheck check = sk ? SketchCheck{sk->lo_scale, sk->state, sk->limit, sk->table} : SketchCheck{};
     const QuantList<CAP> q = quant_list<CAP>(n, out, sw);
+    ResolveStarts<CAP, true> places;
+    for (int i = 0; i < CAP; ++i) places.start[i] = sk && i < n ? out.resolve_start[i] : 0;
     const int layers = ws.n_layers;
     if (scale_mode == 1) {
         if (layers > 0)
             hipLaunchKernelGGL((k_scale_finalize_layers<CAP>), dim3(layers), dim3(kWgThreads), 0, stream, n, q, ws, scales);
         else {
-            if (sk) hipLaunchKernelGGL((k_scale_finalize<1, CAP, true>), dim3(n), dim3(kWgThreads), 0, stream, n, q, ws, (int64_t)0, check, scales);
-            else hipLaunchKernelGGL((k_scale_finalize<1, CAP, false>), dim3(n), dim3(kWgThreads), 0, stream, n, q, ws, (int64_t)0, check, scales);
+            if (sk) hipLaunchKernelGGL((k_scale_finalize<1, CAP, true>), dim3(n), dim3(kWgThreads), 0, stream, n, q, places, ws, (int64_t)0, check, scales);
+            else hipLaunchKernelGGL((k_scale_finalize<1, CAP, false>), dim3(n), dim3(kWgThreads), 0, stream, n, q, ResolveStarts<CAP, false>{}, ws, (int64_t)0, check, scales);
         }
         return hipGetLastError();
     }
@@ -573,8 +561,8 @@ static hipError_t launch_scale_finalize_cap(int n, int scale_mode, const QuantSt
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const dim3 g(n, layers > 0 ? layers : 1), b(kWgThreads);
-    if (sk) hipLaunchKernelGGL((k_scale_finalize<0, CAP, true>), g, b, 0, stream, n, q, ws, ngroup, check, scales);
-    else hipLaunchKernelGGL((k_scale_finalize<0, CAP, false>), g, b, 0, stream, n, q, ws, ngroup, check, scales);
+    if (sk) hipLaunchKernelGGL((k_scale_finalize<0, CAP, true>), g, b, 0, stream, n, q, places, ws, ngroup, check, scales);
+    else hipLaunchKernelGGL((k_scale_finalize<0, CAP, false>), g, b, 0, stream, n, q, ResolveStarts<CAP, false>{}, ws, ngroup, check, scales);
     return hipGetLastError();
 }
 
