@@ -616,7 +616,7 @@ agc_status encode_quantize_impl(agc_ctx* c, const float* G, int64_t ldg, const u
     qs.parts = code.parts && sum_bits <= agc::kPartBits && !sk;
     qs.stage_fills = agc::stage_starts(qs.bits, c->n, qs.parts ? agc::kPartBits : agc::stage_limit(c->n, c->opts.bucket != 0),
                                        qs.stage_start, &qs.stage_bits);
-    if (sk) (void)agc::stage_starts(qs.bits, c->n, agc::resolve_limit(c->n, ghat != nullptr), qs.resolve_start, &qs.resolve_bits);
+    if (sk) (void)agc::stage_starts(qs.bits, c->n, agc::resolve_limit(c->n, ghat != nullptr, c->ws.nseg), qs.resolve_start, &qs.resolve_bits);
     hipError_t e;
     if (c->opts.bucket) {  // one pass: every block finds its own scale
         KernelTimer t{c, 2, stream};

@@ -104,11 +104,15 @@ constexpr unsigned resolve_lds_bytes(int n, int stage_bits, bool fuse)
 }
 // Bits of a fill: what leaves room for six workgroups on a compute unit, which is what its registers allow too (k_resolve, us,
 // five | six | seven at 64 workers x 25.6 M: heavy tails, largest magnitude 404 | 374 | 425, Euclidean 245 | 232 | 282;  50 x 5.4 M,
-// 300 bits, without estimate 86 | 84 | 78), but no less than 48, where that many do not fit.
+// 300 bits, without estimate 86 | 84 | 78), but no less than 48, where that many do not fit.  Vectors of which no more than four or
+// five come to a compute unit have larger fills, hence fewer, one after the other in the chain of a workgroup.  Whole steps, Euclidean,
+// three bits, room for six | for what there are, us: 64 x 600 000 79.2 | 76.3, 64 x 1 M 90.4 | 88.0, 64 x 1.2 M 108.3 | 106.0, 128 x 700 000
+// 131.4 | 123.7;  five bits 64 x 1 M 105.5 | 100.4, 64 x 1.2 M 122.7 | 118.0.
 constexpr int kResolveWgs = 6;
-constexpr int resolve_limit(int n, bool fuse)
+inline int resolve_limit(int n, bool fuse, int64_t groups)
 {
-    const int room = 160 * 1024 / kResolveWgs / 1280 * 1280, rest = (int)resolve_lds_bytes(n, 0, fuse);
+    const int per_cu = groups <= 4 * 256 ? 4 : groups <= 5 * 256 ? 5 : kResolveWgs;
+    const int room = 160 * 1024 / per_cu / 1280 * 1280, rest = (int)resolve_lds_bytes(n, 0, fuse);
     const int bits = (room - rest) / 128;
     return bits < 48 ? 48 : bits;
 }

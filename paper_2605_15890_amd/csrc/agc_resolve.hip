@@ -283,8 +283,8 @@ hipError_t launch_resolve(int n, int64_t d, const Workspace& ws, const SketchDev
 {
     const ResolveArgs a{n, d, (uint32_t)seed, (uint32_t)(seed >> 32), (uint32_t)step, (uint32_t)(step >> 32), ghat,
                         out.resolve_bits, sk};
-    if (out.resolve_bits < 1 || out.resolve_bits > resolve_limit(n, ghat != nullptr)) return hipErrorInvalidValue;
     const dim3 g((unsigned)((d + 1023) / 1024)), b(kQuantThreads);
+    if (out.resolve_bits < 1 || out.resolve_bits > resolve_limit(n, ghat != nullptr, g.x)) return hipErrorInvalidValue;
     const unsigned lds = resolve_lds_bytes(n, out.resolve_bits, ghat != nullptr);
     if (ghat) hipLaunchKernelGGL((k_resolve<true>), g, b, lds, stream, ws.wq, a);
     else hipLaunchKernelGGL((k_resolve<false>), g, b, lds, stream, ws.wq, a);

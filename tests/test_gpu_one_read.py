@@ -383,3 +383,37 @@ def test_the_hook_refuses_other_scales():
         with pytest.raises(api.AgcError):
             ctx.agc_debug_sketch(3)
         ctx.close()
+
+
+@pytest.mark.parametrize("groups", [1024, 1025, 1280, 1281])
+@pytest.mark.parametrize("n,most", [(64, 5), (5, 16), (131, 4)])
+@pytest.mark.parametrize("fused", [True, False])
+def test_fills_by_the_length_of_the_vector(groups, n, most, fused):
+    """Four, five and six workgroups of the code-making kernel on a compute unit have fills of their own: the lengths where their
+    number changes, in one to many fills, against two reads."""
+    import torch
+    rng = np.random.default_rng([groups, n])
+    d = groups * 1024 - 77
+    csr = cyclic_csr(rng, n, 3)
+    bits, w, mask = rng.integers(2, most + 1, n).astype(np.uint8), rng.uniform(0.2, 3.0, n).astype(np.float32), (rng.random(n) < 0.7).astype(np.uint8)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    G = api.padded_rows(n, d)
+    G.normal_(generator=gen)
+    if most == 16:   # every value that is not 0 is a record: 77 +- 15 of them in a block (one standard deviation), room for 160
+        G.mul_(torch.rand(G.shape, device="cuda", generator=gen) < 0.02)
+    outs = []
+    for mode in (1, 2):
+        ctx = api.Context(n, n, d, scale_mode=api.AGC_SCALE_L2, unfused_step=not fused)
+        ctx.agc_set_code(*csr)
+        ctx.agc_debug_sketch(mode)
+        codes, scales, ghat = ctx.alloc_outputs(bits)
+        ctx.agc_step(G, bits, w, mask, 3, 4, codes, scales, ghat)
+        torch.cuda.synchronize()
+        last = ctx.agc_debug_sketch_last()
+        ctx.close()
+        assert last["one_read"] == (mode == 1)
+        if mode == 1:
+            assert last["groups"] == groups and not last["bound_failed"] and last["left"] < groups // 10
+        outs.append([*codes, scales.view(torch.int32), ghat.view(torch.int32)])
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
