@@ -106,9 +106,10 @@ inline double sketch_records(int64_t d, double levels) { return levels / 0.7 * _
 // steps of 1126 shapes (4..64 workers, 15..250 M elements, three to eight bits) with Gaussian, heavy-tailed and layered values:
 // 0.58 of one for every million elements of G that are not read again, less nine for three more launches, 2.8 for every
 // million coordinates (signs and tables by groups of blocks) and six for every million records.
-// Two reads | one, us (and the fit's gain): cyclic, 4 bits 32 x 11.7 M 588 | 390 (169);  3 bits 64 x 25.6 M 2404 | 1580 (861),
-// 64 x 1 M 132 | 108 (24), 32 x 1 M 64 | 56 (7), 32 x 500 000 42 | 45 (-2), 16 x 2 M 69 | 64 (3), 8 x 4 M 70 | 71 (-2);
-// 6 bits 50 x 5.4 M 480 | 435 (26), 16 x 2 M 71 | 72 (-2);  8 bits 64 x 5.4 M 590 | 669 (-18), 4 x 25.6 M 199 | 243 (-43).
+// Two reads | one, us (and the fit's gain), codes made as now, faster than when it was fitted: cyclic, 4 bits 32 x 11.7 M 570 | 383 (169);
+// 3 bits 64 x 25.6 M 2390 | 1468 (861), 64 x 1 M 112 | 88 (24), 32 x 1 M 63 | 57 (7), 32 x 500 000 43 | 46 (-2), 16 x 2 M 69 | 64 (3),
+// 8 x 4 M 70 | 72 (-2);  6 bits 50 x 5.4 M 435 | 324 (26), 16 x 2 M 70 | 73 (-2);  8 bits 64 x 5.4 M heavy tails 567 | 550, alike 568 | 722
+// (-18), 4 x 25.6 M 217 | 253 (-43).
 // A block of average magnitudes may fill three quarters of its room; the rest take k_quantize, and where the norm lies in a few
 // layers, fuller ones do too.  That second pass costs the latency of a wave that walks over all workers and rows however
 // few blocks it has; with sixty layers of magnitudes up to 1000 apart it was needed at 1 % of the shapes with up to 0.2 of the
@@ -132,16 +133,18 @@ inline int sketch_max_cap(int n, int k)
     const int room = 32 * k < 128 * n ? 32 * k : 128 * n;
     return (room + 255) / 256 * 256;
 }
-// G of 4 GB and more, where what the sample, its bounds and three kernels that find nothing to do take (30 us) is little beside
-// what they save or fail to save.  Whether they save anything depends on the values, and the sample decides that on the device
-// (sketch_max_limit); the wider the codes, the fewer the values with which they do.  Whole steps, two reads | one, us: heavy tails (t,
-// three degrees), three bits on average, cyclic 64 workers x 25.6 M 2347 | 1823, 32 x 25.6 M 1150 | 862, 16 x 25.6 M 610 | 528,
-// 8 x 25.6 M 332 | 345, 64 x 6.4 M 609 | 532;  windows of 8 and more, 10 workers and 30 partitions x 25.6 M 1099 | 777;  gathered
-// 64 x 25.6 M 7166 | 4084;  sixty layers of magnitudes up to 1000 apart 64 x 25.6 M 2350 | 2100-2250, 40 x 25.6 M 1457 | 1387.
-// Values that are alike everywhere, which the sample refuses: 64 x 25.6 M 2347 | 2375, 64 x 6.4 M 607 | 627, 10 of 30 x 5.4 M
-// 247 | 265.  Four bits on average, forced: heavy tails 2411 | 2534, layers 2414 | 2742.
+// G of 4 GB and more, where what it takes to find out is little: the sample, its bounds and kernels that have nothing to do, 20-60 us.
+// Whether one read saves anything depends on the values, and the sample decides that on the device (sketch_max_limit); the wider the
+// codes, the fewer the values with which it does.  Whole steps, two reads | one, us: heavy tails (t, three degrees), three bits on
+// average, cyclic 64 workers x 25.6 M 2320 | 1623, 40 x 27 M 1512 | 1095, 24 x 45 M 1507 | 1129, 12 x 90 M 1619 | 1444;  windows, 10 workers
+// and 30 partitions x 36 M 1428 | 923, 64 x 25.6 M 2305 | 1751;  gathered 64 x 25.6 M 6900 | 3745;  sixty layers of magnitudes up to
+// 1000 apart 64 x 25.6 M 2310 | 2057, 40 x 27 M 1520 | 1380, 24 x 45 M 1513 | 1437.  Values that are alike everywhere, which the sample
+// refuses: 64 x 25.6 M 2282 | 2303 and on other cards 2344 | 2372, 2324 | 2387;  40 x 27 M 1518 | 1565, 10 of 30 x 36 M 1428 | 1457,
+// 12 x 90 M 1614 | 1663.  Below the line heavy tails would gain as much (64 x 12.8 M 1196 | 888, 64 x 6.4 M 616 | 492, 32 x 25.6 M
+// 1168 | 845, 16 x 25.6 M 620 | 531) and alike values lose more (64 x 6.4 M 607 | 627, 10 of 30 x 5.4 M 247 | 265).  Eight workers gain
+// nothing (8 x 25.6 M 330 | 344).  Five bits, 64 x 25.6 M, forced: heavy tails 2451 | 2241, with layers 2455 | 1916;  six 2522 | 2743, 2523 | 2177.
 // The vector fills the chip several times over, since the bounds rise with what has been read.  With more than 128 workers too few
-// workgroups fit a compute unit: 128 x 8.5 M 1599 | 1362, 256 x 5.3 M 2094 | 2177.
+// workgroups fit a compute unit: 128 x 8.5 M 1641 | 1302, 256 x 5.3 M 2099 | 2003.
 inline bool use_sketch_max(int64_t d, int n, int k, double levels)
 {
     return k >= 12 && n <= 128 && d >= 20480 * 256 && (int64_t)k * d >= (int64_t)1 << 30 && levels <= 16.0 * n;

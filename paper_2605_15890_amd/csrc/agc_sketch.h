@@ -14,12 +14,13 @@
 // The results are those of the two-read form bit for bit, whatever the sample said.
 //
 // Measured, 64 workers x 25.6 M, three bits on average, Euclidean, interval code, whole step 2416 us with two reads (scale pass
-// 984, quantize pass 1420), 1470 with one: sample and bounds 11 + 5, k_sketch 1210-1240, groups and finalize 13,
-// k_resolve 232, the quantize pass that finds nothing left 7.  A step whose bounds do not hold pays for both forms (some 2670).
+// 984, quantize pass 1420), 1470 with one: sample and bounds 11 + 5, k_sketch 1210-1240, groups and finalize 12,
+// k_resolve 224, the quantize pass that finds nothing left 7.  A step whose bounds do not hold pays for both forms (some 2670).
 // Values that are not alike everywhere, two reads | one: rows of 16384 with the first 256 values 20 times the others, six bits,
-// 64 x 25.6 M 2500 | 1950, 50 x 5.4 M 480 | 437, 64 x 5.4 M three bits 541 | 402; sixty layers of magnitudes up to 1000 apart,
-// eight bits, 64 x 25.6 M 2552 | 2108.  What stays slower: at 64 x 1 M the second pass takes 27 us for however few blocks, so a
-// norm in a 64th of the vector or less, 132 | 139, and such rows, 132 | 141, lose what alike values gain, 132 | 108.
+// 64 x 25.6 M 2498 | 1744 (interval code 2560 | 1793), 50 x 5.4 M 433 | 351, 64 x 5.4 M three bits 529 | 350; sixty layers of magnitudes up
+// to 1000 apart, eight bits, 64 x 25.6 M 2501 | 1915.  What stays slower: at 64 x 1 M the second pass takes 27 us for however few
+// blocks, so a norm in a 64th of the vector or less, 112 | 119 (window of 8 132 | 148), and such rows, 113 | 115 (132 | 140), lose what
+// alike values gain, 112 | 88 (132 | 104).
 #pragma once
 
 #include "agc_device.h"
@@ -355,9 +356,9 @@ __device__ __forceinline__ void raise_bounds(const SketchArgs& a, const uint32_t
 // once and the scale pass runs instead.
 // What bounds it: stores among reads, as in k_sketch.  64 workers x 25.6 M, three bits on average, heavy tails (t, three
 // degrees), cyclic: 1330-1360 us, of which the bare row walk would be 960; some 450 records in a block (343 with the final
-// scales as bounds, 2050 with the sample's).  Whole step 2338 us with two reads (scale pass 940, quantize pass 1390), 1750 with
-// one: sample 10, bounds 5, the scale pass that returns 5, this kernel, finalize 6, k_resolve 374, the quantize pass that finds
-// nothing left 7.  One kernel with both passes: 2384 us for 2374 where values are alike (its registers and LDS are the
+// scales as bounds, 2050 with the sample's); interval code 1400-1430.  Whole step 2338 us with two reads (scale pass 940, quantize pass
+// 1390), 1755-1785 with one: sample 10, bounds 6, the scale pass that returns 5, this kernel, finalize 6, k_resolve 364-374, the quantize
+// pass that finds nothing left 7.  One kernel with both passes: 2384 us for 2374 where values are alike (its registers and LDS are the
 // sketch's), and with the first blocks of all in place of a sample 2123.
 template <int S>
 __global__ __launch_bounds__(kWgThreads) __attribute__((amdgpu_waves_per_eu(S == 0 || S == kStreamDriver ? 1 : 4, S == 0 || S == kStreamDriver ? 8 : 4))) void k_sketch_max(
