@@ -245,13 +245,6 @@ struct QuantList {         // both as kernel arguments of the table kernels, for
     int fuse;
 };
 
-template <int CAP, bool SK>
-struct ResolveStarts {     // and what the finalize kernel needs behind a sketch: stage_starts() of the fills of k_resolve
-    uint16_t start[CAP];
-};
-template <int CAP>
-struct ResolveStarts<CAP, false> {};
-
 struct DecodeStreams {     // the arrived workers of a decode call, in ascending order (host side)
     int n_arrived;
     const void* codes[kArgWorkers];

@@ -418,26 +418,39 @@ __device__ __forceinline__ float unit_weight(float w, float scale, int b)
     return (float)(((double)w * (double)scale) / L);
 }
 
-// What the finalize kernel checks of a sketch, with SK.
-struct SketchCheck {
+// What the finalize kernel needs behind a sketch: what it checks, and the places of k_resolve.  Arguments of these instances alone,
+// since the host pays by the byte.
+template <int CAP, bool SK>
+struct SketchSide {
     const float* lo_scale;  // Euclidean: the lower bounds that it was made with
     uint32_t* state;
-    uint32_t limit;         // largest magnitude: with state[2] above this there is no sketch
     uint4* table;           // k_resolve's
+    uint32_t limit;         // largest magnitude: with state[2] above this there is no sketch
+    uint16_t start[CAP];    // stage_starts() of the fills of k_resolve
 };
+template <int CAP>
+struct SketchSide<CAP, false> {};
+template <int CAP>
+static SketchSide<CAP, true> sketch_side(int n, const SketchDev& sk, const QuantStreams& out)
+{
+    SketchSide<CAP, true> side{sk.lo_scale, sk.state, sk.table, sk.limit, {}};
+    for (int i = 0; i < n; ++i) side.start[i] = out.resolve_start[i];
+    return side;
+}
 
-// One workgroup per worker (and layer, with the Euclidean scale).  SK: behind a sketch; the places of k_resolve are arguments of these
-// instances alone.  Found here from the widths of the workers before, the kernel took 1.3 us longer (64 workers; 64 x 1 M, Euclidean,
-// whole step 90.2 us, 87.0 with the arguments).
+// One workgroup per worker (and layer, with the Euclidean scale).  SK: behind a sketch; with the places of k_resolve found here, from the
+// widths of the workers before, the kernel took 5.96 us instead of 4.72 (64 workers x 1 M, Euclidean).
 template <int MODE, int CAP, bool SK>
-__global__ __launch_bounds__(kWgThreads) void k_scale_finalize(int n, QuantList<CAP> in, ResolveStarts<CAP, SK> places, Workspace ws,
-                                                               int64_t ngroup, SketchCheck check, float* scales)
+__global__ __launch_bounds__(kWgThreads) void k_scale_finalize(int n, QuantList<CAP> in, Workspace ws, int64_t ngroup,
+                                                               SketchSide<CAP, SK> side, float* scales)
 {
     const int i = blockIdx.x;
     const int tid = threadIdx.x;
     float scale;
     uint32_t cost = 0u;  // of the sampled blocks
-    if (SK && MODE == 1 && i == 0 && tid == 0) cost = check.state[2];
+    if constexpr (SK && MODE == 1) {
+        if (i == 0 && tid == 0) cost = side.state[2];
+    }
     if (MODE == 1) {
         __shared__ uint32_t red[kWgThreads];
         // this worker's column of the slot array: read it with loads that see the atomics of the
@@ -487,16 +500,18 @@ __global__ __launch_bounds__(kWgThreads) void k_scale_finalize(int n, QuantList<
         const int b = in.bits[i];
         const WorkerQ q = worker_record(in, i, n, inv16_of(scale, b), unit_weight(in.w[i], scale, b));
         ws.wq[(int64_t)l * n + i] = q;
-        // a weight that is not finite makes NaN of zero levels too, which k_resolve does not add up
         if constexpr (SK) {
-            const uint32_t ends = i == n - 1 || places.start[i + 1] == 0 ? 512u : 0u;
-            check.table[i] = make_uint4(__float_as_uint(q.inv16), __float_as_uint(q.coef), q.bits | (q.arrived << 8) | ends,
-                                        32u * places.start[i]);
+            const uint32_t ends = i == n - 1 || side.start[i + 1] == 0 ? 512u : 0u;
+            side.table[i] = make_uint4(__float_as_uint(q.inv16), __float_as_uint(q.coef), q.bits | (q.arrived << 8) | ends,
+                                       32u * side.start[i]);
+            if (MODE == 1 && i == 0) side.state[2] = 0u;  // the next step's
+            bool made = true;
+            if constexpr (MODE == 1) made = cost <= side.limit;
+            else made = scale >= side.lo_scale[i];
+            // a weight that is not finite makes NaN of zero levels too, which k_resolve does not add up
+            if (!(made && fabsf(q.coef) < __builtin_inff()))
+                (void)__hip_atomic_fetch_or(side.state, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        if (SK && MODE == 1 && i == 0) check.state[2] = 0u;  // the next step's
-        const bool none = MODE == 1 && cost > check.limit;
-        if (SK && !(!none && (MODE == 1 || scale >= check.lo_scale[i]) && fabsf(q.coef) < __builtin_inff()))
-            (void)__hip_atomic_fetch_or(check.state, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -542,17 +557,14 @@ template <int CAP>
 static hipError_t launch_scale_finalize_cap(int n, int scale_mode, const QuantStreams& out, const StepWeights& sw,
                                             const Workspace& ws, const SketchDev* sk, float* scales, hipStream_t stream)
 {
-    const SketchCheck check = sk ? SketchCheck{sk->lo_scale, sk->state, sk->limit, sk->table} : SketchCheck{};
     const QuantList<CAP> q = quant_list<CAP>(n, out, sw);
-    ResolveStarts<CAP, true> places;
-    for (int i = 0; i < CAP; ++i) places.start[i] = sk && i < n ? out.resolve_start[i] : 0;
     const int layers = ws.n_layers;
     if (scale_mode == 1) {
         if (layers > 0)
             hipLaunchKernelGGL((k_scale_finalize_layers<CAP>), dim3(layers), dim3(kWgThreads), 0, stream, n, q, ws, scales);
         else {
-            if (sk) hipLaunchKernelGGL((k_scale_finalize<1, CAP, true>), dim3(n), dim3(kWgThreads), 0, stream, n, q, places, ws, (int64_t)0, check, scales);
-            else hipLaunchKernelGGL((k_scale_finalize<1, CAP, false>), dim3(n), dim3(kWgThreads), 0, stream, n, q, ResolveStarts<CAP, false>{}, ws, (int64_t)0, check, scales);
+            if (sk) hipLaunchKernelGGL((k_scale_finalize<1, CAP, true>), dim3(n), dim3(kWgThreads), 0, stream, n, q, ws, (int64_t)0, sketch_side<CAP>(n, *sk, out), scales);
+            else hipLaunchKernelGGL((k_scale_finalize<1, CAP, false>), dim3(n), dim3(kWgThreads), 0, stream, n, q, ws, (int64_t)0, SketchSide<CAP, false>{}, scales);
         }
         return hipGetLastError();
     }
@@ -561,8 +573,8 @@ static hipError_t launch_scale_finalize_cap(int n, int scale_mode, const QuantSt
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const dim3 g(n, layers > 0 ? layers : 1), b(kWgThreads);
-    if (sk) hipLaunchKernelGGL((k_scale_finalize<0, CAP, true>), g, b, 0, stream, n, q, places, ws, ngroup, check, scales);
-    else hipLaunchKernelGGL((k_scale_finalize<0, CAP, false>), g, b, 0, stream, n, q, ResolveStarts<CAP, false>{}, ws, ngroup, check, scales);
+    if (sk) hipLaunchKernelGGL((k_scale_finalize<0, CAP, true>), g, b, 0, stream, n, q, ws, ngroup, sketch_side<CAP>(n, *sk, out), scales);
+    else hipLaunchKernelGGL((k_scale_finalize<0, CAP, false>), g, b, 0, stream, n, q, ws, ngroup, SketchSide<CAP, false>{}, scales);
     return hipGetLastError();
 }
 
